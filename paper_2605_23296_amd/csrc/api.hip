@@ -188,7 +188,8 @@ static size_t max_partial_cols(const compact_layer_cfg& c) {
     return cols;
 }
 
-static int moe_mtile(const compact_layer_cfg& c) { return c.dtype == COMPACT_BF16 ? gemm_bf16_mtile() : gemm_f32_mtile(); }
+// smallest row tile of the prefill-size expert GEMMs: what the routing plan's tile map is sized for
+static int moe_min_mtile(const compact_layer_cfg& c) { return c.dtype == COMPACT_BF16 ? GEMM_BF16_MIN_MTILE : gemm_f32_mtile(); }
 
 // mt = rows per tile of the plan's tile map: the row tile of the prefill-size expert GEMMs, or 16 for the decode
 // steps' per-expert streaming
@@ -221,7 +222,7 @@ static void carve_prefill(Carver& cv, const compact_layer_cfg& c, int64_t T, Pre
         b.logits = (float*)cv.take((size_t)T * c.n_experts * 4);
         b.idx = (int32_t*)cv.take((size_t)T * c.top_k * 4);
         b.gate = (float*)cv.take((size_t)T * c.top_k * 4);
-        carve_moe_plan(cv, c, T, b.plan, moe_mtile(c));
+        carve_moe_plan(cv, c, T, b.plan, moe_min_mtile(c));
         b.expert_out = cv.take((size_t)T * c.top_k * c.d_model * es);
     }
 }
@@ -1515,12 +1516,19 @@ static int moe_ffn_rows(compact_ctx* ctx, const compact_weights* w, const void* 
                         void* expert_out, void* y, hipStream_t s) {
     const compact_layer_cfg& c = ctx->cfg;
     const int64_t rk = rows * c.top_k;
-    TRY(launch_moe_plan(ctx, idx, gate, rows, moe_mtile(c), plan, s));
+    int mtile = gemm_f32_mtile();
+    if (c.dtype == COMPACT_BF16) {
+        int n_cus = 0;
+        TRY(device_cu_count(ctx, &n_cus));
+        mtile = gemm_bf16_group_mtile(rk, c.n_experts, c.ffn_dim, c.d_model, n_cus);
+    }
+    TRY(launch_moe_plan(ctx, idx, gate, rows, mtile, plan, s));
     GroupedArgs g{};
+    g.mtile = mtile;
     g.tile_expert = plan.tile_expert;
     g.tile_row0 = plan.tile_row0;
     g.tile_rows = plan.tile_rows;
-    g.n_mtiles = plan.max_mtiles;
+    g.n_mtiles = (int32_t)std::min<int64_t>(rk / mtile + c.n_experts, plan.max_mtiles);   // the map's upper bound
     // gate/up + SwiGLU on the rows gathered per expert
     g.a_gather = plan.sorted_token;
     g.row_scale = nullptr;
@@ -1790,7 +1798,7 @@ extern "C" int compact_moe_ffn(compact_ctx* ctx, const compact_weights* w, const
     Carver cv(d_workspace);
     void* act = cv.take((size_t)rows * c.top_k * c.ffn_dim * es);
     MoePlan plan;
-    carve_moe_plan(cv, c, rows, plan, moe_mtile(c));
+    carve_moe_plan(cv, c, rows, plan, moe_min_mtile(c));
     void* expert_out = cv.take((size_t)rows * c.top_k * c.d_model * es);
     if (!d_workspace || cv.off > ws_bytes) return set_err(ctx, COMPACT_EWORKSPACE, "workspace too small for the expert feed-forward");
     return moe_ffn_rows(ctx, w, d_m, d_h, false, d_expert_idx, d_gate, rows, act, plan, expert_out, d_y, (hipStream_t)hip_stream);

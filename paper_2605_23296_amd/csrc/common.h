@@ -167,6 +167,7 @@ struct GroupedArgs {          // all device pointers; null tile_expert => plain 
     const float* row_scale;       // [rows] multiplies the output row (null = 1)
     int64_t b_expert_stride;      // elements between consecutive experts' B
     int32_t n_mtiles;
+    int32_t mtile;                // rows per tile of the map (bf16: 256, 128 or 64)
 };
 // gemm_f32.hip : C = A B^T (+R) ; epilogue 1 = SwiGLU on stacked gate/up
 int launch_gemm_f32(compact_ctx* ctx, const float* A, const float* B, const float* R, float* C,
@@ -177,7 +178,9 @@ int gemm_f32_mtile();
 // epilogue 0: bf16 C = acc (+R); 1: SwiGLU on stacked gate/up; 2: fp32 C = acc (+R).  R is bf16, or fp32 if r_f32.
 int launch_gemm_bf16(compact_ctx* ctx, const bf16* A, const bf16* B, const void* R, bool r_f32, bf16* C,
                      int64_t M, int N, int K, int epilogue, const GroupedArgs* grouped, hipStream_t s);
-int gemm_bf16_mtile();
+// row-tile height for the grouped GEMMs over `rows` routed rows, and the smallest it can give
+int gemm_bf16_group_mtile(int64_t rows, int n_experts, int F, int d, int n_cus);
+#define GEMM_BF16_MIN_MTILE 64
 
 // mxfp4.hip : block-scaled 4-bit expert weights
 int mxfp4_ksplit(int K);

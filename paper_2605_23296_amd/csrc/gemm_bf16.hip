@@ -40,6 +40,8 @@
 // from L2 the clock rises to 1.66).  8B-shaped layer, 32768 rows, before -> now:
 // QKV 1479 -> 1297 us, O 1045 -> 922, gate/up 6290 -> 5560 (1.38 PFLOP/s), down
 // 3418 -> 2890 (1.33); 1652 rows 104 -> 92, 91 -> 79, 419 -> 371, 304 -> 253.
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -91,6 +93,135 @@ __device__ __forceinline__ void wave_priority_normal() {
 #endif
 }
 
+// Where a workgroup's tile lies.  Workgroup ids are dealt to the XCDs round robin: each XCD takes a contiguous
+// range of tiles, walked in groups of GM row tiles per column tile.
+struct TilePos {
+    int64_t m0;       // first row
+    int rows_valid;   // 0: nothing to do
+    int n0;           // first output column
+    const bf16* W;    // the weight matrix (the expert's)
+};
+template <bool GROUPED, int BM, int OUTN, int GM>
+__device__ __forceinline__ TilePos find_tile(const GemmParams& p) {
+    const int total = gridDim.x;
+    const int per = total / 8, rem = total % 8;
+    const int xcd = blockIdx.x % 8, loc = blockIdx.x / 8;
+    const int pid = xcd * per + min(xcd, rem) + loc;
+    const int per_group = GM * p.n_ntiles;
+    const int first_m = (pid / per_group) * GM;
+    const int gsize = min(GM, p.n_mtiles - first_m);
+    const int tm = first_m + (pid % per_group) % gsize;
+    const int tn = (pid % per_group) / gsize;
+    TilePos tp;
+    tp.n0 = tn * OUTN;
+    tp.W = p.W;
+    if (GROUPED) {
+        const int e = p.g.tile_expert[tm];
+        tp.m0 = e < 0 ? 0 : p.g.tile_row0[tm];
+        tp.rows_valid = e < 0 ? 0 : p.g.tile_rows[tm];
+        tp.W += (int64_t)max(e, 0) * p.g.b_expert_stride;
+    } else {
+        tp.m0 = (int64_t)tm * BM;
+        tp.rows_valid = (int)min((int64_t)BM, p.M - tp.m0);
+    }
+    return tp;
+}
+
+// Epilogue of one wavefront: TM x TN MFMA tiles, 32 output rows per pass through a wave-private fp32 slab
+// [32][WOUT + 4].  acc[i][j][e]: output row wrow + i*16 + r of the tile, column n_first + j*16 + c4*4 + e (SwiGLU: the
+// first TN / 2 tiles are the gate, the others the up values of the same columns).  A pass's residual rows are
+// requested one pass ahead; the slab needs no workgroup barrier.
+template <int EPI, bool GROUPED, int TM, int TN>
+__device__ __forceinline__ void store_tile(const GemmParams& p, const floatx4 (&acc)[TM][TN], float* slab, int lane, int wrow,
+                                           int rows_valid, int64_t m0, int n_first) {
+    constexpr int WOUT = (EPI == 1 ? TN / 2 : TN) * 16;
+    constexpr int SLD = WOUT + 4;
+    constexpr int NCH = WOUT / 8;       // 8-column chunks per row
+    constexpr int NU = 32 * NCH / 64;   // chunks per lane and pass
+    static_assert(TM % 2 == 0 && NU >= 1, "passes of 32 rows, at least one chunk per lane");
+    const int r = lane & 15, c4 = lane >> 4;
+    const bool has_r = EPI != 1 && p.R != nullptr;
+    floatx4 rv[2][NU][2];
+    auto load_r = [&](int i, floatx4 (&v)[NU][2]) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int row = (lane + 64 * u) / NCH, c = (lane + 64 * u) % NCH;
+            const int lm = wrow + i * 32 + row, n = n_first + c * 8;
+            if (lm >= rows_valid || n >= p.N) continue;
+            const int64_t o = (m0 + lm) * p.N + n;
+            if (p.r_f32) {
+                const floatx4* rf = reinterpret_cast<const floatx4*>(reinterpret_cast<const float*>(p.R) + o);
+                v[u][0] = rf[0];
+                v[u][1] = rf[1];
+            } else {
+                v[u][0] = *reinterpret_cast<const floatx4*>(p.R + o);
+            }
+        }
+    };
+    if (has_r) load_r(0, rv[0]);
+#pragma unroll
+    for (int i = 0; i < TM / 2; ++i) {
+        if (has_r && i + 1 < TM / 2) load_r(i + 1, rv[(i + 1) & 1]);
+        constexpr int TJ = EPI == 1 ? TN / 2 : TN;
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                floatx4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float a = acc[2 * i + g][j][e];
+                    if (EPI == 1) {
+                        const float u = acc[2 * i + g][j + TN / 2][e];
+                        a = a / (1.0f + __expf(-a)) * u;
+                    }
+                    v[e] = a;
+                }
+                *reinterpret_cast<floatx4*>(slab + (g * 16 + r) * SLD + j * 16 + c4 * 4) = v;
+            }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int row = (lane + 64 * u) / NCH, c = (lane + 64 * u) % NCH;
+            const int lm = wrow + i * 32 + row, n = n_first + c * 8;
+            float v[8];
+            const floatx4 a = *reinterpret_cast<const floatx4*>(slab + row * SLD + c * 8);
+            const floatx4 b = *reinterpret_cast<const floatx4*>(slab + row * SLD + c * 8 + 4);
+            if (lm >= rows_valid || n >= p.N) continue;
+            const int64_t gm = m0 + lm;
+            v[0] = a[0]; v[1] = a[1]; v[2] = a[2]; v[3] = a[3];
+            v[4] = b[0]; v[5] = b[1]; v[6] = b[2]; v[7] = b[3];
+            if (GROUPED && p.g.row_scale) {
+                const float sc = p.g.row_scale[gm];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] *= sc;
+            }
+            if (has_r && p.r_f32) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[e] += rv[i & 1][u][0][e];
+                    v[4 + e] += rv[i & 1][u][1][e];
+                }
+            } else if (has_r) {
+                const bf16x8 rb = __builtin_bit_cast(bf16x8, rv[i & 1][u][0]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] += (float)rb[e];
+            }
+            if (EPI == 2) {   // fp32 output (router logits)
+                float* cf = reinterpret_cast<float*>(p.C) + gm * p.N + n;
+                *reinterpret_cast<floatx4*>(cf) = floatx4{v[0], v[1], v[2], v[3]};
+                *reinterpret_cast<floatx4*>(cf + 4) = floatx4{v[4], v[5], v[6], v[7]};
+            } else {
+                bf16x8 o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (bf16)v[e];
+                *reinterpret_cast<bf16x8*>(p.C + gm * p.N + n) = o;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 template <int EPI, bool GROUPED>
 __global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmParams p) {
     constexpr int BM = 256, BN = 256, WM = 2, WN = 4, BK = GEMM_BK;
@@ -101,32 +232,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmParams p) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16* lds = reinterpret_cast<bf16*>(smem);
 
-    // ---- which tile -------------------------------------------------------
-    const int total = gridDim.x;
-    const int per = total / 8, rem = total % 8;
-    const int xcd = blockIdx.x % 8, loc = blockIdx.x / 8;
-    const int pid = xcd * per + min(xcd, rem) + loc;
-    constexpr int GM = 4;
-    const int per_group = GM * p.n_ntiles;
-    const int first_m = (pid / per_group) * GM;
-    const int gsize = min(GM, p.n_mtiles - first_m);
-    const int tm = first_m + (pid % per_group) % gsize;
-    const int tn = (pid % per_group) / gsize;
-
-    int64_t m0;
-    int rows_valid;
-    const bf16* Wb = p.W;
-    if (GROUPED) {
-        const int e = p.g.tile_expert[tm];
-        if (e < 0) return;
-        m0 = p.g.tile_row0[tm];
-        rows_valid = p.g.tile_rows[tm];
-        Wb += (int64_t)e * p.g.b_expert_stride;
-    } else {
-        m0 = (int64_t)tm * BM;
-        rows_valid = (int)min((int64_t)BM, p.M - m0);
-    }
-    const int n0 = tn * OUTN;
+    const TilePos tp = find_tile<GROUPED, BM, OUTN, 4>(p);
+    if (tp.rows_valid <= 0) return;
+    const int64_t m0 = tp.m0;
+    const int rows_valid = tp.rows_valid, n0 = tp.n0;
+    const bf16* Wb = tp.W;
 
     const int t = threadIdx.x;
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -262,107 +372,255 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmParams p) {
     if (kt < nk) k_tile(kt, 0, wA, wB);
     if (!wm) plain_barrier();
 
-    // ---- epilogue: 32 output rows per pass through a wave-private fp32 slab ----
-    // acc[i][j][e]: output row m = wm*WTM + i*16 + r, column n = j*16 + c4*4 + e.  A pass's residual rows are
-    // requested one pass ahead; the slab needs no workgroup barrier.
-    constexpr int SLD = WOUT + 4;
-    constexpr int NCH = WOUT / 8;       // 8-column chunks per row
-    constexpr int NU = 32 * NCH / 64;   // chunks per lane and pass
-    const bool has_r = EPI != 1 && p.R != nullptr;
-    floatx4 rv[2][NU][2];
-    auto load_r = [&](int i, floatx4 (&v)[NU][2]) {
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const int row = (lane + 64 * u) / NCH, c = (lane + 64 * u) % NCH;
-            const int lm = wm * WTM + i * 32 + row;
-            const int n = n0 + wn * WOUT + c * 8;
-            if (lm >= rows_valid || n >= p.N) continue;
-            const int64_t o = (m0 + lm) * p.N + n;
-            if (p.r_f32) {
-                const floatx4* rf = reinterpret_cast<const floatx4*>(reinterpret_cast<const float*>(p.R) + o);
-                v[u][0] = rf[0];
-                v[u][1] = rf[1];
-            } else {
-                v[u][0] = *reinterpret_cast<const floatx4*>(p.R + o);
-            }
-        }
-    };
     ring_barrier<0>();   // the repeated loads of the last k-tile must not land in the slabs
-    if (has_r) load_r(0, rv[0]);
-    float* slab = reinterpret_cast<float*>(smem) + wave * 32 * SLD;
-#pragma unroll
-    for (int i = 0; i < TM / 2; ++i) {
-        if (has_r && i + 1 < TM / 2) load_r(i + 1, rv[(i + 1) & 1]);
-        constexpr int TJ = EPI == 1 ? TN / 2 : TN;
-#pragma unroll
-        for (int j = 0; j < TJ; ++j)
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                floatx4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float a = acc[2 * i + g][j][e];
-                    if (EPI == 1) {
-                        const float u = acc[2 * i + g][j + TN / 2][e];
-                        a = a / (1.0f + __expf(-a)) * u;
-                    }
-                    v[e] = a;
-                }
-                *reinterpret_cast<floatx4*>(slab + (g * 16 + r) * SLD + j * 16 + c4 * 4) = v;
-            }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const int row = (lane + 64 * u) / NCH, c = (lane + 64 * u) % NCH;
-            const int lm = wm * WTM + i * 32 + row;  // row inside the tile
-            const int n = n0 + wn * WOUT + c * 8;
-            float v[8];
-            const floatx4 a = *reinterpret_cast<const floatx4*>(slab + row * SLD + c * 8);
-            const floatx4 b = *reinterpret_cast<const floatx4*>(slab + row * SLD + c * 8 + 4);
-            if (lm >= rows_valid || n >= p.N) continue;
-            const int64_t gm = m0 + lm;
-            v[0] = a[0]; v[1] = a[1]; v[2] = a[2]; v[3] = a[3];
-            v[4] = b[0]; v[5] = b[1]; v[6] = b[2]; v[7] = b[3];
-            if (GROUPED && p.g.row_scale) {
-                const float sc = p.g.row_scale[gm];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] *= sc;
-            }
-            if (has_r && p.r_f32) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    v[e] += rv[i & 1][u][0][e];
-                    v[4 + e] += rv[i & 1][u][1][e];
-                }
-            } else if (has_r) {
-                const bf16x8 rb = __builtin_bit_cast(bf16x8, rv[i & 1][u][0]);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] += (float)rb[e];
-            }
-            if (EPI == 2) {   // fp32 output (router logits)
-                float* cf = reinterpret_cast<float*>(p.C) + gm * p.N + n;
-                *reinterpret_cast<floatx4*>(cf) = floatx4{v[0], v[1], v[2], v[3]};
-                *reinterpret_cast<floatx4*>(cf + 4) = floatx4{v[4], v[5], v[6], v[7]};
-            } else {
-                bf16x8 o;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (bf16)v[e];
-                *reinterpret_cast<bf16x8*>(p.C + gm * p.N + n) = o;
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
+    store_tile<EPI, GROUPED, TM, TN>(p, acc, reinterpret_cast<float*>(smem) + wave * 32 * (WOUT + 4), lane, wm * WTM, rows_valid, m0,
+                                     n0 + wn * WOUT);
 }
 
+// ---------------------------------------------------------------------------
+// The same schedule over 128 x 256 tiles (wavefronts of 64 x 64, two phases per k-tile: X0 W0, X0 W1): twice the
+// workgroups for calls whose 256 x 256 tiles would leave half the chip idle.  A k-tile is three half tiles (W0, X0,
+// W1); the ring holds three k-tiles (nine slots, 144 KB).  A phase requests three of the six 8-row pieces a wavefront
+// owns of a k-tile; 11 or 12 of them may still fly when the next phase's operands must be there.
+// ---------------------------------------------------------------------------
 template <int EPI, bool GROUPED>
-static int launch_cfg(compact_ctx* ctx, GemmParams& p, hipStream_t s) {
-    constexpr int OUTN = EPI == 1 ? 128 : 256;
-    if (!GROUPED) p.n_mtiles = (int)((p.M + 255) / 256);
+__global__ __launch_bounds__(512) void gemm_bf16_half_kernel(const GemmParams p) {
+    constexpr int BM = 128, BN = 256, WN = 4, BK = GEMM_BK;
+    constexpr int WTM = 64, WTN = 64, TM = WTM / 16, TN = WTN / 16;
+    constexpr int HT = 128 * BK;
+    constexpr int OUTN = EPI == 1 ? BN / 2 : BN;
+    constexpr int WOUT = EPI == 1 ? WTN / 2 : WTN;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    bf16* lds = reinterpret_cast<bf16*>(smem);
+    const TilePos tp = find_tile<GROUPED, BM, OUTN, 8>(p);
+    if (tp.rows_valid <= 0) return;
+    const int n0 = tp.n0;
+    const int t = threadIdx.x;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int r = lane & 15, c4 = lane >> 4;
+
+    // half tiles q = 0: W0, 1: X0, 2: W1 (the order they are read in); pieces, chunks and swizzle as above
+    const bf16* src[3][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int row = (wave * 2 + u) * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ ((row >> 1) & 7);
+        int64_t sr = tp.m0 + min(row, tp.rows_valid - 1);
+        if (GROUPED && p.g.a_gather) sr = p.g.a_gather[sr];
+        src[1][u] = p.X + sr * p.K + c * 8;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            int n;
+            if (EPI == 1)
+                n = min(n0 + row, p.N - 1) + j * p.N;
+            else
+                n = min(n0 + (row >> 5) * 64 + j * 32 + (row & 31), p.N - 1);
+            src[2 * j][u] = tp.W + (int64_t)n * p.K + c * 8;
+        }
+    }
+    floatx4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int nk = p.K / BK;
+    int foff[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) foff[kk] = r * BK + (((4 * kk + c4) ^ ((r >> 1) & 7)) << 3);
+    const bf16* xs = lds + wm * 64 * BK;
+    const bf16* ws = lds + wn * 32 * BK;
+    // piece u of half tile q of k-tile kt, into k-tile buffer buf
+    auto gload = [&](int q, int u, int kt, int buf) {
+        load16_to_lds(src[q][u] + min(kt, nk - 1) * BK, lds + (buf * 3 + q) * HT + (wave * 2 + u) * 8 * BK);
+    };
+    auto read_w = [&](int j, int buf, bf16x8 (&f)[2][2]) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+                f[nt][kk] = *reinterpret_cast<const bf16x8*>(ws + (buf * 3 + 2 * j) * HT + nt * 16 * BK + foff[kk]);
+    };
+    bf16x8 xf[4][2], w0[2][2], w1[2][2];
+    auto mfmas = [&](auto jtag, const bf16x8 (&wf)[2][2]) {
+        constexpr int j = decltype(jtag)::value;
+        wave_priority_high();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) {
+            const int kk = n >> 3, mt = (n >> 1) & 3, nt = (n & 1) ^ (mt & 1);
+            acc[mt][2 * j + nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[nt][kk], xf[mt][kk], acc[mt][2 * j + nt], 0, 0, 0);
+        }
+        wave_priority_normal();
+        plain_barrier();
+    };
+    // k-tile kt in buffer b0, kt + 1 in b1, kt + 2 in b2
+    auto k_tile = [&](int kt, int b0, int b1, int b2) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+                xf[mt][kk] = *reinterpret_cast<const bf16x8*>(xs + (b0 * 3 + 1) * HT + mt * 16 * BK + foff[kk]);
+        gload(2, 0, kt + 2, b2);
+        gload(2, 1, kt + 2, b2);
+        gload(0, 0, kt + 3, b0);
+        ring_barrier<11>();
+        mfmas(std::integral_constant<int, 0>{}, w0);
+        read_w(1, b0, w1);
+        read_w(0, b1, w0);
+        gload(0, 1, kt + 3, b0);
+        gload(1, 0, kt + 3, b0);
+        gload(1, 1, kt + 3, b0);
+        ring_barrier<12>();
+        mfmas(std::integral_constant<int, 1>{}, w1);
+    };
+    // prologue: k-tiles 0 and 1, and W0, X0 of k-tile 2; the first two half tiles have landed when all but 12 pieces have
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int q = 0; q < (i == 2 ? 2 : 3); ++q) {
+            gload(q, 0, i, i);
+            gload(q, 1, i, i);
+        }
+    ring_barrier<12>();
+    read_w(0, 0, w0);
+    ring_barrier<12>();
+    if (wm) plain_barrier();   // the second wave group runs half a phase behind the first
+    int kt = 0;
+    for (; kt + 2 < nk; kt += 3) {
+        k_tile(kt, 0, 1, 2);
+        k_tile(kt + 1, 1, 2, 0);
+        k_tile(kt + 2, 2, 0, 1);
+    }
+    if (kt < nk) k_tile(kt, 0, 1, 2);
+    if (kt + 1 < nk) k_tile(kt + 1, 1, 2, 0);
+    if (!wm) plain_barrier();
+    ring_barrier<0>();   // the repeated loads of the last k-tile must not land in the slabs
+    store_tile<EPI, GROUPED, TM, TN>(p, acc, reinterpret_cast<float*>(smem) + wave * 32 * (WOUT + 4), lane, wm * WTM, tp.rows_valid,
+                                     tp.m0, n0 + wn * WOUT);
+}
+
+// ---------------------------------------------------------------------------
+// Smaller tiles, for calls whose 256 x 256 tiles would leave compute units idle: BM x BN outputs per workgroup of
+// WM x WN wavefronts, k-tiles of 64 in a ring of S LDS stages, one barrier per k-tile, S - 1 k-tiles of loads in
+// flight.  Same layout, same MFMAs in the same order along K as above: an output has the same bits whichever tile it
+// lies in.
+// ---------------------------------------------------------------------------
+template <int BM, int BN, int WM, int WN, int S, int EPI, bool GROUPED>
+__global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_small_kernel(const GemmParams p) {
+    constexpr int NW = WM * WN, BK = GEMM_BK;
+    constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 16, TN = WTN / 16;
+    constexpr int STAGE = (BM + BN) * BK;   // elements
+    constexpr int OUTN = EPI == 1 ? BN / 2 : BN;
+    constexpr int WOUT = EPI == 1 ? WTN / 2 : WTN;
+    constexpr int XU = BM / 8 / NW, WU = BN / 8 / NW;   // 8-row load units per wavefront
+    static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && TN % 2 == 0, "tile rows must split over the wavefronts");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    bf16* lds = reinterpret_cast<bf16*>(smem);
+    const TilePos tp = find_tile<GROUPED, BM, OUTN, 8>(p);
+    if (tp.rows_valid <= 0) return;
+    const int t = threadIdx.x;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int r = lane & 15, c4 = lane >> 4;
+
+    const bf16 *xsrc[XU], *wsrc[WU];
+#pragma unroll
+    for (int u = 0; u < XU; ++u) {
+        const int row = (wave * XU + u) * 8 + (lane >> 3);
+        int64_t sr = tp.m0 + min(row, tp.rows_valid - 1);
+        if (GROUPED && p.g.a_gather) sr = p.g.a_gather[sr];
+        xsrc[u] = p.X + sr * p.K + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+    }
+#pragma unroll
+    for (int u = 0; u < WU; ++u) {
+        const int row = (wave * WU + u) * 8 + (lane >> 3);
+        int n;
+        if (EPI == 1)
+            n = row < BN / 2 ? min(tp.n0 + row, p.N - 1) : p.N + min(tp.n0 + row - BN / 2, p.N - 1);
+        else
+            n = min(tp.n0 + row, p.N - 1);
+        wsrc[u] = tp.W + (int64_t)n * p.K + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+    }
+    const int nk = p.K / BK;
+    auto gload = [&](int kt, int stage) {
+        const int k0 = min(kt, nk - 1) * BK;   // past the end of K: the last k-tile again, into a stage nobody reads
+        bf16* dst = lds + stage * STAGE;
+#pragma unroll
+        for (int u = 0; u < XU; ++u) load16_to_lds(xsrc[u] + k0, dst + (wave * XU + u) * 8 * BK);
+#pragma unroll
+        for (int u = 0; u < WU; ++u) load16_to_lds(wsrc[u] + k0, dst + BM * BK + (wave * WU + u) * 8 * BK);
+    };
+    floatx4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    int foff[2];
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) foff[kk] = r * BK + (((4 * kk + c4) ^ ((r >> 1) & 7)) << 3);
+
+    for (int i = 0; i < S - 1; ++i) gload(i, i);
+    int stage = 0, fill = S - 1;
+    for (int kt = 0; kt < nk; ++kt) {
+        ring_barrier<(S - 2) * (XU + WU)>();   // k-tile kt has landed; everybody is done with the stage to be refilled
+        gload(kt + S - 1, fill);
+        const bf16* xs = lds + stage * STAGE + wm * WTM * BK;
+        const bf16* ws = lds + stage * STAGE + BM * BK;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            bf16x8 xf[TM], wf[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int row = EPI != 1 ? wn * WTN + j * 16
+                                : j < TN / 2 ? wn * (WTN / 2) + j * 16
+                                             : BN / 2 + wn * (WTN / 2) + (j - TN / 2) * 16;
+                wf[j] = *reinterpret_cast<const bf16x8*>(ws + row * BK + foff[kk]);
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i) xf[i] = *reinterpret_cast<const bf16x8*>(xs + i * 16 * BK + foff[kk]);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], xf[i], acc[i][j], 0, 0, 0);
+        }
+        stage = stage + 1 == S ? 0 : stage + 1;
+        fill = fill + 1 == S ? 0 : fill + 1;
+    }
+    ring_barrier<0>();   // the repeated loads must not land in the slabs
+    store_tile<EPI, GROUPED, TM, TN>(p, acc, reinterpret_cast<float*>(smem) + wave * 32 * (WOUT + 4), lane, wm * WTM, tp.rows_valid,
+                                     tp.m0, tp.n0 + wn * WOUT);
+}
+
+template <int BM, int BN, int WM, int WN, int S, int EPI, bool GROUPED>
+static int launch_small(compact_ctx* ctx, GemmParams& p, hipStream_t s) {
+    constexpr int OUTN = EPI == 1 ? BN / 2 : BN;
+    if (!GROUPED) p.n_mtiles = (int)((p.M + BM - 1) / BM);
     p.n_ntiles = (p.N + OUTN - 1) / OUTN;
-    constexpr size_t ring_bytes = (size_t)8 * 128 * GEMM_BK * sizeof(bf16);
-    constexpr size_t slab_bytes = (size_t)8 * 32 * (OUTN / 4 + 4) * sizeof(float);
-    constexpr size_t smem = ring_bytes > slab_bytes ? ring_bytes : slab_bytes;
-    auto kern = gemm_bf16_kernel<EPI, GROUPED>;
+    constexpr size_t smem = (size_t)S * (BM + BN) * GEMM_BK * sizeof(bf16);
+    static_assert((size_t)WM * WN * 32 * (OUTN / WN + 4) * sizeof(float) <= smem, "the epilogue's slabs fit the ring");
+    auto kern = gemm_bf16_small_kernel<BM, BN, WM, WN, S, EPI, GROUPED>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+        attr_set = true;
+    }
+    const int64_t tiles = (int64_t)p.n_mtiles * p.n_ntiles;
+    if (tiles == 0) return COMPACT_OK;
+    kern<<<dim3((unsigned)tiles), WM * WN * 64, smem, s>>>(p);
+    LAUNCH_CHECK(ctx);
+    return COMPACT_OK;
+}
+
+// H: the 128 x 256 form
+template <int EPI, bool GROUPED, bool H>
+static int launch_cfg(compact_ctx* ctx, GemmParams& p, hipStream_t s) {
+    constexpr int OUTN = EPI == 1 ? 128 : 256, BM = H ? 128 : 256;
+    if (!GROUPED) p.n_mtiles = (int)((p.M + BM - 1) / BM);
+    p.n_ntiles = (p.N + OUTN - 1) / OUTN;
+    constexpr size_t smem = (size_t)(H ? 9 : 8) * 128 * GEMM_BK * sizeof(bf16);   // the ring; the epilogue's slabs fit in
+    static_assert((size_t)8 * 32 * (OUTN / 4 + 4) * sizeof(float) <= smem, "the epilogue's slabs fit the ring");
+    auto kern = H ? gemm_bf16_half_kernel<EPI, GROUPED> : gemm_bf16_kernel<EPI, GROUPED>;
     static bool attr_set = false;
     if (!attr_set) {
         HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
@@ -375,13 +633,92 @@ static int launch_cfg(compact_ctx* ctx, GemmParams& p, hipStream_t s) {
     return COMPACT_OK;
 }
 
-// Row-tile height used for the grouped expert GEMMs.
-int gemm_bf16_mtile() { return 256; }
+// ---------------------------------------------------------------------------
+// Which tile.  Every form adds an output's products in the same order, so the choice changes no bit and may look at
+// the number of rows.  Cost of a call = rounds of workgroups over the compute units x time of one tile; the time of
+// a k-tile rises with the share u of busy units (power and L2 traffic).  Constants: microseconds per k-tile (idle chip
+// + share of the load) and per tile, from timings of every form on N x K = 6144 x 4096, 4096 x 4096, 2 * 14336 x 4096,
+// 4096 x 14336, 1536 x 1024 and 2 * 2816 x 1024 at 20 .. 4096 rows.  Measured where the line lies (us, 256 x 256 against
+// 128 x 256): N 4096 K 14336 at 2048 rows 266 / 203, at 2500 rows 272 / 356 (128 x 256 needs a second round); N 6144
+// K 4096 at 2500 rows 97 / 111, at 3000 rows 165 / 146; 2 * 14336 x 4096 at 1652 rows 397 / 368, at 4096 rows 861 / 940.
+// Few rows, N 4096 K 14336: 20 rows 207 (256 x 256) / 157 / 104 (128 x 128) / 85 (64 x 128) / 71 (128 x 64) / 55
+// (64 x 64); 300 rows 211 / 167 / 109 / 94 / 81 / 112; 1000 rows 243 / 187 / 140 / 190 / 192 / 232.
+// ---------------------------------------------------------------------------
+struct TileForm {
+    int bm, bn;
+    double t_idle, t_load, t_tile;
+};
+enum { TILE_256 = 0, TILE_128, TILE_128_128, TILE_128_64, TILE_64_128, TILE_64_64, TILE_FORMS };
+static const TileForm tile_forms[TILE_FORMS] = {{256, 256, 1.00, 0.70, 6.0}, {128, 256, 0.75, 0.25, 2.0}, {128, 128, 0.50, 0.15, 4.0},
+                                                {128, 64, 0.33, 0.08, 3.0},  {64, 128, 0.40, 0.05, 2.0},  {64, 64, 0.25, 0.02, 3.0}};
+
+static double tile_cost(int form, double row_tiles, int N, int K, int epilogue, int n_cus) {
+    const TileForm& f = tile_forms[form];
+    const int outn = epilogue == 1 ? f.bn / 2 : f.bn;
+    const double tiles = row_tiles * ((N + outn - 1) / outn);
+    const double rounds = std::max(1.0, std::ceil(tiles / n_cus));
+    return rounds * ((K / GEMM_BK) * (f.t_idle + f.t_load * tiles / (rounds * n_cus)) + f.t_tile);
+}
+
+static int pick_tile(int64_t M, int N, int K, int epilogue, int n_cus) {
+    int best = TILE_256;
+    double best_cost = 0;
+    for (int form = 0; form < TILE_FORMS; ++form) {
+        const double c = tile_cost(form, (double)((M + tile_forms[form].bm - 1) / tile_forms[form].bm), N, K, epilogue, n_cus);
+        if (form == 0 || c < best_cost) {
+            best = form;
+            best_cost = c;
+        }
+    }
+    return best;
+}
+
+// Row-tile height of the grouped (per-expert) GEMMs of a routed layer over `rows` routed rows (256, 128 or 64): the cost
+// as above for the gate/up and the down projection, with as many row tiles as evenly loaded experts would have.
+int gemm_bf16_group_mtile(int64_t rows, int n_experts, int F, int d, int n_cus) {
+    static const int forms[3] = {TILE_256, TILE_128, TILE_64_128};
+    const double groups = (double)std::min<int64_t>(n_experts, std::max<int64_t>(rows, 1));
+    const double per = rows / groups;
+    int best = 256;
+    double best_cost = 0;
+    for (int i = 0; i < 3; ++i) {
+        const int bm = tile_forms[forms[i]].bm;
+        // a group of `per` rows on average: half a tile more than its rows fill, at least one
+        const double row_tiles = groups * std::max(1.0, per / bm + 0.5);
+        const double c = tile_cost(forms[i], row_tiles, F, d, 1, n_cus) + tile_cost(forms[i], row_tiles, d, F, 0, n_cus);
+        if (i == 0 || c < best_cost) {
+            best = bm;
+            best_cost = c;
+        }
+    }
+    return best;
+}
+
+template <int EPI, bool GROUPED>
+static int launch_form(compact_ctx* ctx, int form, GemmParams& p, hipStream_t s) {
+    switch (form) {
+        case TILE_256: return launch_cfg<EPI, GROUPED, false>(ctx, p, s);
+        case TILE_128: return launch_cfg<EPI, GROUPED, true>(ctx, p, s);
+        case TILE_64_128: return launch_small<64, 128, 2, 4, 6, EPI, GROUPED>(ctx, p, s);
+        default: break;
+    }
+    if constexpr (!GROUPED) {
+        switch (form) {
+            case TILE_128_128: return launch_small<128, 128, 2, 4, 5, EPI, false>(ctx, p, s);
+            case TILE_128_64: return launch_small<128, 64, 4, 2, 6, EPI, false>(ctx, p, s);
+            case TILE_64_64: return launch_small<64, 64, 2, 2, 5, EPI, false>(ctx, p, s);
+            default: break;
+        }
+    }
+    return set_err(ctx, COMPACT_EINVAL, "unknown GEMM tile");
+}
 
 int launch_gemm_bf16(compact_ctx* ctx, const bf16* A, const bf16* B, const void* R, bool r_f32, bf16* C, int64_t M, int N,
                      int K, int epilogue, const GroupedArgs* grouped, hipStream_t s) {
     if (M == 0) return COMPACT_OK;
     if (K % GEMM_BK != 0 || N % 8 != 0) return set_err(ctx, COMPACT_ESHAPE, "bf16 GEMM needs K % 64 == 0 and N % 8 == 0");
+    int n_cus = 0;
+    if (int rc = device_cu_count(ctx, &n_cus)) return rc;
     GemmParams p{};
     p.X = A;
     p.W = B;
@@ -394,10 +731,12 @@ int launch_gemm_bf16(compact_ctx* ctx, const bf16* A, const bf16* B, const void*
     if (grouped) {
         p.g = *grouped;
         p.n_mtiles = grouped->n_mtiles;
-        if (epilogue == 1) return launch_cfg<1, true>(ctx, p, s);
-        return launch_cfg<0, true>(ctx, p, s);
+        const int form = grouped->mtile == 256 ? TILE_256 : grouped->mtile == 128 ? TILE_128 : TILE_64_128;
+        if (tile_forms[form].bm != grouped->mtile) return set_err(ctx, COMPACT_EINVAL, "no grouped GEMM of this row-tile height");
+        return epilogue == 1 ? launch_form<1, true>(ctx, form, p, s) : launch_form<0, true>(ctx, form, p, s);
     }
-    if (epilogue == 1) return launch_cfg<1, false>(ctx, p, s);
-    if (epilogue == 2) return launch_cfg<2, false>(ctx, p, s);
-    return launch_cfg<0, false>(ctx, p, s);
+    const int form = pick_tile(M, N, K, epilogue, n_cus);
+    if (epilogue == 1) return launch_form<1, false>(ctx, form, p, s);
+    if (epilogue == 2) return launch_form<2, false>(ctx, form, p, s);
+    return launch_form<0, false>(ctx, form, p, s);
 }
