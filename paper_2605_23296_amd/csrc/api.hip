@@ -445,16 +445,12 @@ static int gemm_full(compact_ctx* ctx, const void* A, const void* B, const void*
                            nullptr, s);
 }
 
-// decode-size: fp32 split-K partials [ks][M][N]
+// decode-size, bf16 storage: fp32 split-K partials [ks][M][N]
 static int gemm_partials(compact_ctx* ctx, const void* A, const void* B, float* partials, int M, int N, int K, int* ks,
                          hipStream_t s) {
-    if (ctx->cfg.dtype == COMPACT_BF16) {
-        *ks = skinny_ksplit(M, N, K);
-        ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
-        return launch_gemm_skinny(ctx, (const bf16*)A, (const bf16*)B, partials, M, N, K, *ks, s);
-    }
-    *ks = 1;
-    return launch_gemm_f32(ctx, (const float*)A, (const float*)B, nullptr, partials, M, N, K, 0, nullptr, s);
+    *ks = skinny_ksplit(M, N, K);
+    ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
+    return launch_gemm_skinny(ctx, (const bf16*)A, (const bf16*)B, partials, M, N, K, *ks, s);
 }
 
 #define TRY(expr)                      \
@@ -675,6 +671,10 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
         rq.inv_d = 1.0f / (float)c.d_model;
         rq.eps = c.rms_eps;
         TRY(launch_decode_qkv_epilogue(ctx, meta, N, step, b.partials, ks, b.q, kv->d_k, kv->d_v, s, &rq));
+    } else if (c.dtype != COMPACT_BF16) {   // the RMSNorm rides in the projection
+        TRY(launch_gemm_f32(ctx, (const float*)x, (const float*)w->w_qkv, nullptr, b.partials, N, Dtot, c.d_model, 0, nullptr, s,
+                            (const float*)w->g_attn));
+        TRY(launch_decode_qkv_epilogue(ctx, meta, N, step, b.partials, ks, b.q, kv->d_k, kv->d_v, s));
     } else {
         TRY(launch_rmsnorm(ctx, x, false, w->g_attn, b.n, N, s));
         TRY(gemm_partials(ctx, b.n, w->w_qkv, b.partials, N, Dtot, c.d_model, &ks, s));
@@ -716,16 +716,24 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
         rn.eps = c.rms_eps;
         pending_norm = true;
         ffn_in = b.hg;
+    } else if (!bf) {
+        // fp32 storage: h = x + o Wo^T from the projection; a dense layer's gate/up projection norms h itself
+        TRY(launch_gemm_f32(ctx, (const float*)b.o, (const float*)w->w_o, (const float*)x, b.h, N, c.d_model, Dq, 0, nullptr, s));
+        if (c.n_experts > 0) TRY(launch_rmsnorm(ctx, b.h, false, w->g_ffn, b.m, N, s));
     } else {
         TRY(gemm_partials(ctx, b.o, w->w_o, b.partials, N, c.d_model, Dq, &ks, s));
         TRY(launch_residual_norm(ctx, b.partials, ks, x, w->g_ffn, b.h, b.m, N, s));
     }
-    if (c.n_experts == 0) {
-        if (bf && skinny_swiglu_supported(N, c.ffn_dim, c.d_model)) {
+    if (c.n_experts == 0 && !bf) {
+        TRY(launch_gemm_f32(ctx, b.h, (const float*)w->w_gate_up, nullptr, (float*)b.act, N, c.ffn_dim, c.d_model, 1, nullptr, s,
+                            (const float*)w->g_ffn));
+        TRY(launch_gemm_f32(ctx, (const float*)b.act, (const float*)w->w_down, b.h, (float*)y, N, c.d_model, c.ffn_dim, 0, nullptr, s));
+    } else if (c.n_experts == 0) {
+        if (skinny_swiglu_supported(N, c.ffn_dim, c.d_model)) {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
             TRY(launch_gemm_skinny_swiglu(ctx, (const bf16*)ffn_in, (const bf16*)w->w_gate_up, (bf16*)b.act, N, c.ffn_dim,
                                           c.d_model, pending_norm ? &rn : nullptr, s));
-        } else if (bf && swiglu_mt_supported(N, c.ffn_dim, c.d_model) && skinny_swiglu_supported(16, c.ffn_dim, c.d_model)) {
+        } else if (swiglu_mt_supported(N, c.ffn_dim, c.d_model) && skinny_swiglu_supported(16, c.ffn_dim, c.d_model)) {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
             TRY(launch_swiglu_mt(ctx, (const bf16*)ffn_in, (const bf16*)w->w_gate_up, (bf16*)b.act, N, c.ffn_dim, c.d_model,
                                  pending_norm ? &rn : nullptr, s));
@@ -737,7 +745,7 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
             TRY(gemm_partials(ctx, ffn_in, w->w_gate_up, b.partials, N, 2 * c.ffn_dim, c.d_model, &ks, s));
             TRY(launch_swiglu_reduce(ctx, b.partials, ks, b.act, N, c.ffn_dim, s));
         }
-        if (bf && resid_out_stream_supported(N, c.d_model, c.ffn_dim)) {
+        if (resid_out_stream_supported(N, c.d_model, c.ffn_dim)) {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
             TRY(launch_resid_out_stream(ctx, (const bf16*)b.act, (const bf16*)w->w_down, b.h, (bf16*)y, N, c.d_model,
                                         c.ffn_dim, s));

@@ -169,9 +169,11 @@ struct GroupedArgs {          // all device pointers; null tile_expert => plain 
     int32_t n_mtiles;
     int32_t mtile;                // rows per tile of the map (bf16: 256, 128 or 64)
 };
-// gemm_f32.hip : C = A B^T (+R) ; epilogue 1 = SwiGLU on stacked gate/up
+// gemm_f32.hip : C = A B^T (+R) ; epilogue 1 = SwiGLU on stacked gate/up.  norm_g (nullable): A holds un-normalised
+// rows, RMSNorm(.; norm_g) is applied to them on the way (K = d_model)
 int launch_gemm_f32(compact_ctx* ctx, const float* A, const float* B, const float* R, float* C,
-                    int64_t M, int N, int K, int epilogue, const GroupedArgs* grouped, hipStream_t s);
+                    int64_t M, int N, int K, int epilogue, const GroupedArgs* grouped, hipStream_t s,
+                    const float* norm_g = nullptr);
 int gemm_f32_mtile();
 
 // gemm_bf16.hip

@@ -276,10 +276,9 @@ __device__ __forceinline__ float4 sum_slices4(const float* __restrict__ p, size_
 // One workgroup per row, 4 columns per thread and trip (d <= RN_TRIPS * NT * 4 = 8192).
 // ---------------------------------------------------------------------------
 #define RN_TRIPS 8
-template <typename T>
 __global__ __launch_bounds__(NT) void residual_norm_kernel(const float* __restrict__ partials, int ks, int rows,
-                                                           const T* __restrict__ resid, const T* __restrict__ g,
-                                                           float* __restrict__ h_out, T* __restrict__ m_out, int d,
+                                                           const bf16* __restrict__ resid, const bf16* __restrict__ g,
+                                                           float* __restrict__ h_out, bf16* __restrict__ m_out, int d,
                                                            float eps) {
     __shared__ float red[NT / WAVE];
     const int r = blockIdx.x;
@@ -290,7 +289,7 @@ __global__ __launch_bounds__(NT) void residual_norm_kernel(const float* __restri
     for (int it = 0; it < RN_TRIPS; ++it) {
         const int c = (it * NT + threadIdx.x) * 4;
         if (c < d) {
-            const T* rp = resid + (size_t)r * d + c;
+            const bf16* rp = resid + (size_t)r * d + c;
             float4 a = make_float4(to_f32(rp[0]), to_f32(rp[1]), to_f32(rp[2]), to_f32(rp[3]));
             a = sum_slices4(partials + (size_t)r * d + c, ps, ks, a);
             hv[it] = a;
@@ -304,11 +303,11 @@ __global__ __launch_bounds__(NT) void residual_norm_kernel(const float* __restri
     for (int it = 0; it < RN_TRIPS; ++it) {
         const int c = (it * NT + threadIdx.x) * 4;
         if (c < d) {
-            T* mp = m_out + (size_t)r * d + c;
-            mp[0] = from_f32<T>(hv[it].x * inv * to_f32(g[c]));
-            mp[1] = from_f32<T>(hv[it].y * inv * to_f32(g[c + 1]));
-            mp[2] = from_f32<T>(hv[it].z * inv * to_f32(g[c + 2]));
-            mp[3] = from_f32<T>(hv[it].w * inv * to_f32(g[c + 3]));
+            bf16* mp = m_out + (size_t)r * d + c;
+            mp[0] = (bf16)(hv[it].x * inv * to_f32(g[c]));
+            mp[1] = (bf16)(hv[it].y * inv * to_f32(g[c + 1]));
+            mp[2] = (bf16)(hv[it].z * inv * to_f32(g[c + 2]));
+            mp[3] = (bf16)(hv[it].w * inv * to_f32(g[c + 3]));
         }
     }
 }
@@ -317,12 +316,8 @@ int launch_residual_norm(compact_ctx* ctx, const float* partials, int ks, const 
                          void* h_out, void* m_out, int rows, hipStream_t s) {
     const compact_layer_cfg& c = ctx->cfg;
     if (c.d_model > RN_TRIPS * NT * 4) return set_err(ctx, COMPACT_ESHAPE, "d_model above 8192 is not supported by the decode row kernels");
-    if (c.dtype == COMPACT_BF16)
-        residual_norm_kernel<bf16><<<rows, NT, 0, s>>>(partials, ks, rows, (const bf16*)resid, (const bf16*)g,
-                                                      (float*)h_out, (bf16*)m_out, c.d_model, c.rms_eps);
-    else
-        residual_norm_kernel<float><<<rows, NT, 0, s>>>(partials, ks, rows, (const float*)resid, (const float*)g,
-                                                       (float*)h_out, (float*)m_out, c.d_model, c.rms_eps);
+    residual_norm_kernel<<<rows, NT, 0, s>>>(partials, ks, rows, (const bf16*)resid, (const bf16*)g, (float*)h_out, (bf16*)m_out,
+                                             c.d_model, c.rms_eps);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
@@ -331,9 +326,8 @@ int launch_residual_norm(compact_ctx* ctx, const float* partials, int ks, const 
 // Decode: act = silu(gate) * up, gate/up = sum of partials of the stacked
 // projection [rows, 2F]
 // ---------------------------------------------------------------------------
-template <typename T>
 __global__ __launch_bounds__(NT) void swiglu_reduce_kernel(const float* __restrict__ partials, int ks, int rows,
-                                                           T* __restrict__ act, int F) {
+                                                           bf16* __restrict__ act, int F) {
     const int r = blockIdx.y;
     const int c = blockIdx.x * NT + threadIdx.x;
     if (c >= F) return;
@@ -344,15 +338,12 @@ __global__ __launch_bounds__(NT) void swiglu_reduce_kernel(const float* __restri
         up += partials[s * ps + (size_t)r * 2 * F + F + c];
     }
     const float sg = gt / (1.0f + expf(-gt));
-    act[(size_t)r * F + c] = from_f32<T>(sg * up);
+    act[(size_t)r * F + c] = (bf16)(sg * up);
 }
 
 int launch_swiglu_reduce(compact_ctx* ctx, const float* partials, int ks, void* act, int rows, int F, hipStream_t s) {
     dim3 grid((F + NT - 1) / NT, rows);
-    if (ctx->cfg.dtype == COMPACT_BF16)
-        swiglu_reduce_kernel<bf16><<<grid, NT, 0, s>>>(partials, ks, rows, (bf16*)act, F);
-    else
-        swiglu_reduce_kernel<float><<<grid, NT, 0, s>>>(partials, ks, rows, (float*)act, F);
+    swiglu_reduce_kernel<<<grid, NT, 0, s>>>(partials, ks, rows, (bf16*)act, F);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
@@ -360,29 +351,25 @@ int launch_swiglu_reduce(compact_ctx* ctx, const float* partials, int ks, void* 
 // ---------------------------------------------------------------------------
 // Decode: y = resid (fp32) + sum_s partial_s ; 4 columns per thread
 // ---------------------------------------------------------------------------
-template <typename T>
 __global__ __launch_bounds__(NT) void residual_reduce_kernel(const float* __restrict__ partials, int ks, int rows,
-                                                             const float* __restrict__ resid, T* __restrict__ y,
+                                                             const float* __restrict__ resid, bf16* __restrict__ y,
                                                              int cols) {
     const size_t i = ((size_t)blockIdx.x * NT + threadIdx.x) * 4;
     const size_t total = (size_t)rows * cols;
     if (i >= total) return;
     float4 a = *reinterpret_cast<const float4*>(resid + i);
     a = sum_slices4(partials + i, total, ks, a);
-    y[i] = from_f32<T>(a.x);
-    y[i + 1] = from_f32<T>(a.y);
-    y[i + 2] = from_f32<T>(a.z);
-    y[i + 3] = from_f32<T>(a.w);
+    y[i] = (bf16)(a.x);
+    y[i + 1] = (bf16)(a.y);
+    y[i + 2] = (bf16)(a.z);
+    y[i + 3] = (bf16)(a.w);
 }
 
 int launch_residual_reduce(compact_ctx* ctx, const float* partials, int ks, const void* resid, void* y, int rows,
                            int cols, hipStream_t s) {
     const size_t total = (size_t)rows * cols;  // cols is a multiple of 64
     const unsigned grid = (unsigned)((total / 4 + NT - 1) / NT);
-    if (ctx->cfg.dtype == COMPACT_BF16)
-        residual_reduce_kernel<bf16><<<grid, NT, 0, s>>>(partials, ks, rows, (const float*)resid, (bf16*)y, cols);
-    else
-        residual_reduce_kernel<float><<<grid, NT, 0, s>>>(partials, ks, rows, (const float*)resid, (float*)y, cols);
+    residual_reduce_kernel<<<grid, NT, 0, s>>>(partials, ks, rows, (const float*)resid, (bf16*)y, cols);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
