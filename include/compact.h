@@ -224,8 +224,9 @@ int compact_layer_forward(compact_ctx* ctx, const compact_weights* w, int32_t n_
  * tails->h_len[b]; its K/V row is appended to tail b, it attends the shared rows
  * 0..h_prefix_len[b]-1 and tail rows 0..h_len[b] inclusive, tails->h_len[b] is
  * incremented, d_y [N, d] receives the layer outputs.  The shared rows are read
- * from memory once per step for all workers together (a 256-row chunk is
- * multiplied with the query heads of every worker whose prefix covers it).
+ * from memory once per step for all workers together (a 512-row chunk is
+ * multiplied with the query heads of every worker whose prefix covers it, at
+ * most 128 / (query heads per KV head) workers at a time).
  * bf16 storage only.  Errors as compact_decode_step; COMPACT_EINVAL for a
  * decreasing or out-of-range h_prefix_len.  The workspace must hold
  * compact_prefix_workspace_bytes(ctx, N, max h_prefix_len, max tail length). */

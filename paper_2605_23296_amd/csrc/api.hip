@@ -1300,10 +1300,12 @@ static int build_prefix_plan(compact_ctx* ctx, int n_workers, const compact_kv* 
     int w0 = 0;
     for (int r0 = 0; r0 < max_prefix; r0 += PREFIX_CHUNK) {
         while (h_prefix_len[w0] <= r0) ++w0;   // first worker whose prefix reaches into the chunk
-        PrefixItem it{r0, std::min(PREFIX_CHUNK, max_prefix - r0), w0, n_workers - w0, 0, rec};
-        for (int b = w0; b < n_workers; ++b) lists[b].push_back((int32_t)pa.items.size());
-        pa.items.push_back(it);
-        rec += it.nw * G;
+        for (int wf = w0; wf < n_workers; wf += PFX_COLS / G) {
+            PrefixItem it{r0, std::min(PREFIX_CHUNK, max_prefix - r0), wf, std::min(PFX_COLS / G, n_workers - wf), 0, rec};
+            for (int b = wf; b < wf + it.nw; ++b) lists[b].push_back((int32_t)pa.items.size());
+            pa.items.push_back(it);
+            rec += it.nw * G;
+        }
     }
     for (int b = 0; b < n_workers; ++b)
         for (int r0 = 0; r0 < tails->h_len[b] + steps; r0 += PREFIX_CHUNK) {

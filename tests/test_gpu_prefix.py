@@ -64,6 +64,14 @@ def test_prefix_decode_attention_scores_that_grow_or_fall_along_the_history(sign
     prefix_kernel_case(layer, [0, 100, 256, 257, 700, 1500, 1500], [3, 1, 2, 300, 1, 5, 1], grow=sign * per_key)
 
 
+@pytest.mark.parametrize("wl", ["dense_8x4096", "moe_16x8192"])
+def test_prefix_decode_attention_kernel_tile_edges(wl):
+    """Prefixes and tails on and around the 32-row tiles, the 64-row V pairs and the 512-row items; enough workers that the
+    query columns of an item (128) overflow into a second one."""
+    edges = [1, 31, 32, 33, 63, 64, 65, 96, 127, 511, 512, 513, 543, 544, 545, 1023, 1024, 1025, 1057, 1057]
+    prefix_kernel_case(WORKLOADS[wl].layer, edges + [1100] * 15, [1, 2, 31, 32, 33] * 6 + [64, 65, 512, 513, 96])
+
+
 def prefix_kernel_case(layer, prefix, tail, grow=None):
     N, Hq, Hkv, hd = len(prefix), layer.n_q_heads, layer.n_kv_heads, layer.head_dim
     lay = B.Layer(layer, None)
