@@ -698,18 +698,22 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
     const void* ffn_in = b.m;
     RowNorm rn{};
     bool pending_norm = false;
-    // (17 .. 64 rows: the same kernels with several groups of 16 rows per weight fragment, used where the kernel for
-    // at most 16 rows covers the shape too, so that both split K alike and a row's bits do not depend on the batch)
-    const bool o_few = bf && resid_norm_stream_supported(N, c.d_model, Dq);
-    const bool o_many = bf && !o_few && stream_mt_supported(N, c.d_model, Dq) && resid_norm_stream_supported(16, c.d_model, Dq);
-    if (o_few || o_many) {
+    const bool many = bf && N > 16;   // 17 .. 64 rows: projections by the ring GEMM, split over K
+    const float* pre_scale = nullptr;
+    if (many) {
+        {
+            ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
+            TRY(launch_gemm_rows64(ctx, (const bf16*)b.o, (const bf16*)w->w_o, b.partials, N, c.d_model, Dq, s));
+        }
+        // a dense layer's gate/up projection applies 1 / rms to its products, so that its operand is rounded as in the
+        // kernels for at most 16 rows
+        float* rinv = c.n_experts == 0 ? b.ssq_parts : nullptr;
+        TRY(launch_residual_norm(ctx, b.partials, gemm_rows64_slices(c.d_model, Dq), x, w->g_ffn, b.h, b.m, N, s, rinv));
+        pre_scale = rinv;
+    } else if (bf && resid_norm_stream_supported(N, c.d_model, Dq)) {
         ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
-        if (o_few)
-            TRY(launch_resid_norm_stream(ctx, (const bf16*)b.o, (const bf16*)w->w_o, (const bf16*)x, (const bf16*)w->g_ffn, b.h,
-                                         (bf16*)b.hg, b.ssq_parts, N, c.d_model, Dq, s));
-        else
-            TRY(launch_resid_norm_stream_mt(ctx, (const bf16*)b.o, (const bf16*)w->w_o, (const bf16*)x, (const bf16*)w->g_ffn,
-                                            b.h, (bf16*)b.hg, b.ssq_parts, N, c.d_model, Dq, s));
+        TRY(launch_resid_norm_stream(ctx, (const bf16*)b.o, (const bf16*)w->w_o, (const bf16*)x, (const bf16*)w->g_ffn, b.h,
+                                     (bf16*)b.hg, b.ssq_parts, N, c.d_model, Dq, s));
         rn.ssq_parts = b.ssq_parts;
         rn.nparts = c.d_model / 16;
         rn.inv_d = 1.0f / (float)c.d_model;
@@ -728,15 +732,22 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
         TRY(launch_gemm_f32(ctx, b.h, (const float*)w->w_gate_up, nullptr, (float*)b.act, N, c.ffn_dim, c.d_model, 1, nullptr, s,
                             (const float*)w->g_ffn));
         TRY(launch_gemm_f32(ctx, (const float*)b.act, (const float*)w->w_down, b.h, (float*)y, N, c.d_model, c.ffn_dim, 0, nullptr, s));
+    } else if (c.n_experts == 0 && many) {
+        {
+            ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
+            TRY(launch_swiglu_rows64(ctx, (const bf16*)ffn_in, (const bf16*)w->w_gate_up, pre_scale, (bf16*)b.act, N, c.ffn_dim,
+                                     c.d_model, s));
+        }
+        {
+            ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
+            TRY(launch_gemm_rows64(ctx, (const bf16*)b.act, (const bf16*)w->w_down, b.partials, N, c.d_model, c.ffn_dim, s));
+        }
+        TRY(launch_residual_reduce(ctx, b.partials, gemm_rows64_slices(c.d_model, c.ffn_dim), b.h, y, N, c.d_model, s));
     } else if (c.n_experts == 0) {
         if (skinny_swiglu_supported(N, c.ffn_dim, c.d_model)) {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
             TRY(launch_gemm_skinny_swiglu(ctx, (const bf16*)ffn_in, (const bf16*)w->w_gate_up, (bf16*)b.act, N, c.ffn_dim,
                                           c.d_model, pending_norm ? &rn : nullptr, s));
-        } else if (swiglu_mt_supported(N, c.ffn_dim, c.d_model) && skinny_swiglu_supported(16, c.ffn_dim, c.d_model)) {
-            ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
-            TRY(launch_swiglu_mt(ctx, (const bf16*)ffn_in, (const bf16*)w->w_gate_up, (bf16*)b.act, N, c.ffn_dim, c.d_model,
-                                 pending_norm ? &rn : nullptr, s));
         } else {
             if (pending_norm) {
                 TRY(launch_rownorm_apply(ctx, (const bf16*)b.hg, rn, (bf16*)b.m, N, c.d_model, s));
@@ -750,8 +761,6 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
             TRY(launch_resid_out_stream(ctx, (const bf16*)b.act, (const bf16*)w->w_down, b.h, (bf16*)y, N, c.d_model,
                                         c.ffn_dim, s));
         } else {
-            // (more than 16 rows: a whole-K workgroup would have to pull all M x F activations through L2 for its 16 columns,
-            // four times the weight bytes at 64 rows; measured 49 us against 31 us for split-K + reduce on the 8B-shaped layer)
             TRY(gemm_partials(ctx, b.act, w->w_down, b.partials, N, c.d_model, c.ffn_dim, &ks, s));
             TRY(launch_residual_reduce(ctx, b.partials, ks, b.h, y, N, c.d_model, s));
         }

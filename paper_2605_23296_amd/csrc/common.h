@@ -144,8 +144,9 @@ int launch_decode_qkv_epilogue(compact_ctx* ctx, const BlockMeta* d_meta, int n_
                                const float* partials, int ks, void* q_out, void* d_k, void* d_v,
                                hipStream_t s, const RowNorm* norm = nullptr);
 // decode: h = resid + sum partials; writes h and m = RMSNorm(h; g)
+// (rinv_out given: m = bf16(h * g) instead, and the rows' 1 / rms go there)
 int launch_residual_norm(compact_ctx* ctx, const float* partials, int ks, const void* resid,
-                         const void* g, void* h_out, void* m_out, int rows, hipStream_t s);
+                         const void* g, void* h_out, void* m_out, int rows, hipStream_t s, float* rinv_out = nullptr);
 // decode: act = silu(gate) * up from ks partials of the stacked gate/up projection
 int launch_swiglu_reduce(compact_ctx* ctx, const float* partials, int ks, void* act, int rows, int F,
                          hipStream_t s);
@@ -185,6 +186,13 @@ int launch_gemm_bf16(compact_ctx* ctx, const bf16* A, const bf16* B, const void*
 // row-tile height for the grouped GEMMs over `rows` routed rows, and the smallest it can give
 int gemm_bf16_group_mtile(int64_t rows, int n_experts, int F, int d, int n_cus);
 #define GEMM_BF16_MIN_MTILE 64
+
+// decode steps of 17 .. 64 rows: fp32 partials [gemm_rows64_slices(N, K)][M][N], at most ceil(K / 512) slices; act = SwiGLU
+int gemm_rows64_slices(int N, int K);
+int launch_gemm_rows64(compact_ctx* ctx, const bf16* A, const bf16* B, float* partials, int M, int N, int K, hipStream_t s);
+// pre_scale (nullable) [M]: factor of a row's products before the silu
+int launch_swiglu_rows64(compact_ctx* ctx, const bf16* A, const bf16* B, const float* pre_scale, bf16* act, int M, int F, int K,
+                         hipStream_t s);
 
 // mxfp4.hip : block-scaled 4-bit expert weights
 int mxfp4_ksplit(int K);
@@ -232,15 +240,6 @@ int launch_resid_norm_stream(compact_ctx* ctx, const bf16* X, const bf16* W, con
 bool resid_out_stream_supported(int M, int N, int K);
 int launch_resid_out_stream(compact_ctx* ctx, const bf16* X, const bf16* W, const float* resid, bf16* y, int M, int N, int K,
                             hipStream_t s);
-// gemv_stream_mt.hip : the output projection (+ residual, RMSNorm statistics) and the fused gate/up projection for
-// 17 .. 64 rows, whole K (same split over K and summation order as the kernels for at most 16 rows, so a row's result
-// does not depend on how many rows share the step)
-bool stream_mt_supported(int M, int N, int K);
-int launch_resid_norm_stream_mt(compact_ctx* ctx, const bf16* X, const bf16* W, const bf16* resid, const bf16* g, float* h_out,
-                                bf16* hg_out, float* ssq_parts, int M, int N, int K, hipStream_t s);
-bool swiglu_mt_supported(int M, int F, int K);
-int launch_swiglu_mt(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* act, int M, int F, int K, const RowNorm* norm,
-                     hipStream_t s);
 // m = bf16(hg / rms): finishes the RMSNorm whose sums of squares are in `norm`
 int launch_rownorm_apply(compact_ctx* ctx, const bf16* hg, const RowNorm& norm, bf16* m, int rows, int d, hipStream_t s);
 

@@ -58,6 +58,7 @@ struct GemmParams {
     int K;
     int n_mtiles, n_ntiles;
     int r_f32;  // the residual R is fp32 rather than bf16
+    const float* pre_scale;   // SwiGLU: factor of every row's products before the silu (null = 1)
     GroupedArgs g;
 };
 
@@ -168,11 +169,13 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const floatx4 (&
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 floatx4 v;
+                const float ps = EPI == 1 && p.pre_scale ? p.pre_scale[m0 + min(wrow + i * 32 + g * 16 + r, rows_valid - 1)] : 1.0f;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float a = acc[2 * i + g][j][e];
                     if (EPI == 1) {
-                        const float u = acc[2 * i + g][j + TN / 2][e];
+                        a *= ps;
+                        const float u = acc[2 * i + g][j + TN / 2][e] * ps;
                         a = a / (1.0f + __expf(-a)) * u;
                     }
                     v[e] = a;
@@ -541,9 +544,10 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_small_kernel(const Gemm
             n = min(tp.n0 + row, p.N - 1);
         wsrc[u] = tp.W + (int64_t)n * p.K + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
     }
-    const int nk = p.K / BK;
+    // gridDim.y slices of K (partial results, slice by slice in C): this workgroup's k-tiles
+    const int k_lo = p.K / BK * blockIdx.y / gridDim.y, nk = p.K / BK * (blockIdx.y + 1) / gridDim.y - k_lo;
     auto gload = [&](int kt, int stage) {
-        const int k0 = min(kt, nk - 1) * BK;   // past the end of K: the last k-tile again, into a stage nobody reads
+        const int k0 = (k_lo + min(kt, nk - 1)) * BK;   // past the end: the last k-tile again, into a stage nobody reads
         bf16* dst = lds + stage * STAGE;
 #pragma unroll
         for (int u = 0; u < XU; ++u) load16_to_lds(xsrc[u] + k0, dst + (wave * XU + u) * 8 * BK);
@@ -588,12 +592,14 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_small_kernel(const Gemm
         fill = fill + 1 == S ? 0 : fill + 1;
     }
     ring_barrier<0>();   // the repeated loads must not land in the slabs
-    store_tile<EPI, GROUPED, TM, TN>(p, acc, reinterpret_cast<float*>(smem) + wave * 32 * (WOUT + 4), lane, wm * WTM, tp.rows_valid,
+    GemmParams q = p;
+    if (EPI == 2) q.C = reinterpret_cast<bf16*>(reinterpret_cast<float*>(p.C) + (size_t)blockIdx.y * p.M * p.N);
+    store_tile<EPI, GROUPED, TM, TN>(q, acc, reinterpret_cast<float*>(smem) + wave * 32 * (WOUT + 4), lane, wm * WTM, tp.rows_valid,
                                      tp.m0, tp.n0 + wn * WOUT);
 }
 
 template <int BM, int BN, int WM, int WN, int S, int EPI, bool GROUPED>
-static int launch_small(compact_ctx* ctx, GemmParams& p, hipStream_t s) {
+static int launch_small(compact_ctx* ctx, GemmParams& p, hipStream_t s, int k_slices = 1) {
     constexpr int OUTN = EPI == 1 ? BN / 2 : BN;
     if (!GROUPED) p.n_mtiles = (int)((p.M + BM - 1) / BM);
     p.n_ntiles = (p.N + OUTN - 1) / OUTN;
@@ -607,7 +613,7 @@ static int launch_small(compact_ctx* ctx, GemmParams& p, hipStream_t s) {
     }
     const int64_t tiles = (int64_t)p.n_mtiles * p.n_ntiles;
     if (tiles == 0) return COMPACT_OK;
-    kern<<<dim3((unsigned)tiles), WM * WN * 64, smem, s>>>(p);
+    kern<<<dim3((unsigned)tiles, (unsigned)k_slices), WM * WN * 64, smem, s>>>(p);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
@@ -739,4 +745,45 @@ int launch_gemm_bf16(compact_ctx* ctx, const bf16* A, const bf16* B, const void*
     if (epilogue == 1) return launch_form<1, false>(ctx, form, p, s);
     if (epilogue == 2) return launch_form<2, false>(ctx, form, p, s);
     return launch_form<0, false>(ctx, form, p, s);
+}
+
+// ---------------------------------------------------------------------------
+// Decode steps of 17 .. 64 rows: the 64 x 64 form as a weight stream.  Its ring keeps 64 KB of loads in flight per
+// workgroup, two workgroups per CU, and the activations ride along by direct-to-LDS loads: the gate/up projection of the
+// 8B-shaped layer streams its 235 MB in 50 us at 48 rows, what a plain read of them takes (kernels that stage the
+// activations through registers: 59 us at 24 rows, 69 us at 64, against 49 and 55 us so).  Projections whose column tiles
+// leave the chip idle are split over K into slices that depend on N and K alone: output and down projection together
+// 33 us at 24 rows and 38 us at 64 (46 and 56 us before), the step at 64 rows 272 -> 243 us.
+// ---------------------------------------------------------------------------
+int gemm_rows64_slices(int N, int K) {
+    const int tiles = (N + 63) / 64;
+    return std::max(1, std::min(256 / tiles, (K + 511) / 512));
+}
+
+int launch_gemm_rows64(compact_ctx* ctx, const bf16* A, const bf16* B, float* partials, int M, int N, int K, hipStream_t s) {
+    if (M < 1 || M > 64) return set_err(ctx, COMPACT_ESHAPE, "weight-streaming GEMM takes 1..64 activation rows");
+    if (K % GEMM_BK != 0 || N % 8 != 0) return set_err(ctx, COMPACT_ESHAPE, "bf16 GEMM needs K % 64 == 0 and N % 8 == 0");
+    GemmParams p{};
+    p.X = A;
+    p.W = B;
+    p.C = reinterpret_cast<bf16*>(partials);
+    p.M = M;
+    p.N = N;
+    p.K = K;
+    return launch_small<64, 64, 2, 2, 5, 2, false>(ctx, p, s, gemm_rows64_slices(N, K));
+}
+
+int launch_swiglu_rows64(compact_ctx* ctx, const bf16* A, const bf16* B, const float* pre_scale, bf16* act, int M, int F, int K,
+                         hipStream_t s) {
+    if (M < 1 || M > 64) return set_err(ctx, COMPACT_ESHAPE, "weight-streaming GEMM takes 1..64 activation rows");
+    if (K % GEMM_BK != 0 || F % 8 != 0) return set_err(ctx, COMPACT_ESHAPE, "bf16 GEMM needs K % 64 == 0 and N % 8 == 0");
+    GemmParams p{};
+    p.X = A;
+    p.W = B;
+    p.C = act;
+    p.pre_scale = pre_scale;
+    p.M = M;
+    p.N = F;
+    p.K = K;
+    return launch_small<64, 64, 2, 2, 5, 1, false>(ctx, p, s);
 }
