@@ -765,10 +765,17 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
             TRY(launch_residual_reduce(ctx, b.partials, ks, b.h, y, N, c.d_model, s));
         }
     } else {
-        if (pending_norm) TRY(launch_rownorm_apply(ctx, (const bf16*)b.hg, rn, (bf16*)b.m, N, c.d_model, s));
         int32_t* idx = route && route->d_expert_idx ? route->d_expert_idx : b.idx;
         float* gate = route && route->d_gate ? route->d_gate : b.gate;
-        TRY(launch_moe_route(ctx, b.m, w->w_router, N, idx, gate, b.logits, s, b.partials));
+        // few routed rows: router, top-k and routing plan in two launches, the end of the RMSNorm riding in the first
+        const bool fused_route = moe_route_plan_supported(c, N);
+        if (fused_route) {
+            TRY(launch_moe_route_plan(ctx, (const bf16*)b.hg, pending_norm ? &rn : nullptr, (bf16*)b.m, (const bf16*)w->w_router, N,
+                                      idx, gate, b.partials, 16, b.plan, s));
+        } else {
+            if (pending_norm) TRY(launch_rownorm_apply(ctx, (const bf16*)b.hg, rn, (bf16*)b.m, N, c.d_model, s));
+            TRY(launch_moe_route(ctx, b.m, w->w_router, N, idx, gate, b.logits, s, b.partials));
+        }
         if (bf && N * c.top_k <= 256) {
             // few rows per expert: stream every routed expert's weights once (split-K
             // partials in the expert-sorted row order), SwiGLU, down projection, and a
@@ -777,7 +784,7 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
             // into tiles of 16, one grid slice each: an expert with more than 16 rows (possible
             // beyond 16 blocks) is streamed once per tile.
             const int rk = N * c.top_k;
-            TRY(launch_moe_plan(ctx, idx, gate, N, 16, b.plan, s));
+            if (!fused_route) TRY(launch_moe_plan(ctx, idx, gate, N, 16, b.plan, s));
             const bool q4 = w->w_exp_gate_up_q != nullptr;   // block-scaled 4-bit copy of the experts
             // the tile map lists the tiles (then -1): at most one per routed row, and no more than experts + rows / 16
             const int n_listed = std::min(rk, c.n_experts + rk / 16);

@@ -211,6 +211,8 @@ int skinny_ksplit(int M, int N, int K);
 int launch_gemm_skinny(compact_ctx* ctx, const bf16* A, const bf16* B, float* partials, int M, int N, int K,
                        int ks, hipStream_t s, const bf16* norm_g = nullptr, float* norm_ssq_parts = nullptr);
 bool skinny_norm_in_supported(int M, int N, int K);
+int launch_gemm_skinny_rownorm(compact_ctx* ctx, const bf16* hg, const RowNorm& norm, bf16* m_out, const bf16* B, float* partials,
+                               int M, int N, int K, int ks, hipStream_t s);
 // the same per expert, for routed decode rows: expert e multiplies the rows offsets[e] ..
 // offsets[e+1]-1 of the expert-sorted order (at most 16; X is read through a_gather when
 // given); partials[ks][total_rows][N] keep the sorted order
@@ -285,6 +287,11 @@ struct MoePlan {              // device buffers carved from the workspace
 int launch_moe_route(compact_ctx* ctx, const void* m, const void* w_router, int64_t rows, int32_t* idx,
                      float* gate, float* logits, hipStream_t s,
                      float* partials_ws = nullptr);   // partials_ws: [ks][rows][E] scratch; enables the few-rows path
+// decode: router logits of a few rows, top-k and the routing plan (tiles of mtile rows) in two launches.  hg / norm given:
+// m is formed from them on the way (at most 16 rows).  partials_ws: [ks][rows][E] scratch
+bool moe_route_plan_supported(const compact_layer_cfg& c, int rows);
+int launch_moe_route_plan(compact_ctx* ctx, const bf16* hg, const RowNorm* norm, bf16* m, const bf16* w_router, int rows,
+                          int32_t* idx, float* gate, float* partials_ws, int mtile, const MoePlan& plan, hipStream_t s);
 int launch_moe_plan(compact_ctx* ctx, const int32_t* idx, const float* gate, int64_t rows, int mtile,
                     const MoePlan& plan, hipStream_t s);
 // decode: y[t] = h[t] + sum_j gate * (sum over K-slices of partials[slot_of[t*k + j]]), one rounding

@@ -45,9 +45,13 @@ struct SkinnyGroup {
 // staged operand is bf16(x * g) and the workgroups of the first column tile leave
 // ssq_parts[slice][row] = sum of x^2 over the slice; the consumer of the partials
 // multiplies by 1 / rms.
+// Back half of one (null m_out: off): X holds x * g, the staged operand is bf16(X / rms) with 1 / rms from the column-group
+// sums in `rn`, and the workgroups of the first column tile leave it in m_out as well.
 struct SkinnyNormIn {
     const bf16* g = nullptr;
     float* ssq_parts = nullptr;
+    RowNorm rn;
+    bf16* m_out = nullptr;
 };
 
 // RING < SKINNY_STEPS: only the first RING loads of the slice go out at once, the rest one per k-step as the
@@ -114,6 +118,35 @@ __global__ __launch_bounds__(WAVES * 64, RING < SKINNY_STEPS ? 2 : 1) void gemm_
             for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
             if (lane == 0 && blockIdx.y == 0 && row < M) nin.ssq_parts[(size_t)slice * M + row] = ss;
             if (lane < cpr) *reinterpret_cast<bf16x8*>(xs + row * LDX + lane * 8) = v;
+        }
+    } else if (!GROUPED && MT == 1 && nin.m_out) {
+        constexpr int RW = 16 / WAVES, PMAX = 8;   // rows per wavefront; parts per lane (nparts <= 512)
+        float pv[RW][PMAX];
+        bf16x8 v[RW];
+        // all loads before the first sum, none of them conditional (past the end: a piece that is dropped)
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int row = min(wave + i * WAVES, M - 1);
+            v[i] = *reinterpret_cast<const bf16x8*>(X + (size_t)row * K + k0 + min(lane, cpr - 1) * 8);
+#pragma unroll
+            for (int u = 0; u < PMAX; ++u) pv[i][u] = nin.rn.ssq_parts[(size_t)min(lane + 64 * u, nin.rn.nparts - 1) * M + row];
+        }
+        float ss[RW];
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int row = wave + i * WAVES;
+            ss[i] = 0.f;
+#pragma unroll
+            for (int u = 0; u < PMAX; ++u) ss[i] += lane + 64 * u < nin.rn.nparts ? pv[i][u] : 0.f;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) ss[i] += __shfl_xor(ss[i], o, 64);
+            const float rs = 1.0f / sqrtf(ss[i] * nin.rn.inv_d + nin.rn.eps);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[i][j] = row < M ? (bf16)((float)v[i][j] * rs) : (bf16)0.f;
+            if (lane < cpr) {
+                *reinterpret_cast<bf16x8*>(xs + row * LDX + lane * 8) = v[i];
+                if (blockIdx.y == 0 && row < M) *reinterpret_cast<bf16x8*>(nin.m_out + (size_t)row * K + k0 + lane * 8) = v[i];
+            }
         }
     } else {
         for (int q = t; q < MT * 16 * cpr; q += WAVES * 64) {
@@ -350,6 +383,19 @@ int launch_gemm_skinny(compact_ctx* ctx, const bf16* A, const bf16* B, float* pa
         default: return fat ? launch_skinny_cfg<4, 16, 6>(ctx, A, B, partials, M, N, K, ks, nin, s)
                             : launch_skinny_cfg<4, 8>(ctx, A, B, partials, M, N, K, ks, nin, s);
     }
+}
+
+// partials of m B^T for at most 16 rows, m = bf16(hg / rms) left in m_out: the end of an RMSNorm rides in the projection
+// that consumes it
+int launch_gemm_skinny_rownorm(compact_ctx* ctx, const bf16* hg, const RowNorm& norm, bf16* m_out, const bf16* B, float* partials,
+                               int M, int N, int K, int ks, hipStream_t s) {
+    if (M < 1 || M > 16 || N % 16 != 0 || K % 64 != 0 || norm.nparts > 512)
+        return set_err(ctx, COMPACT_ESHAPE, "folding the end of an RMSNorm into the weight-streaming GEMM needs at most 16 rows");
+    if (ks != skinny_ksplit(M, N, K)) return set_err(ctx, COMPACT_EINVAL, "unexpected K split");
+    SkinnyNormIn nin;
+    nin.rn = norm;
+    nin.m_out = m_out;
+    return launch_skinny_cfg<1, 4>(ctx, hg, B, partials, M, N, K, ks, nin, s);
 }
 
 // Per-expert weight streaming for routed decode rows (at most 16 rows per expert):
