@@ -125,6 +125,19 @@ def sub_batch(inp, blocks):
     return one
 
 
+@pytest.mark.parametrize("head_dim", [128, 64])
+def test_merging_few_and_many_records_of_a_block(head_dim):
+    """The merge of a block's split-KV records runs with 64 threads when no block of the call has more than 32 of them and
+    with 256 otherwise, up to 128 (head_dim 128) or 256 (64) at a time: 1, 2, 8, 9, 32, 33 and 131 records, against the
+    checker, and the short blocks again in a call without the long ones, bit for bit."""
+    layer = LayerConfig(d_model=512, n_q_heads=2, n_kv_heads=1, head_dim=head_dim, ffn_dim=256, rope_theta=500000.0, dtype="bf16")
+    lens = [33300, 8192, 8190, 2100, 2046, 256, 7]
+    inp = make_inputs(Workload("records", layer, lens, 7, 2), gain_jitter=True)
+    full = check_dense(inp)
+    few = H.gpu_forward(sub_batch(inp, range(2, 7)))
+    assert np.array_equal(few["y_decode"], full["y_decode"][:, 2:])
+
+
 @pytest.mark.parametrize("n_blocks", [17, 32, 33, 64])
 def test_dense_decode_with_17_to_64_blocks(n_blocks):
     """More than 16 decode rows: the whole-K weight-streaming kernels with two to four groups of 16 rows per weight
