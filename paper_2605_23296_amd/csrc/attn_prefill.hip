@@ -94,6 +94,13 @@ __device__ __forceinline__ void phase_barrier() {
 #endif
 }
 
+// The value itself, computed where it stands: keeps what derives from it in a rare branch from being hoisted out of the
+// loop into registers that the loop needs (a spilled register's reload would wait for every load in flight).
+__device__ __forceinline__ int here(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // PP = false: workgroup = 4 wavefronts = 128 query rows x one query head, two workgroups per
 // CU, two-stage K/V ring, every wavefront runs QK^T -> softmax -> PV per tile.
 // PP = true ("ping-pong"): workgroup = 8 wavefronts = the same 128 query rows x TWO query heads
@@ -123,7 +130,7 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
     const TileItem it = qtiles[blockIdx.x];
     const BlockMeta bm = meta[it.block];
     const int t = threadIdx.x, lane = t & 63;
-    const int wave = t >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int grp = PP ? wave >> 2 : 0, wq = wave & 3;   // head of the pair, 32-row slice of the query tile
     const int head = PP ? blockIdx.y * 2 + grp : blockIdx.y;
     const int kvh = (PP ? blockIdx.y * 2 : blockIdx.y) / (Hq / Hkv);   // the pair shares it (even GQA group)
@@ -176,7 +183,7 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
     }
     const unsigned slab_bytes = (unsigned)bm.capacity * HD * 2u;   // one KV head's K slab, and its V^T slab
     const __amdgpu_buffer_rsrc_t krsrc = raw_buffer(kslab, slab_bytes), vrsrc = raw_buffer(vslab, slab_bytes);
-    auto issue_tile = [&](int kt, int stage) {
+    auto issue_tile = [&](int kt, int stage, bool whole = false) __attribute__((always_inline)) {   // whole: known to lie inside the cache
         const int kv0 = kt * KV_TILE;
         bf16* ks = lds + stage * 2 * KTILE;
         bf16* vs = ks + KTILE;
@@ -198,7 +205,7 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
                     buf_load16_to_lds(vrsrc, vs + (i * NW + wave) * 64 * 8, voff[i] * 2u + vt_off, 0);
                 }
             }
-        } else if (kv0 + KV_TILE <= len) {   // the whole tile lies inside the cache: no clamps
+        } else if (whole || kv0 + KV_TILE <= len) {   // the whole tile lies inside the cache: no clamps
             const bf16* kt0 = kslab + (size_t)kv0 * HD;
             const bf16* vt0 = vslab + kv0;
 #pragma unroll
@@ -207,9 +214,10 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
                 load16_to_lds(vt0 + voff[i], vs + (i * NW + wave) * 64 * 8);
             }
         } else {   // last tile of the block: rows past the end are clamped (their scores are masked)
+            const int ln = here(lane);
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
-                const int L = (i * NW + wave) * 64 + lane;
+                const int L = (i * NW + wave) * 64 + ln;
                 const int krow = L / KCH, kc = (L % KCH) ^ swz<KCH>(krow);
                 const int tok = min(kv0 + krow, len - 1);
                 load16_to_lds(kslab + (size_t)tok * HD + kc * 8, ks + (i * NW + wave) * 64 * 8);
@@ -225,9 +233,10 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
         const int kv0 = kt * KV_TILE;
         if (kv0 + KV_TILE <= len) return;
         bf16* vs = lds + stage * 2 * KTILE + KTILE;
+        const int ln = PP ? here(lane) : lane;
 #pragma unroll
         for (int i = 0; i < NLD; ++i) {
-            const int L = (i * NW + wave) * 64 + lane;
+            const int L = (i * NW + wave) * 64 + ln;
             const int vrow = L >> 3, vc = (L & 7) ^ swz<8>(vrow);
             if (kv0 + vc * 8 + 8 > len) {
                 bf16x8 v = *reinterpret_cast<bf16x8*>(vs + (size_t)L * 8);
@@ -263,7 +272,7 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
     };
     // ---- online softmax of the tile: sacc -> pf.  `diag` (wavefront-uniform) is set only for tiles
     // that straddle the wavefront's diagonal, so the tiles below it carry no compare/select.
-    auto softmax = [&](bool diag, int kv0) {
+    auto softmax = [&](bool diag, int kv0) __attribute__((always_inline)) {
         if (__builtin_amdgcn_readfirstlane((int)diag)) {
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt)
@@ -279,7 +288,7 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
         // loss and the tile's maximum is never formed.  Otherwise (always on the first tile, whose
         // reference is -inf: the sum comes out inf or NaN) the exact maximum is taken, the reference
         // moves there, the accumulators are rescaled and the probabilities are formed again.
-        auto probs = [&]() {
+        auto probs = [&]() __attribute__((always_inline)) {
             const float neg_m = -m_run;
             float ps = 0.f;
 #pragma unroll
@@ -331,30 +340,44 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
             }
         }
     };
-    // Matrix phase of the ping-pong loop: PV of the previous tile, then QK^T of this one, as ONE stream of
-    // 4 DT + 2 KK operand reads and as many MFMAs.  The other wavefront on this SIMD issues no MFMA in the
-    // meantime, so nothing hides an LDS round trip: the reads run AHEAD fragments ahead of the MFMAs (pinned).
-    auto pv_qk = [&](const bf16* vs, const bf16* ks) {
-        constexpr int NV = 4 * DT, NK = 2 * KK, AHEAD = 6;
-        bf16x8 fr[NV + NK];
+    // Matrix phase of the ping-pong loop: PV of the previous tile, then QK^T of this one.  The other wavefront on this SIMD
+    // issues no MFMA in the meantime, so nothing hides an LDS round trip here: the first half of the V^T operands is read
+    // in the softmax phase, the other reads go out two per MFMA as the registers come free and are complete well before
+    // the first MFMA that needs one of them (the compiler waits for every read in flight at the first use of a batch:
+    // with reads six fragments ahead it did so every six MFMAs, and the phase took 1.7 x its MFMAs).  Eight blocks of 4096
+    // tokens, 32 + 8 heads of 128: 1354 -> 1169 us; one block's 2048 rows behind its cache: 313 -> 265 us.  What is left
+    // of a slot over its 32 MFMAs is the issue of the staging loads (400 cycles for a tile's, in the softmax phase; spread
+    // over the softmax or at its start they cost more) and the barriers.
+    constexpr int NVH = PP ? 2 * DT : 1;
+    bf16x8 vfr[NVH];
+    auto read_v = [&](const bf16* vs, int u0, bf16x8 (&f)[NVH]) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int d = 0; d < DT; ++d) {
                 const int row = d * 32 + r;
-                fr[u * DT + d] = *reinterpret_cast<const bf16x8*>(vs + row * KV_TILE + (((u * 2 + h) ^ swz<8>(row)) << 3));
+                f[u * DT + d] = *reinterpret_cast<const bf16x8*>(vs + row * KV_TILE + ((((u0 + u) * 2 + h) ^ swz<8>(row)) << 3));
             }
+    };
+    auto pv_half = [&](int u0, const bf16x8 (&f)[NVH]) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int d = 0; d < DT; ++d) oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[u * DT + d], pf[u0 + u], oacc[d], 0, 0, 0);
+    };
+    auto pv_qk = [&](const bf16* vs, const bf16* ks) {
+        constexpr int NK = 2 * KK;
+        bf16x8 v2[NVH], fr[NK];
+        read_v(vs, 2, v2);
+        pv_half(0, vfr);
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) {
                 const int row = tt * 32 + pi_r;
-                fr[NV + kk * 2 + tt] = *reinterpret_cast<const bf16x8*>(ks + row * HD + (((kk * 2 + h) ^ swz<KCH>(row)) << 3));
+                fr[kk * 2 + tt] = *reinterpret_cast<const bf16x8*>(ks + row * HD + (((kk * 2 + h) ^ swz<KCH>(row)) << 3));
             }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int d = 0; d < DT; ++d) oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[u * DT + d], pf[u], oacc[d], 0, 0, 0);
+        pv_half(2, v2);
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
@@ -363,14 +386,14 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
         for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt)
-                sacc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[NV + kk * 2 + tt], qf[kk], sacc[tt], 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);   // LDS reads
+                sacc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[kk * 2 + tt], qf[kk], sacc[tt], 0, 0, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
 #pragma unroll
-        for (int i = 0; i < NV + NK - AHEAD; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+        for (int i = 0; i < (NVH + NK) / 2; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);   // two LDS reads
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 2 * NVH + NK - 1 - (NVH + NK) / 2, 0);
     };
     // a tile wholly above this wavefront's diagonal is skipped; `diag`: some entry of it may be masked
     auto active = [&](int kt) { return kt * KV_TILE <= q_hi_wave; };
@@ -435,18 +458,14 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
         }
         phase_barrier();
         if (grp == 1) phase_barrier();
-        for (int kt = 0; kt <= n_tiles; ++kt) {
+        auto step = [&](int kt) __attribute__((always_inline)) {
             const bool do_pv = kt > 0 && active(kt - 1), do_qk = kt < n_tiles && active(kt);
             __builtin_amdgcn_s_setprio(3);   // the matrix phase is the one the slot waits for
-            if (do_pv && do_qk) {
-                pv_qk(lds + ((kt - 1) & 3) * 2 * KTILE + KTILE, lds + (kt & 3) * 2 * KTILE);
-            } else {
-                if (do_pv) pv_mm(lds + ((kt - 1) & 3) * 2 * KTILE + KTILE);
-                if (do_qk) qk(lds + (kt & 3) * 2 * KTILE);
-            }
+            if (do_pv) pv_mm(lds + ((kt - 1) & 3) * 2 * KTILE + KTILE);
+            if (do_qk) qk(lds + (kt & 3) * 2 * KTILE);
             __builtin_amdgcn_s_setprio(0);
             phase_barrier();
-            if (kt == n_tiles) break;
+            if (kt == n_tiles) return;
             if (active(kt)) softmax(diag(kt), kt * KV_TILE);
             const int t_wait = kt + 1 + grp, t_issue = kt + 2 + grp;
             if (t_wait < n_tiles) {
@@ -455,7 +474,28 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
             }
             if (t_issue < n_tiles) issue_tile(t_issue, t_issue & 3);
             phase_barrier();
+        };
+        step(0);
+        // The tiles below the diagonal whose successors up to t_issue lie wholly inside the cache: the same phases with no
+        // branch but the softmax's, which leaves the registers to read the V^T operands ahead.  The wavefronts of a
+        // workgroup leave this loop at different tiles; either form passes two barriers per tile.
+        int kt = 1;
+        const int kt_end = min((q_lo_wave + 1) / KV_TILE, min(len / KV_TILE, n_tiles) - 2 - grp);
+        if (kt < kt_end) read_v(lds + KTILE, 0, vfr);
+#pragma unroll 1
+        for (; kt < kt_end; ++kt) {
+            __builtin_amdgcn_s_setprio(3);
+            pv_qk(lds + ((kt - 1) & 3) * 2 * KTILE + KTILE, lds + (kt & 3) * 2 * KTILE);
+            __builtin_amdgcn_s_setprio(0);
+            phase_barrier();
+            read_v(lds + (kt & 3) * 2 * KTILE + KTILE, 0, vfr);
+            softmax(false, 0);
+            wait_vm<0>();
+            issue_tile(kt + 2 + grp, (kt + 2 + grp) & 3, true);
+            phase_barrier();
         }
+#pragma unroll 1
+        for (; kt <= n_tiles; ++kt) step(kt);
         if (grp == 0) phase_barrier();
         wait_vm<0>();
     }

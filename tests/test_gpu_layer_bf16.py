@@ -125,6 +125,19 @@ def sub_batch(inp, blocks):
     return one
 
 
+def test_prefill_attention_at_the_edges_of_its_key_tiles():
+    """head_dim 128, even group: a wavefront walks the key tiles wholly below its diagonal in one loop and the first tile,
+    the diagonal and the ragged end in another; block lengths around one to eight key tiles of 64 and one to four query
+    tiles of 128, every row against the checker, and each block alone bit for bit."""
+    layer = LayerConfig(d_model=512, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=256, rope_theta=500000.0, dtype="bf16")
+    lens = [63, 64, 65, 127, 128, 129, 191, 192, 193, 255, 256, 257, 319, 320, 321, 383, 385, 448, 511, 513]
+    inp = make_inputs(Workload("key_tiles", layer, lens, len(lens), 1), gain_jitter=True)
+    full = check_dense(inp, sampled=False)
+    for b in (2, 8, 11, 13, 17, 19):
+        one = H.gpu_forward(sub_batch(inp, [b]))
+        assert np.array_equal(one["y_prefill"], full["y_prefill"][inp.cu_seqlens[b]:inp.cu_seqlens[b + 1]])
+
+
 @pytest.mark.parametrize("head_dim", [128, 64])
 def test_merging_few_and_many_records_of_a_block(head_dim):
     """The merge of a block's split-KV records runs with 64 threads when no block of the call has more than 32 of them and
