@@ -43,8 +43,8 @@
  *    one for more (beyond 64 blocks the rows of a step go through the second
  *    family in groups of 33 .. 64, each group streaming the weights again): the
  *    caches and every output are bit-identical within a family; across the two,
- *    the caches still are, the outputs agree to rounding (the down projection
- *    adds over K in another order).
+ *    the caches still are, the outputs agree to rounding (the projections after
+ *    the attention add over K in another order).
  */
 #ifndef COMPACT_H
 #define COMPACT_H

@@ -370,9 +370,9 @@ int launch_gemm_skinny(compact_ctx* ctx, const bf16* A, const bf16* B, float* pa
         nin.ssq_parts = norm_ssq_parts;
     }
     // 49 .. 64 rows: two workgroups of 8 wavefronts fit a CU (the staged slice is 66 KB); a grid beyond what the
-    // chip holds at once (the down projection of the 8B-shaped layer: 28 slices x 32 column groups) goes to
-    // workgroups of 16 wavefronts with 6 of the 16 loads up front instead: again two per CU, all resident in one
-    // round, half the activation staging (39.9 -> 34.9 us; at 32 rows the same change cost 2 us and is not made)
+    // chip holds at once (d_model 8192: 16 slices x 80 column groups) goes to workgroups of 16 wavefronts with 6 of the
+    // 16 loads up front instead: again two per CU, half the activation staging (measured at N 4096, K 14336, 28 slices x
+    // 32 column groups: 39.9 -> 34.9 us; at 32 rows the same change cost 2 us and is not made)
     int n_cus = 0;
     if (int rc = device_cu_count(ctx, &n_cus)) return rc;
     const bool fat = (int64_t)ks * ((N + 127) / 128) > 2 * (int64_t)n_cus;
