@@ -74,6 +74,13 @@ int launch_rmsnorm(compact_ctx* ctx, const void* x, bool x_is_f32, const void* g
 // whole launch (32 tiles: 77 -> 17 us).  Bound with many tiles: HBM (read + write
 // of the rows, 8 x 4096: 4.6 TB/s).
 // ---------------------------------------------------------------------------
+// The rotation of one pair, shared with the decode epilogue.  The contraction is written out: left to the compiler it
+// changes with the code around it, and a row rotated in a prefill would no longer have the bits of the same row rotated
+// in a decode step.
+__device__ __forceinline__ void rotate(float lo, float hi, float c, float s, float& olo, float& ohi) {
+    olo = fmaf(lo, c, -(hi * s));
+    ohi = fmaf(hi, c, lo * s);
+}
 #define ROPE_BATCH 4   // pieces a thread loads before it stores any
 template <typename T>
 __global__ __launch_bounds__(NT) void rope_kvwrite_kernel(const BlockMeta* __restrict__ meta,
@@ -131,8 +138,7 @@ __global__ __launch_bounds__(NT) void rope_kvwrite_kernel(const BlockMeta* __res
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float2 t = cs[tok * half + c * 8 + j];
-                olo[j] = lo[u][j] * t.x - hi[u][j] * t.y;
-                ohi[j] = hi[u][j] * t.x + lo[u][j] * t.y;
+                rotate(lo[u][j], hi[u][j], t.x, t.y, olo[j], ohi[j]);
             }
             T* dst = rows + (size_t)tok * ld + head * hd + c * 8;
             if (head >= Hq) dst = kslab + ((size_t)(head - Hq) * bm.capacity + bm.prior + p0 + tok) * hd + c * 8;
@@ -248,8 +254,8 @@ __global__ __launch_bounds__(64) void decode_qkv_epilogue_kernel(const BlockMeta
         double sn, cn;
         sincos((double)(bm.pos_offset + p) * inv_freq, &sn, &cn);
         const float cf = (float)cn, sf = (float)sn;
-        const float olo = lo * cf - hi * sf;
-        const float ohi = hi * cf + lo * sf;
+        float olo, ohi;
+        rotate(lo, hi, cf, sf, olo, ohi);
         T* dst = head < Hq ? q_out + ((size_t)b * Hq + head) * hd + i
                            : kbase + bm.slab + ((size_t)(head - Hq) * bm.capacity + p) * hd + i;
         dst[0] = from_f32<T>(olo);

@@ -102,6 +102,34 @@ def test_gemm_fp32(M, N, K, epi, res):
     ref = O.silu(O.linear(A, Bm[:N])) * O.linear(A, Bm[N:]) if epi else O.linear(A, Bm) + (to_numpy_f64(r) if res else 0.0)
     assert rel_err(to_numpy_f64(c), ref) < 1e-5
 
+# ---------------------------------------------------------------- rotary embedding
+@pytest.mark.parametrize("hd,theta", [(64, 10000.0), (128, 500000.0)])
+def test_rotation_rounds_in_one_stated_order(hd, theta):
+    """fp32 storage shows every bit of the rotation: out_lo = fma(lo, cos, -(hi sin)), out_hi = fma(hi, cos, lo sin), as in
+    the decode step's epilogue, so that a row has the same bits whichever of the two rotates it.  The two factors of an fma
+    and its sum are formed in 64 bits here (the product is exact), cos and sin by another library: both can move a result
+    across a rounding boundary in about one of 2^28 cases.  The other order of out_hi moves 16 % of all values."""
+    layer = LayerConfig(d_model=256, n_q_heads=3, n_kv_heads=1, head_dim=hd, ffn_dim=256, rope_theta=theta, dtype="fp32")
+    lens = [70, 300]
+    lay = B.Layer(layer, None)
+    qkv = rnd((sum(lens), 5 * hd), torch.float32, 11)
+    raw = qkv.cpu().numpy().astype(np.float64).reshape(-1, 5, hd)
+    kv = B.KVCache(layer, [n + 2 for n in lens], "cuda", torch.float32)
+    lay.compact_rope_kvwrite([0, 70, 370], qkv, kv)
+    torch.cuda.synchronize()
+    pos = np.concatenate([np.arange(n) for n in lens]).astype(np.float64)
+    ang = pos[:, None, None] * np.exp2(-2.0 * np.arange(hd // 2) / hd * np.log2(theta))
+    f32 = lambda v: v.astype(np.float32)
+    c, s = f32(np.cos(ang)).astype(np.float64), f32(np.sin(ang)).astype(np.float64)
+    lo, hi = raw[:, :4, :hd // 2], raw[:, :4, hd // 2:]
+    ref = f32(np.concatenate([lo * c - f32(hi * s), hi * c + f32(lo * s)], axis=-1))
+    for b, n in enumerate(lens):
+        kv.h_len[b] = n
+    K = np.concatenate([kv.block_k(b).cpu().numpy() for b in range(2)])
+    q = qkv.cpu().numpy().reshape(-1, 5, hd)[:, :3]
+    assert np.mean(K[:, 0] != ref[:, 3]) < 1e-4
+    assert np.mean(q != ref[:, :3]) < 1e-4
+
 
 # ---------------------------------------------------------------- rotary + KV write, prefill attention
 def attention_case(layer, lens, seed, pos_offset=None, edit=None):
