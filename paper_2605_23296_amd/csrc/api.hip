@@ -698,22 +698,30 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
     const void* ffn_in = b.m;
     RowNorm rn{};
     bool pending_norm = false;
-    const bool many = bf && N > 16;   // 17 .. 64 rows: projections by the ring GEMM, split over K
+    // 17 .. 64 rows of a dense layer: projections by the ring GEMM, split over K.  A routed layer keeps the sums and the
+    // roundings of the kernels for at most 16 rows: its router chooses by them.
+    const bool many = bf && N > 16 && c.n_experts == 0;
+    const bool o_few = bf && resid_norm_stream_supported(N, c.d_model, Dq);
+    const bool o_routed = bf && N > 16 && c.n_experts > 0 && stream_mt_supported(N, c.d_model, Dq) &&
+                          resid_norm_stream_supported(16, c.d_model, Dq);
     const float* pre_scale = nullptr;
     if (many) {
         {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
             TRY(launch_gemm_rows64(ctx, (const bf16*)b.o, (const bf16*)w->w_o, b.partials, N, c.d_model, Dq, s));
         }
-        // a dense layer's gate/up projection applies 1 / rms to its products, so that its operand is rounded as in the
-        // kernels for at most 16 rows
-        float* rinv = c.n_experts == 0 ? b.ssq_parts : nullptr;
-        TRY(launch_residual_norm(ctx, b.partials, gemm_rows64_slices(c.d_model, Dq), x, w->g_ffn, b.h, b.m, N, s, rinv));
-        pre_scale = rinv;
-    } else if (bf && resid_norm_stream_supported(N, c.d_model, Dq)) {
+        // the gate/up projection applies 1 / rms to its products, so that its operand is rounded as in the kernels for at
+        // most 16 rows
+        TRY(launch_residual_norm(ctx, b.partials, gemm_rows64_slices(c.d_model, Dq), x, w->g_ffn, b.h, b.m, N, s, b.ssq_parts));
+        pre_scale = b.ssq_parts;
+    } else if (o_few || o_routed) {
         ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
-        TRY(launch_resid_norm_stream(ctx, (const bf16*)b.o, (const bf16*)w->w_o, (const bf16*)x, (const bf16*)w->g_ffn, b.h,
-                                     (bf16*)b.hg, b.ssq_parts, N, c.d_model, Dq, s));
+        if (o_few)
+            TRY(launch_resid_norm_stream(ctx, (const bf16*)b.o, (const bf16*)w->w_o, (const bf16*)x, (const bf16*)w->g_ffn, b.h,
+                                         (bf16*)b.hg, b.ssq_parts, N, c.d_model, Dq, s));
+        else
+            TRY(launch_resid_norm_stream_mt(ctx, (const bf16*)b.o, (const bf16*)w->w_o, (const bf16*)x, (const bf16*)w->g_ffn,
+                                            b.h, (bf16*)b.hg, b.ssq_parts, N, c.d_model, Dq, s));
         rn.ssq_parts = b.ssq_parts;
         rn.nparts = c.d_model / 16;
         rn.inv_d = 1.0f / (float)c.d_model;
@@ -768,12 +776,14 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
         int32_t* idx = route && route->d_expert_idx ? route->d_expert_idx : b.idx;
         float* gate = route && route->d_gate ? route->d_gate : b.gate;
         // few routed rows: router, top-k and routing plan in two launches, the end of the RMSNorm riding in the first
+        // (at most 16 rows; beyond them it is a launch of its own)
         const bool fused_route = moe_route_plan_supported(c, N);
+        const bool fold_norm = pending_norm && fused_route && N <= 16;
+        if (pending_norm && !fold_norm) TRY(launch_rownorm_apply(ctx, (const bf16*)b.hg, rn, (bf16*)b.m, N, c.d_model, s));
         if (fused_route) {
-            TRY(launch_moe_route_plan(ctx, (const bf16*)b.hg, pending_norm ? &rn : nullptr, (bf16*)b.m, (const bf16*)w->w_router, N,
+            TRY(launch_moe_route_plan(ctx, (const bf16*)b.hg, fold_norm ? &rn : nullptr, (bf16*)b.m, (const bf16*)w->w_router, N,
                                       idx, gate, b.partials, 16, b.plan, s));
         } else {
-            if (pending_norm) TRY(launch_rownorm_apply(ctx, (const bf16*)b.hg, rn, (bf16*)b.m, N, c.d_model, s));
             TRY(launch_moe_route(ctx, b.m, w->w_router, N, idx, gate, b.logits, s, b.partials));
         }
         if (bf && N * c.top_k <= 256) {

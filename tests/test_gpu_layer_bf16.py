@@ -354,6 +354,28 @@ def test_small_moe_layer_17_to_64_blocks(n_blocks):
     assert most > 16 or n_blocks < 40, most      # some expert needs more than one group of 16 rows
 
 
+@pytest.mark.parametrize("n_q_heads", [16, 4])
+@pytest.mark.parametrize("n_blocks", [17, 20, 33, 64, 70])
+def test_routed_steps_have_the_bits_of_small_batches(n_blocks, n_q_heads):
+    """A routed decode step does not change a block's bits when a 17th block joins it: the router chooses by the rows that
+    the output projection leaves, and at a near tie another rounding would change an expert.  Contraction lengths of that
+    projection with a whole-K kernel (2048) and without (512); routing tables, outputs and caches."""
+    layer = LayerConfig(d_model=512, n_q_heads=n_q_heads, n_kv_heads=2, head_dim=128, ffn_dim=256, n_experts=32, top_k=2,
+                        rope_theta=500000.0, dtype="bf16")
+    lens = [(7 * b) % 13 + 1 for b in range(n_blocks)]
+    inp = make_inputs(Workload("routed_rows", layer, lens, n_blocks, 4), gain_jitter=True)
+    full = H.gpu_forward_steps(inp)
+    for b0 in range(0, n_blocks, 16):
+        blocks = list(range(b0, min(b0 + 16, n_blocks)))
+        few = H.gpu_forward_steps(sub_batch(inp, blocks))
+        for s in range(4):
+            assert np.array_equal(few["idx_decode"][s], full["idx_decode"][s][blocks])
+            assert np.array_equal(few["gate_decode"][s], full["gate_decode"][s][blocks])
+        assert np.array_equal(few["y_decode"], full["y_decode"][:, blocks])
+        for i, b in enumerate(blocks):
+            assert np.array_equal(few["K"][i], full["K"][b]) and np.array_equal(few["V"][i], full["V"][b])
+
+
 def test_more_than_64_blocks_in_a_decode_step_dense_and_routed():
     """Beyond 64 decode rows the projections of a step run group of rows after group of rows (70 blocks: two groups
     of 35), the attention once for all blocks: every row of every step against the checker, dense and routed."""
