@@ -775,15 +775,13 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
     } else {
         int32_t* idx = route && route->d_expert_idx ? route->d_expert_idx : b.idx;
         float* gate = route && route->d_gate ? route->d_gate : b.gate;
-        // few routed rows: router, top-k and routing plan in two launches, the end of the RMSNorm riding in the first
-        // (at most 16 rows; beyond them it is a launch of its own)
+        // at most 16 rows: router, top-k and routing plan in two launches, the end of the RMSNorm riding in the first
         const bool fused_route = moe_route_plan_supported(c, N);
-        const bool fold_norm = pending_norm && fused_route && N <= 16;
-        if (pending_norm && !fold_norm) TRY(launch_rownorm_apply(ctx, (const bf16*)b.hg, rn, (bf16*)b.m, N, c.d_model, s));
         if (fused_route) {
-            TRY(launch_moe_route_plan(ctx, (const bf16*)b.hg, fold_norm ? &rn : nullptr, (bf16*)b.m, (const bf16*)w->w_router, N,
+            TRY(launch_moe_route_plan(ctx, (const bf16*)b.hg, pending_norm ? &rn : nullptr, (bf16*)b.m, (const bf16*)w->w_router, N,
                                       idx, gate, b.partials, 16, b.plan, s));
         } else {
+            if (pending_norm) TRY(launch_rownorm_apply(ctx, (const bf16*)b.hg, rn, (bf16*)b.m, N, c.d_model, s));
             TRY(launch_moe_route(ctx, b.m, w->w_router, N, idx, gate, b.logits, s, b.partials));
         }
         if (bf && N * c.top_k <= 256) {

@@ -291,8 +291,8 @@ struct MoePlan {              // device buffers carved from the workspace
 int launch_moe_route(compact_ctx* ctx, const void* m, const void* w_router, int64_t rows, int32_t* idx,
                      float* gate, float* logits, hipStream_t s,
                      float* partials_ws = nullptr);   // partials_ws: [ks][rows][E] scratch; enables the few-rows path
-// decode: router logits of a few rows, top-k and the routing plan (tiles of mtile rows) in two launches.  hg / norm given:
-// m is formed from them on the way (at most 16 rows).  partials_ws: [ks][rows][E] scratch
+// decode: router logits of at most 16 rows, top-k and the routing plan (tiles of mtile rows) in two launches.  hg / norm
+// given: m is formed from them on the way.  partials_ws: [ks][rows][E] scratch
 bool moe_route_plan_supported(const compact_layer_cfg& c, int rows);
 int launch_moe_route_plan(compact_ctx* ctx, const bf16* hg, const RowNorm* norm, bf16* m, const bf16* w_router, int rows,
                           int32_t* idx, float* gate, float* partials_ws, int mtile, const MoePlan& plan, hipStream_t s);

@@ -406,10 +406,11 @@ def test_moe_120b_shape_24_blocks_every_expert_takes_every_row():
     assert most == 24
 
 
-@pytest.mark.parametrize("n_blocks,experts,top_k", [(1, 16, 1), (3, 208, 5), (16, 256, 8), (32, 256, 8), (51, 48, 5), (64, 128, 4)])
+@pytest.mark.parametrize("n_blocks,experts,top_k", [(1, 16, 1), (3, 208, 5), (16, 256, 8), (17, 64, 3), (32, 256, 8), (51, 48, 5), (64, 128, 4)])
 def test_routed_decode_steps_at_the_edges_of_the_one_workgroup_routing(n_blocks, experts, top_k):
-    """Router, top-k and routing plan of a decode step in one workgroup: one routed row, 255 and 256 of them, more rows than
-    wavefronts, expert counts off and on the 64 a lane slot covers.  Routing tables and every row against the checker."""
+    """Router, top-k and routing plan of a decode step: up to 16 rows the last two in one workgroup (one routed row; a row
+    for every wavefront), from 17 rows apart (a plan of 255 and 256 routed rows); expert counts off and on the 64 a lane
+    slot covers.  Routing tables and every row against the checker."""
     layer = copy.deepcopy(SMALL_MOE)
     layer.n_experts, layer.top_k = experts, top_k
     wl = Workload("small_moe", layer, [(5 * b) % 11 + 1 for b in range(n_blocks)], n_blocks, 2)
