@@ -710,10 +710,13 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
             TRY(launch_gemm_rows64(ctx, (const bf16*)b.o, (const bf16*)w->w_o, b.partials, N, c.d_model, Dq, s));
         }
-        // the gate/up projection applies 1 / rms to its products, so that its operand is rounded as in the kernels for at
-        // most 16 rows
-        TRY(launch_residual_norm(ctx, b.partials, gemm_rows64_slices(c.d_model, Dq), x, w->g_ffn, b.h, b.m, N, s, b.ssq_parts));
-        pre_scale = b.ssq_parts;
+        // the gate/up operand is rounded as the kernels for at most 16 rows round it for a layer of this shape
+        NormRounding rounding = NORM_ONCE;
+        if (resid_norm_stream_supported(16, c.d_model, Dq))
+            rounding = skinny_swiglu_supported(16, c.ffn_dim, c.d_model) ? NORM_LATER : NORM_TWICE;
+        TRY(launch_residual_norm(ctx, b.partials, gemm_rows64_slices(c.d_model, Dq), x, w->g_ffn, b.h, b.m, N, s, rounding,
+                                 b.ssq_parts));
+        if (rounding == NORM_LATER) pre_scale = b.ssq_parts;
     } else if (o_few || o_routed) {
         ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
         if (o_few)

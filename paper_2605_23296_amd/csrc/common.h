@@ -143,10 +143,16 @@ int launch_rope_kvwrite(compact_ctx* ctx, const BlockMeta* d_meta, const TileIte
 int launch_decode_qkv_epilogue(compact_ctx* ctx, const BlockMeta* d_meta, int n_blocks, int step,
                                const float* partials, int ks, void* q_out, void* d_k, void* d_v,
                                hipStream_t s, const RowNorm* norm = nullptr);
-// decode: h = resid + sum partials; writes h and m = RMSNorm(h; g)
-// (rinv_out given: m = bf16(h * g) instead, and the rows' 1 / rms go there)
+// decode: h = resid + sum partials; writes h and the rows m that the projections after it read.  A row of m is rounded as
+// the step's other kernels round it, so that it does not depend on how many rows share the step:
+enum NormRounding {
+    NORM_ONCE,    // m = bf16(h g / rms)
+    NORM_TWICE,   // m = bf16(bf16(h g) / rms)
+    NORM_LATER    // m = bf16(h g), the rows' 1 / rms to rinv_out: the consumer multiplies its products by it
+};
 int launch_residual_norm(compact_ctx* ctx, const float* partials, int ks, const void* resid,
-                         const void* g, void* h_out, void* m_out, int rows, hipStream_t s, float* rinv_out = nullptr);
+                         const void* g, void* h_out, void* m_out, int rows, hipStream_t s,
+                         NormRounding rounding = NORM_ONCE, float* rinv_out = nullptr);
 // decode: act = silu(gate) * up from ks partials of the stacked gate/up projection
 int launch_swiglu_reduce(compact_ctx* ctx, const float* partials, int ks, void* act, int rows, int F,
                          hipStream_t s);

@@ -301,7 +301,7 @@ __device__ __forceinline__ float4 sum_slices4(const float* __restrict__ p, size_
 }
 
 // ---------------------------------------------------------------------------
-// Decode: h = resid + sum_s partial_s (kept in fp32), m = RMSNorm(h; g), or m = h * g with the rows' 1 / rms in rinv_out.
+// Decode: h = resid + sum_s partial_s (kept in fp32), m = RMSNorm(h; g) in one of the NormRounding forms.
 // One workgroup of 1024 threads per row, 4 columns per thread and trip (d <= RN_TRIPS * RN_NT * 4 = 8192): a row is one
 // or two trips, whose slices are requested together.  Latency-bound: with 256 threads and up to eight trips 10.5 us at 64
 // rows of 4096, 4 slices.
@@ -311,7 +311,7 @@ __device__ __forceinline__ float4 sum_slices4(const float* __restrict__ p, size_
 __global__ __launch_bounds__(RN_NT) void residual_norm_kernel(const float* __restrict__ partials, int ks, int rows,
                                                               const bf16* __restrict__ resid, const bf16* __restrict__ g,
                                                               float* __restrict__ h_out, bf16* __restrict__ m_out, int d,
-                                                              float eps, float* __restrict__ rinv_out) {
+                                                              float eps, NormRounding rounding, float* __restrict__ rinv_out) {
     __shared__ float red[RN_NT / WAVE];
     const int r = blockIdx.x;
     const size_t ps = (size_t)rows * d;
@@ -337,31 +337,34 @@ __global__ __launch_bounds__(RN_NT) void residual_norm_kernel(const float* __res
     ss = 0.f;
 #pragma unroll
     for (int i = 0; i < RN_NT / WAVE; ++i) ss += red[i];
-    float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    if (rinv_out) {   // the consumer applies the factor
-        if (threadIdx.x == 0) rinv_out[r] = inv;
-        inv = 1.0f;
+    const float inv = 1.0f / sqrtf(ss / (float)d + eps);
+    float first = inv, second = 1.0f;   // factors before and after a rounding to bf16 (a second one of 1 changes nothing)
+    if (rounding != NORM_ONCE) {
+        first = 1.0f;
+        second = rounding == NORM_TWICE ? inv : 1.0f;
     }
+    if (rounding == NORM_LATER && threadIdx.x == 0) rinv_out[r] = inv;
 #pragma unroll
     for (int it = 0; it < RN_TRIPS; ++it) {
         const int c = (it * RN_NT + threadIdx.x) * 4;
         if (c < d) {
             bf16x4 m;
-            m[0] = (bf16)(hv[it].x * inv * to_f32(gv[it][0]));
-            m[1] = (bf16)(hv[it].y * inv * to_f32(gv[it][1]));
-            m[2] = (bf16)(hv[it].z * inv * to_f32(gv[it][2]));
-            m[3] = (bf16)(hv[it].w * inv * to_f32(gv[it][3]));
+            m[0] = (bf16)((float)(bf16)(hv[it].x * first * to_f32(gv[it][0])) * second);
+            m[1] = (bf16)((float)(bf16)(hv[it].y * first * to_f32(gv[it][1])) * second);
+            m[2] = (bf16)((float)(bf16)(hv[it].z * first * to_f32(gv[it][2])) * second);
+            m[3] = (bf16)((float)(bf16)(hv[it].w * first * to_f32(gv[it][3])) * second);
             *reinterpret_cast<bf16x4*>(m_out + (size_t)r * d + c) = m;
         }
     }
 }
 
 int launch_residual_norm(compact_ctx* ctx, const float* partials, int ks, const void* resid, const void* g,
-                         void* h_out, void* m_out, int rows, hipStream_t s, float* rinv_out) {
+                         void* h_out, void* m_out, int rows, hipStream_t s, NormRounding rounding, float* rinv_out) {
     const compact_layer_cfg& c = ctx->cfg;
+    if (rounding == NORM_LATER && !rinv_out) return set_err(ctx, COMPACT_EINVAL, "no room for the rows' 1 / rms");
     if (c.d_model > RN_TRIPS * RN_NT * 4) return set_err(ctx, COMPACT_ESHAPE, "d_model above 8192 is not supported by the decode row kernels");
     residual_norm_kernel<<<rows, RN_NT, 0, s>>>(partials, ks, rows, (const bf16*)resid, (const bf16*)g, (float*)h_out, (bf16*)m_out,
-                                                c.d_model, c.rms_eps, rinv_out);
+                                                c.d_model, c.rms_eps, rounding, rinv_out);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
