@@ -228,7 +228,8 @@ int compact_layer_forward(compact_ctx* ctx, const compact_weights* w, int32_t n_
  * multiplied with the query heads of every worker whose prefix covers it, at
  * most 128 / (query heads per KV head) workers at a time).
  * bf16 storage only.  Errors as compact_decode_step; COMPACT_EINVAL for a
- * decreasing or out-of-range h_prefix_len.  The workspace must hold
+ * decreasing or out-of-range h_prefix_len; COMPACT_ECAPACITY where a worker's
+ * prefix and tail together span more than 1024 pieces of 256 rows.  The workspace must hold
  * compact_prefix_workspace_bytes(ctx, N, max h_prefix_len, max tail length). */
 int compact_prefix_workspace_bytes(const compact_ctx* ctx, int32_t n_workers, int32_t max_prefix_len,
                                    int32_t max_tail_len, size_t* bytes);

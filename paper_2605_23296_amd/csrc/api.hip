@@ -575,6 +575,7 @@ struct PrefixArgs {
     std::vector<int32_t> wl_off, wl;
     int64_t total_recs = 0;
     int max_list = 0;
+    int64_t max_span = 0;   // most 256-row pieces of a worker's prefix and tail
     size_t off_items = 0, off_wl_off = 0, off_wl = 0;   // byte offsets inside Plan::extra
     float* records = nullptr;
 };
@@ -1344,6 +1345,7 @@ static int build_prefix_plan(compact_ctx* ctx, int n_workers, const compact_kv* 
     pa.total_recs = rec;
     pa.wl_off.assign(1, 0);
     for (int b = 0; b < n_workers; ++b) {
+        pa.max_span = std::max(pa.max_span, ((int64_t)h_prefix_len[b] + 255) / 256 + ((int64_t)tails->h_len[b] + steps + 255) / 256);
         pa.max_list = std::max(pa.max_list, (int)lists[b].size());
         pa.wl.insert(pa.wl.end(), lists[b].begin(), lists[b].end());
         pa.wl_off.push_back((int32_t)pa.wl.size());
@@ -1356,6 +1358,13 @@ static int build_prefix_plan(compact_ctx* ctx, int n_workers, const compact_kv* 
     memcpy(plan.extra.data() + pa.off_items, pa.items.data(), pa.items.size() * sizeof(PrefixItem));
     memcpy(plan.extra.data() + pa.off_wl_off, pa.wl_off.data(), pa.wl_off.size() * 4);
     if (!pa.wl.empty()) memcpy(plan.extra.data() + pa.off_wl, pa.wl.data(), pa.wl.size() * 4);
+    return COMPACT_OK;
+}
+
+// The longest history of the prefix-aware calls: the pieces of 256 rows that a worker's prefix and tail span.
+constexpr int PREFIX_MAX_SPAN = 1024;
+static int check_prefix_span(compact_ctx* ctx, const PrefixArgs& pa) {
+    if (pa.max_span > PREFIX_MAX_SPAN) return set_err(ctx, COMPACT_ECAPACITY, "prefix longer than the prefix-aware combine supports");
     return COMPACT_OK;
 }
 
@@ -1396,11 +1405,14 @@ extern "C" int compact_prefix_decode_step(compact_ctx* ctx, const compact_weight
             const int len = tails->h_len[b];
             room = std::min(room, std::min(tails->h_capacity[b] - len, prefix_chunks_for(len + 1) * PREFIX_CHUNK - len));
         }
+        if (pa.max_span == PREFIX_MAX_SPAN)   // no further piece in any tail without a new check
+            for (int b = 0; b < n_workers; ++b) room = std::min(room, (tails->h_len[b] / 256 + 1) * 256 - tails->h_len[b]);
         Carver cv(d_workspace);
         DecodeBufs b;
         carve_decode(cv, ctx->cfg, n_workers, 1, b);
         (void)cv.take((size_t)pa.total_recs * ctx->cfg.n_kv_heads * (ctx->cfg.head_dim + 2) * 4);
         if (cv.off > ws_bytes) return set_err(ctx, COMPACT_EWORKSPACE, "workspace too small for this prefix-aware decode step");
+        TRY(check_prefix_span(ctx, pa));
         StepCache& sc = step_cache_begin(ctx);
         sc.plan = std::move(plan);
         sc.pa = std::move(pa);
@@ -1493,6 +1505,7 @@ extern "C" int compact_prefix_stack_forward(compact_ctx* ctx, int32_t n_layers, 
         end += align_up((size_t)N * c.d_model * es, 256);
     }
     if (end > ws_bytes) return set_err(ctx, COMPACT_EWORKSPACE, "workspace too small for this prefix-aware stack");
+    if (n_steps > 0) TRY(check_prefix_span(ctx, pa));
     for (int l = 0; l < n_layers; ++l) shared[l].h_len[0] = T;
 
     // every layer prefills the whole history as one causal block: its cache serves all workers
@@ -1537,6 +1550,7 @@ extern "C" int compact_attn_decode_prefix(compact_ctx* ctx, int32_t n_workers, c
     for (auto& m : plan.meta) m.len -= 1;
     const size_t need = (size_t)pa.total_recs * ctx->cfg.n_kv_heads * (ctx->cfg.head_dim + 2) * 4;
     if (!d_workspace || ws_bytes < need) return set_err(ctx, COMPACT_EWORKSPACE, "workspace too small for the prefix-aware records");
+    TRY(check_prefix_span(ctx, pa));
     TRY(upload_plan(ctx, plan, s));
     return launch_attn_decode_prefix_bf16(ctx, plan.d_meta, pa.shared, (const PrefixItem*)(plan.d_extra + pa.off_items),
                                           (int)pa.items.size(), (const int32_t*)(plan.d_extra + pa.off_wl_off),

@@ -212,6 +212,30 @@ def test_prefix_aware_calls_reject_bad_arguments_without_a_device():
                                              1 << 30, None) == 5
 
 
+def test_prefix_aware_calls_refuse_more_than_1024_pieces_of_256_rows_without_a_device():
+    """Prefix and tail of a worker, each in pieces of 256 rows; refused before anything is launched, by the step, the kernel
+    hook and the stack."""
+    lay = _fake_layer("dense_8x4096")
+    L, x, ws = lay.L, C.c_void_p(0x30000), C.c_void_p(0x40000)
+    rows = 1 << 19
+    shared, _ks = _kv([rows], [rows])
+    for prefix, lens in (((100, 1023 * 256 + 1), [0, 0]), ((100, 1023 * 256), [0, 256]), ((rows, rows), [1, 1]),
+                         ((100, 300000), [5, 5])):
+        tails, kt = _kv([1024, 1024], lens)
+        pl = (C.c_int32 * 2)(*prefix)
+        assert L.compact_prefix_decode_step(lay.ctx, C.byref(lay.w), 2, x, C.byref(shared), pl, C.byref(tails), x, None, ws,
+                                            1 << 40, None) == 3
+        assert b"prefix longer" in L.compact_last_error(lay.ctx)
+        assert list(kt["len"]) == lens
+        hook, _kh = _kv([1024, 1024], [n + 1 for n in lens])
+        assert L.compact_attn_decode_prefix(lay.ctx, 2, x, C.byref(shared), pl, C.byref(hook), x, ws, 1 << 40, None) == 3
+        assert b"prefix longer" in L.compact_last_error(lay.ctx)
+        empty, _ke = _kv([rows], [0])
+        warr, sarr, tarr = (B.Weights * 1)(lay.w), (B.KV * 1)(empty), (B.KV * 1)(tails)
+        assert L.compact_prefix_stack_forward(lay.ctx, 1, warr, 2, pl, rows, x, 1, x, sarr, tarr, x, ws, 1 << 42, None) == 3
+        assert b"prefix longer" in L.compact_last_error(lay.ctx)
+
+
 def test_stack_call_rejects_bad_arguments_without_a_device():
     lay = _fake_layer()
     L, ctx = lay.L, lay.ctx
