@@ -223,14 +223,17 @@ int compact_layer_forward(compact_ctx* ctx, const compact_weights* w, int32_t n_
  * [N, d] holds worker b's new token at rotary position h_prefix_len[b] +
  * tails->h_len[b]; its K/V row is appended to tail b, it attends the shared rows
  * 0..h_prefix_len[b]-1 and tail rows 0..h_len[b] inclusive, tails->h_len[b] is
- * incremented, d_y [N, d] receives the layer outputs.  The shared rows are read
- * from memory once per step for all workers together (a 512-row chunk is
- * multiplied with the query heads of every worker whose prefix covers it, at
- * most 128 / (query heads per KV head) workers at a time).
+ * incremented, d_y [N, d] receives the layer outputs.  The shared rows are cut
+ * into work items of 128, 256 or 512 rows by shared->h_len[0] and n_kv_heads
+ * alone, so a worker's results do not depend on the other workers.  An item is
+ * multiplied with the query heads of the workers whose prefix covers it, up to
+ * 128 / (query heads per KV head) of them; its rows are read once for these
+ * together, and once more for every further group of as many workers.
  * bf16 storage only.  Errors as compact_decode_step; COMPACT_EINVAL for a
  * decreasing or out-of-range h_prefix_len; COMPACT_ECAPACITY where a worker's
- * prefix and tail together span more than 1024 pieces of 256 rows.  The workspace must hold
- * compact_prefix_workspace_bytes(ctx, N, max h_prefix_len, max tail length). */
+ * prefix and tail together span more than 1024 pieces of 256 rows.  The
+ * workspace must hold compact_prefix_workspace_bytes(ctx, N, max h_prefix_len,
+ * max tail length). */
 int compact_prefix_workspace_bytes(const compact_ctx* ctx, int32_t n_workers, int32_t max_prefix_len,
                                    int32_t max_tail_len, size_t* bytes);
 int compact_prefix_decode_step(compact_ctx* ctx, const compact_weights* w, int32_t n_workers,

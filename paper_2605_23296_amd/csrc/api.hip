@@ -262,7 +262,7 @@ static int decode_max_ksplit(const compact_layer_cfg& c, int N) {
 }
 
 static int chunks_for(int len) { return (len + DECODE_CHUNK - 1) / DECODE_CHUNK; }
-static int prefix_chunks_for(int len) { return (len + PREFIX_CHUNK - 1) / PREFIX_CHUNK; }
+static int tail_chunks_for(int len) { return (len + PREFIX_TAIL_CHUNK - 1) / PREFIX_TAIL_CHUNK; }
 
 extern "C" int compact_workspace_bytes(const compact_ctx* ctx, int64_t max_tokens, int32_t max_blocks,
                                        int32_t max_kv_len, size_t* bytes) {
@@ -1264,9 +1264,30 @@ extern "C" int compact_stack_forward(compact_ctx* ctx, int32_t n_layers, const c
 // ---------------------------------------------------------------------------
 // prefix-aware layout: shared prefix + private tails
 // ---------------------------------------------------------------------------
+// Rows of a work item of the shared history, by its length and the KV heads alone (a worker's sums then do not depend on
+// the other workers).  An item is a workgroup per KV head that walks its rows 32 at a time: short histories need many
+// short ones, and long ones few, since every item leaves a record per query head that is written and merged.  Lines at
+// 128 workgroups of 128 rows and at 256 of 256 rows; measured (8 KV heads of 128, attention and merge from the host, us,
+// items of 512 / 256 / 128 rows): one worker, 2048 rows 23.5 / 19.5 / 18.4, 4096 rows 23.6 / 19.8 / 19.7, 8192 rows
+// 24.2 / 23.0 / 25.4; 16 workers, 8192 rows 26.9 / 26.0 / 29.2; 8 workers, 32768 rows 41.1 / 43.5 / 51.3; 24 workers, 98304
+// rows 106 / 136 / 189.  2 KV heads: 8 workers, 32768 rows 32.1 / 30.7 / 36.0.  Where an item has few columns (one worker,
+// or no grouping) only one or two of its eight wavefronts multiply, and a kernel that splits the rows over all eight was
+// 3 to 11 % faster between 4096 and 32768 rows; from 49152 rows on it was slower there too.
+static const int64_t prefix_item_limit[2] = {128 * 128, 256 * 256};   // most rows x KV heads for items of 128 and of 256 rows
+static int prefix_item_rows(const compact_layer_cfg& c, int shared_len) {
+    const int64_t rows = (int64_t)shared_len * c.n_kv_heads;
+    return rows <= prefix_item_limit[0] ? 128 : rows <= prefix_item_limit[1] ? 256 : 512;
+}
+// most items that a prefix of at most `len` rows can have, whatever the length of the history that it is part of
+static int prefix_max_items(const compact_layer_cfg& c, int len) {
+    const int l128 = (int)std::min<int64_t>(len, prefix_item_limit[0] / c.n_kv_heads);
+    const int l256 = (int)std::min<int64_t>(len, prefix_item_limit[1] / c.n_kv_heads);
+    return std::max({(l128 + 127) / 128, (l256 + 255) / 256, (int)(((int64_t)len + 511) / 512)});
+}
+
 static int64_t prefix_max_recs(const compact_layer_cfg& c, int n_workers, int max_prefix_len, int max_tail_len) {
     const int G = c.n_q_heads / c.n_kv_heads;
-    return ((int64_t)prefix_chunks_for(max_prefix_len) * n_workers + (int64_t)n_workers * prefix_chunks_for(max_tail_len + 1)) * G;
+    return ((int64_t)prefix_max_items(c, max_prefix_len) + tail_chunks_for(max_tail_len + 1)) * n_workers * G;
 }
 
 extern "C" int compact_prefix_workspace_bytes(const compact_ctx* ctx, int32_t n_workers, int32_t max_prefix_len,
@@ -1326,18 +1347,19 @@ static int build_prefix_plan(compact_ctx* ctx, int n_workers, const compact_kv* 
     std::vector<std::vector<int32_t>> lists(n_workers);
     int32_t rec = 0;
     int w0 = 0;
-    for (int r0 = 0; r0 < max_prefix; r0 += PREFIX_CHUNK) {
+    const int item_rows = prefix_item_rows(c, shared_len);
+    for (int r0 = 0; r0 < max_prefix; r0 += item_rows) {
         while (h_prefix_len[w0] <= r0) ++w0;   // first worker whose prefix reaches into the chunk
         for (int wf = w0; wf < n_workers; wf += PFX_COLS / G) {
-            PrefixItem it{r0, std::min(PREFIX_CHUNK, max_prefix - r0), wf, std::min(PFX_COLS / G, n_workers - wf), 0, rec};
+            PrefixItem it{r0, std::min(item_rows, max_prefix - r0), wf, std::min(PFX_COLS / G, n_workers - wf), 0, rec};
             for (int b = wf; b < wf + it.nw; ++b) lists[b].push_back((int32_t)pa.items.size());
             pa.items.push_back(it);
             rec += it.nw * G;
         }
     }
     for (int b = 0; b < n_workers; ++b)
-        for (int r0 = 0; r0 < tails->h_len[b] + steps; r0 += PREFIX_CHUNK) {
-            PrefixItem it{r0, PREFIX_CHUNK, b, 1, 1, rec};
+        for (int r0 = 0; r0 < tails->h_len[b] + steps; r0 += PREFIX_TAIL_CHUNK) {
+            PrefixItem it{r0, PREFIX_TAIL_CHUNK, b, 1, 1, rec};
             lists[b].push_back((int32_t)pa.items.size());
             pa.items.push_back(it);
             rec += G;
@@ -1380,7 +1402,7 @@ extern "C" int compact_prefix_decode_step(compact_ctx* ctx, const compact_weight
     hipStream_t s = (hipStream_t)hip_stream;
     // a plan built for one step covers every further step that opens no new chunk in any tail
     // (the record slots, hence the workspace, stay the same) and still fits the slabs
-    int k = -1, room = PREFIX_CHUNK;
+    int k = -1, room = PREFIX_TAIL_CHUNK;
     std::vector<int64_t> geom;
     if (ctx->step_cache && ctx->step_cache->valid && h_prefix_len && n_workers >= 1 && n_workers <= 64 &&
         shared->d_k && shared->d_v && shared->h_len && shared->h_capacity && shared->h_slab_offset && tails->d_k &&
@@ -1403,10 +1425,8 @@ extern "C" int compact_prefix_decode_step(compact_ctx* ctx, const compact_weight
             geom.push_back(tails->h_capacity[b]);
             geom.push_back(tails->h_slab_offset[b]);
             const int len = tails->h_len[b];
-            room = std::min(room, std::min(tails->h_capacity[b] - len, prefix_chunks_for(len + 1) * PREFIX_CHUNK - len));
+            room = std::min(room, std::min(tails->h_capacity[b] - len, tail_chunks_for(len + 1) * PREFIX_TAIL_CHUNK - len));
         }
-        if (pa.max_span == PREFIX_MAX_SPAN)   // no further piece in any tail without a new check
-            for (int b = 0; b < n_workers; ++b) room = std::min(room, (tails->h_len[b] / 256 + 1) * 256 - tails->h_len[b]);
         Carver cv(d_workspace);
         DecodeBufs b;
         carve_decode(cv, ctx->cfg, n_workers, 1, b);

@@ -3,13 +3,14 @@
 // one shared cache of the whole history): worker b attends rows
 // 0 .. prefix_len[b]-1 of the SHARED slab plus its own private tail.
 //
-// Cascade over the shared rows: a work item is a PREFIX_CHUNK-row chunk of the
-// shared slab together with the workers whose prefix reaches into it (a suffix of
-// the workers, prefixes being nested; at most PFX_COLS query columns = workers x
-// heads of the KV group, more workers make further items over the same rows).  A
-// worker's private tail is a one-worker item of the same kernel.  Every item
-// leaves one record (un-normalised output, max, sum) per (worker, head); a second
-// kernel merges a worker's records.
+// Cascade over the shared rows: a work item is a chunk of 128, 256 or 512 rows of
+// the shared slab (by the length of the history: short ones need the workgroups, long
+// ones the fewer records) together with the workers whose prefix reaches into it (a
+// suffix of the workers, prefixes being nested; at most PFX_COLS query columns =
+// workers x heads of the KV group, more workers make further items over the same
+// rows).  A worker's private tail is cut into one-worker items of the same kernel.
+// Every item leaves one record (un-normalised output, max, sum) per (worker, head); a
+// second kernel merges a worker's records.
 //
 //  * a workgroup of 8 wavefronts walks its item in tiles of 32 rows, two workgroups
 //    per CU.  K and V^T land in LDS by direct 16-byte loads (swizzled slots), read
@@ -36,7 +37,6 @@
 #define PFX_PAIR (2 * PFX_TILE)
 #define PFX_VSLOTS 3
 static_assert(PFX_COLS == PFX_WAVES * 16, "one 16-column MFMA group per wavefront");
-static_assert(PREFIX_CHUNK % PFX_TILE == 0, "an item is a whole number of tiles");
 
 __device__ __forceinline__ float pfx_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(PFX_WAVES * 64, 4) void attn_decode_prefix_kernel(
     int cap, n_rows;   // rows of the item that exist at all
     if (it.tail) {
         const BlockMeta bm = tail_meta[it.w0];
-        n_rows = min(bm.len + step + 1 - it.row0, PREFIX_CHUNK);
+        n_rows = min(bm.len + step + 1 - it.row0, PREFIX_TAIL_CHUNK);
         if (n_rows <= 0) return;   // a tail chunk this step does not reach yet
         cap = bm.capacity;
         kslab = ktail + bm.slab + (size_t)kvh * cap * HD;
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(PFX_WAVES * 64, 4) void attn_decode_prefix_kernel(
 // chunks the step has not reached yet carry weight zero and are never read (nobody
 // wrote them).  256 threads: HD / 2 threads span a record, 512 / HD records are read
 // side by side, 16 loads in flight per thread (4: 30.6 us at 24 workers, 16: 24.5 us); all sums run in a fixed order.
-#define PFX_MAX_ITEMS 1024
+#define PFX_MAX_ITEMS 1088   // a prefix and a tail of 1024 pieces of 256 rows, up to 64 of them in halves
 #define PFX_CT 256
 #define PFX_FLIGHT 16
 template <int HD>

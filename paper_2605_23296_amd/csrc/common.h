@@ -21,9 +21,9 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // (one work item of its kernel).  Fixed, so that the split of a block's cache
 // depends on that block's length only.
 #define DECODE_CHUNK 256
-// The same for the prefix-aware (cascade) decode attention, and the most query columns (workers x heads of a KV group)
-// of one of its work items.
-#define PREFIX_CHUNK 512
+// Prefix-aware (cascade) decode attention: rows of a work item of a worker's private tail, and the most query columns
+// (workers x heads of a KV group) of an item.  The items of the shared rows: prefix_item_rows() in api.hip.
+#define PREFIX_TAIL_CHUNK 256
 #define PFX_COLS 128
 // Query rows per prefill-attention tile and token rows per rotary/KV-write tile.
 #define PREFILL_QTILE 128

@@ -34,7 +34,7 @@ def fill_cache(kv, b, K, V):
     ("moe_16x8192", [64, 300, 301], [5, 1, 257]),                             # head_dim 64, group of 8
     ("dense_8x4096", [0, 0, 40], [3, 1, 2]),                                  # workers without any prefix
     ("dense_8x4096", [90 * (b + 1) for b in range(24)], [1 + b % 3 for b in range(24)]),   # 24 workers: six column groups
-    # items of 1024 rows walked in pieces of 256: prefixes on and around both boundaries, tails that reach into a second item
+    # prefixes on and around item boundaries, tails that reach into further items
     ("dense_8x4096", [255, 256, 1023, 1024, 1025, 2047, 2048, 2049, 2304, 3000], [1, 2, 1030, 1, 3, 1024, 1, 2, 1025, 5]),
     ("moe_16x8192", [1023, 1025, 2300] + [2560] * 10, [1, 260, 3] + [2] * 10),            # head_dim 64: 104 columns, seven groups
     ("dense_8x4096", [1500] * 30, [1 + b % 2 for b in range(30)]),                          # 120 columns: eight column groups
@@ -66,16 +66,37 @@ def test_prefix_decode_attention_scores_that_grow_or_fall_along_the_history(sign
 
 @pytest.mark.parametrize("wl", ["dense_8x4096", "moe_16x8192"])
 def test_prefix_decode_attention_kernel_tile_edges(wl):
-    """Prefixes and tails on and around the 32-row tiles, the 64-row V pairs and the 512-row items; enough workers that the
-    query columns of an item (128) overflow into a second one."""
+    """Prefixes and tails on and around the 32-row tiles, the 64-row V pairs and item edges; enough workers that the query
+    columns of an item (128) overflow into a second one."""
     edges = [1, 31, 32, 33, 63, 64, 65, 96, 127, 511, 512, 513, 543, 544, 545, 1023, 1024, 1025, 1057, 1057]
     prefix_kernel_case(WORKLOADS[wl].layer, edges + [1100] * 15, [1, 2, 31, 32, 33] * 6 + [64, 65, 512, 513, 96])
 
 
-def prefix_kernel_case(layer, prefix, tail, grow=None):
-    N, Hq, Hkv, hd = len(prefix), layer.n_q_heads, layer.n_kv_heads, layer.head_dim
+@pytest.mark.parametrize("hkv,hd,group,rows", [
+    (8, 128, 4, 2048), (8, 128, 4, 2049), (8, 128, 4, 8192), (8, 128, 4, 8193),     # last histories of 128- and 256-row items
+    (1, 64, 16, 16384), (1, 64, 16, 16385), (2, 64, 3, 8193), (16, 128, 1, 4097)])
+def test_prefix_decode_attention_kernel_item_heights(hkv, hd, group, rows):
+    """Work items of 128, 256 and 512 rows, chosen by the length of the history and the KV heads: prefixes on and around the
+    item edges in histories on both sides of the lines, more columns than an item takes.  A worker alone, and the workers of
+    short prefixes alone (their workspace sized for those prefixes), have the same bits."""
+    layer = LayerConfig(d_model=256, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=hd, ffn_dim=256, rope_theta=500000.0, dtype="bf16")
+    prefix = [0, 1, 127, 128, 129, 255, 256, 257, 384, 511, 512, 513, 767, 768, 1024, 1025] + [1500] * 20 + [min(2048, rows), rows]
+    tail = [1 + (37 * b) % 70 for b in range(len(prefix))]
+    tail[3:9] = [127, 128, 129, 255, 256, 257]
+    every = prefix_kernel_case(layer, prefix, tail, rows=rows)
+    for pick in ([len(prefix) - 1], [11], list(range(16))):
+        some = prefix_kernel_case(layer, prefix, tail, rows=rows, pick=pick)
+        assert np.array_equal(some, every[pick])
+
+
+def prefix_kernel_case(layer, prefix, tail, grow=None, rows=None, pick=None):
+    """rows: length of the shared history (default: the longest prefix); pick: the workers that take part (default: all)."""
+    Hq, Hkv, hd = layer.n_q_heads, layer.n_kv_heads, layer.head_dim
     lay = B.Layer(layer, None)
-    T = max(prefix)
+    T = rows or max(prefix)
+    pick = list(range(len(prefix))) if pick is None else pick
+    seeds = pick
+    prefix, tail, N = [prefix[b] for b in pick], [tail[b] for b in pick], len(pick)
     shared = B.KVCache(layer, [max(T, 8) + 9], DEV, torch.bfloat16)
     tails = B.KVCache(layer, [t + 5 for t in tail], DEV, torch.bfloat16)
     for c in (shared, tails):
@@ -85,15 +106,15 @@ def prefix_kernel_case(layer, prefix, tail, grow=None):
     if grow is not None:   # scores that grow along the history: k[j][0] = grow * j against q[0] = 16
         Kp[:, :, 0] = (torch.arange(T, device=Kp.device, dtype=torch.float32) * grow).to(Kp.dtype)[:, None]
     fill_cache(shared, 0, Kp, Vp)
-    Kt = [rnd((t, Hkv, hd), 10 + b) for b, t in enumerate(tail)]
-    Vt = [rnd((t, Hkv, hd), 30 + b) for b, t in enumerate(tail)]
+    Kt = [rnd((t, Hkv, hd), 10 + b) for b, t in zip(seeds, tail)]
+    Vt = [rnd((t, Hkv, hd), 30 + b) for b, t in zip(seeds, tail)]
     for b in range(N):
         fill_cache(tails, b, Kt[b], Vt[b])
-    q = rnd((N, Hq * hd), 3)
+    q = rnd((64, Hq * hd), 3)[seeds].contiguous()
     if grow is not None:
         q.view(N, Hq, hd)[:, :, 0] = 16.0
     o = torch.full((N, Hq * hd), float("nan"), dtype=torch.bfloat16, device=DEV)
-    lay.ws = torch.empty(lay.prefix_workspace_bytes(N, max(T, 1), max(tail)), dtype=torch.uint8, device=DEV)
+    lay.ws = torch.empty(lay.prefix_workspace_bytes(N, max(max(prefix), 1), max(tail)), dtype=torch.uint8, device=DEV)
     lay.compact_attn_decode_prefix(q, shared, prefix, tails, o)
     torch.cuda.synchronize()
     got = to_numpy_f64(o).reshape(N, Hq, hd)
@@ -104,6 +125,7 @@ def prefix_kernel_case(layer, prefix, tail, grow=None):
         ref = O.gqa_attention(to_numpy_f64(q[b]).reshape(1, Hq, hd), K, V, visible=np.array([K.shape[0]]))[0]
         assert vec_rel_err(got[b], ref) < TOL, (b, vec_rel_err(got[b], ref))
         assert rel_err(got[b], ref) < ELEM_TOL
+    return got
 
 
 def run_prefix_layer(inp, n_steps):
