@@ -337,23 +337,29 @@ __global__ __launch_bounds__(DEC_WAVES * 64, HD == 128 ? 3 : 4) void attn_decode
 
 // Merges the chunks of one (block, head) and normalises.  HD / 4 threads span a record, CT * 4 / HD records are read side
 // by side, up to DEC_CFLIGHT per thread at once: they go out before the weights exp2(m_ch - M) are formed, so a merge of up
-// to 128 records (32 k tokens) is one trip to memory.  Calls of at most DEC_CSHORT chunks per block run with 64 threads and
-// little LDS instead of 256 (64 blocks of 2 k tokens: 4.9 us against 7.3).  The sums run over the same interleaved groups
-// of chunks either way, in an order that depends on the number of chunks alone.  Bound: launch and latency.  One block of
-// 32 k tokens 9.8 -> 5.0 us (before: a thread per output element, 8 loads in flight, the weights summed one by one).
+// to 128 records (32 k tokens) is one trip to memory.  Three forms by the most chunks of a block of the call: beyond
+// DEC_CSHORT 256 threads; up to there 64 threads and little LDS (64 blocks of 2 k tokens: 4.9 us against 7.3); and where a
+// thread has at most DEC_CTINY records 64 threads with 40 registers instead of 100 that leave out the steps for chunks that
+// are not there (200 blocks of 100 .. 300 tokens, 64 heads of 64, with the attention: 29.3 and 43.7 us in the second form,
+// 25.4 and 39.3 in this one).  The sums run over the same interleaved groups of chunks in all of them, in an order that
+// depends on the number of chunks alone.  Bound: launch and latency.  One block of 32 k tokens 9.8 -> 5.0 us (before: a
+// thread per output element, 8 loads in flight, the weights summed one by one).
 #define COMBINE_MAX_CHUNKS 2048
 #define DEC_CSHORT 32
 #define DEC_CT 256
 #define DEC_CFLIGHT 16
-template <int HD, bool SHORT>
-__global__ __launch_bounds__(SHORT ? 64 : DEC_CT) void attn_decode_combine_kernel(const BlockMeta* __restrict__ meta, int step,
-                                                                                  int max_chunks, const float* __restrict__ partials,
-                                                                                  bf16* __restrict__ o, int Hq,
-                                                                                  const int32_t* __restrict__ qrow, int64_t n_rec) {
+#define DEC_CTINY 4
+enum { MERGE_FEW, MERGE_SHORT, MERGE_LONG };
+template <int HD, int FORM>
+__global__ __launch_bounds__(FORM == MERGE_LONG ? DEC_CT : 64) void attn_decode_combine_kernel(
+    const BlockMeta* __restrict__ meta, int step, int max_chunks, const float* __restrict__ partials, bf16* __restrict__ o, int Hq,
+    const int32_t* __restrict__ qrow, int64_t n_rec) {
+    constexpr bool SHORT = FORM != MERGE_LONG, FEW = FORM == MERGE_FEW;
+    constexpr int FLIGHT = FEW ? DEC_CTINY : DEC_CFLIGHT;
     constexpr int CT = SHORT ? 64 : DEC_CT;
     constexpr int TPR = HD / 4, NS = CT / TPR;             // threads per record, records side by side
     constexpr int GROUPS = DEC_CT / TPR, NA = GROUPS / NS;   // groups of chunks, and those of one thread
-    static_assert(DEC_CFLIGHT % NA == 0 && (!SHORT || DEC_CFLIGHT * NS >= DEC_CSHORT), "whole rounds over the groups");
+    static_assert(FLIGHT % NA == 0 && (FORM != MERGE_SHORT || FLIGHT * NS >= DEC_CSHORT), "whole rounds over the groups");
     __shared__ float2 sml[SHORT ? DEC_CSHORT : COMBINE_MAX_CHUNKS];
     __shared__ floatx4 part[GROUPS * TPR];
     const int b = blockIdx.y, head = blockIdx.x, t = threadIdx.x, lane = t & 63;
@@ -363,29 +369,33 @@ __global__ __launch_bounds__(SHORT ? 64 : DEC_CT) void attn_decode_combine_kerne
     const size_t rec0 = ((size_t)b * Hq + head) * max_chunks;
     const floatx4* val = reinterpret_cast<const floatx4*>(partials + rec0 * HD);                        // [chunk][HD]
     const float2* ml = reinterpret_cast<const float2*>(partials + (size_t)n_rec * HD + rec0 * 2);       // [chunk](max, sum)
-    floatx4 v[DEC_CFLIGHT];
+    floatx4 v[FLIGHT];
     auto load = [&](int c0) {
 #pragma unroll
-        for (int u = 0; u < DEC_CFLIGHT; ++u)
+        for (int u = 0; u < FLIGHT; ++u)
             if (c0 + u * NS < nch) v[u] = val[(size_t)min(c0 + u * NS + sl, nch - 1) * TPR + e4];
     };
     for (int ch = t; ch < nch; ch += CT) sml[ch] = ml[ch];
     load(0);
     lds_barrier();
-    // every wavefront forms the maximum and the normaliser itself
+    // every wavefront forms the maximum and the normaliser itself; FEW: every `span` lanes hold the same chunks and the
+    // butterflies start there (the steps left out would add zeros)
     float mm = -INFINITY, l = 0.f;
-    for (int ch = lane; ch < nch; ch += 64) mm = fmaxf(mm, sml[ch].x);
+    const int span = !FEW ? 64 : nch > 1 ? 1 << (32 - __builtin_clz(nch - 1)) : 1;
+    for (int ch = lane & (span - 1); ch < nch; ch += 64) mm = fmaxf(mm, sml[ch].x);
 #pragma unroll
-    for (int ofs = 32; ofs > 0; ofs >>= 1) mm = fmaxf(mm, __shfl_xor(mm, ofs, 64));
-    for (int ch = lane; ch < nch; ch += 64) l += fast_exp2(sml[ch].x - mm) * sml[ch].y;
+    for (int ofs = 32; ofs > 0; ofs >>= 1)
+        if (!FEW || ofs < span) mm = fmaxf(mm, __shfl_xor(mm, ofs, 64));
+    for (int ch = lane & (span - 1); ch < nch; ch += 64) l += fast_exp2(sml[ch].x - mm) * sml[ch].y;
 #pragma unroll
-    for (int ofs = 32; ofs > 0; ofs >>= 1) l += __shfl_xor(l, ofs, 64);
+    for (int ofs = 32; ofs > 0; ofs >>= 1)
+        if (!FEW || ofs < span) l += __shfl_xor(l, ofs, 64);
     floatx4 acc[NA];
 #pragma unroll
     for (int j = 0; j < NA; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
     for (int c0 = 0;;) {
 #pragma unroll
-        for (int u = 0; u < DEC_CFLIGHT; ++u) {
+        for (int u = 0; u < FLIGHT; ++u) {
             const int ch = c0 + u * NS + sl;
             if (ch < nch) {
                 const float wgt = fast_exp2(sml[ch].x - mm);
@@ -393,17 +403,20 @@ __global__ __launch_bounds__(SHORT ? 64 : DEC_CT) void attn_decode_combine_kerne
                 for (int e = 0; e < 4; ++e) acc[u % NA][e] += wgt * v[u][e];
             }
         }
-        c0 += DEC_CFLIGHT * NS;
+        c0 += FLIGHT * NS;
         if (SHORT || c0 >= nch) break;
         load(c0);
     }
+    const int groups = FEW ? min(nch, GROUPS) : GROUPS;   // (the others hold zeros)
 #pragma unroll
-    for (int j = 0; j < NA; ++j) part[j * CT + t] = acc[j];
+    for (int j = 0; j < NA; ++j)
+        if (j * NS < groups) part[j * CT + t] = acc[j];
     __syncthreads();
     if (t >= TPR) return;
     floatx4 sum = part[t];
 #pragma unroll
     for (int j = 1; j < GROUPS; ++j) {
+        if (j >= groups) break;
         const floatx4 p = part[j * TPR + t];
 #pragma unroll
         for (int e = 0; e < 4; ++e) sum[e] += p[e];
@@ -440,10 +453,15 @@ int launch_attn_decode_bf16(compact_ctx* ctx, const BlockMeta* d_meta, const Til
     const size_t smem = rec_slots * slot_bytes;
     if (n_rec * (int64_t)1 > INT32_MAX) return set_err(ctx, COMPACT_ECAPACITY, "more split-KV records than the decode attention indexes");
     if (max_chunks > COMBINE_MAX_CHUNKS) return set_err(ctx, COMPACT_ECAPACITY, "KV cache longer than the decode combine supports");
-    const bool brief = max_chunks <= DEC_CSHORT;
-    const int ct = brief ? 64 : DEC_CT;
-    auto combine = c.head_dim == 128 ? (brief ? attn_decode_combine_kernel<128, true> : attn_decode_combine_kernel<128, false>)
-                                     : (brief ? attn_decode_combine_kernel<64, true> : attn_decode_combine_kernel<64, false>);
+    const int side = 64 * 4 / c.head_dim;   // records that 64 threads read side by side
+    const int form = max_chunks <= DEC_CTINY * side ? MERGE_FEW : max_chunks <= DEC_CSHORT ? MERGE_SHORT : MERGE_LONG;
+    const int ct = form == MERGE_LONG ? DEC_CT : 64;
+    auto combine = c.head_dim == 128 ? (form == MERGE_FEW     ? attn_decode_combine_kernel<128, MERGE_FEW>
+                                        : form == MERGE_SHORT ? attn_decode_combine_kernel<128, MERGE_SHORT>
+                                                              : attn_decode_combine_kernel<128, MERGE_LONG>)
+                                     : (form == MERGE_FEW     ? attn_decode_combine_kernel<64, MERGE_FEW>
+                                        : form == MERGE_SHORT ? attn_decode_combine_kernel<64, MERGE_SHORT>
+                                                              : attn_decode_combine_kernel<64, MERGE_LONG>);
     if (c.head_dim == 128) {
         {
             ProfileScope ps(ctx, COMPACT_K_ATTN_DECODE, s);

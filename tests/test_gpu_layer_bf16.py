@@ -140,15 +140,16 @@ def test_prefill_attention_at_the_edges_of_its_key_tiles():
 
 @pytest.mark.parametrize("head_dim", [128, 64])
 def test_merging_few_and_many_records_of_a_block(head_dim):
-    """The merge of a block's split-KV records runs with 64 threads when no block of the call has more than 32 of them and
-    with 256 otherwise, up to 128 (head_dim 128) or 256 (64) at a time: 1, 2, 8, 9, 32, 33 and 131 records, against the
-    checker, and the short blocks again in a call without the long ones, bit for bit."""
+    """The merge of a block's split-KV records has three forms by the most records of a block of the call: up to 8 (head_dim
+    128) or 16 (64), up to 32, and more, up to 128 or 256 at a time.  1, 2, 8, 9, 16, 17, 32, 33 and 131 records, against the
+    checker, and the shorter blocks again in calls without the longer ones, bit for bit."""
     layer = LayerConfig(d_model=512, n_q_heads=2, n_kv_heads=1, head_dim=head_dim, ffn_dim=256, rope_theta=500000.0, dtype="bf16")
-    lens = [33300, 8192, 8190, 2100, 2046, 256, 7]
-    inp = make_inputs(Workload("records", layer, lens, 7, 2), gain_jitter=True)
+    lens = [33300, 8192, 8190, 4350, 4090, 2100, 2046, 256, 7]
+    inp = make_inputs(Workload("records", layer, lens, 9, 2), gain_jitter=True)
     full = check_dense(inp)
-    few = H.gpu_forward(sub_batch(inp, range(2, 7)))
-    assert np.array_equal(few["y_decode"], full["y_decode"][:, 2:])
+    for first in (2, 4, 6, 7, 8):
+        few = H.gpu_forward(sub_batch(inp, range(first, 9)))
+        assert np.array_equal(few["y_decode"], full["y_decode"][:, first:])
 
 
 @pytest.mark.parametrize("n_blocks", [17, 32, 33, 64])
