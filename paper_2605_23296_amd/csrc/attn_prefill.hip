@@ -130,7 +130,10 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
     const TileItem it = qtiles[blockIdx.x];
     const BlockMeta bm = meta[it.block];
     const int t = threadIdx.x, lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    // A scalar wavefront index saves vector address work: 4 % at head_dim 64.  The four-wavefront kernel at head_dim 128 gains
+    // 1 to 2 % on a block of 8000 tokens by it and loses 3 to 4 % on blocks of 1000 to 2000, where few workgroups leave the
+    // longer scalar chain in front of every load bare: there it stays in a vector register.
+    const int wave = PP || HD == 64 ? __builtin_amdgcn_readfirstlane(t >> 6) : t >> 6;
     const int grp = PP ? wave >> 2 : 0, wq = wave & 3;   // head of the pair, 32-row slice of the query tile
     const int head = PP ? blockIdx.y * 2 + grp : blockIdx.y;
     const int kvh = (PP ? blockIdx.y * 2 : blockIdx.y) / (Hq / Hkv);   // the pair shares it (even GQA group)
