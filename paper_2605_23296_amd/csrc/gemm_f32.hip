@@ -3,8 +3,8 @@
 //
 // The mode's layers are small, so what bounds a call is latency: a decode step
 // multiplies a handful of rows with a few hundred weight rows.  Hence small
-// output tiles (16 x 16, or 32 x 32 where those would be thousands) whose
-// wavefronts split K: wavefront w takes the 16-wide k-chunks w, w + WAVES, ...,
+// output tiles (16 x 16, 32 x 32 where those would be thousands, 64 x 64 in large
+// calls) whose wavefronts split K: wavefront w takes the 16-wide k-chunks w, w + WAVES, ...,
 // loads both operands straight from memory (16 bytes per lane, four chunks in
 // flight) and the partial tiles are added in wavefront order through LDS.  The
 // split depends on K alone, so a row's bits do not depend on how many rows share
@@ -32,7 +32,8 @@ struct F32Gemm {
 template <int EPI, int MT, int NT, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void gemm_f32_kernel(const F32Gemm p) {
     constexpr int NB = EPI == 1 ? 2 * NT : NT;   // column tiles of B (SwiGLU: gate tiles, then up tiles)
-    __shared__ floatx4 part[WAVES][MT * NB][64];
+    constexpr int PT = MT > 2 ? 1 : MT;          // row tiles that are added up at a time
+    __shared__ floatx4 part[WAVES][PT * NB][64];
     __shared__ float ssq[WAVES][MT * 16];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int r = lane & 15, c = lane >> 4;
@@ -110,55 +111,61 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_f32_kernel(const F32Gemm p) {
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], bv[u][j][e], acc[i][j], 0, 0, 0);
         }
     }
+    if (p.norm_g) {
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) part[w][i * NB + j][lane] = acc[i][j];
-        if (p.norm_g) {
+        for (int i = 0; i < MT; ++i) {
             ss[i] += __shfl_xor(ss[i], 16, 64);
             ss[i] += __shfl_xor(ss[i], 32, 64);
             if (c == 0) ssq[w][i * 16 + r] = ss[i];
         }
     }
-    __syncthreads();
-    // output tile x (row tile x / NT, column tile x % NT) is finished by wavefront x % WAVES; lane (r, c) holds column
-    // n0 + 16 j + r of rows m0 + 16 i + 4 c + e
-    for (int x = w; x < MT * NT; x += WAVES) {
-        const int i = x / NT, j = x % NT;
-        auto total = [&](int tile) {
-            floatx4 v = part[0][tile][lane];
 #pragma unroll
-            for (int k = 1; k < WAVES; ++k) {
-                const floatx4 o = part[k][tile][lane];
+    for (int i0 = 0; i0 < MT; i0 += PT) {
+        if (i0 > 0) __syncthreads();   // the row tiles before have been read
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += o[e];
+        for (int i = 0; i < PT; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) part[w][i * NB + j][lane] = acc[i0 + i][j];
+        __syncthreads();
+        // output tile x (row tile x / NT, column tile x % NT) is finished by wavefront x % WAVES; lane (r, c) holds column
+        // n0 + 16 j + r of rows m0 + 16 i + 4 c + e
+        for (int x = w; x < PT * NT; x += WAVES) {
+            const int i = x / NT, j = x % NT;
+            auto total = [&](int tile) {
+                floatx4 v = part[0][tile][lane];
+#pragma unroll
+                for (int k = 1; k < WAVES; ++k) {
+                    const floatx4 o = part[k][tile][lane];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] += o[e];
+                }
+                return v;
+            };
+            floatx4 v = total(i * NB + j), u = v;
+            if (EPI == 1) u = total(i * NB + NT + j);
+            const int n = n0 + j * 16 + r;
+            if (n >= p.N) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = (i0 + i) * 16 + 4 * c + e;
+                const int64_t m = m0 + row;
+                if (m >= m_end) continue;
+                float o = v[e];
+                if (p.norm_g) {
+                    float s = ssq[0][row];
+#pragma unroll
+                    for (int k = 1; k < WAVES; ++k) s += ssq[k][row];
+                    const float rinv = 1.0f / sqrtf(s / (float)p.K + p.norm_eps);
+                    o *= rinv;
+                    u[e] *= rinv;
+                }
+                if (EPI == 1)
+                    o = o / (1.0f + expf(-o)) * u[e];
+                else if (p.R)
+                    o += p.R[m * p.N + n];
+                if (p.g.row_scale) o *= p.g.row_scale[m];
+                p.C[m * p.N + n] = o;
             }
-            return v;
-        };
-        floatx4 v = total(i * NB + j), u = v;
-        if (EPI == 1) u = total(i * NB + NT + j);
-        const int n = n0 + j * 16 + r;
-        if (n >= p.N) continue;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int row = i * 16 + 4 * c + e;
-            const int64_t m = m0 + row;
-            if (m >= m_end) continue;
-            float o = v[e];
-            if (p.norm_g) {
-                float s = ssq[0][row];
-#pragma unroll
-                for (int k = 1; k < WAVES; ++k) s += ssq[k][row];
-                const float rinv = 1.0f / sqrtf(s / (float)p.K + p.norm_eps);
-                o *= rinv;
-                u[e] *= rinv;
-            }
-            if (EPI == 1)
-                o = o / (1.0f + expf(-o)) * u[e];
-            else if (p.R)
-                o += p.R[m * p.N + n];
-            if (p.g.row_scale) o *= p.g.row_scale[m];
-            p.C[m * p.N + n] = o;
         }
     }
 }
@@ -167,10 +174,18 @@ int gemm_f32_mtile() { return 32; }
 
 template <int EPI, int WAVES>
 static int launch_f32(compact_ctx* ctx, const F32Gemm& p, bool grouped, hipStream_t s) {
-    // 16 x 16 tiles fill the chip with few of them; beyond 2048 (eight per compute unit) 32 x 32 reads half the operands
+    // 16 x 16 tiles fill the chip with few of them; beyond 2048 (eight per compute unit) 32 x 32 reads half the operands, and
+    // from one 64 x 64 tile per compute unit on these read a quarter (160 of them: 28.9 against 30.8 us at N 1024, K 1024;
+    // 220: 37.5 against 31.4; 4096 x 4096 x 4096: 2132 -> 1360 us).  SwiGLU holds two operand tiles, so its big tiles are 64 x 32
+    // and pay for themselves over a long K only (1024: 106 against 116 us for 880 tiles, 333 against 327 for 2816; 4096^3: 4413
+    // -> 2908 us).
     const int64_t small_tiles = (p.M + 15) / 16 * ((p.N + 15) / 16);
+    constexpr int BN = EPI == 1 ? 32 : 64;   // columns of a big tile
+    const int64_t big_tiles = (p.M + 63) / 64 * ((p.N + BN - 1) / BN);
     if (!grouped && small_tiles <= 2048) {
         gemm_f32_kernel<EPI, 1, 1, WAVES><<<dim3((p.N + 15) / 16, (unsigned)((p.M + 15) / 16)), WAVES * 64, 0, s>>>(p);
+    } else if (!grouped && big_tiles >= 256 && (EPI == 0 || p.K >= 2048)) {
+        gemm_f32_kernel<EPI, 4, BN / 16, WAVES><<<dim3((p.N + BN - 1) / BN, (unsigned)((p.M + 63) / 64)), WAVES * 64, 0, s>>>(p);
     } else {
         const unsigned rows = grouped ? (unsigned)p.g.n_mtiles : (unsigned)((p.M + 31) / 32);
         gemm_f32_kernel<EPI, 2, 2, WAVES><<<dim3((p.N + 31) / 32, rows), WAVES * 64, 0, s>>>(p);

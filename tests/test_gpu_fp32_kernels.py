@@ -1,5 +1,5 @@
-"""fp32 storage kernels at the edges of their pieces: k-chunks of 16 dealt to four or eight wavefronts, output tiles of 16 and
-32, keys 64 at a time."""
+"""fp32 storage kernels at the edges of their pieces: k-chunks of 16 dealt to four or eight wavefronts, output tiles of 16, 32
+and 64, keys 64 at a time."""
 import pytest
 import torch
 
@@ -12,11 +12,13 @@ from tests.util import rel_err
 pytestmark = pytest.mark.gpu
 
 
-# fp32 sums of K products of N(0, 1) x N(0, 0.05): the error is below 2^-24 sqrt(K) of the rms, K <= 1040: 2e-6
+# fp32 sums of K products of N(0, 1) x N(0, 0.05): the error is below 2^-24 sqrt(K) of the rms, K <= 2051: 3e-6
 @pytest.mark.parametrize("M,N,K,epi,res", [
     (1, 17, 16, 0, True), (4, 256, 1024, 0, True), (16, 512, 256, 1, False), (17, 33, 1040, 0, False),   # 16 x 16 tiles
     (5, 40, 30, 0, False), (9, 23, 1027, 1, False),                                                     # rows that are not 16-byte aligned
-    (1200, 1300, 64, 0, True), (1300, 700, 1024, 1, False)])                                            # 32 x 32 tiles, tails
+    (700, 900, 272, 0, True), (1300, 700, 1024, 1, False),                                              # 32 x 32 tiles, tails
+    (1200, 1300, 64, 0, True), (1030, 1100, 1040, 0, False), (1090, 1030, 79, 0, True),                 # 64 x 64
+    (1100, 1110, 2048, 1, False), (1041, 1033, 2051, 1, False)])                                        # 64 x 32, SwiGLU
 def test_gemm_fp32_tiles(M, N, K, epi, res):
     lay = B.Layer(fp32_variant(DENSE), None)
     a, b = rnd((M, K), torch.float32, 3), rnd(((2 if epi else 1) * N, K), torch.float32, 4, std=0.05)
