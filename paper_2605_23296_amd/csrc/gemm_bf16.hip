@@ -747,6 +747,36 @@ int launch_gemm_bf16(compact_ctx* ctx, const bf16* A, const bf16* B, const void*
     return launch_form<0, false>(ctx, form, p, s);
 }
 
+// For the tests, not part of compact.h: the product in tile form `form`, or in the one the rule picks (-1); `picked` receives
+// the rule's form.  And the row-tile height of the grouped products.
+extern "C" int compact_test_gemm_form(compact_ctx* ctx, int32_t form, const void* a, const void* b, const void* r, void* c, int64_t M,
+                                      int32_t N, int32_t K, int32_t epilogue, int32_t* picked, void* hip_stream) {
+    if (!ctx || !a || !b || !c || !picked || M < 1 || N < 8 || N % 8 != 0 || K < GEMM_BK || K % GEMM_BK != 0 || form < -1 ||
+        form >= TILE_FORMS || (epilogue != 0 && epilogue != 1))
+        return COMPACT_EINVAL;
+    int n_cus = 0;
+    if (int rc = device_cu_count(ctx, &n_cus)) return rc;
+    GemmParams p{};
+    p.X = (const bf16*)a;
+    p.W = (const bf16*)b;
+    p.R = (const bf16*)r;
+    p.C = (bf16*)c;
+    p.M = M;
+    p.N = N;
+    p.K = K;
+    *picked = pick_tile(M, N, K, epilogue, n_cus);
+    if (form < 0) form = *picked;
+    hipStream_t s = (hipStream_t)hip_stream;
+    return epilogue == 1 ? launch_form<1, false>(ctx, form, p, s) : launch_form<0, false>(ctx, form, p, s);
+}
+extern "C" int compact_test_group_mtile(compact_ctx* ctx, int64_t rows, int32_t n_experts, int32_t F, int32_t d, int32_t* mtile) {
+    int n_cus = 0;
+    if (!ctx || !mtile) return COMPACT_EINVAL;
+    if (int rc = device_cu_count(ctx, &n_cus)) return rc;
+    *mtile = gemm_bf16_group_mtile(rows, n_experts, F, d, n_cus);
+    return COMPACT_OK;
+}
+
 // ---------------------------------------------------------------------------
 // Decode steps of 17 .. 64 rows: the 64 x 64 form as a weight stream.  Its ring keeps 64 KB of loads in flight per
 // workgroup, two workgroups per CU, and the activations ride along by direct-to-LDS loads: the gate/up projection of the

@@ -1,4 +1,6 @@
 """The tile form of a projection is picked by the size of the call; an output has the same bits in all of them."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -12,7 +14,7 @@ pytestmark = pytest.mark.gpu
 DENSE = WORKLOADS["dense_8x4096"].layer
 
 
-# column tails of 8, K of an odd number of 64-wide k-tiles; the row counts below reach every tile form
+# column tails of 8, K of an odd number of 64-wide k-tiles; whatever forms the rule picks for the row counts below
 @pytest.mark.parametrize("N,K,epi,res", [(4104, 1088, 0, True), (2056, 576, 1, False), (4096, 64, 0, False), (4096, 192, 0, True)])
 def test_rows_have_the_same_bits_in_every_tile_form(N, K, epi, res):
     lay = B.Layer(DENSE, None)
@@ -34,6 +36,53 @@ def test_rows_have_the_same_bits_in_every_tile_form(N, K, epi, res):
         assert bool((c[M] == 7.0).all()), M     # nothing past the last row
 
 
+FORMS = ["256x256", "128x256", "128x128", "128x64", "64x128", "64x64"]
+
+
+def gemm_form(lay, form, a, b, r, c, epi):
+    """The product in tile form `form` (-1: the picked one); returns the form that the rule picks."""
+    picked = C.c_int32(-1)
+    ptr = lambda t: None if t is None else C.c_void_p(t.data_ptr())
+    lay.check(lay.L.compact_test_gemm_form(lay.ctx, C.c_int32(form), ptr(a), ptr(b), ptr(r), ptr(c), C.c_int64(a.shape[0]),
+                                           C.c_int32(c.shape[1]), C.c_int32(a.shape[1]), C.c_int32(epi), C.byref(picked),
+                                           C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    return picked.value
+
+
+# one to four k-tiles of 64 (shorter than the rings: their repeated loads), an odd and a long number of them; one row, rows and
+# columns just under, at and over the tile edges
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 576, 1088])
+@pytest.mark.parametrize("epi,res", [(0, True), (0, False), (1, False)])
+def test_every_tile_form_at_its_edges(K, epi, res):
+    lay = B.Layer(DENSE, None)
+    for M, N in [(1, 8), (63, 136), (65, 56), (128, 64), (129, 264), (257, 520), (300, 128), (511, 1000)]:
+        a, b = rnd((M, K), torch.bfloat16, 3), rnd(((2 if epi else 1) * N, K), torch.bfloat16, 4, std=0.05)
+        r = rnd((M, N), torch.bfloat16, 5) if res else None
+        A, Bm = to_numpy_f64(a), to_numpy_f64(b)
+        ref = O.silu(O.linear(A, Bm[:N])) * O.linear(A, Bm[N:]) if epi else O.linear(A, Bm) + (to_numpy_f64(r) if res else 0.0)
+        first = None
+        for form in range(len(FORMS)):
+            c = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device="cuda")
+            gemm_form(lay, form, a, b, r, c[:M], epi)
+            torch.cuda.synchronize()
+            assert bool((c[M] == 7.0).all()), (M, N, FORMS[form])
+            if first is None:
+                assert rel_err(to_numpy_f64(c[:M]), ref) < 1e-2, (M, N)
+                first = c
+            assert torch.equal(c, first), (M, N, FORMS[form])
+
+
+def test_the_rule_picks_every_tile_form():
+    """Calls at which each form is the cheapest by the rule: a retuned table that drops one shows up here."""
+    lay = B.Layer(DENSE, None)
+    seen = set()
+    for M, N, K, epi in [(8192, 4096, 4096, 0), (2048, 4096, 14336, 0), (1000, 4096, 14336, 0), (300, 4096, 14336, 0), (513, 1024, 2816, 1),
+                         (126, 6144, 14336, 1), (65, 4096, 4096, 0), (65, 512, 64, 0), (20, 4096, 14336, 0), (200, 14336, 4096, 1)]:
+        a, b = torch.empty((M, K), dtype=torch.bfloat16, device="cuda"), torch.empty(((1 + epi) * N, K), dtype=torch.bfloat16, device="cuda")
+        seen.add(gemm_form(lay, -1, a.zero_(), b.zero_(), None, torch.empty((M, N), dtype=torch.bfloat16, device="cuda"), epi))
+    assert sorted(FORMS[f] for f in seen) == sorted(FORMS)
+
+
 def test_routed_rows_have_the_same_bits_at_every_row_tile_height():
     E, k, d, F, rows = 8, 4, 1024, 1408, 9000
     layer = LayerConfig(d_model=d, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn_dim=F, n_experts=E, top_k=k, dtype="bf16")
@@ -49,8 +98,13 @@ def test_routed_rows_have_the_same_bits_at_every_row_tile_height():
     gate = torch.softmax(torch.randn((rows, k), generator=g), dim=1).cuda()
     full = torch.empty_like(h)
     lay.compact_moe_ffn(m, h, idx, gate, full)
+    heights = set()
     for n in (70, 300, 1500, 3000, 6000):   # row tiles of 64, 128 and 256
+        mt = C.c_int32(0)
+        lay.check(lay.L.compact_test_group_mtile(lay.ctx, C.c_int64(n * k), C.c_int32(E), C.c_int32(F), C.c_int32(d), C.byref(mt)))
+        heights.add(mt.value)
         y = torch.empty((n, d), dtype=bf, device="cuda")
         lay.compact_moe_ffn(m[:n], h[:n], idx[:n].contiguous(), gate[:n].contiguous(), y)
         torch.cuda.synchronize()
         assert torch.equal(y, full[:n]), n
+    assert heights == {64, 128, 256}
