@@ -643,8 +643,10 @@ static int launch_cfg(compact_ctx* ctx, GemmParams& p, hipStream_t s) {
 // Which tile.  Every form adds an output's products in the same order, so the choice changes no bit and may look at
 // the number of rows.  Cost of a call = rounds of workgroups over the compute units x time of one tile; the time of
 // a k-tile rises with the share u of busy units (power and L2 traffic).  Constants: microseconds per k-tile (idle chip
-// + share of the load) and per tile, from timings of every form on N x K = 6144 x 4096, 4096 x 4096, 2 * 14336 x 4096,
-// 4096 x 14336, 1536 x 1024 and 2 * 2816 x 1024 at 20 .. 4096 rows.  Measured where the line lies (us, 256 x 256 against
+// + share of the load) and per tile, fitted to timings of all six forms at 354 shapes (65 .. 20000 rows, 64 .. 14336
+// columns, K 64 .. 14336, both epilogues): the picked form is at most 7 % slower than the best of the six at any of them,
+// 0.3 % on average.  (Constants fitted to long K alone priced the tiles of K <= 512 wrongly, by up to 25 %: 20000 x 640, K
+// 64, SwiGLU 23.5 us in 128 x 256 tiles against 20.2 in 256 x 256.)  Measured where the line lies (us, 256 x 256 against
 // 128 x 256): N 4096 K 14336 at 2048 rows 266 / 203, at 2500 rows 272 / 356 (128 x 256 needs a second round); N 6144
 // K 4096 at 2500 rows 97 / 111, at 3000 rows 165 / 146; 2 * 14336 x 4096 at 1652 rows 397 / 368, at 4096 rows 861 / 940.
 // Few rows, N 4096 K 14336: 20 rows 207 (256 x 256) / 157 / 104 (128 x 128) / 85 (64 x 128) / 71 (128 x 64) / 55
@@ -655,8 +657,8 @@ struct TileForm {
     double t_idle, t_load, t_tile;
 };
 enum { TILE_256 = 0, TILE_128, TILE_128_128, TILE_128_64, TILE_64_128, TILE_64_64, TILE_FORMS };
-static const TileForm tile_forms[TILE_FORMS] = {{256, 256, 1.00, 0.70, 6.0}, {128, 256, 0.75, 0.25, 2.0}, {128, 128, 0.50, 0.15, 4.0},
-                                                {128, 64, 0.33, 0.08, 3.0},  {64, 128, 0.40, 0.05, 2.0},  {64, 64, 0.25, 0.02, 3.0}};
+static const TileForm tile_forms[TILE_FORMS] = {{256, 256, 1.00, 0.70, 4.8}, {128, 256, 0.75, 0.24, 2.7}, {128, 128, 0.55, 0.13, 1.7},
+                                                {128, 64, 0.31, 0.03, 2.2},  {64, 128, 0.40, 0.04, 3.3},  {64, 64, 0.25, 0.05, 2.5}};
 
 static double tile_cost(int form, double row_tiles, int N, int K, int epilogue, int n_cus) {
     const TileForm& f = tile_forms[form];
