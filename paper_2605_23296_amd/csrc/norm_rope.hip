@@ -285,29 +285,41 @@ int launch_decode_qkv_epilogue(compact_ctx* ctx, const BlockMeta* d_meta, int n_
     return COMPACT_OK;
 }
 
-// sum of ks partial float4s at p, p + ps, ... in slice order, loads issued in groups of 8 (past the end: the last again)
+// sum of ks partial float4s at p, p + ps, ... in slice order, loads issued in groups of 8; the last group is of 1, 4 or 8
+// (past the end: the last slice again, not added)
+template <int U>
+__device__ __forceinline__ void add_slices4(const float* __restrict__ p, size_t ps, int n, float4& acc) {
+    float4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const float4*>(p + min(u, n - 1) * ps);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u < n) {
+            acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w;
+        }
+}
 __device__ __forceinline__ float4 sum_slices4(const float* __restrict__ p, size_t ps, int ks, float4 acc) {
-    for (int s = 0; s < ks; s += 8) {
-        float4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(p + min(s + u, ks - 1) * ps);
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (s + u < ks) {
-                acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w;
-            }
-    }
+    int s = 0;
+    for (; s + 8 <= ks; s += 8) add_slices4<8>(p + s * ps, ps, 8, acc);
+    const int left = ks - s;
+    if (left > 4)
+        add_slices4<8>(p + s * ps, ps, left, acc);
+    else if (left > 1)
+        add_slices4<4>(p + s * ps, ps, left, acc);
+    else if (left == 1)
+        add_slices4<1>(p + s * ps, ps, 1, acc);
     return acc;
 }
 
 // ---------------------------------------------------------------------------
 // Decode: h = resid + sum_s partial_s (kept in fp32), m = RMSNorm(h; g) in one of the NormRounding forms.
-// One workgroup of 1024 threads per row, 4 columns per thread and trip (d <= RN_TRIPS * RN_NT * 4 = 8192): a row is one
-// or two trips, whose slices are requested together.  Latency-bound: with 256 threads and up to eight trips 10.5 us at 64
-// rows of 4096, 4 slices.
+// One workgroup of 1024 threads per row, 4 columns per thread and trip: a row is one or two trips, whose slices are
+// requested together; 256 threads for rows of at most 1024 columns (the same sums: the other wavefronts would add zeros).
+// Latency-bound: with 256 threads and up to eight trips 10.5 us at 64 rows of 4096, 4 slices; whole steps of 4 to 16 rows of
+// d 512 with 1024 threads 41.2 .. 42.4 us, with 256 40.7 .. 41.5.
 // ---------------------------------------------------------------------------
-#define RN_NT 1024
-#define RN_TRIPS 2
+#define RN_MAX_D 8192
+template <int RN_NT, int RN_TRIPS>
 __global__ __launch_bounds__(RN_NT) void residual_norm_kernel(const float* __restrict__ partials, int ks, int rows,
                                                               const bf16* __restrict__ resid, const bf16* __restrict__ g,
                                                               float* __restrict__ h_out, bf16* __restrict__ m_out, int d,
@@ -328,7 +340,7 @@ __global__ __launch_bounds__(RN_NT) void residual_norm_kernel(const float* __res
             a = sum_slices4(partials + (size_t)r * d + c, ps, ks, a);
             hv[it] = a;
             *reinterpret_cast<float4*>(h_out + (size_t)r * d + c) = a;
-            ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
+            ss += fmaf(a.w, a.w, fmaf(a.z, a.z, fmaf(a.x, a.x, a.y * a.y)));   // (written out: the same in both forms)
         }
     }
     ss = wave_sum(ss);
@@ -362,9 +374,14 @@ int launch_residual_norm(compact_ctx* ctx, const float* partials, int ks, const 
                          void* h_out, void* m_out, int rows, hipStream_t s, NormRounding rounding, float* rinv_out) {
     const compact_layer_cfg& c = ctx->cfg;
     if (rounding == NORM_LATER && !rinv_out) return set_err(ctx, COMPACT_EINVAL, "no room for the rows' 1 / rms");
-    if (c.d_model > RN_TRIPS * RN_NT * 4) return set_err(ctx, COMPACT_ESHAPE, "d_model above 8192 is not supported by the decode row kernels");
-    residual_norm_kernel<<<rows, RN_NT, 0, s>>>(partials, ks, rows, (const bf16*)resid, (const bf16*)g, (float*)h_out, (bf16*)m_out,
-                                                c.d_model, c.rms_eps, rounding, rinv_out);
+    if (c.d_model > RN_MAX_D) return set_err(ctx, COMPACT_ESHAPE, "d_model above 8192 is not supported by the decode row kernels");
+    if (c.d_model <= 1024)
+        residual_norm_kernel<256, 1><<<rows, 256, 0, s>>>(partials, ks, rows, (const bf16*)resid, (const bf16*)g, (float*)h_out,
+                                                          (bf16*)m_out, c.d_model, c.rms_eps, rounding, rinv_out);
+    else
+        residual_norm_kernel<1024, RN_MAX_D / 4096><<<rows, 1024, 0, s>>>(partials, ks, rows, (const bf16*)resid, (const bf16*)g,
+                                                                         (float*)h_out, (bf16*)m_out, c.d_model, c.rms_eps, rounding,
+                                                                         rinv_out);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
