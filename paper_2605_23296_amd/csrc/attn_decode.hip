@@ -453,6 +453,16 @@ int launch_attn_decode_bf16(compact_ctx* ctx, const BlockMeta* d_meta, const Til
     const size_t smem = rec_slots * slot_bytes;
     if (n_rec * (int64_t)1 > INT32_MAX) return set_err(ctx, COMPACT_ECAPACITY, "more split-KV records than the decode attention indexes");
     if (max_chunks > COMBINE_MAX_CHUNKS) return set_err(ctx, COMPACT_ECAPACITY, "KV cache longer than the decode combine supports");
+    {
+        ProfileScope ps(ctx, COMPACT_K_ATTN_DECODE, s);
+        if (c.head_dim == 128)
+            attn_decode_bf16_kernel<128><<<grid, DEC_WAVES * 64, smem, s>>>(d_meta, d_chunks, n_chunks, step, max_chunks, q, d_k, d_v, partials,
+                                                                           c.n_q_heads, c.n_kv_heads, scale_log2, d_qrow, q_stride, n_rec, rec_slots);
+        else
+            attn_decode_bf16_kernel<64><<<grid, DEC_WAVES * 64, smem, s>>>(d_meta, d_chunks, n_chunks, step, max_chunks, q, d_k, d_v, partials,
+                                                                          c.n_q_heads, c.n_kv_heads, scale_log2, d_qrow, q_stride, n_rec, rec_slots);
+    }
+    LAUNCH_CHECK(ctx);
     const int side = 64 * 4 / c.head_dim;   // records that 64 threads read side by side
     const int form = max_chunks <= DEC_CTINY * side ? MERGE_FEW : max_chunks <= DEC_CSHORT ? MERGE_SHORT : MERGE_LONG;
     const int ct = form == MERGE_LONG ? DEC_CT : 64;
@@ -462,23 +472,7 @@ int launch_attn_decode_bf16(compact_ctx* ctx, const BlockMeta* d_meta, const Til
                                      : (form == MERGE_FEW     ? attn_decode_combine_kernel<64, MERGE_FEW>
                                         : form == MERGE_SHORT ? attn_decode_combine_kernel<64, MERGE_SHORT>
                                                               : attn_decode_combine_kernel<64, MERGE_LONG>);
-    if (c.head_dim == 128) {
-        {
-            ProfileScope ps(ctx, COMPACT_K_ATTN_DECODE, s);
-            attn_decode_bf16_kernel<128><<<grid, DEC_WAVES * 64, smem, s>>>(d_meta, d_chunks, n_chunks, step, max_chunks, q, d_k, d_v, partials,
-                                                                           c.n_q_heads, c.n_kv_heads, scale_log2, d_qrow, q_stride, n_rec, rec_slots);
-        }
-        LAUNCH_CHECK(ctx);
-        combine<<<cgrid, ct, 0, s>>>(d_meta, step, max_chunks, partials, o, c.n_q_heads, d_qrow, n_rec);
-    } else {
-        {
-            ProfileScope ps(ctx, COMPACT_K_ATTN_DECODE, s);
-            attn_decode_bf16_kernel<64><<<grid, DEC_WAVES * 64, smem, s>>>(d_meta, d_chunks, n_chunks, step, max_chunks, q, d_k, d_v, partials,
-                                                                          c.n_q_heads, c.n_kv_heads, scale_log2, d_qrow, q_stride, n_rec, rec_slots);
-        }
-        LAUNCH_CHECK(ctx);
-        combine<<<cgrid, ct, 0, s>>>(d_meta, step, max_chunks, partials, o, c.n_q_heads, d_qrow, n_rec);
-    }
+    combine<<<cgrid, ct, 0, s>>>(d_meta, step, max_chunks, partials, o, c.n_q_heads, d_qrow, n_rec);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
