@@ -170,7 +170,7 @@ struct PrefillBufs {
 };
 
 struct DecodeBufs {
-    void *n, *q, *o, *m, *act;
+    void *q, *o, *m, *act;
     void* hg;          // bf16(h * g_ffn): the FFN input before its 1/rms factor
     float* ssq_parts;  // [d_model / 16][N] column-group sums of squares of h
     float *h, *partials, *attn_partials;
@@ -231,7 +231,6 @@ static int decode_max_ksplit(const compact_layer_cfg& c, int N);
 
 static void carve_decode(Carver& cv, const compact_layer_cfg& c, int N, int max_chunks, DecodeBufs& b) {
     const size_t es = dtype_size(c.dtype);
-    b.n = cv.take((size_t)N * c.d_model * es);
     b.q = cv.take((size_t)N * c.n_q_heads * c.head_dim * es);
     b.o = cv.take((size_t)N * c.n_q_heads * c.head_dim * es);
     b.m = cv.take((size_t)N * c.d_model * es);
@@ -659,7 +658,7 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
     if (part & DECODE_FRONT) {
     // RMSNorm + QKV projection.  bf16 storage: the projection stages bf16(x * g) itself and leaves the row sums of squares, the
     // epilogue multiplies by 1 / rms before the rotation.
-    if (c.dtype == COMPACT_BF16 && skinny_norm_in_supported(N, Dtot, c.d_model)) {
+    if (c.dtype == COMPACT_BF16) {
         ks = skinny_ksplit(N, Dtot, c.d_model);
         {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
@@ -672,13 +671,9 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
         rq.inv_d = 1.0f / (float)c.d_model;
         rq.eps = c.rms_eps;
         TRY(launch_decode_qkv_epilogue(ctx, meta, N, step, b.partials, ks, b.q, kv->d_k, kv->d_v, s, &rq));
-    } else if (c.dtype != COMPACT_BF16) {   // the RMSNorm rides in the projection
+    } else {   // the RMSNorm rides in the projection
         TRY(launch_gemm_f32(ctx, (const float*)x, (const float*)w->w_qkv, nullptr, b.partials, N, Dtot, c.d_model, 0, nullptr, s,
                             (const float*)w->g_attn));
-        TRY(launch_decode_qkv_epilogue(ctx, meta, N, step, b.partials, ks, b.q, kv->d_k, kv->d_v, s));
-    } else {
-        TRY(launch_rmsnorm(ctx, x, false, w->g_attn, b.n, N, s));
-        TRY(gemm_partials(ctx, b.n, w->w_qkv, b.partials, N, Dtot, c.d_model, &ks, s));
         TRY(launch_decode_qkv_epilogue(ctx, meta, N, step, b.partials, ks, b.q, kv->d_k, kv->d_v, s));
     }
     }

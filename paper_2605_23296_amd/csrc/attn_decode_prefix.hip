@@ -60,13 +60,6 @@ __device__ __forceinline__ float over_rows(float x) {
     return x;
 }
 
-// The value itself, computed where it stands: keeps what derives from it in a rare branch from being hoisted out of the
-// loop into registers that the loop needs.
-__device__ __forceinline__ int here(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
-
 // Waits until at most N of this wavefront's loads are in flight and its LDS reads have returned, then joins the barrier.
 template <int N>
 __device__ __forceinline__ void pfx_barrier() {

@@ -94,13 +94,6 @@ __device__ __forceinline__ void phase_barrier() {
 #endif
 }
 
-// The value itself, computed where it stands: keeps what derives from it in a rare branch from being hoisted out of the
-// loop into registers that the loop needs (a spilled register's reload would wait for every load in flight).
-__device__ __forceinline__ int here(int x) {
-    asm volatile("" : "+v"(x));
-    return x;
-}
-
 // PP = false: workgroup = 4 wavefronts = 128 query rows x one query head, two workgroups per
 // CU, two-stage K/V ring, every wavefront runs QK^T -> softmax -> PV per tile.
 // PP = true ("ping-pong"): workgroup = 8 wavefronts = the same 128 query rows x TWO query heads
@@ -108,7 +101,7 @@ __device__ __forceinline__ int here(int x) {
 // group 1 (waves 4-7, second head) run the same loop one phase apart, with a workgroup barrier
 // at every phase boundary: while one group's wavefront is in its matrix phase (PV of the previous
 // tile, QK^T of this one: 32 MFMAs) the other wavefront on the same SIMD is in its softmax phase
-// (VALU only), so the matrix pipe and the vector ALU work at the same time instead of both
+// (VALU, staging and early V^T reads), so the matrix pipe and the vector ALU work at the same time instead of both
 // wavefronts asking for the same one.  Both groups read the same K/V tiles (one staging for two
 // heads); a tile stays live for four phases, hence a four-stage ring.
 template <int HD, bool PP>
@@ -434,13 +427,13 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
         // Phase 2j of a group: PV of tile j-1 and QK^T of tile j ("matrix phase"); phase 2j+1: softmax
         // of tile j.  Group 0 runs phase s in time slot s, group 1 in slot s + 1; slots are separated by
         // workgroup barriers, and every wavefront passes the same number of them (2 n_tiles + 3).
-        // Tile T is read in slots 2T .. 2T+3 (K by both groups, then V^T by both) and its stage is free
-        // again from slot 2T+4 on.  The staging rides in the softmax phases, which are the shorter ones
-        // and read no LDS (while a load that writes LDS is pending, the compiler turns every wait for
-        // an LDS read into a wait for all of them): in its softmax phase j, group g first waits for its
-        // part of tile j+1+g, issued one softmax phase earlier, then issues its part of tile j+2+g.
-        // Group 0 thus confirms tile T in slot 2T-1 and group 1 in slot 2T-2, before the barrier that
-        // precedes the first read; the stage of tile j+2+g was last read in slot 2j-1+2g.
+        // Tile T is read in slots 2T .. 2T+3: K in slot 2T by group 0 and 2T+1 by group 1, V^T in 2T+2 and 2T+3, the first
+        // half of V^T one slot earlier by a wavefront below its diagonal.  Its stage is free again from slot 2T+4 on.  The
+        // staging rides in the softmax phases, which are the shorter ones: in its softmax phase j, group g first waits for
+        // its part of tile j+1+g, issued one softmax phase earlier, then issues its part of tile j+2+g (after the early V^T
+        // reads: while a load that writes LDS is pending, the compiler turns every wait for an LDS read into a wait for all
+        // of them).  Group 0 thus confirms tile T in slot 2T-1 and group 1 in slot 2T-2, before the barrier that precedes
+        // the first read; the stage of tile j+2+g was last read in slot 2j-1+2g and is refilled in slot 2j+1+g.
         issue_tile(0, 0);
         if (n_tiles > 1) issue_tile(1, 1);
         if (grp == 1) {   // group 1 runs one tile ahead with its loads

@@ -107,6 +107,13 @@ int device_cu_count(compact_ctx* ctx, int* n_cus);
     } while (0)
 #define LAUNCH_CHECK(ctx) HIP_TRY(ctx, hipGetLastError())
 
+// The value itself, computed where it stands: keeps what derives from it in a rare branch from being hoisted out of the
+// loop into registers that the loop needs (a spilled register's reload would wait for every load in flight).
+__device__ __forceinline__ int here(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // 16-byte global load whose result goes straight into LDS: lane l of the wave
 // deposits its 16 bytes at lds_base + 16 * l (lds_base is wave-uniform); the
 // global address is per lane.  Completion is tracked by the vector-memory counter.
@@ -216,7 +223,6 @@ int skinny_ksplit(int M, int N, int K);
 // norm_ssq_parts[ks][M] receives the per-slice sums of x^2 (the consumer applies 1 / rms)
 int launch_gemm_skinny(compact_ctx* ctx, const bf16* A, const bf16* B, float* partials, int M, int N, int K,
                        int ks, hipStream_t s, const bf16* norm_g = nullptr, float* norm_ssq_parts = nullptr);
-bool skinny_norm_in_supported(int M, int N, int K);
 int launch_gemm_skinny_rownorm(compact_ctx* ctx, const bf16* hg, const RowNorm& norm, bf16* m_out, const bf16* B, float* partials,
                                int M, int N, int K, int ks, hipStream_t s);
 // the same per expert, for routed decode rows: expert e multiplies the rows offsets[e] ..

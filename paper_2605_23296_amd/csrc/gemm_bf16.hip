@@ -7,7 +7,7 @@
 //    in tiles of 64 (a k-tile row is one 128-byte line);
 //  * the k-tiles of X and W pass through LDS as half tiles of 128 rows (16 KB), a
 //    ring of eight of them (two k-tiles, 128 KB), filled by 16-byte direct-to-LDS
-//    global loads; a half tile is requested eight phases before the one that reads
+//    global loads; a half tile is requested seven phases before the one that reads
 //    it and has six phases (about 3000 clocks) to arrive;
 //  * one k-tile = four phases, one per quarter of the wave's output: read the half
 //    tile the quarter needs newly (X0, W1, X1, then W0 of the next k-tile; the

@@ -355,8 +355,6 @@ static int launch_skinny_cfg(compact_ctx* ctx, const bf16* A, const bf16* B, flo
 // more rows the staged activation slice grows, so 8 wavefronts (128 weight rows)
 // share it: half the activation traffic per weight byte, the same number of
 // wavefronts per compute unit.
-bool skinny_norm_in_supported(int M, int N, int K) { return M >= 1 && M <= 64 && N % 16 == 0 && K % 64 == 0; }
-
 int launch_gemm_skinny(compact_ctx* ctx, const bf16* A, const bf16* B, float* partials, int M, int N, int K, int ks,
                        hipStream_t s, const bf16* norm_g, float* norm_ssq_parts) {
     if (M < 1 || M > 64) return set_err(ctx, COMPACT_ESHAPE, "weight-streaming GEMM takes 1..64 activation rows");
@@ -364,15 +362,15 @@ int launch_gemm_skinny(compact_ctx* ctx, const bf16* A, const bf16* B, float* pa
     if (ks != skinny_ksplit(M, N, K)) return set_err(ctx, COMPACT_EINVAL, "unexpected K split");
     SkinnyNormIn nin;
     if (norm_g) {
-        if (!skinny_norm_in_supported(M, N, K) || !norm_ssq_parts)
-            return set_err(ctx, COMPACT_ESHAPE, "folding the RMSNorm into the weight-streaming GEMM needs K % 64 == 0");
+        if (!norm_ssq_parts) return set_err(ctx, COMPACT_EINVAL, "no room for the row sums of squares");
         nin.g = norm_g;
         nin.ssq_parts = norm_ssq_parts;
     }
     // 49 .. 64 rows: two workgroups of 8 wavefronts fit a CU (the staged slice is 66 KB); a grid beyond what the
-    // chip holds at once (d_model 8192: 16 slices x 80 column groups) goes to workgroups of 16 wavefronts with 6 of the
-    // 16 loads up front instead: again two per CU, half the activation staging (measured at N 4096, K 14336, 28 slices x
-    // 32 column groups: 39.9 -> 34.9 us; at 32 rows the same change cost 2 us and is not made)
+    // chip holds at once (the q/k/v projection of a layer with d_model 8192: 16 slices x 80 column groups) goes to
+    // workgroups of 16 wavefronts with 6 of the 16 loads up front instead: again two per CU, half the activation staging.
+    // 64 rows, N 10240, K 8192: 62.9 -> 51.1 us, a whole step of such a layer 181.5 -> 174.4 (at 32 rows the same change
+    // cost 2 us and is not made)
     int n_cus = 0;
     if (int rc = device_cu_count(ctx, &n_cus)) return rc;
     const bool fat = (int64_t)ks * ((N + 127) / 128) > 2 * (int64_t)n_cus;

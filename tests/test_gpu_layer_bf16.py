@@ -154,11 +154,11 @@ def test_merging_few_and_many_records_of_a_block(head_dim):
 
 @pytest.mark.parametrize("n_blocks", [17, 32, 33, 64])
 def test_dense_decode_with_17_to_64_blocks(n_blocks):
-    """More than 16 decode rows: the whole-K weight-streaming kernels with two to four groups of 16 rows per weight
-    fragment (output projection, gate/up; tile edges at 17, 32, 33 and 64 rows) and the split-K down projection,
-    against the checker.  A block's bits do not depend on which other blocks share the step, nor on its place in the
-    batch: checked against another batch of more than 16 blocks.  Against the block decoded alone the caches agree
-    bit for bit and the outputs to rounding (up to 16 rows the down projection adds over K in another order)."""
+    """More than 16 decode rows of a dense layer: output, gate/up and down projection by the 64 x 64 form of the ring GEMM, K
+    split into slices that depend on the weight's shape alone (row counts on and off its 16-row MFMA tiles), against the
+    checker.  A block's bits do not depend on which other blocks share the step, nor on its place in the batch: checked
+    against another batch of more than 16 blocks.  Against the block decoded alone the caches agree bit for bit and the
+    outputs to rounding (up to 16 rows these three projections add over K in another order)."""
     lens = [(7 * b) % 50 + 1 for b in range(n_blocks)]
     inp = make_inputs(WORKLOADS["dense_8x4096"], block_lens=lens, decode_steps=2, gain_jitter=True)
     full = check_dense(inp, sampled=False)
@@ -196,9 +196,8 @@ def test_dense_steps_round_the_ffn_input_alike_in_both_families(d_model, n_q_hea
 
 @pytest.mark.parametrize("n_blocks", [20, 47])
 def test_dense_decode_with_17_to_64_blocks_at_the_smallest_shapes(n_blocks):
-    """The 17..64-row kernels at the smallest contraction lengths they take (output projection K = 2048,
-    gate/up K = 2048, an FFN width of 17 workgroups of 64 columns), two and three groups of 16 rows:
-    every row against the checker."""
+    """Narrow weights in the 17..64-row kernels: 32 and 34 column tiles, K = 2048 in four slices and 1088 in three of unequal
+    length, a gate/up projection of 34 workgroups: every row against the checker."""
     layer = LayerConfig(d_model=2048, n_q_heads=16, n_kv_heads=4, head_dim=128, ffn_dim=1088, rope_theta=500000.0, dtype="bf16")
     lens = [(11 * b) % 37 + 1 for b in range(n_blocks)]
     inp = make_inputs(Workload("edge_rows", layer, lens, n_blocks, 2), gain_jitter=True)
