@@ -1259,25 +1259,31 @@ extern "C" int compact_stack_forward(compact_ctx* ctx, int32_t n_layers, const c
 // ---------------------------------------------------------------------------
 // prefix-aware layout: shared prefix + private tails
 // ---------------------------------------------------------------------------
-// Rows of a work item of the shared history, by its length and the KV heads alone (a worker's sums then do not depend on
-// the other workers).  An item is a workgroup per KV head that walks its rows 32 at a time: short histories need many
-// short ones, and long ones few, since every item leaves a record per query head that is written and merged.  Lines at
-// 128 workgroups of 128 rows and at 256 of 256 rows; measured (8 KV heads of 128, attention and merge from the host, us,
-// items of 512 / 256 / 128 rows): one worker, 2048 rows 23.5 / 19.5 / 18.4, 4096 rows 23.6 / 19.8 / 19.7, 8192 rows
-// 24.2 / 23.0 / 25.4; 16 workers, 8192 rows 26.9 / 26.0 / 29.2; 8 workers, 32768 rows 41.1 / 43.5 / 51.3; 24 workers, 98304
-// rows 106 / 136 / 189.  2 KV heads: 8 workers, 32768 rows 32.1 / 30.7 / 36.0.  Where an item has few columns (one worker,
-// or no grouping) only one or two of its eight wavefronts multiply, and a kernel that splits the rows over all eight was
-// 3 to 11 % faster between 4096 and 32768 rows; from 49152 rows on it was slower there too.
-static const int64_t prefix_item_limit[2] = {128 * 128, 256 * 256};   // most rows x KV heads for items of 128 and of 256 rows
+// Rows of a work item of the shared history, by its length and the layer alone (a worker's sums then do not depend on the
+// other workers).  An item is a workgroup per KV head that walks its rows 32 at a time: short histories need many short
+// ones, and long ones few, since every item leaves a record per query head that is written and merged.  Lines at 256
+// workgroups of 128 rows and 384 of 256 (head_dim 64, whose workgroups are smaller: 512 and 512).  Measured as whole steps of
+// a layer of the 8B shape (us, items of 128 / 256 / 512 rows): 3 workers: 1000 rows 106.1 / 108.5 / 112.9, 4096 rows 108.3 /
+// 108.8 / 112.7, 12288 rows 118.0 / 114.4 / 114.4, 24576 rows 131.8 / 126.9 / 123.4; 20 workers: 4096 rows 126.9 / 128.0 /
+// 130.9, 49152 rows 190.9 / 171.9 / 165.2.  64 heads of 64, 3 workers: 4096 rows 105.8 / 106.8 / 111.7, 16384 rows 113.8 /
+// 112.2 / 113.4, 49152 rows 132.8 / 126.5 / 125.5.  Where an item has few columns (one to three workers, or no grouping) only one
+// or two of its eight wavefronts multiply; a kernel that split the rows over all eight was 1 to 2 % of a step faster there
+// between 4096 and 16384 rows, and 3 to 18 % slower with 8 to 20 workers.
+static void prefix_item_limits(const compact_layer_cfg& c, int64_t (&rows)[2]) {   // longest histories for 128- and 256-row items
+    rows[0] = (c.head_dim == 128 ? 256 : 512) * 128 / c.n_kv_heads;
+    rows[1] = (c.head_dim == 128 ? 384 : 512) * 256 / c.n_kv_heads;
+}
 static int prefix_item_rows(const compact_layer_cfg& c, int shared_len) {
-    const int64_t rows = (int64_t)shared_len * c.n_kv_heads;
-    return rows <= prefix_item_limit[0] ? 128 : rows <= prefix_item_limit[1] ? 256 : 512;
+    int64_t lim[2];
+    prefix_item_limits(c, lim);
+    return shared_len <= lim[0] ? 128 : shared_len <= lim[1] ? 256 : 512;
 }
 // most items that a prefix of at most `len` rows can have, whatever the length of the history that it is part of
 static int prefix_max_items(const compact_layer_cfg& c, int len) {
-    const int l128 = (int)std::min<int64_t>(len, prefix_item_limit[0] / c.n_kv_heads);
-    const int l256 = (int)std::min<int64_t>(len, prefix_item_limit[1] / c.n_kv_heads);
-    return std::max({(l128 + 127) / 128, (l256 + 255) / 256, (int)(((int64_t)len + 511) / 512)});
+    int64_t lim[2];
+    prefix_item_limits(c, lim);
+    const int64_t l128 = std::min<int64_t>(len, lim[0]), l256 = std::min<int64_t>(len, lim[1]);
+    return (int)std::max({(l128 + 127) / 128, (l256 + 255) / 256, ((int64_t)len + 511) / 512});
 }
 
 static int64_t prefix_max_recs(const compact_layer_cfg& c, int n_workers, int max_prefix_len, int max_tail_len) {

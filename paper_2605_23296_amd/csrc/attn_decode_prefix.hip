@@ -273,7 +273,7 @@ __global__ __launch_bounds__(PFX_WAVES * 64, 4) void attn_decode_prefix_kernel(
 // chunks the step has not reached yet carry weight zero and are never read (nobody
 // wrote them).  256 threads: HD / 2 threads span a record, 512 / HD records are read
 // side by side, 16 loads in flight per thread (4: 30.6 us at 24 workers, 16: 24.5 us); all sums run in a fixed order.
-#define PFX_MAX_ITEMS 1088   // a prefix and a tail of 1024 pieces of 256 rows, up to 64 of them in halves
+#define PFX_MAX_ITEMS 1280   // a prefix and a tail of 1024 pieces of 256 rows, up to 256 of them in halves
 #define PFX_CT 256
 #define PFX_FLIGHT 16
 template <int HD>

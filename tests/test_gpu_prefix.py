@@ -73,10 +73,10 @@ def test_prefix_decode_attention_kernel_tile_edges(wl):
 
 
 @pytest.mark.parametrize("hkv,hd,group,rows", [
-    (8, 128, 4, 2048), (8, 128, 4, 2049), (8, 128, 4, 8192), (8, 128, 4, 8193),     # last histories of 128- and 256-row items
-    (1, 64, 16, 16384), (1, 64, 16, 16385), (2, 64, 3, 8193), (16, 128, 1, 4097)])
+    (8, 128, 4, 2048), (8, 128, 4, 4096), (8, 128, 4, 4097), (8, 128, 4, 12288), (8, 128, 4, 12289),   # the lines at head_dim 128
+    (8, 64, 3, 8192), (8, 64, 8, 8193), (8, 64, 8, 16385), (2, 64, 16, 32769), (16, 128, 1, 2049)])
 def test_prefix_decode_attention_kernel_item_heights(hkv, hd, group, rows):
-    """Work items of 128, 256 and 512 rows, chosen by the length of the history and the KV heads: prefixes on and around the
+    """Work items of 128, 256 and 512 rows, chosen by the length of the history and the layer: prefixes on and around the
     item edges in histories on both sides of the lines, more columns than an item takes.  A worker alone, and the workers of
     short prefixes alone (their workspace sized for those prefixes), have the same bits."""
     layer = LayerConfig(d_model=256, n_q_heads=hkv * group, n_kv_heads=hkv, head_dim=hd, ffn_dim=256, rope_theta=500000.0, dtype="bf16")
