@@ -16,8 +16,9 @@
 //    different groups that run half a phase apart, so one group's MFMAs (256
 //    clocks of the matrix pipe) cover the other group's reads and requests.
 //    Barriers wait for LDS reads and for all but the newest 12 loads, so nothing
-//    drains.  Matrix pipe busy: 90 % of the clocks (counters; 74 % in the form
-//    before, eight wavefronts that read, load and multiply in lock step);
+//    drains.  Matrix pipe busy: 85 to 88 % of the clocks in the 8 x 4096 pass (counters;
+//    73 to 75 % in the form before, eight wavefronts that read, load and multiply in
+//    lock step);
 //  * v_mfma_f32_16x16x32_bf16: the chip runs this kernel at its power limit, and
 //    this form spends less than 32x32x16 (half the accumulator traffic per flop):
 //    1.30 against 1.14 PFLOP/s with the same schedule, same bits;
@@ -36,8 +37,8 @@
 //  * workgroup ids are remapped so that each XCD (own L2) gets a contiguous
 //    range of tiles, walked in groups of 4 row tiles per column tile (8: the down
 //    projection 3 % slower, the others equal; 16: 7 .. 13 % slower).
-// Bound: the power limit (90 % matrix-pipe busy at 1.52 GHz; with the loads served
-// from L2 the clock rises to 1.66).  8B-shaped layer, 32768 rows, before -> now:
+// Bound: the power limit (the gate/up projection of that pass: matrix pipe 85 % busy at
+// 1.60 GHz; a probe whose loads all hit L2 ran at a clock 9 % higher).  8B-shaped layer, 32768 rows, before -> now:
 // QKV 1479 -> 1297 us, O 1045 -> 922, gate/up 6290 -> 5560 (1.38 PFLOP/s), down
 // 3418 -> 2890 (1.33); 1652 rows 104 -> 92, 91 -> 79, 419 -> 371, 304 -> 253.
 #include <algorithm>
