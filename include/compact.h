@@ -43,8 +43,10 @@
  *    one for more (beyond 64 blocks the rows of a step go through the second
  *    family in groups of 33 .. 64, each group streaming the weights again): the
  *    caches and every output are bit-identical within a family; across the two,
- *    the caches still are, the outputs agree to rounding (the projections after
- *    the attention add over K in another order).
+ *    the caches still are, the outputs of dense layers agree to rounding (the
+ *    projections after the attention add over K in another order).  Routed layers
+ *    choose their experts from the same bits in both families; their outputs are
+ *    bit-identical as long as blocks x top_k of a step or group is at most 256.
  */
 #ifndef COMPACT_H
 #define COMPACT_H
