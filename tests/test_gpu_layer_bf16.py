@@ -142,7 +142,7 @@ def test_prefill_attention_at_the_edges_of_its_key_tiles():
 def test_merging_few_and_many_records_of_a_block(head_dim):
     """The merge of a block's split-KV records has three forms by the most records of a block of the call: up to 8 (head_dim
     128) or 16 (64), up to 32, and more, up to 128 or 256 at a time.  1, 2, 8, 9, 16, 17, 32, 33 and 131 records, against the
-    checker, and the shorter blocks again in calls without the longer ones, bit for bit."""
+    oracle, and the shorter blocks again in calls without the longer ones, bit for bit."""
     layer = LayerConfig(d_model=512, n_q_heads=2, n_kv_heads=1, head_dim=head_dim, ffn_dim=256, rope_theta=500000.0, dtype="bf16")
     lens = [33300, 8192, 8190, 4350, 4090, 2100, 2046, 256, 7]
     inp = make_inputs(Workload("records", layer, lens, 9, 2), gain_jitter=True)
@@ -156,7 +156,7 @@ def test_merging_few_and_many_records_of_a_block(head_dim):
 def test_dense_decode_with_17_to_64_blocks(n_blocks):
     """More than 16 decode rows of a dense layer: output, gate/up and down projection by the 64 x 64 form of the ring GEMM, K
     split into slices that depend on the weight's shape alone (row counts on and off its 16-row MFMA tiles), against the
-    checker.  A block's bits do not depend on which other blocks share the step, nor on its place in the batch: checked
+    oracle.  A block's bits do not depend on which other blocks share the step, nor on its place in the batch: checked
     against another batch of more than 16 blocks.  Against the block decoded alone the caches agree bit for bit and the
     outputs to rounding (up to 16 rows these three projections add over K in another order)."""
     lens = [(7 * b) % 50 + 1 for b in range(n_blocks)]
@@ -197,7 +197,7 @@ def test_dense_steps_round_the_ffn_input_alike_in_both_families(d_model, n_q_hea
 @pytest.mark.parametrize("n_blocks", [20, 47])
 def test_dense_decode_with_17_to_64_blocks_at_the_smallest_shapes(n_blocks):
     """Narrow weights in the 17..64-row kernels: 32 and 34 column tiles, K = 2048 in four slices and 1088 in three of unequal
-    length, a gate/up projection of 34 workgroups: every row against the checker."""
+    length, a gate/up projection of 34 workgroups: every row against the oracle."""
     layer = LayerConfig(d_model=2048, n_q_heads=16, n_kv_heads=4, head_dim=128, ffn_dim=1088, rope_theta=500000.0, dtype="bf16")
     lens = [(11 * b) % 37 + 1 for b in range(n_blocks)]
     inp = make_inputs(Workload("edge_rows", layer, lens, n_blocks, 2), gain_jitter=True)
@@ -427,7 +427,7 @@ def test_moe_120b_shape_24_blocks_every_expert_takes_every_row():
 def test_routed_decode_steps_at_the_edges_of_the_one_workgroup_routing(n_blocks, experts, top_k):
     """Router, top-k and routing plan of a decode step: up to 16 rows the last two in one workgroup (one routed row; a row
     for every wavefront), from 17 rows apart (a plan of 255 and 256 routed rows); expert counts off and on the 64 a lane
-    slot covers.  Routing tables and every row against the checker."""
+    slot covers.  Routing tables and every row against the oracle."""
     layer = copy.deepcopy(SMALL_MOE)
     layer.n_experts, layer.top_k = experts, top_k
     wl = Workload("small_moe", layer, [(5 * b) % 11 + 1 for b in range(n_blocks)], n_blocks, 2)
