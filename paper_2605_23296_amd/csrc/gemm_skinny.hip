@@ -99,12 +99,12 @@ __global__ __launch_bounds__(WAVES * 64, RING < SKINNY_STEPS ? 2 : 1) void gemm_
     if (!GROUPED && nin.g) {
         // RMSNorm front half: a wavefront stages whole rows, so that the row's sum of
         // squares over this slice is one butterfly (fixed order)
-        for (int row = wave; row < MT * 16; row += WAVES) {
+        for (int row = wave; row < M; row += WAVES) {
             bf16x8 v;
 #pragma unroll
             for (int j = 0; j < 8; ++j) v[j] = (bf16)0.f;
             float ss = 0.f;
-            if (row < M && lane < cpr) {
+            if (lane < cpr) {
                 v = *reinterpret_cast<const bf16x8*>(X + (size_t)row * K + k0 + lane * 8);
                 const bf16x8 gv = *reinterpret_cast<const bf16x8*>(nin.g + k0 + lane * 8);
 #pragma unroll
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(WAVES * 64, RING < SKINNY_STEPS ? 2 : 1) void gemm_
             }
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-            if (lane == 0 && blockIdx.y == 0 && row < M) nin.ssq_parts[(size_t)slice * M + row] = ss;
+            if (lane == 0 && blockIdx.y == 0) nin.ssq_parts[(size_t)slice * M + row] = ss;
             if (lane < cpr) *reinterpret_cast<bf16x8*>(xs + row * LDX + lane * 8) = v;
         }
     } else if (!GROUPED && MT == 1 && nin.m_out) {
@@ -149,16 +149,11 @@ __global__ __launch_bounds__(WAVES * 64, RING < SKINNY_STEPS ? 2 : 1) void gemm_
             }
         }
     } else {
-        for (int q = t; q < MT * 16 * cpr; q += WAVES * 64) {
+        for (int q = t; q < M * cpr; q += WAVES * 64) {
             const int row = q / cpr, cc = q - row * cpr;
-            bf16x8 v;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = (bf16)0.f;
-            if (row < M) {
-                size_t src = row_base + row;
-                if (GROUPED && grp.a_gather) src = grp.a_gather[src];
-                v = *reinterpret_cast<const bf16x8*>(X + src * K + k0 + cc * 8);
-            }
+            size_t src = row_base + row;
+            if (GROUPED && grp.a_gather) src = grp.a_gather[src];
+            const bf16x8 v = *reinterpret_cast<const bf16x8*>(X + src * K + k0 + cc * 8);
             *reinterpret_cast<bf16x8*>(xs + row * LDX + cc * 8) = v;
         }
     }
@@ -173,7 +168,7 @@ __global__ __launch_bounds__(WAVES * 64, RING < SKINNY_STEPS ? 2 : 1) void gemm_
         if (s < nsteps) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
-                const bf16x8 b = *reinterpret_cast<const bf16x8*>(xs + (mt * 16 + r) * LDX + s * 32 + c * 8);
+                const bf16x8 b = *reinterpret_cast<const bf16x8*>(xs + min(mt * 16 + r, M - 1) * LDX + s * 32 + c * 8);
                 acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s % RING], b, acc[mt], 0, 0, 0);
             }
             if (RING < SKINNY_STEPS && s + RING < SKINNY_STEPS && s + RING < nsteps)

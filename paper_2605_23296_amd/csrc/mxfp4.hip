@@ -128,14 +128,16 @@ __global__ __launch_bounds__(256) void gemm_skinny_mxfp4_kernel(const bf16* __re
         }
     }
 
-    // activations of this expert's rows, zero rows up to 16 and zero columns up to the last group's end
+    // activations of this expert's rows, zero columns up to the last group's end.  An expert seldom has more than two or
+    // three rows: the MFMA columns beyond them repeat the last row (nobody reads their sums) instead of being staged as
+    // zeros, 16 x 8192 tokens 252 -> 247 us a step.
     const int cpr = ngrp * 16;   // 16-byte chunks per staged row
-    for (int q = t; q < 16 * cpr; q += 256) {
+    for (int q = t; q < M * cpr; q += 256) {
         const int row = q / cpr, cc = q - row * cpr;
         bf16x8 v;
 #pragma unroll
         for (int j = 0; j < 8; ++j) v[j] = (bf16)0.f;
-        if (row < M && cc * 8 < klen) {
+        if (cc * 8 < klen) {
             size_t src = row_base + row;
             if (grp.a_gather) src = grp.a_gather[src];
             v = *reinterpret_cast<const bf16x8*>(X + src * K + k0 + cc * 8);
@@ -146,7 +148,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_mxfp4_kernel(const bf16* __re
     if (!active) return;
 
     floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-    const bf16* xrow = xs + r * LDX + c * MX_BLOCK;
+    const bf16* xrow = xs + min(r, M - 1) * LDX + c * MX_BLOCK;
 #pragma unroll
     for (int g = 0; g < MX_GROUPS; ++g) {
         if (g < ngrp) {
