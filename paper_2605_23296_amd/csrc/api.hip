@@ -671,6 +671,9 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
         rq.inv_d = 1.0f / (float)c.d_model;
         rq.eps = c.rms_eps;
         TRY(launch_decode_qkv_epilogue(ctx, meta, N, step, b.partials, ks, b.q, kv->d_k, kv->d_v, s, &rq));
+    } else if (qkv_rope_f32_supported(c, N)) {
+        TRY(launch_qkv_rope_f32(ctx, meta, N, step, (const float*)x, (const float*)w->g_attn, (const float*)w->w_qkv, (float*)b.q,
+                                (float*)kv->d_k, (float*)kv->d_v, s));
     } else {   // the RMSNorm rides in the projection
         TRY(launch_gemm_f32(ctx, (const float*)x, (const float*)w->w_qkv, nullptr, b.partials, N, Dtot, c.d_model, 0, nullptr, s,
                             (const float*)w->g_attn));

@@ -1,72 +1,9 @@
 // fp32 attention of the fp32 storage mode.  A wavefront takes its keys 64 at a
-// time: lane = key for the scores (every lane reads its own K row and the query
-// from LDS), one wave-wide maximum and sum, then lane = output element for
-// P V (the V slab is transposed: a lane walks its own row in 16-byte pieces, the
-// probabilities come from LDS).  So the dependent chain is one reduction per 64
-// keys; visiting one key at a time it was 14.6 us for a decode step over 144 rows
-// and 65 us for the prefill of four blocks of 128.
-#include "common.h"
-#include "vecio.h"
-
-#define F32_KEYS 64
-
-// running softmax state of one query row held across a wavefront:
-// lane l owns output elements l and l + 64 (the second only when hd = 128)
-struct RowState {
-    float m, l, acc[2];
-};
-
-// keys j0 .. j0 + n - 1 (n <= 64) of one KV head; qs: the query row (LDS), ps: 64 floats of the wavefront (LDS).
-
-template <int HD>
-__device__ __forceinline__ void visit_keys(RowState& st, const float* qs, float* ps, const float* __restrict__ kslab,
-                                           const float* __restrict__ vslab, int64_t vstride, int j0, int n, float scale) {
-    const int lane = threadIdx.x & (WAVE - 1);
-    float sc = -INFINITY;
-    {
-        const float* kr = kslab + (size_t)(j0 + min(lane, n - 1)) * HD;
-        float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int d = 0; d < HD; d += 4) {
-            const float4 k = *reinterpret_cast<const float4*>(kr + d);
-            const float4 q = *reinterpret_cast<const float4*>(qs + d);
-            a.x = fmaf(q.x, k.x, a.x); a.y = fmaf(q.y, k.y, a.y); a.z = fmaf(q.z, k.z, a.z); a.w = fmaf(q.w, k.w, a.w);
-        }
-        if (lane < n) sc = ((a.x + a.y) + (a.z + a.w)) * scale;
-    }
-    const float mn = fmaxf(st.m, wave_max(sc));
-    const float corr = expf(st.m - mn);   // exp(-inf) = 0 on the first keys
-    const float p = expf(sc - mn);
-    st.l = st.l * corr + wave_sum(p);
-    st.m = mn;
-    ps[lane] = p;
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int u = 0; u < HD / 64; ++u) {
-        const float* vr = vslab + (int64_t)(u * 64 + lane) * vstride + j0;
-        float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-        const int n4 = n & ~3;   // (slab rows are whole 16-byte pieces, j0 is a multiple of 4)
-        int k = 0;
-        for (; k + 16 <= n4; k += 16) {
-            float4 v[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const float4*>(vr + k + 4 * i);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float4 w = *reinterpret_cast<const float4*>(ps + k + 4 * i);
-                a.x = fmaf(w.x, v[i].x, a.x); a.y = fmaf(w.y, v[i].y, a.y); a.z = fmaf(w.z, v[i].z, a.z); a.w = fmaf(w.w, v[i].w, a.w);
-            }
-        }
-        for (; k < n4; k += 4) {
-            const float4 v = *reinterpret_cast<const float4*>(vr + k);
-            const float4 w = *reinterpret_cast<const float4*>(ps + k);
-            a.x = fmaf(w.x, v.x, a.x); a.y = fmaf(w.y, v.y, a.y); a.z = fmaf(w.z, v.z, a.z); a.w = fmaf(w.w, v.w, a.w);
-        }
-        for (; k < n; ++k) a.x = fmaf(ps[k], vr[k], a.x);
-        st.acc[u] = st.acc[u] * corr + ((a.x + a.y) + (a.z + a.w));
-    }
-    __builtin_amdgcn_wave_barrier();
-}
+// time (attn_f32.h): scores, one wave-wide maximum and sum, then P V (the V slab is
+// transposed).  So the dependent chain is one reduction per 64 keys; visiting one key
+// at a time it was 14.6 us for a decode step over 144 rows and 65 us for the prefill
+// of four blocks of 128.
+#include "attn_f32.h"
 
 template <int HD>
 __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(const BlockMeta* __restrict__ meta,
@@ -94,7 +31,7 @@ __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(const BlockMeta* 
         visit_keys<HD>(st, qs[w], ps[w], kslab, vslab, bm.capacity, j, min(F32_KEYS, n_keys - j), scale);
     float* orow = o + (size_t)(bm.row0 + i) * Hq * HD + h * HD;
 #pragma unroll
-    for (int u = 0; u < HD / 64; ++u) orow[u * 64 + lane] = st.acc[u] / st.l;
+    for (int u = 0; u < HD / 64; ++u) orow[state_element(u)] = st.acc[u] / st.l;
 }
 
 int launch_attn_prefill_f32(compact_ctx* ctx, const BlockMeta* d_meta, int n_blocks, int max_len, const float* qkv,
@@ -139,18 +76,11 @@ __global__ __launch_bounds__(256) void attn_decode_f32_kernel(const BlockMeta* _
     for (int u = 0; u < HD / 64; ++u) sacc[w][u * 64 + lane] = st.acc[u];
     __syncthreads();
     if (w == 0) {
-        float m = -INFINITY;
-        for (int i = 0; i < 4; ++i) m = fmaxf(m, sm[i]);
-        float l = 0.f, a[2] = {0.f, 0.f};
-        for (int i = 0; i < 4; ++i) {
-            const float f = sl[i] > 0.f ? expf(sm[i] - m) : 0.f;  // a wavefront may have seen no key
-            l += sl[i] * f;
-#pragma unroll
-            for (int u = 0; u < HD / 64; ++u) a[u] += sacc[i][u * 64 + lane] * f;
-        }
+        float out[2];
+        merge_states<HD>(sm, sl, sacc, out);
         float* orow = o + (size_t)blockIdx.y * Hq * HD + h * HD;
 #pragma unroll
-        for (int u = 0; u < HD / 64; ++u) orow[u * 64 + lane] = a[u] / l;
+        for (int u = 0; u < HD / 64; ++u) orow[state_element(u)] = out[u];
     }
 }
 

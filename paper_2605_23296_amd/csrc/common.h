@@ -191,6 +191,10 @@ int launch_gemm_f32(compact_ctx* ctx, const float* A, const float* B, const floa
                     int64_t M, int N, int K, int epilogue, const GroupedArgs* grouped, hipStream_t s,
                     const float* norm_g = nullptr);
 int gemm_f32_mtile();
+// decode rows: RMSNorm, q/k/v projection, rotation and cache append in one kernel
+bool qkv_rope_f32_supported(const compact_layer_cfg& c, int rows);
+int launch_qkv_rope_f32(compact_ctx* ctx, const BlockMeta* d_meta, int rows, int step, const float* x, const float* g,
+                        const float* w_qkv, float* q, float* d_k, float* d_v, hipStream_t s);
 
 // gemm_bf16.hip
 // epilogue 0: bf16 C = acc (+R); 1: SwiGLU on stacked gate/up; 2: fp32 C = acc (+R).  R is bf16, or fp32 if r_f32.

@@ -10,7 +10,7 @@
 // split depends on K alone, so a row's bits do not depend on how many rows share
 // the call.  Before (64 x 64 tiles, one sequence over K): 4 rows x 256 columns,
 // K 1024, 60 us.
-#include "common.h"
+#include "vecio.h"
 
 #define F32_CHUNK 16   // k per chunk: one float4 per lane, four MFMAs
 
@@ -26,6 +26,82 @@ struct F32Gemm {
     GroupedArgs g;
 };
 
+__device__ __forceinline__ int wave_index() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#else
+    return 0;
+#endif
+}
+
+// Wavefront w's share of MT x NB output tiles (rows arow[], weight rows brow[] of the lane), and with a norm its share of the
+// rows' sums of squares.  UN: chunks in flight.
+template <int MT, int NB, int WAVES, int UN>
+__device__ __forceinline__ void accumulate(const F32Gemm& p, const float* const (&arow)[MT], const float* const (&brow)[NB], int w,
+                                           int c, floatx4 (&acc)[MT][NB], float (&ss)[MT]) {
+    // lane (r, c) holds k = 16 q + 4 c .. + 3 of row r: MFMA e takes element e of every lane, so a chunk's products are
+    // added in the order k = e, 4 + e, 8 + e, 12 + e, the same for both operands
+    auto load = [&](const float* row, int q) {
+        const int k = q * F32_CHUNK + c * 4;
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (k + e < p.K) v[e] = row[k + e];
+        return v;
+    };
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        ss[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int nq = (p.K + F32_CHUNK - 1) / F32_CHUNK;
+    for (int q0 = w; q0 < nq; q0 += UN * WAVES) {
+        floatx4 av[UN][MT], bv[UN][NB], gv[UN];
+        if (p.vec) {   // past K: the last chunk again, which is not multiplied
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int k = min(q0 + u * WAVES, nq - 1) * F32_CHUNK + c * 4;
+#pragma unroll
+                for (int j = 0; j < NB; ++j) bv[u][j] = *reinterpret_cast<const floatx4*>(brow[j] + k);
+                if (p.norm_g) gv[u] = *reinterpret_cast<const floatx4*>(p.norm_g + k);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) av[u][i] = *reinterpret_cast<const floatx4*>(arow[i] + k);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int q = q0 + u * WAVES;
+#pragma unroll
+                for (int i = 0; i < MT; ++i) av[u][i] = load(arow[i], q);
+#pragma unroll
+                for (int j = 0; j < NB; ++j) bv[u][j] = load(brow[j], q);
+                if (p.norm_g) gv[u] = load(p.norm_g, q);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            if (q0 + u * WAVES >= nq) continue;
+            if (p.norm_g) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        ss[i] = fmaf(av[u][i][e], av[u][i][e], ss[i]);
+                        av[u][i][e] *= gv[u][e];
+                    }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], bv[u][j][e], acc[i][j], 0, 0, 0);
+        }
+    }
+}
+
 // EPI 0: C = acc (+R).  EPI 1: B is [2N, K] (gate rows then up rows); C = silu(A Bg^T) * (A Bu^T).
 // With a GroupedArgs map, row tile blockIdx.y covers rows tile_row0 .. +tile_rows of the expert-sorted order, reads A
 // rows through a_gather and uses expert tile_expert's slice of B.
@@ -35,7 +111,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_f32_kernel(const F32Gemm p) {
     constexpr int PT = MT > 2 ? 1 : MT;          // row tiles that are added up at a time
     __shared__ floatx4 part[WAVES][PT * NB][64];
     __shared__ float ssq[WAVES][MT * 16];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, w = wave_index();
     const int r = lane & 15, c = lane >> 4;
     int64_t m0 = (int64_t)blockIdx.y * 16 * MT, m_end = p.M;
     const float* B = p.B;
@@ -56,61 +132,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_f32_kernel(const F32Gemm p) {
     }
 #pragma unroll
     for (int j = 0; j < NB; ++j) brow[j] = B + (int64_t)(min(n0 + (j % NT) * 16 + r, p.N - 1) + (j / NT) * p.N) * p.K;
-    // lane (r, c) holds k = 16 q + 4 c .. + 3 of row r: MFMA e takes element e of every lane, so a chunk's products are
-    // added in the order k = e, 4 + e, 8 + e, 12 + e, the same for both operands
-    auto load = [&](const float* row, int q) {
-        const int k = q * F32_CHUNK + c * 4;
-        floatx4 v = {0.f, 0.f, 0.f, 0.f};
-        if (p.vec) {
-            if (k < p.K) v = *reinterpret_cast<const floatx4*>(row + k);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (k + e < p.K) v[e] = row[k + e];
-        }
-        return v;
-    };
     floatx4 acc[MT][NB];
     float ss[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-        ss[i] = 0.f;
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    const int nq = (p.K + F32_CHUNK - 1) / F32_CHUNK;
-    constexpr int UN = MT * NB > 4 ? 2 : 4;   // chunks in flight (chunks past K load zeros)
-    for (int q0 = w; q0 < nq; q0 += UN * WAVES) {
-        floatx4 av[UN][MT], bv[UN][NB], gv[UN];
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int q = q0 + u * WAVES;
-#pragma unroll
-            for (int i = 0; i < MT; ++i) av[u][i] = load(arow[i], q);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) bv[u][j] = load(brow[j], q);
-            if (p.norm_g) gv[u] = load(p.norm_g, q);
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            if (p.norm_g) {
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        ss[i] = fmaf(av[u][i][e], av[u][i][e], ss[i]);
-                        av[u][i][e] *= gv[u][e];
-                    }
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < NB; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], bv[u][j][e], acc[i][j], 0, 0, 0);
-        }
-    }
+    // one 16 x 16 tile over K = 1024 in one trip: 6.4 -> 4.9 us
+    constexpr int UN = MT * NB > 4 ? 2 : MT * NB == 1 && WAVES == 8 ? 8 : 4;
+    accumulate<MT, NB, WAVES, UN>(p, arow, brow, w, c, acc, ss);
     if (p.norm_g) {
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
@@ -118,6 +144,42 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_f32_kernel(const F32Gemm p) {
             ss[i] += __shfl_xor(ss[i], 32, 64);
             if (c == 0) ssq[w][i * 16 + r] = ss[i];
         }
+    }
+    if constexpr (MT == 1 && NT == 1) {
+        // one output per thread: few rows make latency, so the square root, the division and the exponential of an output
+        // run beside those of the others
+#pragma unroll
+        for (int j = 0; j < NB; ++j) part[w][j][lane] = acc[0][j];
+        const int row = threadIdx.x >> 4, n = n0 + (threadIdx.x & 15);
+        const int64_t m = m0 + row;
+        const bool finish = threadIdx.x < 256 && m < m_end && n < p.N;
+        float res = 0.f;
+        if (EPI == 0 && finish && p.R) res = p.R[m * p.N + n];
+        __syncthreads();
+        if (!finish) return;
+        // output (row, column) is element row % 4 of lane (column, row / 4)
+        const int from = (row >> 2) * 16 + (threadIdx.x & 15), e = row & 3;
+        float o = part[0][0][from][e], u = part[0][NB - 1][from][e];
+#pragma unroll
+        for (int k = 1; k < WAVES; ++k) {
+            o += part[k][0][from][e];
+            u += part[k][NB - 1][from][e];
+        }
+        if (p.norm_g) {
+            float s = ssq[0][row];
+#pragma unroll
+            for (int k = 1; k < WAVES; ++k) s += ssq[k][row];
+            const float rinv = 1.0f / sqrtf(s / (float)p.K + p.norm_eps);
+            o *= rinv;
+            u *= rinv;
+        }
+        if (EPI == 1)
+            o = o / (1.0f + expf(-o)) * u;
+        else if (p.R)
+            o += res;
+        if (p.g.row_scale) o *= p.g.row_scale[m];
+        p.C[m * p.N + n] = o;
+        return;
     }
 #pragma unroll
     for (int i0 = 0; i0 < MT; i0 += PT) {
@@ -168,6 +230,112 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_f32_kernel(const F32Gemm p) {
             }
         }
     }
+}
+
+// Decode rows: RMSNorm, q/k/v projection, rotation and cache append in one kernel.  A workgroup is two groups of WAVES
+// wavefronts: columns i0 .. i0 + 15 of a head and the HD / 2 columns further that they are rotated with.  Sums, factors and
+// rotation are those of gemm_f32_kernel and of the decode epilogue (norm_rope.hip), so a row has the same bits either way;
+// the angles are formed before the sums.  Bound: latency, the launch that it saves was 2.7 of a step's 28 us (d 256).
+struct F32QkvOut {
+    const BlockMeta* meta;
+    float *q, *k, *v;
+    int step, Hq, Hkv, hd;
+    double log2_theta;
+};
+// SINE: wavefronts beside the two groups that form the angles (0: the first of group 0, after their sums).
+template <int WAVES, int SINE>
+__global__ __launch_bounds__((2 * WAVES + SINE) * 64) void qkv_rope_f32_kernel(const F32Gemm p, const F32QkvOut o) {
+    __shared__ floatx4 part[2 * WAVES][64];
+    __shared__ float2 angle[256];
+    __shared__ float ssq[WAVES][16];
+    const int lane = threadIdx.x & 63, w = wave_index();
+    const int grp = w / WAVES, wg = w % WAVES;
+    const int r = lane & 15, c = lane >> 4;
+    const int per_head = o.hd / 32, head = blockIdx.x / per_head, i0 = blockIdx.x % per_head * 16;
+    const int m0 = blockIdx.y * 16;
+    // thread t < 256 finishes row m0 + t / 16, elements i0 + t % 16 and o.hd / 2 further
+    const int row = (threadIdx.x & 255) >> 4, m = min(m0 + row, (int)p.M - 1), col = i0 + (threadIdx.x & 15);
+    const bool finish = threadIdx.x < 256 && m0 + row < p.M;
+    const BlockMeta bm = o.meta[m];
+    auto form_angle = [&]() {
+        if (m0 + row >= p.M || head >= o.Hq + o.Hkv) return;
+        const double inv_freq = exp2(-2.0 * (double)col / (double)o.hd * o.log2_theta);
+        double sn, cn;
+        sincos((double)(bm.pos_offset + bm.len + o.step) * inv_freq, &sn, &cn);
+        angle[threadIdx.x & 255] = make_float2((float)cn, (float)sn);
+    };
+    if (w >= 2 * WAVES) {
+        form_angle();
+    } else {
+        const float* arow[1] = {p.A + (int64_t)min(m0 + r, (int)p.M - 1) * p.K};
+        const float* brow[1] = {p.B + (int64_t)(head * o.hd + grp * (o.hd / 2) + i0 + r) * p.K};
+        floatx4 acc[1][1];
+        float ss[1];
+        accumulate<1, 1, WAVES, 4>(p, arow, brow, wg, c, acc, ss);
+        ss[0] += __shfl_xor(ss[0], 16, 64);
+        ss[0] += __shfl_xor(ss[0], 32, 64);
+        if (grp == 0 && c == 0) ssq[wg][r] = ss[0];
+        part[w][lane] = acc[0][0];
+        if (SINE == 0 && threadIdx.x < 256) form_angle();
+    }
+    __syncthreads();
+    if (!finish) return;
+    float s = ssq[0][row];
+#pragma unroll
+    for (int k = 1; k < WAVES; ++k) s += ssq[k][row];
+    const float rinv = 1.0f / sqrtf(s / (float)p.K + p.norm_eps);
+    // output (row, column) of a tile is element row % 4 of lane (column, row / 4)
+    const int from = (row >> 2) * 16 + (threadIdx.x & 15), e = row & 3;
+    float lo = part[0][from][e], up = part[WAVES][from][e];
+#pragma unroll
+    for (int k = 1; k < WAVES; ++k) {
+        lo += part[k][from][e];
+        up += part[WAVES + k][from][e];
+    }
+    lo *= rinv;
+    up *= rinv;
+    const int pos = bm.len + o.step;
+    if (head < o.Hq + o.Hkv) {
+        float olo, ohi;
+        rotate(lo, up, angle[threadIdx.x].x, angle[threadIdx.x].y, olo, ohi);
+        float* dst = head < o.Hq ? o.q + ((int64_t)m * o.Hq + head) * o.hd
+                                 : o.k + bm.slab + ((int64_t)(head - o.Hq) * bm.capacity + pos) * o.hd;
+        dst[col] = olo;
+        dst[o.hd / 2 + col] = ohi;
+    } else {
+        float* vcol = o.v + bm.slab + (int64_t)(head - o.Hq - o.Hkv) * o.hd * bm.capacity + pos;
+        vcol[(int64_t)col * bm.capacity] = lo;
+        vcol[(int64_t)(o.hd / 2 + col) * bm.capacity] = up;
+    }
+}
+
+// Covers what the 16 x 16 tiles of launch_f32 cover; beyond that larger tiles and a launch of its own for the rotation.
+bool qkv_rope_f32_supported(const compact_layer_cfg& c, int rows) {
+    const int64_t cols = (int64_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+    return c.dtype == COMPACT_FP32 && (rows + 15) / 16 * (cols / 16) <= 2048;
+}
+
+int launch_qkv_rope_f32(compact_ctx* ctx, const BlockMeta* d_meta, int rows, int step, const float* x, const float* g,
+                        const float* w_qkv, float* q, float* d_k, float* d_v, hipStream_t s) {
+    const compact_layer_cfg& c = ctx->cfg;
+    if (!qkv_rope_f32_supported(c, rows)) return set_err(ctx, COMPACT_ESHAPE, "fused q/k/v decode kernel does not cover this shape");
+    F32Gemm p{};
+    p.A = x;
+    p.B = w_qkv;
+    p.M = rows;
+    p.N = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+    p.K = c.d_model;
+    p.vec = p.K % F32_CHUNK == 0 && (((uintptr_t)x | (uintptr_t)w_qkv | (uintptr_t)g) & 15) == 0;
+    p.norm_g = g;
+    p.norm_eps = c.rms_eps;
+    const F32QkvOut o{d_meta, q, d_k, d_v, step, c.n_q_heads, c.n_kv_heads, c.head_dim, log2((double)c.rope_theta)};
+    const dim3 grid(p.N / 32, (rows + 15) / 16);
+    if (p.K >= 1024)
+        qkv_rope_f32_kernel<8, 0><<<grid, 1024, 0, s>>>(p, o);
+    else
+        qkv_rope_f32_kernel<4, 4><<<grid, 768, 0, s>>>(p, o);
+    LAUNCH_CHECK(ctx);
+    return COMPACT_OK;
 }
 
 int gemm_f32_mtile() { return 32; }

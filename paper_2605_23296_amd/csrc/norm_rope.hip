@@ -74,13 +74,6 @@ int launch_rmsnorm(compact_ctx* ctx, const void* x, bool x_is_f32, const void* g
 // whole launch (32 tiles: 77 -> 17 us).  Bound with many tiles: HBM (read + write
 // of the rows, 8 x 4096: 4.6 TB/s).
 // ---------------------------------------------------------------------------
-// The rotation of one pair, shared with the decode epilogue.  The contraction is written out: left to the compiler it
-// changes with the code around it, and a row rotated in a prefill would no longer have the bits of the same row rotated
-// in a decode step.
-__device__ __forceinline__ void rotate(float lo, float hi, float c, float s, float& olo, float& ohi) {
-    olo = fmaf(lo, c, -(hi * s));
-    ohi = fmaf(hi, c, lo * s);
-}
 #define ROPE_BATCH 4   // pieces a thread loads before it stores any
 template <typename T>
 __global__ __launch_bounds__(NT) void rope_kvwrite_kernel(const BlockMeta* __restrict__ meta,

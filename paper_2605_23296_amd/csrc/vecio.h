@@ -39,3 +39,11 @@ __device__ __forceinline__ float wave_max(float v) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
     return v;
 }
+
+// The rotation of one pair, shared with the decode epilogue.  The contraction is written out: left to the compiler it
+// changes with the code around it, and a row rotated in a prefill would no longer have the bits of the same row rotated
+// in a decode step.
+__device__ __forceinline__ void rotate(float lo, float hi, float c, float s, float& olo, float& ohi) {
+    olo = fmaf(lo, c, -(hi * s));
+    ohi = fmaf(hi, c, lo * s);
+}

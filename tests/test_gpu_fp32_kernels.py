@@ -1,5 +1,8 @@
 """fp32 storage kernels at the edges of their pieces: k-chunks of 16 dealt to four or eight wavefronts, output tiles of 16, 32
 and 64, keys 64 at a time."""
+import copy
+
+import numpy as np
 import pytest
 import torch
 
@@ -45,3 +48,25 @@ def test_prefill_attention_fp32_key_pieces(layer):
 def test_decode_attention_fp32_key_pieces(layer):
     # fewer pieces than wavefronts, exactly one each, a second round that only some wavefronts take part in
     decode_case(fp32_variant(layer), [1, 3, 63, 64, 65, 192, 255, 256, 257, 333, 600], 62)
+
+
+# 16-column tiles beyond 2048 leave the kernel that projects, rotates and appends in one launch; four wavefronts a tile below
+# d_model 1024, eight from there on; both head sizes; row counts around a tile of 16
+@pytest.mark.parametrize("d_model,head_dim,n_blocks", [(256, 64, 1100), (1088, 128, 700)])
+def test_decode_rows_have_the_same_bits_in_the_fused_and_the_separate_projection(d_model, head_dim, n_blocks):
+    from paper_2605_23296_amd.workloads import LayerConfig, Workload, make_inputs
+    from tests import harness as H
+    layer = LayerConfig(d_model=d_model, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, ffn_dim=128, rope_theta=10000.0, dtype="fp32")
+    lens = [1 + (b * 5) % 3 for b in range(n_blocks)]
+    big = make_inputs(Workload("many", layer, lens, n_blocks, 2), gain_jitter=True)
+    lay = H.gpu_layer(big)
+    full = H.gpu_forward(big, lay=lay)
+    cu = big.cu_seqlens
+    for n in (1, 15, 16, 17, 33):
+        few = copy.copy(big)
+        few.block_lens, few.cu_seqlens = lens[:n], cu[:n + 1]
+        few.x_prefill, few.x_decode = big.x_prefill[:cu[n]].contiguous(), big.x_decode[:, :n].contiguous()
+        g = H.gpu_forward(few, lay=lay)
+        assert np.array_equal(g["y_decode"], full["y_decode"][:, :n]), n
+        for b in (0, n - 1):
+            assert np.array_equal(g["K"][b], full["K"][b]) and np.array_equal(g["V"][b], full["V"][b]), (n, b)
