@@ -137,3 +137,45 @@ def test_dense_8x4096_in_chunks_of_1024_matches_the_one_piece_prefill():
         assert torch.equal(g["kv"].block_v(b), kv.block_v(b))
     d = (g["y"].float() - y.float()).norm(dim=1) / y.float().norm(dim=1)
     assert d.max().item() < 2e-2, d.max().item()
+
+
+# Few rows behind a long cache: their keys are shared among 2 .. 16 items.  Chunks of 1 to 600 rows, caches that end on and off
+# the 64-row key tiles, the fewest cached rows that are cut (1024: two items of 8 tiles) and one less; both attention kernels
+# of head_dim 128 and that of 64.
+@pytest.mark.parametrize("heads", [(4, 2, 128), (3, 1, 128), (8, 2, 64)], ids=str)
+def test_few_rows_behind_a_long_cache(heads):
+    layer = LayerConfig(d_model=256, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=heads[2], ffn_dim=256, rope_theta=500000.0)
+    lens = [1023 + 1 + 1 + 17 + 129, 1500 + 600 + 64, 520 + 120]
+    cuts = [[1023, 1, 1, 17, 129], [1500, 600, 64], [520, 120]]
+    inp = make_inputs(Workload("long_cache", layer, lens, 3, 1), gain_jitter=True)
+    check(inp, cuts, 1)
+    # a block's rows do not depend on what shares the calls
+    full = run_chunked(inp, cuts)
+    import copy
+    for b in range(3):
+        one = copy.copy(inp)
+        one.block_lens, one.cu_seqlens = [lens[b]], [0, lens[b]]
+        one.x_prefill = inp.x_prefill[inp.cu_seqlens[b]:inp.cu_seqlens[b + 1]].contiguous()
+        g = run_chunked(one, [cuts[b]])
+        assert torch.equal(g["y"].view(torch.int16), full["y"][inp.cu_seqlens[b]:inp.cu_seqlens[b + 1]].view(torch.int16)), b
+
+
+def test_a_workspace_without_room_for_shared_keys_still_serves():
+    """The records of shared keys come out of the workspace; one that holds everything else gives the same rows to rounding."""
+    layer = LayerConfig(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=256, rope_theta=500000.0)
+    inp = make_inputs(Workload("long_cache", layer, [2064], 1, 1))
+    lay = H.gpu_layer(inp)
+    x = inp.x_prefill.to(DEV)
+    outs = []
+    for roomy in (True, False):
+        kv = B.KVCache(layer, [2072], DEV, torch.bfloat16)
+        y = torch.empty(2064, 256, dtype=torch.bfloat16, device=DEV)
+        lay.ensure_workspace(2048, 1, 2072, DEV)
+        lay.compact_prefill([0, 2048], x[:2048].contiguous(), kv, y[:2048])
+        if not roomy:
+            # 16 rows: n, m, qkv, o, h, act of 16 rows of at most 1024 columns, a 256-byte gap after each
+            lay.ws = torch.empty(16 * (256 * 2 + 1024 * 2 + 512 * 2 + 256 * 4 + 256 * 2) + 6 * 256, dtype=torch.uint8, device=DEV)
+        tail = torch.empty(16, 256, dtype=torch.bfloat16, device=DEV)
+        lay.compact_prefill_extend([0, 16], x[2048:].contiguous(), kv, tail)
+        outs.append(to_numpy_f64(tail))
+    assert np.linalg.norm(outs[0] - outs[1]) < 4e-3 * np.linalg.norm(outs[1])
