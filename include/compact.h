@@ -47,8 +47,6 @@
  *    projections after the attention add over K in another order).  Routed layers
  *    choose their experts from the same bits in both families; their outputs are
  *    bit-identical as long as blocks x top_k of a step or group is at most 256.
- *    Dense layers of d_model 8192 whose query heads span 2048 or 4096 columns have
- *    a third family, for at most 8 blocks.
  */
 #ifndef COMPACT_H
 #define COMPACT_H

@@ -749,22 +749,18 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
     // 17 .. 64 rows of a dense layer: projections by the ring GEMM, split over K.  A routed layer keeps the sums and the
     // roundings of the kernels for at most 16 rows: its router chooses by them.
     const bool many = bf && N > 16 && c.n_experts == 0;
-    const bool o_few = bf && resid_norm_stream_supported(N, c.d_model, Dq);
-    const bool o_routed = bf && N > 16 && c.n_experts > 0 && stream_mt_supported(N, c.d_model, Dq) &&
-                          resid_norm_stream_supported(16, c.d_model, Dq);
+    const bool o_few = bf && N <= 16 && (c.n_experts == 0 || stream_mt_supported(17, c.d_model, Dq));
+    const bool o_routed = bf && N > 16 && c.n_experts > 0 && stream_mt_supported(N, c.d_model, Dq);
     const float* pre_scale = nullptr;
     if (many) {
         {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
             TRY(launch_gemm_rows64(ctx, (const bf16*)b.o, (const bf16*)w->w_o, b.partials, N, c.d_model, Dq, s));
         }
-        // the gate/up operand is rounded as the kernels for at most 16 rows round it for a layer of this shape
-        NormRounding rounding = NORM_ONCE;
-        if (resid_norm_stream_supported(16, c.d_model, Dq))
-            rounding = skinny_swiglu_supported(16, c.ffn_dim, c.d_model) ? NORM_LATER : NORM_TWICE;
-        TRY(launch_residual_norm(ctx, b.partials, gemm_rows64_slices(c.d_model, Dq), x, w->g_ffn, b.h, b.m, N, s, rounding,
+        // the gate/up operand is rounded as the kernels for at most 16 rows round it
+        TRY(launch_residual_norm(ctx, b.partials, gemm_rows64_slices(c.d_model, Dq), x, w->g_ffn, b.h, b.m, N, s, NORM_LATER,
                                  b.ssq_parts));
-        if (rounding == NORM_LATER) pre_scale = b.ssq_parts;
+        pre_scale = b.ssq_parts;
     } else if (o_few || o_routed) {
         ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
         if (o_few)
@@ -803,25 +799,15 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
         }
         TRY(launch_residual_reduce(ctx, b.partials, gemm_rows64_slices(c.d_model, c.ffn_dim), b.h, y, N, c.d_model, s));
     } else if (c.n_experts == 0) {
-        if (skinny_swiglu_supported(N, c.ffn_dim, c.d_model)) {
+        {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
-            TRY(launch_gemm_skinny_swiglu(ctx, (const bf16*)ffn_in, (const bf16*)w->w_gate_up, (bf16*)b.act, N, c.ffn_dim,
-                                          c.d_model, pending_norm ? &rn : nullptr, s));
-        } else {
-            if (pending_norm) {
-                TRY(launch_rownorm_apply(ctx, (const bf16*)b.hg, rn, (bf16*)b.m, N, c.d_model, s));
-                ffn_in = b.m;
-            }
-            TRY(gemm_partials(ctx, ffn_in, w->w_gate_up, b.partials, N, 2 * c.ffn_dim, c.d_model, &ks, s));
-            TRY(launch_swiglu_reduce(ctx, b.partials, ks, b.act, N, c.ffn_dim, s));
+            TRY(launch_swiglu_stream(ctx, (const bf16*)ffn_in, (const bf16*)w->w_gate_up, (bf16*)b.act, N, c.ffn_dim, c.d_model,
+                                     pending_norm ? &rn : nullptr, s));
         }
-        if (resid_out_stream_supported(N, c.d_model, c.ffn_dim)) {
+        {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
             TRY(launch_resid_out_stream(ctx, (const bf16*)b.act, (const bf16*)w->w_down, b.h, (bf16*)y, N, c.d_model,
                                         c.ffn_dim, s));
-        } else {
-            TRY(gemm_partials(ctx, b.act, w->w_down, b.partials, N, c.d_model, c.ffn_dim, &ks, s));
-            TRY(launch_residual_reduce(ctx, b.partials, ks, b.h, y, N, c.d_model, s));
         }
     } else {
         int32_t* idx = route && route->d_expert_idx ? route->d_expert_idx : b.idx;

@@ -170,7 +170,6 @@ int launch_decode_qkv_epilogue(compact_ctx* ctx, const BlockMeta* d_meta, int n_
 // the step's other kernels round it, so that it does not depend on how many rows share the step:
 enum NormRounding {
     NORM_ONCE,    // m = bf16(h g / rms)
-    NORM_TWICE,   // m = bf16(bf16(h g) / rms)
     NORM_LATER    // m = bf16(h g), the rows' 1 / rms to rinv_out: the consumer multiplies its products by it
 };
 int launch_residual_norm(compact_ctx* ctx, const float* partials, int ks, const void* resid,
@@ -255,23 +254,18 @@ int launch_gemm_skinny_grouped(compact_ctx* ctx, const bf16* X, const int32_t* a
 // expert_list (nullable): the experts to run, one per grid slice, -1 = none; spares launching a slice per idle
 // expert.  With tile_row0 / tile_rows (the routing plan's tile map, tiles of at most 16 rows) a grid slice is a
 // tile: an expert with more than 16 rows is streamed once per tile of 16
-// decode gate/up projection with the SwiGLU fused in (no partials): act[M, F] =
-// silu(r X Wg^T) * (r X Wu^T); X may hold un-normalised rows (x * g) whose 1/rms r
-// comes from `norm` (null: r = 1)
-bool skinny_swiglu_supported(int M, int F, int K);
-int launch_gemm_skinny_swiglu(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* act, int M, int F, int K,
-                              const RowNorm* norm, hipStream_t s);
 // C = sum of partials (+R), rounded to bf16
 int launch_skinny_finish(compact_ctx* ctx, const float* partials, int ks, const bf16* R, bf16* C, int M, int N,
                          hipStream_t s);
 
-// gemv_stream.hip : whole-K decode projections with the following step fused in (bf16, <= 16 rows)
+// gemv_stream.hip : whole-K decode projections with the following step fused in (bf16, at most 16 rows, N % 16 == 0, K % 64 == 0)
 // h = resid + X W^T (fp32), hg = bf16(h * g), ssq_parts[N / 16][M] = column-group sums of h^2
-bool resid_norm_stream_supported(int M, int N, int K);
 int launch_resid_norm_stream(compact_ctx* ctx, const bf16* X, const bf16* W, const bf16* resid, const bf16* g, float* h_out,
                              bf16* hg_out, float* ssq_parts, int M, int N, int K, hipStream_t s);
-// y = bf16(resid_f32 + X W^T), K a multiple of 512
-bool resid_out_stream_supported(int M, int N, int K);
+// act[M, F] = silu(r X Wg^T) * (r X Wu^T); X may hold un-normalised rows (x * g) whose 1/rms r comes from `norm` (null: r = 1)
+int launch_swiglu_stream(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* act, int M, int F, int K, const RowNorm* norm,
+                         hipStream_t s);
+// y = bf16(resid_f32 + X W^T)
 int launch_resid_out_stream(compact_ctx* ctx, const bf16* X, const bf16* W, const float* resid, bf16* y, int M, int N, int K,
                             hipStream_t s);
 // gemv_stream_mt.hip : the same projection for 17 .. 64 rows, with the sums of the kernel for at most 16 (routed layers)

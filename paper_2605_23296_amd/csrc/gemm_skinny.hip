@@ -183,153 +183,6 @@ __global__ __launch_bounds__(WAVES * 64, RING < SKINNY_STEPS ? 2 : 1) void gemm_
     }
 }
 
-// ---------------------------------------------------------------------------
-// Gate/up projection of the decode step with the SwiGLU fused in:
-// act[M, F] = silu(X Wg^T) * (X Wu^T) for M <= MROWS activation rows.
-// A workgroup (16 wavefronts) owns 32 act columns = SG_TILES = four MFMA tiles of 8 gate +
-// 8 up weight rows, over the whole K.  Wavefront (rt, kw) streams tile rt's
-// k-steps kw, kw+4, kw+8, ... so that the four wavefronts of a tile read
-// neighbouring 64-byte pieces of the same weight rows at the same time; each
-// keeps a ring of 8 loads in flight.  The partial tiles are added in kw order
-// through LDS (over the staged activations, dead by then), then gate and up
-// values (32 lanes apart in the accumulator layout) are paired by shuffle.  No
-// split-K partials leave the kernel.  SPW = k-steps of 32 per wavefront = K / 128.
-// Four tiles per workgroup with 64 registers per lane: two workgroups per CU hold
-// all 448 workgroups of the 8B-shaped layer at once (two tiles, 8 wavefronts, a
-// ring of 16: 896 workgroups in 1.75 rounds and twice the activation staging,
-// 52.2 us against 49.6 us).
-// ---------------------------------------------------------------------------
-#define SG_TILES 4
-#define SG_RING 8
-template <int MROWS, int SPW>
-__global__ __launch_bounds__(SG_TILES * 256, 2) void gemm_skinny_swiglu_kernel(const bf16* __restrict__ X, const bf16* __restrict__ W,
-                                                                 bf16* __restrict__ act, int M, int F, const RowNorm norm) {
-    constexpr int K = SPW * 128;
-    constexpr int LDX = K + 8;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    bf16* xs = reinterpret_cast<bf16*>(smem);                                          // [MROWS][LDX]
-    float* red = reinterpret_cast<float*>(smem);  // [4 SG_TILES][64][4], over the activations once every wavefront is done with them
-    __shared__ float rinv[16];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int rt = wave >> 2, kw = wave & 3;
-    const int r = lane & 15, c = lane >> 4;
-    const int j0 = blockIdx.x * (SG_TILES * 8);
-
-    // weight row of MFMA row r: 8 gate rows then the 8 matching up rows
-    const int col = min(j0 + rt * 8 + (r & 7), F - 1);
-    const bf16* wrow = W + (size_t)(r < 8 ? col : F + col) * K + kw * 32 + c * 8;
-    bf16x8 ring[SG_RING];
-#pragma unroll
-    for (int i = 0; i < SG_RING && i < SPW; ++i) ring[i] = *reinterpret_cast<const bf16x8*>(wrow + i * 128);
-
-    // activations: all of K for the M rows
-    constexpr int CPR = K / 8;
-    for (int q = t; q < MROWS * CPR; q += SG_TILES * 256) {
-        const int row = q / CPR, cc = q - row * CPR;
-        bf16x8 v;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (bf16)0.f;
-        if (row < M) v = *reinterpret_cast<const bf16x8*>(X + (size_t)row * K + cc * 8);
-        *reinterpret_cast<bf16x8*>(xs + row * LDX + cc * 8) = v;
-    }
-    // Column-group sums of squares of the rows this wavefront finishes (rows w and
-    // w + 8): only loaded here (behind the weight ring and the activations),
-    // lane-strided; they are added up after the main loop, so nothing waits for them.
-    constexpr int NRW = MROWS / 8, PMAX = 8;   // rows per wavefront; parts per lane (nparts <= 512)
-    float pv[NRW][PMAX];
-#pragma unroll
-    for (int j = 0; j < NRW; ++j)
-#pragma unroll
-        for (int u = 0; u < PMAX; ++u) {
-            const int row = wave + 8 * j, pidx = lane + 64 * u;
-            pv[j][u] = (norm.ssq_parts && wave < 8 && row < M && pidx < norm.nparts) ? norm.ssq_parts[(size_t)pidx * M + row] : 0.f;
-        }
-    __syncthreads();
-
-    floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-    const bool xvalid = r < MROWS;
-    const bf16* xrow = xs + (xvalid ? r : 0) * LDX + kw * 32 + c * 8;
-#pragma unroll
-    for (int i = 0; i < SPW; ++i) {
-        bf16x8 b = *reinterpret_cast<const bf16x8*>(xrow + i * 128);
-        if (MROWS < 16 && !xvalid) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) b[j] = (bf16)0.f;
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ring[i % SG_RING], b, acc, 0, 0, 0);
-        if (i + SG_RING < SPW) ring[i % SG_RING] = *reinterpret_cast<const bf16x8*>(wrow + (i + SG_RING) * 128);
-    }
-
-    // 1/rms of the rows: a fixed summation order (per lane, then a butterfly)
-#pragma unroll
-    for (int j = 0; j < NRW; ++j) {
-        float ss = 0.f;
-#pragma unroll
-        for (int u = 0; u < PMAX; ++u) ss += pv[j][u];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-        if (lane == 0 && wave < 8) rinv[wave + 8 * j] = norm.ssq_parts ? 1.0f / sqrtf(ss * norm.inv_d + norm.eps) : 1.0f;
-    }
-    // add the four k-interleaves of each tile in kw order
-    __syncthreads();   // the activations are dead: the partial tiles take their place
-    *reinterpret_cast<floatx4*>(red + (wave * 64 + lane) * 4) = acc;
-    __syncthreads();
-    if (kw != 0) return;
-    floatx4 v = acc;
-#pragma unroll
-    for (int w = 1; w < 4; ++w) {
-        const floatx4 o = *reinterpret_cast<const floatx4*>(red + ((rt * 4 + w) * 64 + lane) * 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] += o[e];
-    }
-    // v[e]: activation row r, MFMA row 4c + e: c < 2 gate of column 4c + e, c >= 2 up of column 4(c-2) + e
-    const float rs = rinv[xvalid ? r : 0];
-    bf16x4 out;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const float up = __shfl_xor(v[e], 32, 64) * rs;
-        const float g = v[e] * rs;
-        out[e] = (bf16)(g / (1.0f + __expf(-g)) * up);
-    }
-    if (c < 2 && r < M && j0 + rt * 8 + 4 * c < F) *reinterpret_cast<bf16x4*>(act + (size_t)r * F + j0 + rt * 8 + 4 * c) = out;
-}
-
-static size_t swiglu_smem(int mrows, int K) { return std::max((size_t)mrows * (K + 8) * sizeof(bf16), (size_t)SG_TILES * 4 * 64 * 4 * sizeof(float)); }
-
-// whether the fused SwiGLU kernel covers this shape (K in {2048, 4096, 8192}, the LDS holds the activations)
-bool skinny_swiglu_supported(int M, int F, int K) {
-    if (M < 1 || M > 16 || F % 16 != 0) return false;
-    if (K != 2048 && K != 4096 && K != 8192) return false;
-    return swiglu_smem(M <= 8 ? 8 : 16, K) <= 160 * 1024;
-}
-
-template <int MROWS, int SPT>
-static int launch_swiglu_cfg(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* act, int M, int F, const RowNorm& norm,
-                             hipStream_t s) {
-    const size_t smem = swiglu_smem(MROWS, SPT * 128);
-    static bool attr = false;
-    if (!attr) {
-        HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_skinny_swiglu_kernel<MROWS, SPT>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-        attr = true;
-    }
-    gemm_skinny_swiglu_kernel<MROWS, SPT><<<(F + SG_TILES * 8 - 1) / (SG_TILES * 8), SG_TILES * 256, smem, s>>>(X, W, act, M, F, norm);
-    LAUNCH_CHECK(ctx);
-    return COMPACT_OK;
-}
-
-int launch_gemm_skinny_swiglu(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* act, int M, int F, int K,
-                              const RowNorm* norm, hipStream_t s) {
-    if (!skinny_swiglu_supported(M, F, K)) return set_err(ctx, COMPACT_ESHAPE, "fused gate/up decode kernel does not cover this shape");
-    const RowNorm rn = norm ? *norm : RowNorm{};
-    const bool small = M <= 8;
-    switch (K) {
-        case 2048: return small ? launch_swiglu_cfg<8, 16>(ctx, X, W, act, M, F, rn, s) : launch_swiglu_cfg<16, 16>(ctx, X, W, act, M, F, rn, s);
-        case 4096: return small ? launch_swiglu_cfg<8, 32>(ctx, X, W, act, M, F, rn, s) : launch_swiglu_cfg<16, 32>(ctx, X, W, act, M, F, rn, s);
-        default: return launch_swiglu_cfg<8, 64>(ctx, X, W, act, M, F, rn, s);   // K = 8192 fits 8 rows only
-    }
-}
-
 template <int MT, int WAVES, int RING = SKINNY_STEPS>
 static int launch_skinny_cfg(compact_ctx* ctx, const bf16* A, const bf16* B, float* partials, int M, int N, int K, int ks,
                              const SkinnyNormIn& nin, hipStream_t s) {

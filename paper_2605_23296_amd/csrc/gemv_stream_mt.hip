@@ -35,8 +35,8 @@ __device__ __forceinline__ void mts_barrier() {
 #endif
 }
 
-// A slice of SLICE consecutive k of all MT*16 activation rows, copied by NT threads: chunk q (16 bytes) of the
-// slice = row q / (SLICE/8), piece q % (SLICE/8); rows past M are zero.
+// A slice of SLICE k of all MT*16 activation rows, runs of 32 that lie 64 apart, copied by NT threads: chunk q (16 bytes)
+// of the slice = row q / (SLICE/8), piece q % (SLICE/8); rows past M are zero.
 template <int MT, int SLICE, int NT>
 struct SliceStager {
     static constexpr int CPR = SLICE / 8;                 // 16-byte pieces per row
@@ -48,7 +48,7 @@ struct SliceStager {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int q = min(t + i * NT, TOTAL - 1), row = q / CPR, cc = q % CPR;   // past the end: the last piece again
-            v[i] = *reinterpret_cast<const bf16x8*>(X + (size_t)min(row, M - 1) * K + k0 + cc * 8);   // unconditional
+            v[i] = *reinterpret_cast<const bf16x8*>(X + (size_t)min(row, M - 1) * K + k0 + (cc >> 2) * 64 + (cc & 3) * 8);   // unconditional
         }
     }
     __device__ __forceinline__ void store(bf16* xs, int M, int t) const {
@@ -67,8 +67,8 @@ struct SliceStager {
 };
 
 // ---------------------------------------------------------------------------
-// One 16-column tile per workgroup of 16 wavefronts, wavefront kw takes the k-steps kw, kw + 16, ...: k-step j of
-// every wavefront lies in the j-th slice of 512 k.
+// One 16-column tile per workgroup of 16 wavefronts, wavefront kw takes the 64-wide pieces kw, kw + 16, ... of K, a half
+// (k-step) at a time: the j-th k-steps of all wavefronts are the j-th slice of 512 k.
 // h = resid + X W^T (fp32), hg = bf16(h * g), ssq_parts[tile][m] = sum over the tile's columns of h^2: the output
 // projection with the residual add and the front half of the next RMSNorm.
 // ---------------------------------------------------------------------------
@@ -89,14 +89,17 @@ __global__ __launch_bounds__(MTS_WAVES * 64) void stream_tile_mt_kernel(const bf
     const int r = lane & 15, c = lane >> 4;
     const int tile = blockIdx.x;
     const int S = K / 512;   // slices = k-steps per wavefront
-    const bf16* w0 = W + (size_t)(tile * 16 + r) * K + kw * 32 + c * 8;
+    const bf16* w0 = W + (size_t)(tile * 16 + r) * K + c * 8;
+    // k-steps 2 i and 2 i + 1 of a wavefront are the halves of one 64-wide piece
+    auto first = [](int j) { return (j >> 1) * 1024 + (j & 1) * 32; };   // of wavefront 0
+    auto wk = [&](int j) { return first(j) + kw * 64; };
     bf16x8 wf[MTS_RING];
 #pragma unroll
-    for (int i = 0; i < MTS_RING; ++i) wf[i] = *reinterpret_cast<const bf16x8*>(w0 + (size_t)min(i, S - 1) * 512);
+    for (int i = 0; i < MTS_RING; ++i) wf[i] = *reinterpret_cast<const bf16x8*>(w0 + wk(min(i, S - 1)));
     Stager st;
-    st.load(X, M, K, 0, t);
+    st.load(X, M, K, first(0), t);
     st.store(xs0, M, t);
-    st.load(X, M, K, min(1, S - 1) * 512, t);
+    st.load(X, M, K, first(1), t);
     mts_barrier();
     floatx4 acc[MT];
 #pragma unroll
@@ -113,10 +116,10 @@ __global__ __launch_bounds__(MTS_WAVES * 64) void stream_tile_mt_kernel(const bf
                     const bf16x8 b = *reinterpret_cast<const bf16x8*>(xs + (mt * 16 + r) * LDX + kw * 32 + c * 8);
                     acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i], b, acc[mt], 0, 0, 0);
                 }
-                wf[i] = *reinterpret_cast<const bf16x8*>(w0 + (size_t)min(j + MTS_RING, S - 1) * 512);
+                wf[i] = *reinterpret_cast<const bf16x8*>(w0 + wk(min(j + MTS_RING, S - 1)));
                 // slice j + 1 (loaded one round ago) goes into the buffer round j - 1 has finished with
                 st.store(xn, M, t);
-                st.load(X, M, K, min(j + 2, S - 1) * 512, t);
+                st.load(X, M, K, first(min(j + 2, S - 1)), t);
                 mts_barrier();
             }
         }
@@ -157,7 +160,7 @@ __global__ __launch_bounds__(MTS_WAVES * 64) void stream_tile_mt_kernel(const bf
     if (c == 0 && m < M) ssq_parts[(size_t)tile * M + m] = ss;
 }
 
-bool stream_mt_supported(int M, int N, int K) { return M > 16 && M <= 64 && N % 16 == 0 && K >= 512 && K % 512 == 0; }
+bool stream_mt_supported(int M, int N, int K) { return M > 16 && M <= 64 && N % 16 == 0 && K >= 1024 && K % 1024 == 0; }
 
 template <int MT>
 static int launch_tile_cfg(compact_ctx* ctx, const bf16* X, const bf16* W, const bf16* resid, const bf16* g, float* h_out,

@@ -343,21 +343,17 @@ __global__ __launch_bounds__(RN_NT) void residual_norm_kernel(const float* __res
 #pragma unroll
     for (int i = 0; i < RN_NT / WAVE; ++i) ss += red[i];
     const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-    float first = inv, second = 1.0f;   // factors before and after a rounding to bf16 (a second one of 1 changes nothing)
-    if (rounding != NORM_ONCE) {
-        first = 1.0f;
-        second = rounding == NORM_TWICE ? inv : 1.0f;
-    }
+    const float f = rounding == NORM_LATER ? 1.0f : inv;
     if (rounding == NORM_LATER && threadIdx.x == 0) rinv_out[r] = inv;
 #pragma unroll
     for (int it = 0; it < RN_TRIPS; ++it) {
         const int c = (it * RN_NT + threadIdx.x) * 4;
         if (c < d) {
             bf16x4 m;
-            m[0] = (bf16)((float)(bf16)(hv[it].x * first * to_f32(gv[it][0])) * second);
-            m[1] = (bf16)((float)(bf16)(hv[it].y * first * to_f32(gv[it][1])) * second);
-            m[2] = (bf16)((float)(bf16)(hv[it].z * first * to_f32(gv[it][2])) * second);
-            m[3] = (bf16)((float)(bf16)(hv[it].w * first * to_f32(gv[it][3])) * second);
+            m[0] = (bf16)(hv[it].x * f * to_f32(gv[it][0]));
+            m[1] = (bf16)(hv[it].y * f * to_f32(gv[it][1]));
+            m[2] = (bf16)(hv[it].z * f * to_f32(gv[it][2]));
+            m[3] = (bf16)(hv[it].w * f * to_f32(gv[it][3]));
             *reinterpret_cast<bf16x4*>(m_out + (size_t)r * d + c) = m;
         }
     }

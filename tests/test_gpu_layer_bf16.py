@@ -194,6 +194,22 @@ def test_dense_steps_round_the_ffn_input_alike_in_both_families(d_model, n_q_hea
     assert share < 0.02
 
 
+# Whole-K streaming projections: units of 64 k dealt to 16 wavefronts (one unit, an odd number below and above 16, exact
+# rounds), 1 to 8 tiles per workgroup and more than one round of workgroups (FFN widths of 8-column tiles against 256 compute
+# units), column tails of the last workgroup; one to 16 rows, both sides of 8.
+@pytest.mark.parametrize("d_model,n_q_heads,ffn_dim", [(64, 1, 64), (320, 2, 2112), (1088, 4, 4160), (192, 20, 6208), (128, 2, 8256),
+                                                       (128, 2, 10304), (64, 1, 12352), (64, 1, 14400), (64, 1, 16448), (64, 1, 40000)])
+def test_decode_projections_at_the_edges_of_their_units_and_tiles(d_model, n_q_heads, ffn_dim):
+    layer = LayerConfig(d_model=d_model, n_q_heads=n_q_heads, n_kv_heads=n_q_heads // 2 or 1, head_dim=64, ffn_dim=ffn_dim,
+                        rope_theta=500000.0, dtype="bf16")
+    inp = make_inputs(Workload("units", layer, [2 + b % 3 for b in range(16)], 16, 2), gain_jitter=True)
+    check_dense(inp, sampled=False)
+    full = H.gpu_forward(inp)
+    for n in (1, 8, 9):
+        g = H.gpu_forward(sub_batch(inp, range(n)))
+        assert np.array_equal(g["y_decode"], full["y_decode"][:, :n]), n
+
+
 @pytest.mark.parametrize("n_blocks", [20, 47])
 def test_dense_decode_with_17_to_64_blocks_at_the_smallest_shapes(n_blocks):
     """Narrow weights in the 17..64-row kernels: 32 and 34 column tiles, K = 2048 in four slices and 1088 in three of unequal
