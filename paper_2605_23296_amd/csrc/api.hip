@@ -706,8 +706,12 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
     int ks = 1;
     if (part & DECODE_FRONT) {
     // RMSNorm + QKV projection.  bf16 storage: the projection stages bf16(x * g) itself and leaves the row sums of squares, the
-    // epilogue multiplies by 1 / rms before the rotation.
-    if (c.dtype == COMPACT_BF16) {
+    // epilogue multiplies by 1 / rms before the rotation; with few rows one kernel does both, to the same bits.
+    if (qkv_stream_supported(c, N)) {
+        ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
+        TRY(launch_qkv_stream(ctx, meta, N, step, (const bf16*)x, (const bf16*)w->g_attn, (const bf16*)w->w_qkv, (bf16*)b.q,
+                              (bf16*)kv->d_k, (bf16*)kv->d_v, s));
+    } else if (c.dtype == COMPACT_BF16) {
         ks = skinny_ksplit(N, Dtot, c.d_model);
         {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);

@@ -236,6 +236,11 @@ int launch_gemm_skinny_grouped_mxfp4(compact_ctx* ctx, const bf16* X, const int3
                                      const int32_t* expert_list = nullptr, int n_listed = 0,
                                      const int32_t* tile_row0 = nullptr, const int32_t* tile_rows = nullptr);
 
+// q/k/v projection of few decode rows with its RMSNorm, rotary embedding and cache append (qkv_stream.hip)
+bool qkv_stream_supported(const compact_layer_cfg& c, int rows);
+int launch_qkv_stream(compact_ctx* ctx, const BlockMeta* d_meta, int rows, int step, const bf16* x, const bf16* g, const bf16* W,
+                      bf16* q, bf16* k, bf16* v, hipStream_t s);
+
 // gemm_skinny.hip : partials[ks][M][N] (fp32) = A[M,K] B[N,K]^T split over K
 int skinny_ksplit(int M, int N, int K);
 // norm_g (nullable): A holds un-normalised rows x; the operand becomes bf16(x * norm_g) and

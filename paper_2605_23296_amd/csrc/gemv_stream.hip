@@ -29,32 +29,10 @@
 #include <type_traits>
 
 #include "common.h"
+#include "stream_lds.h"
 
 #define GS_WAVES 16
 #define GS_MAX_TILES 8
-
-__device__ __forceinline__ float gs_wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-// Waits until at most N of this wavefront's loads are in flight (they land in order); its LDS operations are waited for too.
-template <int N>
-__device__ __forceinline__ void gs_wait() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    static_assert(N >= 0 && N < 64, "vector-memory counter is 6 bits");
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
-    __builtin_amdgcn_sched_barrier(0);
-#endif
-}
-__device__ __forceinline__ void gs_lds_done() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
-    __builtin_amdgcn_sched_barrier(0);
-#endif
-}
 
 enum StreamStep {
     STREAM_RESID_NORM,   // h = resid + X W^T (fp32), hg = bf16(h * g), ssq_parts[tile][m] = sum over the tile's columns of h^2
@@ -90,11 +68,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void row_stream_kernel(const StreamA
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ float rinv[16];
     const int lane = threadIdx.x & 63;
-#if defined(__HIP_DEVICE_COMPILE__)
-    const int kw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#else
-    const int kw = 0;
-#endif
+    const int kw = gs_wave();
     const int r = lane & 15, c = lane >> 4;
     const int tile0 = blockIdx.x * T;
 
