@@ -1306,21 +1306,27 @@ extern "C" int compact_stack_forward(compact_ctx* ctx, int32_t n_layers, const c
 // 112.2 / 113.4, 49152 rows 132.8 / 126.5 / 125.5.  Where an item has few columns (one to three workers, or no grouping) only one
 // or two of its eight wavefronts multiply; a kernel that split the rows over all eight was 1 to 2 % of a step faster there
 // between 4096 and 16384 rows, and 3 to 18 % slower with 8 to 20 workers.
-static void prefix_item_limits(const compact_layer_cfg& c, int64_t (&rows)[2]) {   // longest histories for 128- and 256-row items
+// Items of 1024 rows from where they are still one round of resident workgroups (2 per compute unit, 3 at head_dim 64): half the
+// records again.  512 / 768 / 1024 rows, dense layer of the 8B shape: 24 x 4096 204.0 / 198.7 / 199.9, 32 x 4096 248.2 / 243.1 /
+// 235.3, 48 x 1500 221.9 / 214.3 / 217.7, 16 x 4096 161.5 / 159.4 / 158.9, below that line either way: 14 x 4096 152.3 / 155.0 /
+// 151.0, 8 x 4096 124.6 / 123.0 / 127.0; 24 x 4096 with heads of 64 175.4 / 173.4 / 174.3.  2048 rows: 208.6 at 24 x 4096.
+static void prefix_item_limits(const compact_layer_cfg& c, int64_t (&rows)[3]) {   // longest histories for 128-, 256- and 512-row items
     rows[0] = (c.head_dim == 128 ? 256 : 512) * 128 / c.n_kv_heads;
     rows[1] = (c.head_dim == 128 ? 384 : 512) * 256 / c.n_kv_heads;
+    rows[2] = (c.head_dim == 128 ? 512 : 768) * 1024 / c.n_kv_heads;
 }
 static int prefix_item_rows(const compact_layer_cfg& c, int shared_len) {
-    int64_t lim[2];
+    int64_t lim[3];
     prefix_item_limits(c, lim);
-    return shared_len <= lim[0] ? 128 : shared_len <= lim[1] ? 256 : 512;
+    return shared_len <= lim[0] ? 128 : shared_len <= lim[1] ? 256 : shared_len <= lim[2] ? 512 : 1024;
 }
 // most items that a prefix of at most `len` rows can have, whatever the length of the history that it is part of
 static int prefix_max_items(const compact_layer_cfg& c, int len) {
-    int64_t lim[2];
+    int64_t lim[3];
     prefix_item_limits(c, lim);
-    const int64_t l128 = std::min<int64_t>(len, lim[0]), l256 = std::min<int64_t>(len, lim[1]);
-    return (int)std::max({(l128 + 127) / 128, (l256 + 255) / 256, ((int64_t)len + 511) / 512});
+    int64_t most = ((int64_t)len + 1023) / 1024;
+    for (int i = 0, h = 128; i < 3; ++i, h *= 2) most = std::max(most, (std::min<int64_t>(len, lim[i]) + h - 1) / h);
+    return (int)most;
 }
 
 static int64_t prefix_max_recs(const compact_layer_cfg& c, int n_workers, int max_prefix_len, int max_tail_len) {

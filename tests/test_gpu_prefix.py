@@ -89,6 +89,12 @@ def test_prefix_decode_attention_kernel_item_heights(hkv, hd, group, rows):
         assert np.array_equal(some, every[pick])
 
 
+@pytest.mark.parametrize("hkv,hd,rows", [(32, 128, 16384), (32, 128, 16385), (64, 64, 12289)])
+def test_prefix_decode_attention_kernel_items_of_1024_rows(hkv, hd, rows):
+    """The line between items of 512 and of 1024 rows: the cases of the other heights."""
+    test_prefix_decode_attention_kernel_item_heights(hkv, hd, 1, rows)
+
+
 def prefix_kernel_case(layer, prefix, tail, grow=None, rows=None, pick=None):
     """rows: length of the shared history (default: the longest prefix); pick: the workers that take part (default: all)."""
     Hq, Hkv, hd = layer.n_q_heads, layer.n_kv_heads, layer.head_dim
