@@ -1,4 +1,4 @@
-// q/k/v projection of a decode step (bf16 storage, few rows) with the RMSNorm before it and the rotary embedding
+// q/k/v projection of a decode step (bf16 storage, at most 64 rows) with the RMSNorm before it and the rotary embedding
 // and the cache append behind it: one launch, nothing written but the rotated query rows, the K rows and the V columns.
 //
 //  * a workgroup owns P groups of 8 weight rows and all of K; wavefront w streams the w-th slice of 512 k through a
@@ -9,12 +9,13 @@
 //  * x arrives as it is: bf16(x g) is formed on the operand fragment, the sum of x^2 of a row from the same registers;
 //  * the angles (64 bits) are formed by two wavefronts of their own beside the stream (by all, behind it, where 16 stream);
 //  * slices, the order of the MFMA steps inside one, the order in which slices are added and the tree of a row's
-//    sum of squares are those of gemm_skinny_kernel and decode_qkv_epilogue_kernel: a row has the same bits here and
-//    in a step of more rows, which those two serve.
-// 6144 x 4096 at 8 / 24 rows: 12.0 + 4.5 / 15.7 + 5.1 us (split-K projection and epilogue) -> 12.3 / 15.0; 5120 x 2880 at 16 rows
-// 10.1 us.  50 MB at 6.1 TB/s, what a long stream of such loads reaches, would be 8.2 us; the rest is the first loads' way and the sums.
-// Three groups of 8 rows per workgroup (256 workgroups) instead of two tiles of 16 (192), and the angles out of the
-// stream's way: 15.0 -> 12.3.  17 .. 32 rows only up to eight slices, beyond 32 the rows crowd out the ring.
+//    sum of squares are those of gemm_skinny_kernel and decode_qkv_epilogue_kernel, which serve the wider layers' steps of
+//    more than 16 rows: a row has the same bits there.
+// 6144 x 4096 at 8 / 24 / 64 rows: 12.0 + 4.5 / 15.7 + 5.1 / 21.5 + 7.2 us (split-K projection and epilogue) -> 12.3 / 15.0 / 19.3;
+// 5120 x 2880 at 16 rows 10.1 us.  50 MB at 6.1 TB/s, what a long stream of such loads reaches, would be 8.2 us; the rest is the
+// first loads' way, the sums and the activation rows, which every workgroup reads (64 rows,
+// three groups per workgroup instead of six: 24.6 us).  At 8 rows two tiles of 16 weight rows per workgroup (192
+// workgroups) and the angles in the streaming wavefronts: 15.0 us.
 #include <algorithm>
 #include <type_traits>
 
@@ -61,9 +62,16 @@ struct QkvStreamShape {
 };
 
 template <int P, int XI, int D>
-__global__ __launch_bounds__(QS_MAX_WAVES * 64) void qkv_stream_kernel(const QkvStreamArgs p, const int slices) {
+__global__ __launch_bounds__(QS_MAX_WAVES * 64) void qkv_stream_kernel(QkvStreamArgs p, const int slices) {
     typedef QkvStreamShape<P, XI, D> Shape;
     constexpr int T = Shape::T, MT = Shape::MT, NL = Shape::LOADS, R = XI * 8;
+    {   // rows of this workgroup
+        const int m0 = blockIdx.y * R;
+        p.M = min(p.M - m0, R);
+        p.X += (size_t)m0 * p.K;
+        p.meta += m0;
+        p.q += (size_t)m0 * p.Hq * p.hd;
+    }
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, w = gs_wave(), waves = blockDim.x >> 6;
     const int r = lane & 15, c = lane >> 4, lrow = lane >> 3;
@@ -244,7 +252,7 @@ static int launch_qs_cfg(compact_ctx* ctx, const QkvStreamArgs& p, int slices, h
         attr = true;
     }
     const int waves = std::min(slices + QS_ANGLE_WAVES, QS_MAX_WAVES);
-    kern<<<(p.n_groups + P - 1) / P, waves * 64, QkvStreamShape<P, XI, D>::smem(slices), s>>>(p, slices);
+    kern<<<dim3((p.n_groups + P - 1) / P, (p.M + XI * 8 - 1) / (XI * 8)), waves * 64, QkvStreamShape<P, XI, D>::smem(slices), s>>>(p, slices);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
@@ -259,10 +267,10 @@ static int launch_qs_depth(compact_ctx* ctx, const QkvStreamArgs& p, int slices,
     return set_err(ctx, COMPACT_ESHAPE, "fused q/k/v projection: no ring fits");
 }
 
-// 17 .. 32 rows: up to eight slices (the ring of one unit fits for every number of groups)
+// 17 .. 64 rows: up to eight slices (the ring of one unit fits for every number of groups)
 bool qkv_stream_supported(const compact_layer_cfg& c, int rows) {
     return c.dtype == COMPACT_BF16 && c.d_model % 64 == 0 && rows >= 1 &&
-           (rows <= 16 ? c.d_model <= QS_MAX_WAVES * QS_SLICE : rows <= 32 && c.d_model <= 8 * QS_SLICE);
+           (rows <= 16 ? c.d_model <= QS_MAX_WAVES * QS_SLICE : rows <= 64 && c.d_model <= 8 * QS_SLICE);
 }
 
 int launch_qkv_stream(compact_ctx* ctx, const BlockMeta* d_meta, int rows, int step, const bf16* x, const bf16* g, const bf16* W,
@@ -290,27 +298,31 @@ int launch_qkv_stream(compact_ctx* ctx, const BlockMeta* d_meta, int rows, int s
     const int slices = (c.d_model + QS_SLICE - 1) / QS_SLICE;
     int n_cus = 0;
     if (int rc = device_cu_count(ctx, &n_cus)) return rc;
+    // more than 32 rows: two workgroups with half of them each share the weights' way through the L2 of their XCD
+    const int halves = rows > 32 ? 2 : 1;
     // groups per workgroup: the rounds of one workgroup per compute unit that cost the fewest groups, more groups where equal
     int best = 1;
     int64_t best_cost = 0;
-    for (int n : {1, 2, 3, 5}) {
-        const int64_t wgs = (p.n_groups + n - 1) / n, cost = (wgs + n_cus - 1) / n_cus * n;
-        if (n == 1 || (cost <= best_cost && p.n_groups > n_cus)) {
+    for (int n : {1, 2, 3, 5, 6}) {
+        const int64_t wgs = (int64_t)halves * ((p.n_groups + n - 1) / n), cost = (wgs + n_cus - 1) / n_cus * n;
+        if (n == 1 || (cost <= best_cost && halves * p.n_groups > n_cus)) {
             best = n;
             best_cost = cost;
         }
     }
     auto go = [&](auto tag) {
         constexpr int P = decltype(tag)::value;
-        return rows <= 8    ? launch_qs_depth<P, 1>(ctx, p, slices, s)
-               : rows <= 16 ? launch_qs_depth<P, 2>(ctx, p, slices, s)
-               : rows <= 24 ? launch_qs_depth<P, 3>(ctx, p, slices, s)
+        const int each = (rows + halves - 1) / halves;
+        return each <= 8    ? launch_qs_depth<P, 1>(ctx, p, slices, s)
+               : each <= 16 ? launch_qs_depth<P, 2>(ctx, p, slices, s)
+               : each <= 24 ? launch_qs_depth<P, 3>(ctx, p, slices, s)
                             : launch_qs_depth<P, 4>(ctx, p, slices, s);
     };
     switch (best) {
         case 1: return go(std::integral_constant<int, 1>{});
         case 2: return go(std::integral_constant<int, 2>{});
         case 3: return go(std::integral_constant<int, 3>{});
-        default: return go(std::integral_constant<int, 5>{});
+        case 5: return go(std::integral_constant<int, 5>{});
+        default: return go(std::integral_constant<int, 6>{});
     }
 }

@@ -194,18 +194,18 @@ def test_dense_steps_round_the_ffn_input_alike_in_both_families(d_model, n_q_hea
     assert share < 0.02
 
 
-# The q/k/v projection of a step of at most 32 rows: slices of 512 k (one unit of 64, one whole, a second of one unit, 15 and 16,
-# where one and no wavefront is left for the angles; beyond eight slices up to 16 rows), 1, 2, 3 and 5 groups of 8 weight rows per
+# The q/k/v projection of a step of at most 64 rows: slices of 512 k (one unit of 64, one whole, a second of one unit, 15 and 16,
+# where one and no wavefront is left for the angles; beyond eight slices up to 16 rows), 1, 2, 3, 5 and 6 groups of 8 weight rows per
 # workgroup, the last one short; rows on both sides of the multiples of 8.
 @pytest.mark.parametrize("d_model,n_q_heads,n_kv_heads,head_dim", [(64, 1, 1, 64), (512, 2, 1, 128), (576, 36, 3, 64), (128, 64, 8, 64),
                                                                     (192, 130, 13, 64), (7680, 2, 1, 64), (8192, 2, 2, 128)])
 def test_decode_qkv_has_the_same_bits_at_every_row_count(d_model, n_q_heads, n_kv_heads, head_dim):
     layer = LayerConfig(d_model=d_model, n_q_heads=n_q_heads, n_kv_heads=n_kv_heads, head_dim=head_dim, ffn_dim=64,
                         rope_theta=500000.0, dtype="bf16")
-    inp = make_inputs(Workload("qkv_rows", layer, [1 + b % 5 for b in range(34)], 34, 2), gain_jitter=True)
+    inp = make_inputs(Workload("qkv_rows", layer, [1 + b % 5 for b in range(64)], 64, 2), gain_jitter=True)
     full = check_dense(inp, sampled=False)
-    for n in (1, 8, 9, 16, 17, 25, 32):
-        g = check_dense(sub_batch(inp, range(n)), sampled=False) if n in (9, 25) else H.gpu_forward(sub_batch(inp, range(n)))
+    for n in (1, 8, 9, 16, 17, 25, 32, 33, 49):
+        g = check_dense(sub_batch(inp, range(n)), sampled=False) if n in (9, 25, 33) else H.gpu_forward(sub_batch(inp, range(n)))
         for b in range(n):
             assert np.array_equal(g["K"][b], full["K"][b]) and np.array_equal(g["V"][b], full["V"][b]), (n, b)
 
