@@ -592,10 +592,12 @@ int launch_attn_prefill_merge(compact_ctx* ctx, const PrefillMerge* d_merges, in
 // workgroups of 300 us.  Their keys are shared among as many items as bring the block's workgroups to 256.  The rule looks at
 // the block alone, so a row's bits do not depend on what shares the call; a block without cached rows is never cut (its rows
 // have the bits of compact_prefill).  A record costs 32 KB of traffic per row and item (32 heads of 128), which a call whose
-// blocks fill the chip anyway pays for nothing: hence at most 4 items of at least 1024 keys for more than 128 rows.
+// blocks fill the chip anyway pays for nothing: hence at most 4 items of at least 1024 keys for more than 128 rows, and one
+// beyond 256.  (Cut into two to four, 512 rows behind 16384 alone are 597 -> 430 us, but three blocks of 500 behind 8000 845 ->
+// 865, and with 16 heads of 64 five blocks of 317 .. 1270 behind 14000 467 -> 537.)
 // Whole calls, 32 + 8 heads of 128, before -> now: 16 rows behind 16384 470 -> 215 us, behind 4096 246 -> 180; 256 behind 16384
-// 532 -> 328; 1024 behind 16384 811 -> 716; six blocks of 16 behind 4096 260 -> 249, of 256 behind 16384 1057 -> 1068 (with
-// eight items 1160).  16 heads of 64, three blocks of 16 behind 4096 111 -> 71, of 256 behind 16384 294 -> 165.
+// 524 -> 320; six blocks of 16 behind 4096 260 -> 249, of 256 behind 16384 1034 -> 1046 (with eight items 1160).  16 heads of 64,
+// three blocks of 16 behind 4096 111 -> 71, of 256 behind 16384 274 -> 153.
 #define PREFILL_SPLIT_WGS 256
 static int prefill_wgs_per_tile(const compact_layer_cfg& c) {
     const bool pair = c.head_dim == 128 && (c.n_q_heads / c.n_kv_heads) % 2 == 0;
@@ -605,14 +607,14 @@ int attn_prefill_splits(const compact_layer_cfg& c, int block_rows, int prior, i
     if (prior == 0) return 1;
     const int wgs = (block_rows + PREFILL_QTILE - 1) / PREFILL_QTILE * prefill_wgs_per_tile(c);
     const int whole = (prior + row0) / KV_TILE;   // key tiles below the diagonal of every row
-    const int most = block_rows <= 64 ? PREFILL_MAX_SPLITS : block_rows <= 128 ? 8 : 4;
+    const int most = block_rows <= 64 ? PREFILL_MAX_SPLITS : block_rows <= 128 ? 8 : block_rows <= 256 ? 4 : 1;
     return std::max(1, std::min({PREFILL_SPLIT_WGS / wgs, most, whole / (block_rows <= 64 ? 8 : 16)}));
 }
 int64_t attn_prefill_max_part_rows(const compact_layer_cfg& c, int64_t T, int n_blocks) {
-    const int per = PREFILL_SPLIT_WGS / prefill_wgs_per_tile(c);   // q tiles x splits of a block at most
+    const int per = PREFILL_SPLIT_WGS / prefill_wgs_per_tile(c);
     if (c.dtype != COMPACT_BF16 || per < 2) return 0;
-    // (64 rows x 16 and 128 x 8 are fewer than what larger blocks reach)
-    return std::min<int64_t>(T * std::min(per, PREFILL_MAX_SPLITS), (int64_t)n_blocks * std::max(per, 8) * PREFILL_QTILE);
+    // (64 rows x 16 items, 128 x 8, 256 x 4)
+    return std::min<int64_t>(T * std::min(per, PREFILL_MAX_SPLITS), (int64_t)n_blocks * 8 * PREFILL_QTILE);
 }
 
 template <int HD, bool PP>
