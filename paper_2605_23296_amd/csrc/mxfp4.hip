@@ -8,18 +8,25 @@
 // of an element and a scale is exact in bf16, so the weights are expanded in
 // registers and fed to the same bf16 MFMA as the 16-bit path:
 //
-//  * a lane loads 16 bytes = one whole block of 32 elements of one weight row
-//    plus its scale byte; the four lane groups of an MFMA row take four
-//    consecutive blocks, so a wave-instruction still reads 64 contiguous bytes
-//    of each of 16 rows;
+//  * a lane loads 16 bytes = one whole block of 32 elements of one weight row;
+//    the four lane groups of an MFMA row take four consecutive blocks, so a
+//    wave-instruction still reads 64 contiguous bytes of each of 16 rows;
+//  * the scale bytes of a slice go through LDS, 32 contiguous bytes of each of
+//    16 rows in one load.  A load costs the address path a clock per group of four
+//    lanes that is not one contiguous run, whatever it brings: a byte per lane and
+//    block, the scales cost as much as the codes (16 rows of the 120B-shaped layer,
+//    gate/up + down: 123 us, a step 241 -> 229 so).  The codes through LDS as well,
+//    two whole rows per load: half the workgroups per compute unit, 137 us;
 //  * expansion is the hardware's scaled conversion (v_cvt_scalef32_pk_bf16_fp4:
 //    one byte = two elements -> two bf16, times a float scale), so a block of
 //    32 costs 16 conversions and the elements come out in their natural order.
 #include "common.h"
+#include "stream_lds.h"
 
 #define MX_BLOCK 32
 #define MX_KSLICE 1024                       // k per workgroup: 8 blocks per lane in flight
 #define MX_GROUPS (MX_KSLICE / (4 * MX_BLOCK))
+#define MX_WAVE_BYTES (16 * MX_KSLICE / MX_BLOCK)   // a wavefront's scales in LDS
 
 int mxfp4_ksplit(int K) { return (K + MX_KSLICE - 1) / MX_KSLICE; }
 
@@ -74,7 +81,8 @@ int launch_mxfp4_dequant(compact_ctx* ctx, const uint8_t* codes, const uint8_t* 
 // ---------------------------------------------------------------------------
 // Per-expert weight streaming for routed decode rows, 4-bit weights:
 // partials[slice][sorted row][N] = X[rows of expert e, kslice] W_e[N, kslice]^T.
-// grid (k-slices, N / 64, experts); 4 wavefronts of 16 weight rows each.
+// grid (k-slices, N / 64, experts); 4 wavefronts of 16 weight rows each.  X, like the scales, lands in LDS directly, its source
+// rows looked up before the weights are asked for (16 x 8192, a step: 252 -> 247 us when only the rows that are there were staged).
 // ---------------------------------------------------------------------------
 struct MxGroup {
     const int32_t* expert_list;  // [gridDim.z] experts to run, -1 = none (null: expert = blockIdx.z)
@@ -93,7 +101,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_mxfp4_kernel(const bf16* __re
     constexpr int LDX = MX_KSLICE + 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16* xs = reinterpret_cast<bf16*>(smem);  // [16][LDX]
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int lane = threadIdx.x & 63, wave = gs_wave();
     const int r = lane & 15, c = lane >> 4;
     const int e = grp.expert_list ? grp.expert_list[blockIdx.z] : (int)blockIdx.z;
     if (e < 0) return;
@@ -106,61 +114,78 @@ __global__ __launch_bounds__(256) void gemm_skinny_mxfp4_kernel(const bf16* __re
     const int k0 = slice * MX_KSLICE;
     const int klen = min(MX_KSLICE, K - k0);
     const int nblk = klen / MX_BLOCK;            // blocks of this slice
-    const int ngrp = (nblk + 3) / 4;             // MFMA groups of four blocks (the last may be partial)
     const int n0 = (blockIdx.y * 4 + wave) * 16;
     const bool active = n0 < N;
+    uint8_t* const scales = reinterpret_cast<uint8_t*>(smem) + 16 * LDX * sizeof(bf16) + wave * MX_WAVE_BYTES;   // [16 rows][32]
 
-    // the weight stream goes first: everything below overlaps with it
+    int src[4];   // rows of X that this wavefront stages
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        src[i] = row_base + min(wave + 4 * i, M - 1);
+        if (grp.a_gather) src[i] = grp.a_gather[src[i]];
+    }
+    // the weight stream goes first: everything below overlaps with it.  Past the row's end: its last block again.
     uint4 cw[MX_GROUPS];
-    uint32_t sc[MX_GROUPS];
     if (active) {
         const uint8_t* wp = Wq + (size_t)(n0 + r) * (K / 2) + k0 / 2;
-        const uint8_t* sp = Ws + (size_t)(n0 + r) * (K / MX_BLOCK) + k0 / MX_BLOCK;
 #pragma unroll
-        for (int g = 0; g < MX_GROUPS; ++g) {
-            const int blk = 4 * g + c;
-            cw[g] = make_uint4(0u, 0u, 0u, 0u);   // a block past the row's end contributes nothing
-            sc[g] = 127u;
-            if (blk < nblk) {
-                cw[g] = *reinterpret_cast<const uint4*>(wp + (size_t)blk * 16);
-                sc[g] = sp[blk];
-            }
+        for (int g = 0; g < MX_GROUPS; ++g) cw[g] = *reinterpret_cast<const uint4*>(wp + min(4 * g + c, nblk - 1) * 16);
+    }
+    // Activations of this expert's rows, a wavefront per row, past the row's end its last piece again.  An expert seldom has
+    // more than two or three rows: the MFMA columns beyond them repeat the last row (nobody reads their sums).
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (wave + 4 * i < M) {
+            const bf16* xp = X + (size_t)src[i] * K + k0;
+#pragma unroll
+            for (int j = 0; j < MX_KSLICE / 512; ++j)
+                load16_to_lds(xp + min(j * 64 + lane, klen / 8 - 1) * 8, xs + (wave + 4 * i) * LDX + j * 512);
+        }
+    // Scale bytes: four lanes a row, eight bytes each (rows are K / 32 bytes, so any alignment); a short row's pieces overlap.
+    if (active) {
+        const uint8_t* sp = Ws + (size_t)(n0 + (lane >> 2)) * (K / MX_BLOCK) + k0 / MX_BLOCK;
+        uint8_t* const dst = scales + (lane >> 2) * 32;
+        if (nblk >= 8) {
+            const int at = min((lane & 3) * 8, nblk - 8);
+            uint64_t v;
+            __builtin_memcpy(&v, sp + at, 8);
+            __builtin_memcpy(dst + at, &v, 8);
+        } else {
+#pragma unroll 1
+            for (int j = lane & 3; j < nblk; j += 4) dst[j] = sp[j];
         }
     }
-
-    // activations of this expert's rows, zero columns up to the last group's end.  An expert seldom has more than two or
-    // three rows: the MFMA columns beyond them repeat the last row (nobody reads their sums) instead of being staged as
-    // zeros, 16 x 8192 tokens 252 -> 247 us a step.
-    const int cpr = ngrp * 16;   // 16-byte chunks per staged row
-    for (int q = t; q < M * cpr; q += 256) {
-        const int row = q / cpr, cc = q - row * cpr;
-        bf16x8 v;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (bf16)0.f;
-        if (cc * 8 < klen) {
-            size_t src = row_base + row;
-            if (grp.a_gather) src = grp.a_gather[src];
-            v = *reinterpret_cast<const bf16x8*>(X + src * K + k0 + cc * 8);
-        }
-        *reinterpret_cast<bf16x8*>(xs + row * LDX + cc * 8) = v;
-    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_s_waitcnt(0);   // what was loaded into LDS has landed
+#endif
     __syncthreads();
     if (!active) return;
 
     floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
     const bf16* xrow = xs + min(r, M - 1) * LDX + c * MX_BLOCK;
+    auto group = [&](int g, bool whole) {
+        const int blk = 4 * g + c;
+        const bool there = whole || blk < nblk;   // a block past the row's end contributes nothing
+        const uint32_t sb = scales[r * 32 + blk];
+                const float scale = e8m0_to_float(there ? sb : 127u);
+        const uint32_t w[4] = {cw[g].x, cw[g].y, cw[g].z, cw[g].w};
 #pragma unroll
-    for (int g = 0; g < MX_GROUPS; ++g) {
-        if (g < ngrp) {
-            const float scale = e8m0_to_float(sc[g]);
-            const uint32_t w[4] = {cw[g].x, cw[g].y, cw[g].z, cw[g].w};
+        for (int d = 0; d < 4; ++d) {
+            bf16x8 b = *reinterpret_cast<const bf16x8*>(xrow + g * 4 * MX_BLOCK + d * 8);
+            if (!there) {
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const bf16x8 a = fp4_expand8(w[d], scale);
-                const bf16x8 b = *reinterpret_cast<const bf16x8*>(xrow + g * 4 * MX_BLOCK + d * 8);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+                for (int j = 0; j < 8; ++j) b[j] = (bf16)0.f;
             }
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp4_expand8(there ? w[d] : 0u, scale), b, acc, 0, 0, 0);
         }
+    };
+    if (nblk == MX_KSLICE / MX_BLOCK) {
+#pragma unroll
+        for (int g = 0; g < MX_GROUPS; ++g) group(g, true);
+    } else {
+#pragma unroll
+        for (int g = 0; g < MX_GROUPS; ++g)
+            if (4 * g < nblk) group(g, false);
     }
     // acc[e]: activation row r, weight row n0 + 4c + e
     if (r < M) *reinterpret_cast<floatx4*>(P + ((size_t)slice * grp.total_rows + row_base + r) * N + n0 + 4 * c) = acc;
@@ -174,7 +199,7 @@ int launch_gemm_skinny_grouped_mxfp4(compact_ctx* ctx, const bf16* X, const int3
     if (ks != mxfp4_ksplit(K)) return set_err(ctx, COMPACT_EINVAL, "unexpected K split");
     MxGroup g{expert_list, tile_row0, tile_rows, offsets, a_gather, (int64_t)N * (K / 2), (int64_t)N * (K / MX_BLOCK), total_rows};
     dim3 grid(ks, (N + 63) / 64, expert_list ? n_listed : n_experts);
-    const size_t smem = (size_t)16 * (MX_KSLICE + 8) * sizeof(bf16);
+    constexpr int smem = 16 * (MX_KSLICE + 8) * (int)sizeof(bf16) + 4 * MX_WAVE_BYTES;
     gemm_skinny_mxfp4_kernel<<<grid, 256, smem, s>>>(X, Wq, Ws, partials, N, K, g);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;

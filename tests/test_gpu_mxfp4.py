@@ -107,6 +107,13 @@ def test_routed_decode_steps_streaming_4bit_experts(d, F, spread, lens):
     log.check("rows with a close call: %d of %d (all compared) |" % (n_close, S * N))
 
 
+@pytest.mark.parametrize("d,F,blocks", [(1344, 1472, 18), (64, 1280, 7), (320, 64, 33)])
+def test_4bit_experts_at_the_edges_of_the_scale_loads(d, F, blocks):
+    """Slices of 10 and 14 blocks (pieces of eight scale bytes that overlap, at odd addresses), of exactly 8, of 2 (byte by
+    byte), and of 32 + 10; one to more than 16 rows of an expert."""
+    test_routed_decode_steps_streaming_4bit_experts(d, F, 0, [3] * blocks)
+
+
 def test_4bit_and_16bit_paths_agree_on_the_same_values():
     """The 4-bit streaming kernels and the 16-bit ones read the same numbers (the bf16 copy is
     the exact expansion), so a decode step must agree far inside the bf16 tolerance."""
