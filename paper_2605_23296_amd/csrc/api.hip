@@ -1306,25 +1306,30 @@ extern "C" int compact_stack_forward(compact_ctx* ctx, int32_t n_layers, const c
 // 112.2 / 113.4, 49152 rows 132.8 / 126.5 / 125.5.  Where an item has few columns (one to three workers, or no grouping) only one
 // or two of its eight wavefronts multiply; a kernel that split the rows over all eight was 1 to 2 % of a step faster there
 // between 4096 and 16384 rows, and 3 to 18 % slower with 8 to 20 workers.
-// Items of 1024 rows from where they are still one round of resident workgroups (2 per compute unit, 3 at head_dim 64): half the
-// records again.  512 / 768 / 1024 rows, dense layer of the 8B shape: 24 x 4096 204.0 / 198.7 / 199.9, 32 x 4096 248.2 / 243.1 /
-// 235.3, 48 x 1500 221.9 / 214.3 / 217.7, 16 x 4096 161.5 / 159.4 / 158.9, below that line either way: 14 x 4096 152.3 / 155.0 /
-// 151.0, 8 x 4096 124.6 / 123.0 / 127.0; 24 x 4096 with heads of 64 175.4 / 173.4 / 174.3.  2048 rows: 208.6 at 24 x 4096.
+// Beyond 1024 rows for each workgroup that stays resident (2 per compute unit, 3 at head_dim 64) items of 832 to 1536 rows that
+// make whole rounds of them: half the records or fewer, and no round that is nearly empty.  Items of 512 / 1024 rows / this rule:
+// 3 workers: 66500 rows 157.2 / 162.2 / 147.7 us a step, 80000 rows 161.5 / 163.1 / 157.4, 98304 rows 177.0 / 175.0 / 173.4; 24
+// workers: 179.9 / 180.6 / 172.4, 191.8 / 192.4 / 182.9, 205.3 / 202.4 / 198.9; 40 workers (two groups of columns): 200.7 / 200.8 /
+// 201.8, 210.9 / 208.1 / 210.6, 234.2 / 225.9 / 236.0.  Between 32768 and 65536 rows taller items gain and lose about as often.
+static int64_t prefix_resident(const compact_layer_cfg& c) { return std::max(1, (c.head_dim == 128 ? 512 : 768) / c.n_kv_heads); }
 static void prefix_item_limits(const compact_layer_cfg& c, int64_t (&rows)[3]) {   // longest histories for 128-, 256- and 512-row items
     rows[0] = (c.head_dim == 128 ? 256 : 512) * 128 / c.n_kv_heads;
     rows[1] = (c.head_dim == 128 ? 384 : 512) * 256 / c.n_kv_heads;
-    rows[2] = (c.head_dim == 128 ? 512 : 768) * 1024 / c.n_kv_heads;
+    rows[2] = std::max(rows[1], prefix_resident(c) * 1024);
 }
 static int prefix_item_rows(const compact_layer_cfg& c, int shared_len) {
     int64_t lim[3];
     prefix_item_limits(c, lim);
-    return shared_len <= lim[0] ? 128 : shared_len <= lim[1] ? 256 : shared_len <= lim[2] ? 512 : 1024;
+    if (shared_len <= lim[2]) return shared_len <= lim[0] ? 128 : shared_len <= lim[1] ? 256 : 512;
+    const int64_t once = prefix_resident(c), rounds = (shared_len + once * 1536 - 1) / (once * 1536);
+    return (int)(((shared_len + rounds * once - 1) / (rounds * once) + PREFILL_KTILE - 1) / PREFILL_KTILE * PREFILL_KTILE);
 }
-// most items that a prefix of at most `len` rows can have, whatever the length of the history that it is part of
+// most items that a prefix of at most `len` rows can have, whatever the length of the history that it is part of (beyond the
+// last line an item has more than 768 rows)
 static int prefix_max_items(const compact_layer_cfg& c, int len) {
     int64_t lim[3];
     prefix_item_limits(c, lim);
-    int64_t most = ((int64_t)len + 1023) / 1024;
+    int64_t most = ((int64_t)len + 767) / 768;
     for (int i = 0, h = 128; i < 3; ++i, h *= 2) most = std::max(most, (std::min<int64_t>(len, lim[i]) + h - 1) / h);
     return (int)most;
 }

@@ -3,7 +3,7 @@
 // one shared cache of the whole history): worker b attends rows
 // 0 .. prefix_len[b]-1 of the SHARED slab plus its own private tail.
 //
-// Cascade over the shared rows: a work item is a chunk of 128 .. 1024 rows of
+// Cascade over the shared rows: a work item is a chunk of 128 .. 1536 rows of
 // the shared slab (by the length of the history: short ones need the workgroups, long
 // ones the fewer records) together with the workers whose prefix reaches into it (a
 // suffix of the workers, prefixes being nested; at most PFX_COLS query columns =

@@ -89,9 +89,10 @@ def test_prefix_decode_attention_kernel_item_heights(hkv, hd, group, rows):
         assert np.array_equal(some, every[pick])
 
 
-@pytest.mark.parametrize("hkv,hd,rows", [(32, 128, 16384), (32, 128, 16385), (64, 64, 12289)])
-def test_prefix_decode_attention_kernel_items_of_1024_rows(hkv, hd, rows):
-    """The line between items of 512 and of 1024 rows: the cases of the other heights."""
+@pytest.mark.parametrize("hkv,hd,rows", [(32, 128, 16384), (32, 128, 16385), (32, 128, 24576), (32, 128, 24577), (64, 64, 12289), (64, 64, 18500)])
+def test_prefix_decode_attention_kernel_items_beyond_512_rows(hkv, hd, rows):
+    """The line to the items that make whole rounds of workgroups, and between one round of them and two: the cases of the
+    other heights."""
     test_prefix_decode_attention_kernel_item_heights(hkv, hd, 1, rows)
 
 
