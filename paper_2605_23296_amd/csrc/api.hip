@@ -236,6 +236,15 @@ static PrefillParts carve_prefill_parts(Carver& cv, const compact_layer_cfg& c, 
     return p;
 }
 
+// room for them in a workspace: rows as wide as the model at least, so that it grows with the layer as the other buffers do
+// (the references and sums, 8 bytes per head of 64 or 128, in an eighth of a byte per element)
+static void reserve_prefill_parts(Carver& cv, const compact_layer_cfg& c, int64_t part_rows) {
+    if (part_rows == 0) return;
+    const size_t cols = std::max(c.n_q_heads * c.head_dim, c.d_model);
+    cv.take((size_t)part_rows * cols * 4);
+    cv.take((size_t)part_rows * ((cols + 7) / 8));
+}
+
 static int decode_max_ksplit(const compact_layer_cfg& c, int N);
 
 static void carve_decode(Carver& cv, const compact_layer_cfg& c, int N, int max_chunks, DecodeBufs& b) {
@@ -282,7 +291,7 @@ extern "C" int compact_workspace_bytes(const compact_ctx* ctx, int64_t max_token
     PrefillBufs pb;
     DecodeBufs db;
     carve_prefill(cp, ctx->cfg, max_tokens, pb);
-    carve_prefill_parts(cp, ctx->cfg, attn_prefill_max_part_rows(ctx->cfg, max_tokens, max_blocks));
+    reserve_prefill_parts(cp, ctx->cfg, attn_prefill_max_part_rows(ctx->cfg, max_tokens, max_blocks));
     carve_decode(cd, ctx->cfg, max_blocks, chunks_for(max_kv_len), db);
     // the decode region follows the prefill region, so a forward pass can keep
     // the prefill outputs alive while it decodes
