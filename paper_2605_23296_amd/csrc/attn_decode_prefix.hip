@@ -25,7 +25,8 @@
 //  * the walk must not spill: a scratch reload waits for every load in flight and
 //    drains the ring (236 us instead of 96), hence here() in the rare branches;
 //  * bound: HBM (a step reads every shared row once).  24 workers over 98304 rows
-//    (403 MB): 119 -> 96 us, the merge of its records 25.6 -> 12.8 us; 8 workers over
+//    (403 MB): 119 -> 96 us, the merge of its records 25.6 -> 12.8 us,
+//    with items of 1536 rows 7.5; 8 workers over
 //    32768 rows: both together 52.7 -> 49.8 us.  (Before: 256-row items, the rows
 //    split over the wavefronts, maxima and probabilities exchanged through LDS, three
 //    barriers per 16 columns; twice the records.)  Loads alone take 87 us.

@@ -14,9 +14,9 @@
 //  * the scale bytes of a slice go through LDS, 32 contiguous bytes of each of
 //    16 rows in one load.  A load costs the address path a clock per group of four
 //    lanes that is not one contiguous run, whatever it brings: a byte per lane and
-//    block, the scales cost as much as the codes (16 rows of the 120B-shaped layer,
-//    gate/up + down: 123 us, a step 241 -> 229 so).  The codes through LDS as well,
-//    two whole rows per load: half the workgroups per compute unit, 137 us;
+//    block, the scales cost as much as the codes (16 rows of the 120B-shaped layer: a
+//    step 241 -> 229 us, gate/up + down 119 of it).  The codes through LDS as well,
+//    two whole rows per load: half the workgroups per compute unit, 257 us a step;
 //  * expansion is the hardware's scaled conversion (v_cvt_scalef32_pk_bf16_fp4:
 //    one byte = two elements -> two bf16, times a float scale), so a block of
 //    32 costs 16 conversions and the elements come out in their natural order.
