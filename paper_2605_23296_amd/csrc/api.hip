@@ -227,24 +227,6 @@ static void carve_prefill(Carver& cv, const compact_layer_cfg& c, int64_t T, Pre
     }
 }
 
-// behind the prefill buffers: records of attention items that share a row's keys
-static PrefillParts carve_prefill_parts(Carver& cv, const compact_layer_cfg& c, int64_t part_rows) {
-    PrefillParts p;
-    if (part_rows == 0) return p;
-    p.o = (float*)cv.take((size_t)part_rows * c.n_q_heads * c.head_dim * 4);
-    p.ml = (float2*)cv.take((size_t)part_rows * c.n_q_heads * sizeof(float2));
-    return p;
-}
-
-// room for them in a workspace: rows as wide as the model at least, so that it grows with the layer as the other buffers do
-// (the references and sums, 8 bytes per head of 64 or 128, in an eighth of a byte per element)
-static void reserve_prefill_parts(Carver& cv, const compact_layer_cfg& c, int64_t part_rows) {
-    if (part_rows == 0) return;
-    const size_t cols = std::max(c.n_q_heads * c.head_dim, c.d_model);
-    cv.take((size_t)part_rows * cols * 4);
-    cv.take((size_t)part_rows * ((cols + 7) / 8));
-}
-
 static int decode_max_ksplit(const compact_layer_cfg& c, int N);
 
 static void carve_decode(Carver& cv, const compact_layer_cfg& c, int N, int max_chunks, DecodeBufs& b) {
@@ -291,7 +273,6 @@ extern "C" int compact_workspace_bytes(const compact_ctx* ctx, int64_t max_token
     PrefillBufs pb;
     DecodeBufs db;
     carve_prefill(cp, ctx->cfg, max_tokens, pb);
-    reserve_prefill_parts(cp, ctx->cfg, attn_prefill_max_part_rows(ctx->cfg, max_tokens, max_blocks));
     carve_decode(cd, ctx->cfg, max_blocks, chunks_for(max_kv_len), db);
     // the decode region follows the prefill region, so a forward pass can keep
     // the prefill outputs alive while it decodes
@@ -304,16 +285,13 @@ extern "C" int compact_workspace_bytes(const compact_ctx* ctx, int64_t max_token
 // ---------------------------------------------------------------------------
 struct Plan {
     std::vector<BlockMeta> meta;
-    std::vector<TileItem> rope_tiles;
-    std::vector<PrefillItem> q_items;   // prefill attention work list
-    std::vector<PrefillMerge> merges;   // rows whose keys several items share (uploaded in `extra`)
-    int64_t part_rows = 0;              // records of those items
+    std::vector<TileItem> rope_tiles, q_tiles;
     std::vector<TileItem> kv_chunks;   // decode attention work list: (block, first cached row of a chunk)
     int max_len = 0;
     // device views
     const BlockMeta* d_meta = nullptr;
     const TileItem* d_rope_tiles = nullptr;
-    const PrefillItem* d_q_items = nullptr;
+    const TileItem* d_q_tiles = nullptr;
     const TileItem* d_kv_chunks = nullptr;
     std::vector<char> extra;           // further host-built tables, uploaded behind the lists
     const char* d_extra = nullptr;
@@ -323,7 +301,7 @@ static int upload_plan(compact_ctx* ctx, Plan& p, hipStream_t s) {
     ++ctx->upload_serial;   // the device views of every earlier plan are gone
     const size_t b0 = align_up(p.meta.size() * sizeof(BlockMeta), 256);
     const size_t b1 = align_up(p.rope_tiles.size() * sizeof(TileItem), 256);
-    const size_t b2 = align_up(p.q_items.size() * sizeof(PrefillItem), 256);
+    const size_t b2 = align_up(p.q_tiles.size() * sizeof(TileItem), 256);
     const size_t b3 = align_up(p.kv_chunks.size() * sizeof(TileItem), 256);
     const size_t b4 = align_up(p.extra.size(), 256);
     const size_t total = b0 + b1 + b2 + b3 + b4;
@@ -350,7 +328,7 @@ static int upload_plan(compact_ctx* ctx, Plan& p, hipStream_t s) {
     char* hs = (char*)ctx->h_stage;
     memcpy(hs, p.meta.data(), p.meta.size() * sizeof(BlockMeta));
     if (!p.rope_tiles.empty()) memcpy(hs + b0, p.rope_tiles.data(), p.rope_tiles.size() * sizeof(TileItem));
-    if (!p.q_items.empty()) memcpy(hs + b0 + b1, p.q_items.data(), p.q_items.size() * sizeof(PrefillItem));
+    if (!p.q_tiles.empty()) memcpy(hs + b0 + b1, p.q_tiles.data(), p.q_tiles.size() * sizeof(TileItem));
     if (!p.kv_chunks.empty()) memcpy(hs + b0 + b1 + b2, p.kv_chunks.data(), p.kv_chunks.size() * sizeof(TileItem));
     if (!p.extra.empty()) memcpy(hs + b0 + b1 + b2 + b3, p.extra.data(), p.extra.size());
     HIP_TRY(ctx, hipMemcpyAsync(ctx->d_meta, hs, total, hipMemcpyHostToDevice, s));
@@ -359,7 +337,7 @@ static int upload_plan(compact_ctx* ctx, Plan& p, hipStream_t s) {
     char* dm = (char*)ctx->d_meta;
     p.d_meta = (const BlockMeta*)dm;
     p.d_rope_tiles = (const TileItem*)(dm + b0);
-    p.d_q_items = (const PrefillItem*)(dm + b0 + b1);
+    p.d_q_tiles = (const TileItem*)(dm + b0 + b1);
     p.d_kv_chunks = (const TileItem*)(dm + b0 + b1 + b2);
     p.d_extra = dm + b0 + b1 + b2 + b3;
     return COMPACT_OK;
@@ -407,19 +385,8 @@ static int check_blocks(compact_ctx* ctx, int n_blocks, const int32_t* cu) {
     return COMPACT_OK;
 }
 
-// causal work of an item: heaviest first
-static void sort_prefill_items(Plan& p) {
-    const std::vector<BlockMeta>& mt = p.meta;
-    auto tiles = [&mt](const PrefillItem& i) {
-        return (i.kt_end < 0 ? (mt[i.block].prior + i.row0) / PREFILL_KTILE + 2 : i.kt_end) - i.kt_lo;
-    };
-    std::stable_sort(p.q_items.begin(), p.q_items.end(), [&](const PrefillItem& a, const PrefillItem& b) { return tiles(a) > tiles(b); });
-}
-
-// extend: the rows of the call are appended behind the h_len[b] rows the cache holds.  split (nullable): the layer, whose rule
-// may share the keys of few rows behind a long cache among several items
-static void build_prefill_plan(const compact_kv* kv, int n_blocks, const int32_t* cu, Plan& p, bool extend = false,
-                               const compact_layer_cfg* split = nullptr) {
+// extend: the rows of the call are appended behind the h_len[b] rows the cache holds
+static void build_prefill_plan(const compact_kv* kv, int n_blocks, const int32_t* cu, Plan& p, bool extend = false) {
     p.meta.resize(n_blocks);
     for (int b = 0; b < n_blocks; ++b) {
         BlockMeta& m = p.meta[b];
@@ -431,22 +398,13 @@ static void build_prefill_plan(const compact_kv* kv, int n_blocks, const int32_t
         m.slab = kv->h_slab_offset[b];
         p.max_len = std::max(p.max_len, m.len);
         for (int r = 0; r < m.len; r += ROPE_TILE) p.rope_tiles.push_back({b, r});
-        for (int r = 0; r < m.len; r += PREFILL_QTILE) {
-            const int n = split ? attn_prefill_splits(*split, m.len, m.prior, r) : 1;
-            if (n == 1) {
-                p.q_items.push_back({b, r, 0, -1, -1});
-                continue;
-            }
-            const int rows = std::min(PREFILL_QTILE, m.len - r), whole = (m.prior + r) / PREFILL_KTILE;
-            p.merges.push_back({m.row0 + r, rows, n, (int32_t)p.part_rows});
-            for (int i = 0; i < n; ++i) {
-                p.q_items.push_back({b, r, (int32_t)((int64_t)whole * i / n),
-                                     i == n - 1 ? -1 : (int32_t)((int64_t)whole * (i + 1) / n), (int32_t)p.part_rows});
-                p.part_rows += rows;
-            }
-        }
+        for (int r = 0; r < m.len; r += PREFILL_QTILE) p.q_tiles.push_back({b, r});
     }
-    sort_prefill_items(p);
+    // causal work of a query tile grows with its cache row: heaviest first
+    const std::vector<BlockMeta>& mt = p.meta;
+    std::stable_sort(p.q_tiles.begin(), p.q_tiles.end(), [&mt](const TileItem& a, const TileItem& b) {
+        return mt[a.block].prior + a.row0 > mt[b.block].prior + b.row0;
+    });
 }
 
 // Work list of the split-KV decode attention: every DECODE_CHUNK-row chunk that some
@@ -504,13 +462,11 @@ static int gemm_partials(compact_ctx* ctx, const void* A, const void* B, float* 
 // prefill
 // ---------------------------------------------------------------------------
 static int run_attn_prefill(compact_ctx* ctx, const Plan& p, int n_blocks, const void* qkv, const compact_kv* kv, void* o,
-                            hipStream_t s, const PrefillParts& parts = PrefillParts{}) {
+                            hipStream_t s) {
     ProfileScope ps(ctx, COMPACT_K_ATTN_PREFILL, s);
-    if (ctx->cfg.dtype == COMPACT_BF16) {
-        TRY(launch_attn_prefill_bf16(ctx, p.d_meta, p.d_q_items, (int)p.q_items.size(), (const bf16*)qkv,
-                                     (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)o, s, parts));
-        return launch_attn_prefill_merge(ctx, (const PrefillMerge*)p.d_extra, (int)p.merges.size(), parts, (bf16*)o, s);
-    }
+    if (ctx->cfg.dtype == COMPACT_BF16)
+        return launch_attn_prefill_bf16(ctx, p.d_meta, p.d_q_tiles, (int)p.q_tiles.size(), (const bf16*)qkv,
+                                        (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)o, s);
     return launch_attn_prefill_f32(ctx, p.d_meta, n_blocks, p.max_len, (const float*)qkv, (const float*)kv->d_k,
                                    (const float*)kv->d_v, (float*)o, s);
 }
@@ -527,7 +483,6 @@ static int prefill_impl(compact_ctx* ctx, const compact_weights* w, int n_blocks
     Carver cv(ws);
     PrefillBufs b;
     carve_prefill(cv, c, T, b);
-    const PrefillParts parts = carve_prefill_parts(cv, c, plan.part_rows);
     if (cv.off > ws_bytes) return set_err(ctx, COMPACT_EWORKSPACE, "workspace too small for this prefill");
     const int Dq = c.n_q_heads * c.head_dim, Dtot = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
 
@@ -535,7 +490,7 @@ static int prefill_impl(compact_ctx* ctx, const compact_weights* w, int n_blocks
     TRY(launch_rmsnorm(ctx, x, false, w->g_attn, b.n, T, s));
     TRY(gemm_full(ctx, b.n, w->w_qkv, nullptr, false, b.qkv, T, Dtot, c.d_model, 0, s));
     TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), b.qkv, kv->d_k, kv->d_v, s));
-    TRY(run_attn_prefill(ctx, plan, n_blocks, b.qkv, kv, b.o, s, parts));
+    TRY(run_attn_prefill(ctx, plan, n_blocks, b.qkv, kv, b.o, s));
     TRY(gemm_full(ctx, b.o, w->w_o, x, false, b.h, T, c.d_model, Dq, 2, s));   // h = x + o Wo^T, kept in fp32
     TRY(launch_rmsnorm(ctx, b.h, true, w->g_ffn, b.n, T, s));
     if (c.n_experts == 0) {
@@ -590,20 +545,7 @@ extern "C" int compact_prefill_extend(compact_ctx* ctx, const compact_weights* w
             return set_err(ctx, COMPACT_ECAPACITY, "block " + std::to_string(b) + ": cached rows + chunk exceed its KV slab");
     }
     Plan plan;
-    build_prefill_plan(kv, n_blocks, h_cu_seqlens, plan, true, ctx->cfg.dtype == COMPACT_BF16 ? &ctx->cfg : nullptr);
-    if (plan.part_rows > 0) {
-        // a workspace that was sized for fewer blocks may have no room for the records: every row's keys in one item then
-        Carver cv(nullptr);
-        PrefillBufs b;
-        carve_prefill(cv, ctx->cfg, h_cu_seqlens[n_blocks], b);
-        carve_prefill_parts(cv, ctx->cfg, plan.part_rows);
-        if (cv.off > ws_bytes) {
-            plan = Plan();
-            build_prefill_plan(kv, n_blocks, h_cu_seqlens, plan, true);
-        }
-        const char* m = (const char*)plan.merges.data();
-        plan.extra.assign(m, m + plan.merges.size() * sizeof(PrefillMerge));
-    }
+    build_prefill_plan(kv, n_blocks, h_cu_seqlens, plan, true);
     TRY(prefill_impl(ctx, w, n_blocks, h_cu_seqlens, d_x, kv, d_y, nullptr, route, d_workspace, ws_bytes, plan,
                      (hipStream_t)hip_stream));
     for (int b = 0; b < n_blocks; ++b) kv->h_len[b] += h_cu_seqlens[b + 1] - h_cu_seqlens[b];
@@ -1148,7 +1090,7 @@ extern "C" int compact_mixed_forward(compact_ctx* ctx, const compact_weights* w,
             if (i < n_chunk) {
                 const int L = h_cu_seqlens[b + 1] - h_cu_seqlens[b];
                 if (bf)
-                    for (int r = 0; r < cnt; r += PREFILL_QTILE) plan.q_items.push_back({i, r, 0, -1, -1});
+                    for (int r = 0; r < cnt; r += PREFILL_QTILE) plan.q_tiles.push_back({i, r});
                 for (int r = 0; r < cnt; ++r) {
                     src_tab.push_back(h_cu_seqlens[b] + done[b] + r);                       // row of x_prefill (base 0)
                     dst_tab.push_back(d_y_last && done[b] + r == L - 1 ? -b - 2 : -1);      // the block's last row -> y_last[b]
@@ -1166,7 +1108,12 @@ extern "C" int compact_mixed_forward(compact_ctx* ctx, const compact_weights* w,
             }
             Tm += cnt;
         }
-        sort_prefill_items(plan);
+        {
+            const std::vector<BlockMeta>& mt = plan.meta;
+            std::stable_sort(plan.q_tiles.begin(), plan.q_tiles.end(), [&mt](const TileItem& a, const TileItem& b2) {
+                return mt[a.block].prior + a.row0 > mt[b2.block].prior + b2.row0;
+            });
+        }
         MixExtra mx;
         mx.dec_meta = put(plan.extra, dec_meta);
         mx.qrow = put(plan.extra, qrow);
@@ -1183,7 +1130,7 @@ extern "C" int compact_mixed_forward(compact_ctx* ctx, const compact_weights* w,
         if (bf) {
             {
                 ProfileScope ps(ctx, COMPACT_K_ATTN_PREFILL, s);
-                TRY(launch_attn_prefill_bf16(ctx, plan.d_meta, plan.d_q_items, (int)plan.q_items.size(), (const bf16*)pb.qkv,
+                TRY(launch_attn_prefill_bf16(ctx, plan.d_meta, plan.d_q_tiles, (int)plan.q_tiles.size(), (const bf16*)pb.qkv,
                                              (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)pb.o, s));
             }
             if (n_dec > 0)   // one query row per decoding block, read in place from the packed QKV rows
@@ -1331,7 +1278,7 @@ static int prefix_item_rows(const compact_layer_cfg& c, int shared_len) {
     prefix_item_limits(c, lim);
     if (shared_len <= lim[2]) return shared_len <= lim[0] ? 128 : shared_len <= lim[1] ? 256 : 512;
     const int64_t once = prefix_resident(c), rounds = (shared_len + once * 1536 - 1) / (once * 1536);
-    return (int)(((shared_len + rounds * once - 1) / (rounds * once) + PREFILL_KTILE - 1) / PREFILL_KTILE * PREFILL_KTILE);
+    return (int)(((shared_len + rounds * once - 1) / (rounds * once) + PFX_ROWS - 1) / PFX_ROWS * PFX_ROWS);
 }
 // most items that a prefix of at most `len` rows can have, whatever the length of the history that it is part of (beyond the
 // last line an item has more than 768 rows)

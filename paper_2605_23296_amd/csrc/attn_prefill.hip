@@ -24,12 +24,9 @@
 //    is one 16-byte read of the V^T tile;
 //  * causal tiles above the diagonal are skipped per wavefront; rows of the
 //    V^T tile past the block's length are zeroed when staged.
-#include <algorithm>
-
 #include "common.h"
 
-#define KV_TILE PREFILL_KTILE
-#define PREFILL_MAX_SPLITS 16
+#define KV_TILE 64
 #define LOG2E 1.4426950408889634f
 
 typedef float floatx2 __attribute__((ext_vector_type(2)));
@@ -109,11 +106,11 @@ __device__ __forceinline__ void phase_barrier() {
 // heads); a tile stays live for four phases, hence a four-stage ring.
 template <int HD, bool PP>
 __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(const BlockMeta* __restrict__ meta,
-                                                                           const PrefillItem* __restrict__ items,
+                                                                           const TileItem* __restrict__ qtiles,
                                                                            const bf16* __restrict__ qkv,
                                                                            const bf16* __restrict__ kbase,
                                                                            const bf16* __restrict__ vbase, bf16* __restrict__ o,
-                                                                           int Hq, int Hkv, float scale_log2, const PrefillParts parts) {
+                                                                           int Hq, int Hkv, float scale_log2) {
     constexpr int KK = HD / 16;        // k16 steps of S^T
     constexpr int DT = HD / 32;        // 32-row tiles of O^T
     constexpr int KCH = HD / 8;        // 16-byte chunks per K row
@@ -123,9 +120,8 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16* lds = reinterpret_cast<bf16*>(smem);  // [stages][K tile | V^T tile]
 
-    const PrefillItem it = items[blockIdx.x];
+    const TileItem it = qtiles[blockIdx.x];
     const BlockMeta bm = meta[it.block];
-    const int k0 = it.kt_lo * KV_TILE;   // cache rows below count from the item's first key
     const int t = threadIdx.x, lane = t & 63;
     // A scalar wavefront index saves vector address work: 4 % at head_dim 64.  The four-wavefront kernel at head_dim 128 gains
     // 1 to 2 % on a block of 8000 tokens by it and loses 3 to 4 % on blocks of 1000 to 2000, where few workgroups leave the
@@ -136,16 +132,15 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
     const int kvh = (PP ? blockIdx.y * 2 : blockIdx.y) / (Hq / Hkv);   // the pair shares it (even GQA group)
     const int r = lane & 31, h = lane >> 5;
     const int ld = (Hq + 2 * Hkv) * HD;
-    const int prior = bm.prior - k0;     // query row i of the call is cache row prior + i
-    const int qlen = prior + bm.len;     // cache rows once this call's rows are in
-    const int len = it.kt_end < 0 ? qlen : it.kt_end * KV_TILE - k0;   // rows of the item's keys
+    const int len = bm.prior + bm.len;   // cache rows once this call's rows are in
+    const int prior = bm.prior;          // query row i of the call is cache row prior + i
 
-    const bf16* kslab = kbase + bm.slab + (size_t)kvh * bm.capacity * HD + (size_t)k0 * HD;
-    const bf16* vslab = vbase + bm.slab + (size_t)kvh * HD * bm.capacity + k0;
+    const bf16* kslab = kbase + bm.slab + (size_t)kvh * bm.capacity * HD;
+    const bf16* vslab = vbase + bm.slab + (size_t)kvh * HD * bm.capacity;
 
     // ---- Q^T operand: lane (q = r, h) holds Q[q][kk*16 + h*8 .. +7] -----------
     const int qrow = prior + it.row0 + wq * 32 + r;   // as a cache row
-    const int qrow_c = min(qrow, qlen - 1);
+    const int qrow_c = min(qrow, len - 1);
     const bf16* qp = qkv + (size_t)(bm.row0 + qrow_c - prior) * ld + head * HD + h * 8;
     bf16x8 qf[KK];
 #pragma unroll
@@ -158,10 +153,10 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
         for (int e = 0; e < 16; ++e) oacc[d][e] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
 
-    const int q_hi_wg = min(prior + it.row0 + PREFILL_QTILE, qlen) - 1;   // last query row of the workgroup
+    const int q_hi_wg = min(prior + it.row0 + PREFILL_QTILE, len) - 1;   // last query row of the workgroup
     const int q_hi_wave = prior + it.row0 + wq * 32 + 31;                // last query row of this wave
     const int q_lo_wave = prior + it.row0 + wq * 32;                     // first query row of this wave
-    const int n_tiles = it.kt_end < 0 ? q_hi_wg / KV_TILE + 1 : it.kt_end - it.kt_lo;
+    const int n_tiles = q_hi_wg / KV_TILE + 1;
 
     // ---- staging: 16-byte global loads that land in LDS directly ---------------------
     // A wave-instruction fills 64 consecutive 16-byte chunks of a tile; chunk L of the K tile is
@@ -183,8 +178,7 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
         voff[i] = (unsigned)(vrow * bm.capacity + vc * 8);
     }
     const unsigned slab_bytes = (unsigned)bm.capacity * HD * 2u;   // one KV head's K slab, and its V^T slab
-    const __amdgpu_buffer_rsrc_t krsrc = raw_buffer(kslab, slab_bytes - (unsigned)k0 * HD * 2u),
-                                 vrsrc = raw_buffer(vslab, slab_bytes - (unsigned)k0 * 2u);
+    const __amdgpu_buffer_rsrc_t krsrc = raw_buffer(kslab, slab_bytes), vrsrc = raw_buffer(vslab, slab_bytes);
     auto issue_tile = [&](int kt, int stage, bool whole = false) __attribute__((always_inline)) {   // whole: known to lie inside the cache
         const int kv0 = kt * KV_TILE;
         bf16* ks = lds + stage * 2 * KTILE;
@@ -224,7 +218,7 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
                 const int tok = min(kv0 + krow, len - 1);
                 load16_to_lds(kslab + (size_t)tok * HD + kc * 8, ks + (i * NW + wave) * 64 * 8);
                 const int vrow = L >> 3, vc = (L & 7) ^ swz<8>(vrow);
-                const int vt = min(kv0 + vc * 8, bm.capacity - k0 - 8);
+                const int vt = min(kv0 + vc * 8, bm.capacity - 8);
                 load16_to_lds(vslab + (size_t)vrow * bm.capacity + vt, vs + (i * NW + wave) * 64 * 8);
             }
         }
@@ -310,7 +304,7 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
         float ps = probs();
         // (query columns past the block's end see unmasked cache rows past it -- whatever the slab holds --
         // and must not take part in the decision: a row's bits may depend on its own block only)
-        if (__any(!(ps < 4096.0f) && qrow < qlen)) {
+        if (__any(!(ps < 4096.0f) && qrow < len)) {
             float mx = -INFINITY;
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt)
@@ -504,17 +498,7 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
 
     // ---- normalise and store: lane (q = r) holds elements d*32 + (e/4)*8 + h*4 + (e%4) ----
     l_run += __shfl_xor(l_run, 32, 64);
-    if (qrow < qlen && it.part >= 0) {
-        const size_t row = (size_t)it.part + wq * 32 + r;
-        float* op = parts.o + (row * Hq + head) * HD;
-#pragma unroll
-        for (int d = 0; d < DT; ++d)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<floatx4*>(op + d * 32 + g * 8 + h * 4) =
-                    floatx4{oacc[d][g * 4], oacc[d][g * 4 + 1], oacc[d][g * 4 + 2], oacc[d][g * 4 + 3]};
-        if (h == 0) parts.ml[row * Hq + head] = make_float2(m_run, l_run);
-    } else if (qrow < qlen) {
+    if (qrow < len) {
         const float inv = 1.0f / l_run;
         bf16* op = o + (size_t)(bm.row0 + qrow - prior) * Hq * HD + head * HD;
 #pragma unroll
@@ -529,98 +513,9 @@ __global__ __launch_bounds__(PP ? 512 : 256, 2) void attn_prefill_bf16_kernel(co
     }
 }
 
-// Output rows whose keys several items shared, 4 elements per thread: the items' records weighted by their scaling references
-// and added in key order.  All records of a thread go out together (past the last: it again, with weight 0).  Bound: reading
-// the records, 16 rows x 16 records of 4096 columns 29 -> 6 us against one record after the other.
-#define MERGE_COLS 1024   // columns per workgroup
-template <int P>
-__device__ __forceinline__ void merge_parts(const PrefillMerge& mg, const PrefillParts& parts, bf16* __restrict__ o, int row, int c,
-                                            int Hq, int hd) {
-    const int head = c / hd, cols = Hq * hd;
-    float2 ml[P];
-    floatx4 v[P];
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-        const size_t pr = (size_t)mg.part0 + (size_t)min(i, mg.n_parts - 1) * mg.rows + row;
-        ml[i] = parts.ml[pr * Hq + head];
-        v[i] = *reinterpret_cast<const floatx4*>(parts.o + pr * cols + c);
-    }
-    float m = ml[0].x, l = 0.f;
-#pragma unroll
-    for (int i = 1; i < P; ++i) m = fmaxf(m, ml[i].x);
-    floatx4 a = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-        if (i >= mg.n_parts) break;
-        const float f = __builtin_amdgcn_exp2f(ml[i].x - m);
-        l = fmaf(ml[i].y, f, l);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) a[e] = fmaf(v[i][e], f, a[e]);
-    }
-    const float inv = 1.0f / l;
-    bf16x4 out;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) out[e] = (bf16)(a[e] * inv);
-    *reinterpret_cast<bf16x4*>(o + (size_t)(mg.out_row + row) * cols + c) = out;
-}
-__global__ __launch_bounds__(MERGE_COLS / 4) void attn_prefill_merge_kernel(const PrefillMerge* __restrict__ merges,
-                                                                            const PrefillParts parts, bf16* __restrict__ o, int Hq,
-                                                                            int hd) {
-    const PrefillMerge mg = merges[blockIdx.x];
-    const int row = blockIdx.y, c = blockIdx.z * MERGE_COLS + threadIdx.x * 4;
-    if (row >= mg.rows || c >= Hq * hd) return;
-    if (mg.n_parts <= 4)
-        merge_parts<4>(mg, parts, o, row, c, Hq, hd);
-    else if (mg.n_parts <= 8)
-        merge_parts<8>(mg, parts, o, row, c, Hq, hd);
-    else
-        merge_parts<PREFILL_MAX_SPLITS>(mg, parts, o, row, c, Hq, hd);
-}
-
-int launch_attn_prefill_merge(compact_ctx* ctx, const PrefillMerge* d_merges, int n_merges, const PrefillParts& parts, bf16* o,
-                              hipStream_t s) {
-    if (n_merges == 0) return COMPACT_OK;
-    const compact_layer_cfg& c = ctx->cfg;
-    const int cols = c.n_q_heads * c.head_dim;
-    attn_prefill_merge_kernel<<<dim3(n_merges, PREFILL_QTILE, (cols + MERGE_COLS - 1) / MERGE_COLS), MERGE_COLS / 4, 0, s>>>(
-        d_merges, parts, o, c.n_q_heads, c.head_dim);
-    LAUNCH_CHECK(ctx);
-    return COMPACT_OK;
-}
-
-// A few rows behind a long cache are a handful of workgroups, each walking all of the cache: 16 rows behind 16384 were 16
-// workgroups of 300 us.  Their keys are shared among as many items as bring the block's workgroups to 256.  The rule looks at
-// the block alone, so a row's bits do not depend on what shares the call; a block without cached rows is never cut (its rows
-// have the bits of compact_prefill).  A record costs 32 KB of traffic per row and item (32 heads of 128), which a call whose
-// blocks fill the chip anyway pays for nothing: hence at most 4 items of at least 1024 keys for more than 128 rows, and one
-// beyond 256.  (Cut into two to four, 512 rows behind 16384 alone are 597 -> 430 us, but three blocks of 500 behind 8000 845 ->
-// 865, and with 16 heads of 64 five blocks of 317 .. 1270 behind 14000 467 -> 537.)
-// Whole calls, 32 + 8 heads of 128, before -> now: 16 rows behind 16384 470 -> 215 us, behind 4096 246 -> 180; 256 behind 16384
-// 524 -> 320; six blocks of 16 behind 4096 260 -> 249, of 256 behind 16384 1034 -> 1046 (with eight items 1160).  16 heads of 64,
-// three blocks of 16 behind 4096 111 -> 71, of 256 behind 16384 274 -> 153.
-#define PREFILL_SPLIT_WGS 256
-static int prefill_wgs_per_tile(const compact_layer_cfg& c) {
-    const bool pair = c.head_dim == 128 && (c.n_q_heads / c.n_kv_heads) % 2 == 0;
-    return pair ? c.n_q_heads / 2 : c.n_q_heads;
-}
-int attn_prefill_splits(const compact_layer_cfg& c, int block_rows, int prior, int row0) {
-    if (prior == 0) return 1;
-    const int wgs = (block_rows + PREFILL_QTILE - 1) / PREFILL_QTILE * prefill_wgs_per_tile(c);
-    const int whole = (prior + row0) / KV_TILE;   // key tiles below the diagonal of every row
-    const int most = block_rows <= 64 ? PREFILL_MAX_SPLITS : block_rows <= 128 ? 8 : block_rows <= 256 ? 4 : 1;
-    return std::max(1, std::min({PREFILL_SPLIT_WGS / wgs, most, whole / (block_rows <= 64 ? 8 : 16)}));
-}
-int64_t attn_prefill_max_part_rows(const compact_layer_cfg& c, int64_t T, int n_blocks) {
-    const int per = PREFILL_SPLIT_WGS / prefill_wgs_per_tile(c);
-    if (c.dtype != COMPACT_BF16 || per < 2) return 0;
-    // (64 rows x 16 items, 128 x 8, 256 x 4)
-    return std::min<int64_t>(T * std::min(per, PREFILL_MAX_SPLITS), (int64_t)n_blocks * 8 * PREFILL_QTILE);
-}
-
 template <int HD, bool PP>
-static int launch_prefill_variant(compact_ctx* ctx, const BlockMeta* d_meta, const PrefillItem* d_items, int n_items,
-                                  const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, float scale_log2,
-                                  const PrefillParts& parts, hipStream_t s) {
+static int launch_prefill_variant(compact_ctx* ctx, const BlockMeta* d_meta, const TileItem* d_qtiles, int n_qtiles,
+                                  const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, float scale_log2, hipStream_t s) {
     const compact_layer_cfg& c = ctx->cfg;
     auto kern = attn_prefill_bf16_kernel<HD, PP>;
     const size_t smem = (size_t)(PP ? 4 : 2) * 2 * KV_TILE * HD * sizeof(bf16);
@@ -629,23 +524,23 @@ static int launch_prefill_variant(compact_ctx* ctx, const BlockMeta* d_meta, con
         HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
         attr_set = true;
     }
-    dim3 grid(n_items, PP ? c.n_q_heads / 2 : c.n_q_heads);
-    kern<<<grid, PP ? 512 : 256, smem, s>>>(d_meta, d_items, qkv, d_k, d_v, o, c.n_q_heads, c.n_kv_heads, scale_log2, parts);
+    dim3 grid(n_qtiles, PP ? c.n_q_heads / 2 : c.n_q_heads);
+    kern<<<grid, PP ? 512 : 256, smem, s>>>(d_meta, d_qtiles, qkv, d_k, d_v, o, c.n_q_heads, c.n_kv_heads, scale_log2);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
 
-int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, const PrefillItem* d_items, int n_items,
-                             const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s, const PrefillParts& parts) {
-    if (n_items == 0) return COMPACT_OK;
+int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, const TileItem* d_qtiles, int n_qtiles,
+                             const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s) {
+    if (n_qtiles == 0) return COMPACT_OK;
     const compact_layer_cfg& c = ctx->cfg;
     const float scale_log2 = LOG2E / sqrtf((float)c.head_dim);
     // two query heads of one KV head per workgroup whenever the GQA group is even
     const bool pair = (c.n_q_heads / c.n_kv_heads) % 2 == 0;
     if (c.head_dim == 128)
-        return pair ? launch_prefill_variant<128, true>(ctx, d_meta, d_items, n_items, qkv, d_k, d_v, o, scale_log2, parts, s)
-                    : launch_prefill_variant<128, false>(ctx, d_meta, d_items, n_items, qkv, d_k, d_v, o, scale_log2, parts, s);
+        return pair ? launch_prefill_variant<128, true>(ctx, d_meta, d_qtiles, n_qtiles, qkv, d_k, d_v, o, scale_log2, s)
+                    : launch_prefill_variant<128, false>(ctx, d_meta, d_qtiles, n_qtiles, qkv, d_k, d_v, o, scale_log2, s);
     // head_dim 64 halves the matrix phase but not the softmax: the phases no longer balance (measured 31 % against
     // 38 % of peak), so it stays with the four-wavefront kernel
-    return launch_prefill_variant<64, false>(ctx, d_meta, d_items, n_items, qkv, d_k, d_v, o, scale_log2, parts, s);
+    return launch_prefill_variant<64, false>(ctx, d_meta, d_qtiles, n_qtiles, qkv, d_k, d_v, o, scale_log2, s);
 }

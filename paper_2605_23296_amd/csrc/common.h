@@ -25,9 +25,9 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // (workers x heads of a KV group) of an item.  The items of the shared rows: prefix_item_rows() in api.hip.
 #define PREFIX_TAIL_CHUNK 256
 #define PFX_COLS 128
+#define PFX_ROWS 64   // rows of a pair of its tiles: items beyond 512 rows are multiples of it
 // Query rows per prefill-attention tile and token rows per rotary/KV-write tile.
 #define PREFILL_QTILE 128
-#define PREFILL_KTILE 64   // keys per tile of the prefill attention
 #define ROPE_TILE 64
 
 // Per-block metadata as the kernels see it (device copy lives in the context).
@@ -52,21 +52,6 @@ struct RowNorm {
 struct TileItem {  // (block, first block-local row) of a row tile
     int32_t block;
     int32_t row0;
-};
-
-// Work item of the prefill attention: query rows row0 .. of a block against the key tiles of 64 from kt_lo on, up to the
-// rows' diagonal (kt_end < 0) or to kt_end - 1, all of them below it.  part < 0: the output rows; otherwise the item is one of
-// several that share the rows' keys, and leaves un-normalised rows part .. in the partial buffers.
-struct PrefillItem {
-    int32_t block, row0, kt_lo, kt_end, part;
-};
-// Rows whose keys were shared: rows out_row .. out_row + rows - 1 of the call from n_parts records, part0 + i * rows + row.
-struct PrefillMerge {
-    int32_t out_row, rows, n_parts, part0;
-};
-struct PrefillParts {
-    float* o = nullptr;    // [part rows][Hq * hd]
-    float2* ml = nullptr;  // [part rows][Hq]: scaling reference (log2), sum
 };
 
 // Work item of the prefix-aware decode attention: rows row0 .. row0 + n_rows - 1 of
@@ -287,15 +272,8 @@ int launch_attn_decode_f32(compact_ctx* ctx, const BlockMeta* d_meta, int n_bloc
                            const float* d_k, const float* d_v, float* o, hipStream_t s);
 
 // attn_prefill.hip (bf16 MFMA)
-int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, const PrefillItem* d_items, int n_items,
-                             const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s,
-                             const PrefillParts& parts = PrefillParts{});
-// the items of query rows row0 .. row0 + rows - 1 behind `prior` cached rows are cut into this many (1: not at all)
-int attn_prefill_splits(const compact_layer_cfg& c, int block_rows, int prior, int row0);
-// most part rows of a call of T rows in n_blocks blocks
-int64_t attn_prefill_max_part_rows(const compact_layer_cfg& c, int64_t T, int n_blocks);
-int launch_attn_prefill_merge(compact_ctx* ctx, const PrefillMerge* d_merges, int n_merges, const PrefillParts& parts, bf16* o,
-                              hipStream_t s);
+int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, const TileItem* d_qtiles, int n_qtiles,
+                             const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s);
 
 // attn_decode.hip (bf16 MFMA, split-KV)
 size_t attn_decode_partial_floats(const compact_layer_cfg& cfg, int n_blocks, int max_chunks);

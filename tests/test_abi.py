@@ -77,6 +77,20 @@ def test_workspace_holds_a_model_width_row_where_the_projection_rows_are_narrowe
     assert a >= T * (2 * 1024 + 2 * 1024 + 2 * 256 + 4 * 1024 + 2 * 1024)
 
 
+@pytest.mark.parametrize("name", ["dense_8x4096", "tiny_fp32"])
+@pytest.mark.parametrize("blocks", [1, 64])
+def test_workspace_of_prefill_tokens_is_their_activations(name, blocks):
+    """The part of the workspace that grows with the prefill tokens: n (or m), the stacked q/k/v rows (of at least d columns), o,
+    h (fp32) and the FFN activation, whatever the number of blocks; each at a multiple of 256 bytes."""
+    c = WORKLOADS[name].layer
+    lay = B.Layer(c, None)
+    es = 2 if c.dtype == "bf16" else 4
+    cols = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim
+    for T in (64, 2048):
+        want = T * (es * (c.d_model + max(cols, c.d_model) + c.n_q_heads * c.head_dim + c.ffn_dim) + 4 * c.d_model)
+        assert lay.workspace_bytes(T, blocks, 4096) - lay.workspace_bytes(0, blocks, 4096) == want
+
+
 def _fake_layer(name="tiny_fp32"):
     layer = WORKLOADS[name].layer
 

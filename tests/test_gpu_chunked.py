@@ -139,9 +139,8 @@ def test_dense_8x4096_in_chunks_of_1024_matches_the_one_piece_prefill():
     assert d.max().item() < 2e-2, d.max().item()
 
 
-# Few rows behind a long cache: their keys are shared among 2 .. 16 items.  Chunks of 1 to 600 rows, caches that end on and off
-# the 64-row key tiles, the fewest cached rows that are cut (1024: two items of 8 tiles) and one less; both attention kernels
-# of head_dim 128 and that of 64.
+# Few rows behind a long cache, whose keys one workgroup per query tile and head walks.  Chunks of 1 to 600 rows, caches that
+# end on and off the 64-row key tiles; both attention kernels of head_dim 128 and that of 64.
 @pytest.mark.parametrize("heads", [(4, 2, 128), (3, 1, 128), (8, 2, 64)], ids=str)
 def test_few_rows_behind_a_long_cache(heads):
     layer = LayerConfig(d_model=256, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=heads[2], ffn_dim=256, rope_theta=500000.0)
@@ -161,7 +160,7 @@ def test_few_rows_behind_a_long_cache(heads):
 
 
 def test_a_workspace_without_room_for_shared_keys_still_serves():
-    """The records of shared keys come out of the workspace; one that holds everything else gives the same rows to rounding."""
+    """A workspace of the activations' size and no more serves rows behind a long cache."""
     layer = LayerConfig(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=128, ffn_dim=256, rope_theta=500000.0)
     inp = make_inputs(Workload("long_cache", layer, [2064], 1, 1))
     lay = H.gpu_layer(inp)
@@ -179,3 +178,37 @@ def test_a_workspace_without_room_for_shared_keys_still_serves():
         lay.compact_prefill_extend([0, 16], x[2048:].contiguous(), kv, tail)
         outs.append(to_numpy_f64(tail))
     assert np.linalg.norm(outs[0] - outs[1]) < 4e-3 * np.linalg.norm(outs[1])
+
+
+@pytest.mark.parametrize("heads", [(4, 2, 128), (3, 1, 128), (8, 2, 64)], ids=str)
+def test_rows_behind_a_long_cache_have_the_same_bits_in_any_workspace(heads):
+    """The bits of a block's rows depend neither on what shares the call nor on how much larger than the activations the
+    workspace is."""
+    layer = LayerConfig(d_model=256, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=heads[2], ffn_dim=256, rope_theta=500000.0)
+    prior, rows = 2048, (16, 48, 64)
+    inp = make_inputs(Workload("long_cache", layer, [prior + r for r in rows], 3, 1))
+    lay = H.gpu_layer(inp)
+    x, cu = inp.x_prefill.to(DEV), inp.cu_seqlens
+    cols = (heads[0] + 2 * heads[1]) * heads[2]
+
+    def tails(blocks, extra):
+        kv = B.KVCache(layer, [prior + rows[b] for b in blocks], DEV, torch.bfloat16)
+        lay.ws = None
+        lay.ensure_workspace(prior * len(blocks), len(blocks), prior + 64, DEV)
+        y = torch.empty(prior * len(blocks), 256, dtype=torch.bfloat16, device=DEV)
+        lay.compact_prefill([prior * i for i in range(len(blocks) + 1)], torch.cat([x[cu[b]:cu[b] + prior] for b in blocks]), kv, y)
+        T = sum(rows[b] for b in blocks)
+        # n, m, qkv, o, h, act of T rows, a 256-byte gap after each
+        lay.ws = torch.empty(T * (2 * 256 + 2 * cols + 2 * heads[0] * heads[2] + 4 * 256 + 2 * 256) + 6 * 256 + extra,
+                             dtype=torch.uint8, device=DEV)
+        out = torch.empty(T, 256, dtype=torch.bfloat16, device=DEV)
+        ends = [0] + [int(v) for v in np.cumsum([rows[b] for b in blocks])]
+        lay.compact_prefill_extend(ends, torch.cat([x[cu[b] + prior:cu[b + 1]] for b in blocks]), kv, out)
+        torch.cuda.synchronize()
+        return [out[ends[i]:ends[i + 1]].view(torch.int16).clone() for i in range(len(blocks))]
+
+    want = [tails([b], 0)[0] for b in range(3)]
+    for extra in (0, 1 << 18, 1 << 20, 1 << 24):
+        for b, got in enumerate(tails([0, 1, 2], extra)):
+            assert torch.equal(got, want[b]), (extra, b)
+            assert torch.equal(tails([b], extra)[0], want[b]), (extra, b)
