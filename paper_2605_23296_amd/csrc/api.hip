@@ -704,8 +704,12 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
     // 17 .. 64 rows of a dense layer: projections by the ring GEMM, split over K.  A routed layer keeps the sums and the
     // roundings of the kernels for at most 16 rows: its router chooses by them.
     const bool many = bf && N > 16 && c.n_experts == 0;
-    const bool o_few = bf && N <= 16 && (c.n_experts == 0 || stream_mt_supported(17, c.d_model, Dq));
-    const bool o_routed = bf && N > 16 && c.n_experts > 0 && stream_mt_supported(N, c.d_model, Dq);
+    // A routed layer's FFN input is a tensor that the router and the experts read.  The whole-K kernels leave it as bf16(h g), to be
+    // rounded once more behind its 1 / rms: only layers of 2048 and 4096 query columns take them, as ever.  All others keep
+    // one rounding of fp32 (and are no slower beyond 16 rows: 5120 columns, 64 rows 209.6 us a step against 243.4).
+    const bool o_whole_k = c.n_experts == 0 || Dq == 2048 || Dq == 4096;
+    const bool o_few = bf && N <= 16 && o_whole_k;
+    const bool o_routed = bf && N > 16 && c.n_experts > 0 && o_whole_k && stream_mt_supported(N, c.d_model, Dq);
     const float* pre_scale = nullptr;
     if (many) {
         {

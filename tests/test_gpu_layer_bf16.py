@@ -226,6 +226,45 @@ def test_decode_projections_at_the_edges_of_their_units_and_tiles(d_model, n_q_h
         assert np.array_equal(g["y_decode"], full["y_decode"][:, :n]), n
 
 
+@pytest.mark.parametrize("n_q_heads,head_dim", [(16, 64), (24, 128)])   # 1024 and 3072 query columns
+@pytest.mark.parametrize("rows", [1, 16, 17, 64])
+def test_routed_steps_round_the_ffn_input_once(n_q_heads, head_dim, rows):
+    """Routed layers of other than 2048 and 4096 query columns: the router reads m = bf16(h g / rms), rounded once.  W_o = 0 makes
+    h the (exact) input row, and of the rows drawn those are kept in which no element of h g / rms lies so close to a boundary
+    of bf16 (8 x 2^-24 of the value: rms, its square root, quotient and two products) that fp32 might round it to the other side:
+    m is known.  The gates then differ from the exact ones by the order of fp32 sums, some 1e-6; rounded twice, a fifth of m
+    moves by a step of bf16 and the gates by 1e-3."""
+    from paper_2605_23296_amd import binding as B
+    layer = LayerConfig(d_model=512, n_q_heads=n_q_heads, n_kv_heads=2, head_dim=head_dim, ffn_dim=64, n_experts=16, top_k=4,
+                        rope_theta=500000.0, dtype="bf16")
+    inp = make_inputs(Workload("rounding", layer, [1] * 128, 128, 1), gain_jitter=True)
+    inp.weights["w_o"] = torch.zeros_like(inp.weights["w_o"])
+    inp.weights["w_router"] = inp.weights["w_router"] * 4
+    x, g, wr = inp.x_decode[0], inp.weights["g_ffn"].double(), inp.weights["w_router"].double()
+    h = x.double()
+    rms = torch.sqrt((h * h).mean(1, keepdim=True) + layer.rms_eps)
+    v = h * g / rms
+    step = 2.0 ** (torch.floor(torch.log2(v.abs().clamp_min(1e-30))) - 7)
+    known = (((v - v.to(torch.bfloat16).double()).abs() - step / 2).abs() > 8 * 2.0 ** -24 * v.abs()).all(1)
+    assert known.sum() >= rows
+    x, h, rms, v = x[known][:rows].contiguous(), h[known][:rows], rms[known][:rows], v[known][:rows]
+    lay = H.gpu_layer(inp)
+    kv = B.KVCache(layer, [8] * rows, "cuda", torch.bfloat16)
+    lay.ensure_workspace(0, rows, 8, "cuda")
+    xg = x.to("cuda")
+    idx = torch.empty(rows, 4, dtype=torch.int32, device="cuda")
+    gate = torch.empty(rows, 4, dtype=torch.float32, device="cuda")
+    lay.compact_decode_step(xg, kv, torch.empty_like(xg), (idx, gate))
+
+    def gates(m):
+        return torch.softmax((m.to(torch.bfloat16).double() @ wr.T).gather(1, idx.cpu().long()), 1)
+
+    once, twice = gates(v), gates((h * g).to(torch.bfloat16).double() / rms)
+    off, apart = (gate.cpu().double() - once).norm().item(), (twice - once).norm().item()
+    print("distance from the gates of one rounding %.1e, of those of two %.1e" % (off, apart))
+    assert off < 0.05 * apart
+
+
 @pytest.mark.parametrize("n_blocks", [20, 47])
 def test_dense_decode_with_17_to_64_blocks_at_the_smallest_shapes(n_blocks):
     """Narrow weights in the 17..64-row kernels: 32 and 34 column tiles, K = 2048 in four slices and 1088 in three of unequal
