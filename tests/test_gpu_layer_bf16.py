@@ -265,6 +265,46 @@ def test_routed_steps_round_the_ffn_input_once(n_q_heads, head_dim, rows):
     assert off < 0.05 * apart
 
 
+@pytest.mark.parametrize("rows", [1, 16])
+def test_swiglu_of_a_decode_step_is_exact_to_the_last_bits_of_fp32(rows):
+    """silu(g) u at known g and u: x has one element, 16 of d 256, so that rms = 1 and the products are the weights; W_o = 0 and a
+    permutation as W_down bring the activations out as they are.  g in -80 .. -8 and u in 1 .. 2 such that silu(g) u lies
+    4e-7 .. 5e-6 (relative) beside a boundary of bf16: fp32 with an exponential of one ulp, a sum, a quotient and a product is
+    within 2^-23 + 3 x 2^-24 = 3e-7 and rounds to the right side; exp2 of a rounded argument is off by up to 3.4e-6."""
+    from paper_2605_23296_amd import binding as B
+    d = 256
+    layer = LayerConfig(d_model=d, n_q_heads=1, n_kv_heads=1, head_dim=64, ffn_dim=d, rms_eps=1e-30, dtype="bf16")
+    inp = make_inputs(Workload("swiglu", layer, [1] * rows, rows, 1))
+    gs = -torch.arange(1, 1 << 15, dtype=torch.int32).to(torch.int16).view(torch.bfloat16).double()
+    gs = gs[(gs < -8) & (gs > -80)]
+    us = 1 + torch.arange(128, dtype=torch.float64) / 128
+    v = (gs / (1 + torch.exp(-gs)))[:, None] * us[None]
+    step = 2.0 ** (torch.floor(torch.log2(v.abs())) - 7)
+    beside = ((v - v.to(torch.bfloat16).double()).abs() - step / 2).abs() / v.abs()
+    gi, ui = torch.nonzero((beside > 4e-7) & (beside < 5e-6), as_tuple=True)
+    n = min(len(gi), d - 1)
+    assert n > 50
+    order = beside[gi, ui].argsort()[:n]
+    gi, ui = gi[order], ui[order]
+    w = {k: torch.zeros_like(t) for k, t in inp.weights.items()}
+    w["g_attn"].fill_(1.0)
+    w["g_ffn"].fill_(1.0)
+    w["w_gate_up"][:n, 0] = (gs[gi] / 16).to(torch.bfloat16)
+    w["w_gate_up"][d:d + n, 0] = (us[ui] / 16).to(torch.bfloat16)
+    w["w_down"][torch.arange(1, n + 1), torch.arange(n)] = 1.0
+    inp.weights = w
+    lay = H.gpu_layer(inp)
+    kv = B.KVCache(layer, [8] * rows, "cuda", torch.bfloat16)
+    lay.ensure_workspace(0, rows, 8, "cuda")
+    x = torch.zeros(rows, d, dtype=torch.bfloat16, device="cuda")
+    x[:, 0] = 16.0
+    y = torch.empty_like(x)
+    lay.compact_decode_step(x, kv, y)
+    wrong = (y[:, 1:n + 1].cpu() != v[gi, ui].to(torch.bfloat16)[None]).sum(1)
+    print("wrongly rounded of %d: %s" % (n, wrong.tolist()))
+    assert wrong.max() == 0
+
+
 @pytest.mark.parametrize("n_blocks", [20, 47])
 def test_dense_decode_with_17_to_64_blocks_at_the_smallest_shapes(n_blocks):
     """Narrow weights in the 17..64-row kernels: 32 and 34 column tiles, K = 2048 in four slices and 1088 in three of unequal
