@@ -5,8 +5,8 @@
 // multiplies a handful of rows with a few hundred weight rows.  Hence small
 // output tiles (16 x 16, 32 x 32 where those would be thousands, 64 x 64 in large
 // calls) whose wavefronts split K: wavefront w takes the 16-wide k-chunks w, w + WAVES, ...,
-// loads both operands straight from memory (16 bytes per lane, four chunks in
-// flight) and the partial tiles are added in wavefront order through LDS.  The
+// loads both operands straight from memory (16 bytes per lane, two to eight
+// chunks in flight) and the partial tiles are added in wavefront order through LDS.  The
 // split depends on K alone, so a row's bits do not depend on how many rows share
 // the call.  Before (64 x 64 tiles, one sequence over K): 4 rows x 256 columns,
 // K 1024, 60 us.
@@ -35,7 +35,7 @@ __device__ __forceinline__ int wave_index() {
 }
 
 // Wavefront w's share of MT x NB output tiles (rows arow[], weight rows brow[] of the lane), and with a norm its share of the
-// rows' sums of squares.  UN: chunks in flight.
+// rows' sums of squares.  UN: chunks in flight, whose loads go out in one batch.
 template <int MT, int NB, int WAVES, int UN>
 __device__ __forceinline__ void accumulate(const F32Gemm& p, const float* const (&arow)[MT], const float* const (&brow)[NB], int w,
                                            int c, floatx4 (&acc)[MT][NB], float (&ss)[MT]) {
@@ -105,13 +105,15 @@ __device__ __forceinline__ void accumulate(const F32Gemm& p, const float* const 
 // EPI 0: C = acc (+R).  EPI 1: B is [2N, K] (gate rows then up rows); C = silu(A Bg^T) * (A Bu^T).
 // With a GroupedArgs map, row tile blockIdx.y covers rows tile_row0 .. +tile_rows of the expert-sorted order, reads A
 // rows through a_gather and uses expert tile_expert's slice of B.
-template <int EPI, int MT, int NT, int WAVES>
+// UN: chunks in flight.  BATCH: their loads in one batch (accumulate()), or each behind a test of its own, with zeros past K.  The
+// sums are the same.  launch_f32 says which form is taken where.
+template <int EPI, int MT, int NT, int WAVES, int UN, bool BATCH>
 __global__ __launch_bounds__(WAVES * 64) void gemm_f32_kernel(const F32Gemm p) {
     constexpr int NB = EPI == 1 ? 2 * NT : NT;   // column tiles of B (SwiGLU: gate tiles, then up tiles)
     constexpr int PT = MT > 2 ? 1 : MT;          // row tiles that are added up at a time
     __shared__ floatx4 part[WAVES][PT * NB][64];
     __shared__ float ssq[WAVES][MT * 16];
-    const int lane = threadIdx.x & 63, w = wave_index();
+    const int lane = threadIdx.x & 63, w = BATCH ? wave_index() : (int)(threadIdx.x >> 6);
     const int r = lane & 15, c = lane >> 4;
     int64_t m0 = (int64_t)blockIdx.y * 16 * MT, m_end = p.M;
     const float* B = p.B;
@@ -134,9 +136,61 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_f32_kernel(const F32Gemm p) {
     for (int j = 0; j < NB; ++j) brow[j] = B + (int64_t)(min(n0 + (j % NT) * 16 + r, p.N - 1) + (j / NT) * p.N) * p.K;
     floatx4 acc[MT][NB];
     float ss[MT];
-    // one 16 x 16 tile over K = 1024 in one trip: 6.4 -> 4.9 us
-    constexpr int UN = MT * NB > 4 ? 2 : MT * NB == 1 && WAVES == 8 ? 8 : 4;
-    accumulate<MT, NB, WAVES, UN>(p, arow, brow, w, c, acc, ss);
+    if constexpr (BATCH) {
+        accumulate<MT, NB, WAVES, UN>(p, arow, brow, w, c, acc, ss);
+    } else {
+        // (this loop in a function of its own: other registers, and 20 % of the time of large products more)
+        auto load = [&](const float* row, int q) {
+            const int k = q * F32_CHUNK + c * 4;
+            floatx4 v = {0.f, 0.f, 0.f, 0.f};
+            if (p.vec) {
+                if (k < p.K) v = *reinterpret_cast<const floatx4*>(row + k);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (k + e < p.K) v[e] = row[k + e];
+            }
+            return v;
+        };
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            ss[i] = 0.f;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+        const int nq = (p.K + F32_CHUNK - 1) / F32_CHUNK;
+        for (int q0 = w; q0 < nq; q0 += UN * WAVES) {
+            floatx4 av[UN][MT], bv[UN][NB], gv[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int q = q0 + u * WAVES;
+#pragma unroll
+                for (int i = 0; i < MT; ++i) av[u][i] = load(arow[i], q);
+#pragma unroll
+                for (int j = 0; j < NB; ++j) bv[u][j] = load(brow[j], q);
+                if (p.norm_g) gv[u] = load(p.norm_g, q);
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                if (p.norm_g) {
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            ss[i] = fmaf(av[u][i][e], av[u][i][e], ss[i]);
+                            av[u][i][e] *= gv[u][e];
+                        }
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int j = 0; j < NB; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], bv[u][j][e], acc[i][j], 0, 0, 0);
+            }
+        }
+    }
     if (p.norm_g) {
 #pragma unroll
         for (int i = 0; i < MT; ++i) {
@@ -350,13 +404,40 @@ static int launch_f32(compact_ctx* ctx, const F32Gemm& p, bool grouped, hipStrea
     const int64_t small_tiles = (p.M + 15) / 16 * ((p.N + 15) / 16);
     constexpr int BN = EPI == 1 ? 32 : 64;   // columns of a big tile
     const int64_t big_tiles = (p.M + 63) / 64 * ((p.N + BN - 1) / BN);
+    const dim3 small((p.N + 15) / 16, (unsigned)((p.M + 15) / 16)), big((p.N + BN - 1) / BN, (unsigned)((p.M + 63) / 64));
+    const dim3 middle((p.N + 31) / 32, grouped ? (unsigned)p.g.n_mtiles : (unsigned)((p.M + 31) / 32));
+    const int64_t middle_tiles = (int64_t)middle.x * middle.y;
+    constexpr int T = WAVES * 64;
+    // Loads in one batch or one by one, eight or four chunks in flight, as measured (us, the form not taken -> the one taken):
+    // - a wavefront that has fewer chunks than a batch asks for the last one again and again: one by one (K 64: 512 x 1024
+    //   SwiGLU 12.6 -> 9.4, 2048 x 2816 59.3 -> 40.1);
+    // - 16 x 16 tiles: in a batch; over K >= 1024 eight chunks at once while there is one tile per compute unit (one tile
+    //   6.4 -> 4.9), four with more (17 x 4096, K 4096: 31.6 -> 28.9);
+    // - 32 x 32 tiles: in a batch (512 x 1024, K 512 SwiGLU 26.5 -> 23.5), but for SwiGLU over K < 1024 that takes the registers of
+    //   one resident workgroup out of three, which matters where three make one round (256 x 2816, K 512: 28.9 -> 25.8);
+    // - 64 x 64 tiles over K >= 1536: one by one (1024 x 4096, K 8192: 770 -> 653, K 2880 237 -> 219); 1024 <= K < 1536: in a
+    //   batch (1024 x 1024: 36.4 -> 33.2); K < 1024: a batch leaves one resident workgroup of two, so it is taken where one
+    //   per compute unit covers the tiles (1024 x 1024, K 512: 20.5 -> 17.3) or three rounds stand against two (1024 x
+    //   2816, K 768: 87 -> 72), and not elsewhere (2048 x 2816, K 256: 82.6 -> 61.2).
+    const int chunks = p.K / (F32_CHUNK * WAVES);   // of a wavefront, at least
     if (!grouped && small_tiles <= 2048) {
-        gemm_f32_kernel<EPI, 1, 1, WAVES><<<dim3((p.N + 15) / 16, (unsigned)((p.M + 15) / 16)), WAVES * 64, 0, s>>>(p);
+        constexpr int UN = EPI == 0 && WAVES == 8 ? 8 : 4;
+        if (UN == 8 && small_tiles <= 256)
+            gemm_f32_kernel<EPI, 1, 1, WAVES, UN, true><<<small, T, 0, s>>>(p);
+        else if (chunks >= 4)
+            gemm_f32_kernel<EPI, 1, 1, WAVES, 4, true><<<small, T, 0, s>>>(p);
+        else
+            gemm_f32_kernel<EPI, 1, 1, WAVES, 4, false><<<small, T, 0, s>>>(p);
     } else if (!grouped && big_tiles >= 256 && (EPI == 0 || p.K >= 2048)) {
-        gemm_f32_kernel<EPI, 4, BN / 16, WAVES><<<dim3((p.N + BN - 1) / BN, (unsigned)((p.M + 63) / 64)), WAVES * 64, 0, s>>>(p);
+        const bool batch = EPI == 0 && (WAVES == 8 ? p.K < 1536 : big_tiles == 256 || (p.K >= 512 && big_tiles > 512 && big_tiles <= 768));
+        if (batch)
+            gemm_f32_kernel<EPI, 4, BN / 16, WAVES, 2, EPI == 0><<<big, T, 0, s>>>(p);
+        else
+            gemm_f32_kernel<EPI, 4, BN / 16, WAVES, 2, false><<<big, T, 0, s>>>(p);
+    } else if (chunks >= 2 && !(EPI == 1 && WAVES == 4 && middle_tiles > 512 && middle_tiles <= 768)) {
+        gemm_f32_kernel<EPI, 2, 2, WAVES, EPI == 1 ? 2 : 4, true><<<middle, T, 0, s>>>(p);
     } else {
-        const unsigned rows = grouped ? (unsigned)p.g.n_mtiles : (unsigned)((p.M + 31) / 32);
-        gemm_f32_kernel<EPI, 2, 2, WAVES><<<dim3((p.N + 31) / 32, rows), WAVES * 64, 0, s>>>(p);
+        gemm_f32_kernel<EPI, 2, 2, WAVES, EPI == 1 ? 2 : 4, false><<<middle, T, 0, s>>>(p);
     }
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;

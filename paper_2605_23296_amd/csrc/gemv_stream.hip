@@ -200,7 +200,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void row_stream_kernel(const StreamA
         for (int e = 0; e < 4; ++e) {
             const float up = __shfl_xor(v[e], 32, 64) * rs;
             const float g = v[e] * rs;
-            out[e] = (bf16)(g / (1.0f + expf(-g)) * up);    // (__expf: off by up to 3.4e-6 of the value at g = -80)
+            out[e] = (bf16)(g / (1.0f + expf(-g)) * up);   // (__expf: off by up to 3.4e-6 of the value at g = -80)
         }
         if (c < 2 && r < p.M) *reinterpret_cast<bf16x4*>(p.out + (size_t)r * p.N + tile * 8 + 4 * c) = out;
     } else if (STEP == STREAM_RESID_OUT) {

@@ -21,7 +21,11 @@ pytestmark = pytest.mark.gpu
     (5, 40, 30, 0, False), (9, 23, 1027, 1, False),                                                     # rows that are not 16-byte aligned
     (700, 900, 272, 0, True), (1300, 700, 1024, 1, False),                                              # 32 x 32 tiles, tails
     (1200, 1300, 64, 0, True), (1030, 1100, 1040, 0, False), (1090, 1030, 79, 0, True),                 # 64 x 64
-    (1100, 1110, 2048, 1, False), (1041, 1033, 2051, 1, False)])                                        # 64 x 32, SwiGLU
+    (1100, 1110, 2048, 1, False), (1041, 1033, 2051, 1, False),                                         # 64 x 32, SwiGLU
+    # the same tiles where their loads go out one by one, or in a batch, as the other lines do not have them
+    (17, 2100, 1040, 0, True), (500, 1000, 144, 1, False),                                              # 16 x 16
+    (700, 900, 80, 0, True), (700, 900, 272, 1, False), (900, 1000, 272, 1, False),                     # 32 x 32
+    (1024, 1023, 528, 0, True), (1500, 1600, 528, 0, False), (1030, 1100, 1552, 0, True)])              # 64 x 64
 def test_gemm_fp32_tiles(M, N, K, epi, res):
     lay = B.Layer(fp32_variant(DENSE), None)
     a, b = rnd((M, K), torch.float32, 3), rnd(((2 if epi else 1) * N, K), torch.float32, 4, std=0.05)
