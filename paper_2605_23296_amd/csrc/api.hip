@@ -761,7 +761,7 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
         {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);
             TRY(launch_swiglu_stream(ctx, (const bf16*)ffn_in, (const bf16*)w->w_gate_up, (bf16*)b.act, N, c.ffn_dim, c.d_model,
-                                     pending_norm ? &rn : nullptr, s));
+                                     rn, s));
         }
         {
             ProfileScope ps(ctx, COMPACT_K_GEMM_SKINNY, s);

@@ -252,8 +252,8 @@ int launch_skinny_finish(compact_ctx* ctx, const float* partials, int ks, const 
 // h = resid + X W^T (fp32), hg = bf16(h * g), ssq_parts[N / 16][M] = column-group sums of h^2
 int launch_resid_norm_stream(compact_ctx* ctx, const bf16* X, const bf16* W, const bf16* resid, const bf16* g, float* h_out,
                              bf16* hg_out, float* ssq_parts, int M, int N, int K, hipStream_t s);
-// act[M, F] = silu(r X Wg^T) * (r X Wu^T); X may hold un-normalised rows (x * g) whose 1/rms r comes from `norm` (null: r = 1)
-int launch_swiglu_stream(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* act, int M, int F, int K, const RowNorm* norm,
+// act[M, F] = silu(r X Wg^T) * (r X Wu^T); X holds un-normalised rows (x * g) whose 1/rms r comes from `norm`
+int launch_swiglu_stream(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* act, int M, int F, int K, const RowNorm& norm,
                          hipStream_t s);
 // y = bf16(resid_f32 + X W^T)
 int launch_resid_out_stream(compact_ctx* ctx, const bf16* X, const bf16* W, const float* resid, bf16* y, int M, int N, int K,

@@ -26,14 +26,6 @@ struct F32Gemm {
     GroupedArgs g;
 };
 
-__device__ __forceinline__ int wave_index() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#else
-    return 0;
-#endif
-}
-
 // Wavefront w's share of MT x NB output tiles (rows arow[], weight rows brow[] of the lane), and with a norm its share of the
 // rows' sums of squares.  UN: chunks in flight, whose loads go out in one batch.
 template <int MT, int NB, int WAVES, int UN>

@@ -30,6 +30,7 @@
 
 #include "common.h"
 #include "stream_lds.h"
+#include "vecio.h"
 
 #define GS_WAVES 16
 #define GS_MAX_TILES 8
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void row_stream_kernel(const StreamA
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ float rinv[16];
     const int lane = threadIdx.x & 63;
-    const int kw = gs_wave();
+    const int kw = wave_index();
     const int r = lane & 15, c = lane >> 4;
     const int tile0 = blockIdx.x * T;
 
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(GS_WAVES * 64) void row_stream_kernel(const StreamA
 #pragma unroll
         for (int u = 0; u < PMAX; ++u) {
             const int pidx = lane + 64 * u;
-            pv[u] = p.norm.ssq_parts && kw < p.M && pidx < p.norm.nparts ? p.norm.ssq_parts[(size_t)pidx * p.M + kw] : 0.f;
+            pv[u] = kw < p.M && pidx < p.norm.nparts ? p.norm.ssq_parts[(size_t)pidx * p.M + kw] : 0.f;
         }
     }
 
@@ -174,8 +175,8 @@ __global__ __launch_bounds__(GS_WAVES * 64) void row_stream_kernel(const StreamA
         float ss = 0.f;   // a fixed summation order: per lane, then a butterfly
 #pragma unroll
         for (int u = 0; u < PMAX; ++u) ss += pv[u];
-        ss = gs_wave_sum(ss);
-        if (lane == 0) rinv[kw] = p.norm.ssq_parts ? 1.0f / sqrtf(ss * p.norm.inv_d + p.norm.eps) : 1.0f;
+        ss = wave_sum(ss);
+        if (lane == 0) rinv[kw] = 1.0f / sqrtf(ss * p.norm.inv_d + p.norm.eps);
     }
     __syncthreads();   // the rings are dead: the partial tiles take their place
     floatx4* red = reinterpret_cast<floatx4*>(smem);   // [GS_WAVES][T][64]
@@ -313,9 +314,9 @@ int launch_resid_out_stream(compact_ctx* ctx, const bf16* X, const bf16* W, cons
     return launch_stream<STREAM_RESID_OUT>(ctx, p, s);
 }
 
-int launch_swiglu_stream(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* act, int M, int F, int K,
-                              const RowNorm* norm, hipStream_t s) {
-    if (norm && norm->nparts > 512) return set_err(ctx, COMPACT_ESHAPE, "fused gate/up decode kernel takes 512 column groups at most");
+int launch_swiglu_stream(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* act, int M, int F, int K, const RowNorm& norm,
+                         hipStream_t s) {
+    if (norm.nparts > 512) return set_err(ctx, COMPACT_ESHAPE, "fused gate/up decode kernel takes 512 column groups at most");
     StreamArgs p{};
     p.X = X;
     p.W = W;
@@ -324,7 +325,7 @@ int launch_swiglu_stream(compact_ctx* ctx, const bf16* X, const bf16* W, bf16* a
     p.K = K;
     p.n_tiles = F / 8;
     p.out = act;
-    if (norm) p.norm = *norm;
+    p.norm = norm;
     return launch_stream<STREAM_SWIGLU>(ctx, p, s);
 }
 
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(256) void rownorm_apply_kernel(const bf16* __restri
     if (threadIdx.x < 64) {
         float ss = 0.f;
         for (int p = threadIdx.x; p < norm.nparts; p += 64) ss += norm.ssq_parts[(size_t)p * rows + row];
-        ss = gs_wave_sum(ss);
+        ss = wave_sum(ss);
         if (threadIdx.x == 0) s_rinv = 1.0f / sqrtf(ss * norm.inv_d + norm.eps);
     }
     __syncthreads();

@@ -22,6 +22,7 @@
 //    32 costs 16 conversions and the elements come out in their natural order.
 #include "common.h"
 #include "stream_lds.h"
+#include "vecio.h"
 
 #define MX_BLOCK 32
 #define MX_KSLICE 1024                       // k per workgroup: 8 blocks per lane in flight
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_mxfp4_kernel(const bf16* __re
     constexpr int LDX = MX_KSLICE + 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16* xs = reinterpret_cast<bf16*>(smem);  // [16][LDX]
-    const int lane = threadIdx.x & 63, wave = gs_wave();
+    const int lane = threadIdx.x & 63, wave = wave_index();
     const int r = lane & 15, c = lane >> 4;
     const int e = grp.expert_list ? grp.expert_list[blockIdx.z] : (int)blockIdx.z;
     if (e < 0) return;
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(256) void gemm_skinny_mxfp4_kernel(const bf16* __re
         const int blk = 4 * g + c;
         const bool there = whole || blk < nblk;   // a block past the row's end contributes nothing
         const uint32_t sb = scales[r * 32 + blk];
-                const float scale = e8m0_to_float(there ? sb : 127u);
+        const float scale = e8m0_to_float(there ? sb : 127u);
         const uint32_t w[4] = {cw[g].x, cw[g].y, cw[g].z, cw[g].w};
 #pragma unroll
         for (int d = 0; d < 4; ++d) {

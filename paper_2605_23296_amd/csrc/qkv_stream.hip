@@ -73,7 +73,7 @@ __global__ __launch_bounds__(QS_MAX_WAVES * 64) void qkv_stream_kernel(QkvStream
         p.q += (size_t)m0 * p.Hq * p.hd;
     }
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int lane = threadIdx.x & 63, w = gs_wave(), waves = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, w = wave_index(), waves = blockDim.x >> 6;
     const int r = lane & 15, c = lane >> 4, lrow = lane >> 3;
     float2* const angle = reinterpret_cast<float2*>(smem + slices * Shape::AREA);                   // [P][R][4]
     float* const ssq = reinterpret_cast<float*>(smem + slices * Shape::AREA + Shape::ANGLES * 8);   // [slices][R]
@@ -298,7 +298,9 @@ int launch_qkv_stream(compact_ctx* ctx, const BlockMeta* d_meta, int rows, int s
     const int slices = (c.d_model + QS_SLICE - 1) / QS_SLICE;
     int n_cus = 0;
     if (int rc = device_cu_count(ctx, &n_cus)) return rc;
-    // more than 32 rows: two workgroups with half of them each share the weights' way through the L2 of their XCD
+    // More than 32 rows: two workgroups with half of them each read the same weights, one grid row apart.  Workgroups go round the
+    // eight XCDs, so the second reading finds them in its XCD's L2 where a grid row is a multiple of 8 workgroups (768 groups: 128
+    // of 6 each) and in the cache behind the L2s elsewhere.
     const int halves = rows > 32 ? 2 : 1;
     // groups per workgroup: the rounds of one workgroup per compute unit that cost the fewest groups, more groups where equal
     int best = 1;

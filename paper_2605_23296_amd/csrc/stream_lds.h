@@ -2,11 +2,6 @@
 #pragma once
 #include "common.h"
 
-__device__ __forceinline__ float gs_wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 // Waits until at most N of this wavefront's loads are in flight (they land in order); its LDS operations are waited for too.
 template <int N>
 __device__ __forceinline__ void gs_wait() {
@@ -22,13 +17,5 @@ __device__ __forceinline__ void gs_lds_done() {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
     __builtin_amdgcn_sched_barrier(0);
-#endif
-}
-// index of the wavefront in its workgroup, as a scalar
-__device__ __forceinline__ int gs_wave() {
-#if defined(__HIP_DEVICE_COMPILE__)
-    return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#else
-    return 0;
 #endif
 }

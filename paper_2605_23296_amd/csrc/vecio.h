@@ -39,6 +39,14 @@ __device__ __forceinline__ float wave_max(float v) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
     return v;
 }
+// index of the wavefront in its workgroup, as a scalar
+__device__ __forceinline__ int wave_index() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#else
+    return 0;
+#endif
+}
 
 // The rotation of one pair, shared with the decode epilogue.  The contraction is written out: left to the compiler it
 // changes with the code around it, and a row rotated in a prefill would no longer have the bits of the same row rotated
