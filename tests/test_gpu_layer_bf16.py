@@ -180,7 +180,7 @@ def test_dense_decode_with_17_to_64_blocks(n_blocks):
 @pytest.mark.parametrize("d_model,n_q_heads", [(1024, 4), (1024, 16), (2048, 16), (2048, 4)])
 def test_dense_steps_round_the_ffn_input_alike_in_both_families(d_model, n_q_heads):
     """A dense step of 17 blocks adds its projections in another order than a step of at most 16, and nothing more: the FFN
-    input is rounded to bf16 the same way (once; twice; before the 1 / rms), whichever way the layer's shape takes.  Sums of
+    input is rounded to bf16 the same way (once, before the 1 / rms), whatever the layer's shape.  Sums of
     another order move an fp32 value by some 1e-7 of the scale, so about one bf16 value in 10^3 falls on the other side of a
     rounding boundary (2^-9 apart); an input rounded otherwise moves outputs by about 1e-3 of the scale, a fifth of them
     over a boundary (measured: 0.05 .. 0.4 % against 18 .. 34 %)."""
