@@ -227,7 +227,7 @@ int compact_layer_forward(compact_ctx* ctx, const compact_weights* w, int32_t n_
  * 0..h_prefix_len[b]-1 and tail rows 0..h_len[b] inclusive, tails->h_len[b] is
  * incremented, d_y [N, d] receives the layer outputs.  The shared rows are cut
  * into work items of 128, 256 or 512 rows, those of long histories (beyond 65536
- * rows with 8 KV heads) of 832 to 1536, by shared->h_len[0] and the layer
+ * rows with 8 KV heads of 128) of 832 to 1536, by shared->h_len[0] and the layer
  * alone, so a worker's results do not depend on the other workers.  An item is
  * multiplied with the query heads of the workers whose prefix covers it, up to
  * 128 / (query heads per KV head) of them; its rows are read once for these

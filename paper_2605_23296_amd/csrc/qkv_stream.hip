@@ -9,8 +9,8 @@
 //  * x arrives as it is: bf16(x g) is formed on the operand fragment, the sum of x^2 of a row from the same registers;
 //  * the angles (64 bits) are formed by two wavefronts of their own beside the stream (by all, behind it, where 16 stream);
 //  * slices, the order of the MFMA steps inside one, the order in which slices are added and the tree of a row's
-//    sum of squares are those of gemm_skinny_kernel and decode_qkv_epilogue_kernel, which serve the wider layers' steps of
-//    more than 16 rows: a row has the same bits there.
+//    sum of squares are those of gemm_skinny_kernel and decode_qkv_epilogue_kernel, which serve the steps that
+//    qkv_stream_supported() leaves out: a row has the same bits there.
 // 6144 x 4096 at 8 / 24 / 64 rows: 12.0 + 4.5 / 15.7 + 5.1 / 21.5 + 7.2 us (split-K projection and epilogue) -> 12.3 / 15.0 / 19.3;
 // 5120 x 2880 at 16 rows 10.1 us.  50 MB at 6.1 TB/s, what a long stream of such loads reaches, would be 8.2 us; the rest is the
 // first loads' way, the sums and the activation rows, which every workgroup reads (64 rows,
@@ -267,8 +267,13 @@ static int launch_qs_depth(compact_ctx* ctx, const QkvStreamArgs& p, int slices,
     return set_err(ctx, COMPACT_ESHAPE, "fused q/k/v projection: no ring fits");
 }
 
-// 17 .. 64 rows: up to eight slices (the ring of one unit fits for every number of groups)
+// 17 .. 64 rows: up to eight slices (the ring of one unit fits for every number of groups).  33 .. 40 rows take two workgroups with
+// room for 48; where these need a second round the split-K kernel and its epilogue are faster (whole steps of 33 rows, little beside
+// the projection: d 4096, 1024 groups 70.2 us against 72.3, 1792 groups 93.1 against 96.5; d 2880, 1280 groups 65.8 against 69.1;
+// at 48 rows both alike), but for short contractions, where launches count (d 1024, 1792 groups: 50.0 against 49.9).
 bool qkv_stream_supported(const compact_layer_cfg& c, int rows) {
+    const bool one_round = (c.n_q_heads + 2 * c.n_kv_heads) * (c.head_dim / 8) <= 128 * 6;   // two halves, six groups each
+    if (rows > 32 && rows <= 40 && !one_round && c.d_model > 1024) return false;
     return c.dtype == COMPACT_BF16 && c.d_model % 64 == 0 && rows >= 1 &&
            (rows <= 16 ? c.d_model <= QS_MAX_WAVES * QS_SLICE : rows <= 64 && c.d_model <= 8 * QS_SLICE);
 }
@@ -302,11 +307,15 @@ int launch_qkv_stream(compact_ctx* ctx, const BlockMeta* d_meta, int rows, int s
     // eight XCDs, so the second reading finds them in its XCD's L2 where a grid row is a multiple of 8 workgroups (768 groups: 128
     // of 6 each) and in the cache behind the L2s elsewhere.
     const int halves = rows > 32 ? 2 : 1;
-    // groups per workgroup: the rounds of one workgroup per compute unit that cost the fewest groups, more groups where equal
+    const int each = (rows + halves - 1) / halves;
+    // Groups per workgroup: the rounds of one workgroup per compute unit that cost the fewest loads per unit, of the groups and of
+    // the activation rows, more groups where equal.  By the groups alone, 896 of them were one per workgroup beyond 32 rows, seven
+    // rounds that asked for four pieces of rows beside each of weights (d 4096, 64 rows: a step 104.9 us, now 74.7), 1792
+    // likewise (64 rows 127.7 -> 103.7, 16 rows 79.2 -> 65.3).
     int best = 1;
     int64_t best_cost = 0;
     for (int n : {1, 2, 3, 5, 6}) {
-        const int64_t wgs = (int64_t)halves * ((p.n_groups + n - 1) / n), cost = (wgs + n_cus - 1) / n_cus * n;
+        const int64_t wgs = (int64_t)halves * ((p.n_groups + n - 1) / n), cost = (wgs + n_cus - 1) / n_cus * (n + (each + 7) / 8);
         if (n == 1 || (cost <= best_cost && halves * p.n_groups > n_cus)) {
             best = n;
             best_cost = cost;
@@ -314,7 +323,6 @@ int launch_qkv_stream(compact_ctx* ctx, const BlockMeta* d_meta, int rows, int s
     }
     auto go = [&](auto tag) {
         constexpr int P = decltype(tag)::value;
-        const int each = (rows + halves - 1) / halves;
         return each <= 8    ? launch_qs_depth<P, 1>(ctx, p, slices, s)
                : each <= 16 ? launch_qs_depth<P, 2>(ctx, p, slices, s)
                : each <= 24 ? launch_qs_depth<P, 3>(ctx, p, slices, s)

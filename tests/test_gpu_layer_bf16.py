@@ -196,9 +196,10 @@ def test_dense_steps_round_the_ffn_input_alike_in_both_families(d_model, n_q_hea
 
 def qkv_groups_per_workgroup(groups, rows, n_cus):
     """launch_qkv_stream's rule: rounds of one workgroup per compute unit (two per group span beyond 32 rows) that cost the fewest
-    groups, more groups per workgroup where equal."""
+    loads (a workgroup's groups and its rows in eights), more groups per workgroup where equal."""
     halves = 2 if rows > 32 else 1
-    cost = {n: -(-halves * -(-groups // n) // n_cus) * n for n in (1, 2, 3, 5, 6)}
+    pieces = -(-(-(-rows // halves)) // 8)
+    cost = {n: -(-halves * -(-groups // n) // n_cus) * (n + pieces) for n in (1, 2, 3, 5, 6)}
     if halves * groups <= n_cus:
         return 1
     return max(n for n in cost if cost[n] == min(cost.values()))
@@ -206,10 +207,11 @@ def qkv_groups_per_workgroup(groups, rows, n_cus):
 
 # The q/k/v projection of a step of at most 64 rows: slices of 512 k (one unit of 64, one whole, a second of one unit, 15 and 16,
 # where one and no wavefront is left for the angles; beyond eight slices up to 16 rows), 1, 2, 3, 5 and 6 groups of 8 weight rows per
-# workgroup (`per_wg`: with 16 and with 64 rows), the last one short; rows on both sides of the multiples of 8.
+# workgroup (`per_wg`: with 16 and with 64 rows), the last one short; rows on both sides of the multiples of 8; a layer of more than
+# 768 groups, whose steps of 33 .. 40 rows go through the split-K kernel.
 @pytest.mark.parametrize("d_model,n_q_heads,n_kv_heads,head_dim,per_wg", [
     (64, 1, 1, 64, (1, 1)), (512, 2, 1, 128, (1, 1)), (576, 36, 3, 64, (2, 3)), (128, 64, 8, 64, (3, 5)), (192, 130, 13, 64, (5, 5)),
-    (192, 72, 8, 64, (3, 6)), (7680, 2, 1, 64, (1, 1)), (8192, 2, 2, 128, (1, 1))])
+    (192, 72, 8, 64, (3, 6)), (1088, 50, 10, 128, (5, 5)), (7680, 2, 1, 64, (1, 1)), (8192, 2, 2, 128, (1, 1))])
 def test_decode_qkv_has_the_same_bits_at_every_row_count(d_model, n_q_heads, n_kv_heads, head_dim, per_wg):
     n_cus = torch.cuda.get_device_properties(0).multi_processor_count
     groups = (n_q_heads + 2 * n_kv_heads) * head_dim // 8
