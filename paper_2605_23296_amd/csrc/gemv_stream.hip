@@ -249,8 +249,10 @@ static int launch_stream_cfg(compact_ctx* ctx, const StreamArgs& p, hipStream_t 
     return COMPACT_OK;
 }
 
-// Tiles per workgroup: as many as let one workgroup per compute unit cover them all (at most GS_MAX_TILES; then the rounds
-// that cost the fewest tiles).  The sums of a row do not depend on it.
+// Tiles per workgroup: the rounds of one workgroup per compute unit that cost the fewest loads, of the tiles and of the
+// activation rows (at most GS_MAX_TILES); one per workgroup while that is one round.  The sums of a row do not depend on it.
+// By the tiles alone, an FFN of 20544 took one tile per workgroup in eleven rounds, each asking for the rows again (d 5120, 16
+// rows: a step 194 us; six tiles, two rounds: 149); one of 25600 and d 5120 likewise (235 -> 176 us).
 template <StreamStep STEP>
 static int launch_stream(compact_ctx* ctx, const StreamArgs& p, hipStream_t s) {
     if (p.M < 1 || p.M > 16 || p.K % 64 != 0 || p.K < 64 || p.N < 16 || p.N % 16 != 0)
@@ -260,8 +262,8 @@ static int launch_stream(compact_ctx* ctx, const StreamArgs& p, hipStream_t s) {
     int best = 1;
     int64_t best_cost = 0;
     for (int t = 1; t <= GS_MAX_TILES; ++t) {
-        const int64_t wgs = (p.n_tiles + t - 1) / t, cost = (wgs + n_cus - 1) / n_cus * t;
-        if (t == 1 || cost <= best_cost) {
+        const int64_t wgs = (p.n_tiles + t - 1) / t, cost = (wgs + n_cus - 1) / n_cus * (2 * t + (p.M + 7) / 8);
+        if (t == 1 || cost < best_cost) {
             best = t;
             best_cost = cost;
         }
