@@ -10,6 +10,8 @@
 // split depends on K alone, so a row's bits do not depend on how many rows share
 // the call.  Before (64 x 64 tiles, one sequence over K): 4 rows x 256 columns,
 // K 1024, 60 us.
+#include <type_traits>
+
 #include "vecio.h"
 
 #define F32_CHUNK 16   // k per chunk: one float4 per lane, four MFMAs
@@ -48,12 +50,14 @@ __device__ __forceinline__ void accumulate(const F32Gemm& p, const float* const 
         for (int j = 0; j < NB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
     const int nq = (p.K + F32_CHUNK - 1) / F32_CHUNK;
-    for (int q0 = w; q0 < nq; q0 += UN * WAVES) {
+    auto trip = [&](int q0, auto whole) __attribute__((always_inline)) {   // whole: all of the batch lies inside K
+        constexpr bool WHOLE = decltype(whole)::value;
         floatx4 av[UN][MT], bv[UN][NB], gv[UN];
-        if (p.vec) {   // past K: the last chunk again, which is not multiplied
+        if (p.vec) {
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
-                const int k = min(q0 + u * WAVES, nq - 1) * F32_CHUNK + c * 4;
+                if (!WHOLE && q0 + u * WAVES >= nq) break;
+                const int k = (q0 + u * WAVES) * F32_CHUNK + c * 4;
 #pragma unroll
                 for (int j = 0; j < NB; ++j) bv[u][j] = *reinterpret_cast<const floatx4*>(brow[j] + k);
                 if (p.norm_g) gv[u] = *reinterpret_cast<const floatx4*>(p.norm_g + k);
@@ -73,7 +77,7 @@ __device__ __forceinline__ void accumulate(const F32Gemm& p, const float* const 
         }
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            if (q0 + u * WAVES >= nq) continue;
+            if (!WHOLE && q0 + u * WAVES >= nq) break;
             if (p.norm_g) {
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
@@ -91,7 +95,10 @@ __device__ __forceinline__ void accumulate(const F32Gemm& p, const float* const 
                     for (int j = 0; j < NB; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u][i][e], bv[u][j][e], acc[i][j], 0, 0, 0);
         }
-    }
+    };
+    int q0 = w;
+    for (; q0 + (UN - 1) * WAVES < nq; q0 += UN * WAVES) trip(q0, std::true_type{});
+    if (q0 < nq) trip(q0, std::false_type{});   // (asking for the last chunk again where there is none: K 1152, 512 x 1024 43.5 us)
 }
 
 // EPI 0: C = acc (+R).  EPI 1: B is [2N, K] (gate rows then up rows); C = silu(A Bg^T) * (A Bu^T).
@@ -398,38 +405,29 @@ static int launch_f32(compact_ctx* ctx, const F32Gemm& p, bool grouped, hipStrea
     const int64_t big_tiles = (p.M + 63) / 64 * ((p.N + BN - 1) / BN);
     const dim3 small((p.N + 15) / 16, (unsigned)((p.M + 15) / 16)), big((p.N + BN - 1) / BN, (unsigned)((p.M + 63) / 64));
     const dim3 middle((p.N + 31) / 32, grouped ? (unsigned)p.g.n_mtiles : (unsigned)((p.M + 31) / 32));
-    const int64_t middle_tiles = (int64_t)middle.x * middle.y;
     constexpr int T = WAVES * 64;
-    // Loads in one batch or one by one, eight or four chunks in flight, as measured (us, the form not taken -> the one taken):
-    // - a wavefront that has fewer chunks than a batch asks for the last one again and again: one by one (K 64: 512 x 1024
-    //   SwiGLU 12.6 -> 9.4, 2048 x 2816 59.3 -> 40.1);
-    // - 16 x 16 tiles: in a batch; over K >= 1024 eight chunks at once while there is one tile per compute unit (one tile
-    //   6.4 -> 4.9), four with more (17 x 4096, K 4096: 31.6 -> 28.9);
-    // - 32 x 32 tiles: in a batch (512 x 1024, K 512 SwiGLU 26.5 -> 23.5), but for SwiGLU over K < 1024 that takes the registers of
-    //   one resident workgroup out of three, which matters where three make one round (256 x 2816, K 512: 28.9 -> 25.8);
-    // - 64 x 64 tiles over K >= 1536: one by one (1024 x 4096, K 8192: 770 -> 653, K 2880 237 -> 219); 1024 <= K < 1536: in a
-    //   batch (1024 x 1024: 36.4 -> 33.2); K < 1024: a batch leaves one resident workgroup of two, so it is taken where one
-    //   per compute unit covers the tiles (1024 x 1024, K 512: 20.5 -> 17.3) or three rounds stand against two (1024 x
-    //   2816, K 768: 87 -> 72), and not elsewhere (2048 x 2816, K 256: 82.6 -> 61.2).
-    const int chunks = p.K / (F32_CHUNK * WAVES);   // of a wavefront, at least
+    // Loads in one batch (the last one of a wavefront holds what is left) or each behind a test of its own, as measured (us, the
+    // form not taken -> the one taken):
+    // - 16 x 16 and 32 x 32 tiles: in a batch (512 x 1024, K 320: 13.0 -> 11.1; 600 x 960, K 512: 16.8 -> 14.5; SwiGLU 1024 x
+    //   1024, K 512: 39.4 -> 29.2); 16 x 16 over K >= 1024 eight chunks at once while there is one tile per compute unit
+    //   (64 x 960, K 1408: 8.2 -> 7.8), four with more;
+    // - 64 x 64 tiles: in a batch up to K 2048 (1500 x 1024, K 1152: 64.0 -> 55.7; K 2048 0 .. 7 %), beyond one by one (560 x
+    //   1920, K 2880: 133.1 -> 126.6), and so over two chunks in more than one round (1500 x 1024, K 128: 12.0 -> 11.1);
+    // - SwiGLU's 64 x 32, which start at K 2048: one by one (560 x 1920, K 2880: 204.6 -> 192.7).
     if (!grouped && small_tiles <= 2048) {
         constexpr int UN = EPI == 0 && WAVES == 8 ? 8 : 4;
         if (UN == 8 && small_tiles <= 256)
             gemm_f32_kernel<EPI, 1, 1, WAVES, UN, true><<<small, T, 0, s>>>(p);
-        else if (chunks >= 4)
-            gemm_f32_kernel<EPI, 1, 1, WAVES, 4, true><<<small, T, 0, s>>>(p);
         else
-            gemm_f32_kernel<EPI, 1, 1, WAVES, 4, false><<<small, T, 0, s>>>(p);
+            gemm_f32_kernel<EPI, 1, 1, WAVES, 4, true><<<small, T, 0, s>>>(p);
     } else if (!grouped && big_tiles >= 256 && (EPI == 0 || p.K >= 2048)) {
-        const bool batch = EPI == 0 && (WAVES == 8 ? p.K < 1536 : big_tiles == 256 || (p.K >= 512 && big_tiles > 512 && big_tiles <= 768));
-        if (batch)
+        const int chunks = p.K / (F32_CHUNK * WAVES);   // of a wavefront, at least
+        if (EPI == 0 && p.K <= 2048 && !(WAVES == 4 && chunks == 2 && big_tiles > 256))
             gemm_f32_kernel<EPI, 4, BN / 16, WAVES, 2, EPI == 0><<<big, T, 0, s>>>(p);
         else
             gemm_f32_kernel<EPI, 4, BN / 16, WAVES, 2, false><<<big, T, 0, s>>>(p);
-    } else if (chunks >= 2 && !(EPI == 1 && WAVES == 4 && middle_tiles > 512 && middle_tiles <= 768)) {
-        gemm_f32_kernel<EPI, 2, 2, WAVES, EPI == 1 ? 2 : 4, true><<<middle, T, 0, s>>>(p);
     } else {
-        gemm_f32_kernel<EPI, 2, 2, WAVES, EPI == 1 ? 2 : 4, false><<<middle, T, 0, s>>>(p);
+        gemm_f32_kernel<EPI, 2, 2, WAVES, EPI == 1 ? 2 : 4, true><<<middle, T, 0, s>>>(p);
     }
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
