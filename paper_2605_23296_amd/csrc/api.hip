@@ -288,6 +288,11 @@ struct Plan {
     std::vector<TileItem> rope_tiles, q_tiles;
     std::vector<TileItem> kv_chunks;   // decode attention work list: (block, first cached row of a chunk)
     int max_len = 0;
+    int max_keys() const {   // most cache rows that a row of the plan's blocks attends
+        int most = 0;
+        for (const BlockMeta& m : meta) most = std::max(most, m.prior + m.len);
+        return most;
+    }
     // device views
     const BlockMeta* d_meta = nullptr;
     const TileItem* d_rope_tiles = nullptr;
@@ -467,7 +472,7 @@ static int run_attn_prefill(compact_ctx* ctx, const Plan& p, int n_blocks, const
     if (ctx->cfg.dtype == COMPACT_BF16)
         return launch_attn_prefill_bf16(ctx, p.d_meta, p.d_q_tiles, (int)p.q_tiles.size(), (const bf16*)qkv,
                                         (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)o, s);
-    return launch_attn_prefill_f32(ctx, p.d_meta, n_blocks, p.max_len, (const float*)qkv, (const float*)kv->d_k,
+    return launch_attn_prefill_f32(ctx, p.d_meta, n_blocks, p.max_len, p.max_keys(), (const float*)qkv, (const float*)kv->d_k,
                                    (const float*)kv->d_v, (float*)o, s);
 }
 
@@ -1144,7 +1149,7 @@ extern "C" int compact_mixed_forward(compact_ctx* ctx, const compact_weights* w,
                                             (const int32_t*)(plan.d_extra + mx.qrow), Dtot));
         } else {
             // fp32 storage: a decoding block is a chunk of one row to the plain kernel
-            TRY(launch_attn_prefill_f32(ctx, plan.d_meta, n_part, plan.max_len, (const float*)pb.qkv, (const float*)kv->d_k,
+            TRY(launch_attn_prefill_f32(ctx, plan.d_meta, n_part, plan.max_len, plan.max_keys(), (const float*)pb.qkv, (const float*)kv->d_k,
                                         (const float*)kv->d_v, (float*)pb.o, s));
         }
         TRY(gemm_full(ctx, pb.o, w->w_o, xp, false, pb.h, Tm, c.d_model, Dq, 2, s));

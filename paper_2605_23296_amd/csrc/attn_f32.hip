@@ -5,7 +5,11 @@
 // of four blocks of 128.
 #include "attn_f32.h"
 
-template <int HD>
+// head_dim 128: few keys take the forms for 16 and 32, and a call whose rows all have at most MOST = 32 a kernel of these alone.
+// The form for 64 keeps the 64 loads of a piece in 256 registers, so one wavefront per SIMD; calls of short blocks, 8 heads,
+// lost by it against lane = key with 90 registers (64 blocks of 40 tokens 364 -> 381 us, 300 of 5 225 -> 264; now 340 and 205).
+// At head_dim 64 (163 registers) the one form is the faster one throughout, and so it is in a decode step.
+template <int HD, int MOST>
 __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(const BlockMeta* __restrict__ meta,
                                                                const float* __restrict__ qkv,
                                                                const float* __restrict__ kbase,
@@ -28,21 +32,23 @@ __global__ __launch_bounds__(256) void attn_prefill_f32_kernel(const BlockMeta* 
     RowState st = {-INFINITY, 0.f, {0.f, 0.f}};
     const int n_keys = bm.prior + i + 1;
     for (int j = 0; j < n_keys; j += F32_KEYS)
-        visit_keys<HD>(st, qs[w], ps[w], kslab, vslab, bm.capacity, j, min(F32_KEYS, n_keys - j), scale);
+        visit_keys<HD, HD == 128, MOST>(st, qs[w], ps[w], kslab, vslab, bm.capacity, j, min(F32_KEYS, n_keys - j), scale);
     float* orow = o + (size_t)(bm.row0 + i) * Hq * HD + h * HD;
 #pragma unroll
     for (int u = 0; u < HD / 64; ++u) orow[state_element(u)] = st.acc[u] / st.l;
 }
 
-int launch_attn_prefill_f32(compact_ctx* ctx, const BlockMeta* d_meta, int n_blocks, int max_len, const float* qkv,
+int launch_attn_prefill_f32(compact_ctx* ctx, const BlockMeta* d_meta, int n_blocks, int max_len, int max_keys, const float* qkv,
                             const float* d_k, const float* d_v, float* o, hipStream_t s) {
     const compact_layer_cfg& c = ctx->cfg;
     dim3 grid((max_len + 3) / 4, c.n_q_heads, n_blocks);
     const float scale = 1.0f / sqrtf((float)c.head_dim);
-    if (c.head_dim == 128)
-        attn_prefill_f32_kernel<128><<<grid, 256, 0, s>>>(d_meta, qkv, d_k, d_v, o, c.n_q_heads, c.n_kv_heads, scale);
+    if (c.head_dim == 128 && max_keys <= 32)
+        attn_prefill_f32_kernel<128, 32><<<grid, 256, 0, s>>>(d_meta, qkv, d_k, d_v, o, c.n_q_heads, c.n_kv_heads, scale);
+    else if (c.head_dim == 128)
+        attn_prefill_f32_kernel<128, F32_KEYS><<<grid, 256, 0, s>>>(d_meta, qkv, d_k, d_v, o, c.n_q_heads, c.n_kv_heads, scale);
     else
-        attn_prefill_f32_kernel<64><<<grid, 256, 0, s>>>(d_meta, qkv, d_k, d_v, o, c.n_q_heads, c.n_kv_heads, scale);
+        attn_prefill_f32_kernel<64, F32_KEYS><<<grid, 256, 0, s>>>(d_meta, qkv, d_k, d_v, o, c.n_q_heads, c.n_kv_heads, scale);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }

@@ -266,7 +266,7 @@ int launch_resid_norm_stream_mt(compact_ctx* ctx, const bf16* X, const bf16* W, 
 int launch_rownorm_apply(compact_ctx* ctx, const bf16* hg, const RowNorm& norm, bf16* m, int rows, int d, hipStream_t s);
 
 // attn_f32.hip
-int launch_attn_prefill_f32(compact_ctx* ctx, const BlockMeta* d_meta, int n_blocks, int max_len,
+int launch_attn_prefill_f32(compact_ctx* ctx, const BlockMeta* d_meta, int n_blocks, int max_len, int max_keys,
                             const float* qkv, const float* d_k, const float* d_v, float* o, hipStream_t s);
 int launch_attn_decode_f32(compact_ctx* ctx, const BlockMeta* d_meta, int n_blocks, int step, const float* q,
                            const float* d_k, const float* d_v, float* o, hipStream_t s);

@@ -49,6 +49,28 @@ def test_prefill_attention_fp32_key_pieces(layer):
 
 
 @pytest.mark.parametrize("layer", [MOE, DENSE], ids=["hd64", "hd128"])
+def test_prefill_attention_fp32_short_blocks(layer):
+    # forms for 16 and 32 keys, and calls whose rows all have at most 32: a row's bits do not depend on a longer block beside it
+    lay, short = fp32_variant(layer), [1, 2, 15, 16, 17, 20, 31, 32]
+    attention_case(lay, short, 63)
+    qkv = rnd((sum(short) + 33, lay.Dq + 2 * lay.Dkv), torch.float32, 64)
+    out = []
+    for lens in (short, short + [33]):
+        cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
+        rows = qkv[:cu[-1]].clone()
+        kv = B.KVCache(lay, lens, "cuda", torch.float32)
+        kv.k.fill_(float("nan"))
+        kv.v.fill_(float("nan"))
+        gpu = B.Layer(lay, None)
+        gpu.compact_rope_kvwrite(cu, rows, kv)
+        o = torch.empty((cu[-1], lay.Dq), dtype=torch.float32, device="cuda")
+        gpu.compact_attn_prefill(cu, rows, kv, o)
+        torch.cuda.synchronize()
+        out.append(o[:sum(short)])
+    assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("layer", [MOE, DENSE], ids=["hd64", "hd128"])
 def test_decode_attention_fp32_key_pieces(layer):
     # fewer pieces than wavefronts, exactly one each, a second round that only some wavefronts take part in
     decode_case(fp32_variant(layer), [1, 3, 63, 64, 65, 192, 255, 256, 257, 333, 600], 62)
