@@ -226,12 +226,13 @@ int compact_layer_forward(compact_ctx* ctx, const compact_weights* w, int32_t n_
  * tails->h_len[b]; its K/V row is appended to tail b, it attends the shared rows
  * 0..h_prefix_len[b]-1 and tail rows 0..h_len[b] inclusive, tails->h_len[b] is
  * incremented, d_y [N, d] receives the layer outputs.  The shared rows are cut
- * into work items of 128, 256 or 512 rows, those of long histories (beyond 65536
- * rows with 8 KV heads of 128) of 832 to 1536, by shared->h_len[0] and the layer
- * alone, so a worker's results do not depend on the other workers.  An item is
- * multiplied with the query heads of the workers whose prefix covers it, up to
- * 128 / (query heads per KV head) of them; its rows are read once for these
- * together, and once more for every further group of as many workers.
+ * into work items of 128, 256 or 512 rows, those of long histories of layers with
+ * 1, 2, 4 or 8 KV heads (beyond 65536 rows with 8 of 128) of 832 to 1536, by
+ * shared->h_len[0] and the layer alone, so a worker's results do not depend on
+ * the other workers.  An item is multiplied with the query heads of the workers
+ * whose prefix covers it, up to 128 / (query heads per KV head) of them; its rows
+ * are read once for these together, and once more for every further group of as
+ * many workers.
  * bf16 storage only.  Errors as compact_decode_step; COMPACT_EINVAL for a
  * decreasing or out-of-range h_prefix_len; COMPACT_ECAPACITY where a worker's
  * prefix and tail together span more than 1024 pieces of 256 rows.  The

@@ -1276,11 +1276,15 @@ extern "C" int compact_stack_forward(compact_ctx* ctx, int32_t n_layers, const c
 // 3 workers: 66500 rows 157.2 / 162.2 / 147.7 us a step, 80000 rows 161.5 / 163.1 / 157.4, 98304 rows 177.0 / 175.0 / 173.4; 24
 // workers: 179.9 / 180.6 / 172.4, 191.8 / 192.4 / 182.9, 205.3 / 202.4 / 198.9; 40 workers (two groups of columns): 200.7 / 200.8 /
 // 201.8, 210.9 / 208.1 / 210.6, 234.2 / 225.9 / 236.0.  Between 32768 and 65536 rows taller items gain and lose about as often.
+// What they save is records and their merge, and a head has fewer of those the more KV heads share the resident workgroups: only
+// layers whose KV heads divide 8 take them (two passes, 1 / 24 workers, items of 512 rows -> this rule: 4 heads of 128, 133,693
+// rows 158 -> 138 / 203 -> 181 us; 8 heads, 66,846 rows 160 -> 139 / 206 -> 194; 12 heads, 43,868 rows 160 -> 144 / 210 -> 229; 16
+// heads, 40,960 rows 185 -> 182 / 246 -> 264; 16 heads of 64, 61,440 rows 136 -> 153 / 181 -> 191).
 static int64_t prefix_resident(const compact_layer_cfg& c) { return std::max(1, (c.head_dim == 128 ? 512 : 768) / c.n_kv_heads); }
 static void prefix_item_limits(const compact_layer_cfg& c, int64_t (&rows)[3]) {   // longest histories for 128-, 256- and 512-row items
     rows[0] = (c.head_dim == 128 ? 256 : 512) * 128 / c.n_kv_heads;
     rows[1] = (c.head_dim == 128 ? 384 : 512) * 256 / c.n_kv_heads;
-    rows[2] = std::max(rows[1], prefix_resident(c) * 1024);
+    rows[2] = 8 % c.n_kv_heads == 0 ? std::max(rows[1], prefix_resident(c) * 1024) : INT64_MAX;
 }
 static int prefix_item_rows(const compact_layer_cfg& c, int shared_len) {
     int64_t lim[3];

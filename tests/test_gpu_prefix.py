@@ -91,9 +91,18 @@ def test_prefix_decode_attention_kernel_item_heights(hkv, hd, group, rows):
 
 @pytest.mark.parametrize("hkv,hd,rows", [(32, 128, 16384), (32, 128, 16385), (32, 128, 24576), (32, 128, 24577), (64, 64, 12289), (64, 64, 18500)])
 def test_prefix_decode_attention_kernel_items_beyond_512_rows(hkv, hd, rows):
-    """The line to the items that make whole rounds of workgroups, and between one round of them and two: the cases of the
-    other heights."""
+    """Long histories of layers with many KV heads, which keep items of 512 rows: the cases of the other heights."""
     test_prefix_decode_attention_kernel_item_heights(hkv, hd, 1, rows)
+
+
+@pytest.mark.parametrize("hkv,hd,rows,item", [(8, 128, 65536, 512), (8, 128, 65537, 1088), (8, 128, 98305, 832), (8, 64, 98305, 1088)])
+def test_prefix_decode_attention_kernel_items_of_whole_rounds(hkv, hd, rows, item):
+    """The line to the items that make whole rounds of workgroups, and between one round of them and two: prefixes around an
+    item boundary and the whole history; a worker has the same bits alone."""
+    layer = LayerConfig(d_model=512, n_q_heads=hkv, n_kv_heads=hkv, head_dim=hd, ffn_dim=512, rope_theta=1e4, dtype="bf16")
+    prefix, tail = [item, item + 1, rows], [1, 40, 257]
+    every = prefix_kernel_case(layer, prefix, tail, rows=rows)
+    assert np.array_equal(prefix_kernel_case(layer, prefix, tail, rows=rows, pick=[1])[0], every[1])
 
 
 def prefix_kernel_case(layer, prefix, tail, grow=None, rows=None, pick=None):
