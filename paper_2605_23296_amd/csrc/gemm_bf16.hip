@@ -58,6 +58,7 @@ struct GemmParams {
     int N;  // output columns (F for the SwiGLU epilogue, whose W has 2N rows)
     int K;
     int n_mtiles, n_ntiles;
+    int n_full;  // 256 x 256 kernel, plain product: workgroups that take a whole tile (the others take halves)
     int r_f32;  // the residual R is fp32 rather than bf16
     const float* pre_scale;   // SwiGLU: factor of every row's products before the silu (null = 1)
     GroupedArgs g;
@@ -103,17 +104,24 @@ struct TilePos {
     int n0;           // first output column
     const bf16* W;    // the weight matrix (the expert's)
 };
+// workgroup i of n that are dealt round robin -> its place in the order of tiles
+__device__ __forceinline__ int xcd_order(int i, int n) {
+    const int per = n / 8, rem = n % 8, xcd = i % 8;
+    return xcd * per + min(xcd, rem) + i / 8;
+}
+// place in the order -> row tile, column tile (n_mtiles row tiles)
+template <int GM>
+__device__ __forceinline__ void tile_at(int pid, int n_mtiles, int n_ntiles, int& tm, int& tn) {
+    const int per_group = GM * n_ntiles;
+    const int first_m = (pid / per_group) * GM;
+    const int gsize = min(GM, n_mtiles - first_m);
+    tm = first_m + (pid % per_group) % gsize;
+    tn = (pid % per_group) / gsize;
+}
 template <bool GROUPED, int BM, int OUTN, int GM>
 __device__ __forceinline__ TilePos find_tile(const GemmParams& p) {
-    const int total = gridDim.x;
-    const int per = total / 8, rem = total % 8;
-    const int xcd = blockIdx.x % 8, loc = blockIdx.x / 8;
-    const int pid = xcd * per + min(xcd, rem) + loc;
-    const int per_group = GM * p.n_ntiles;
-    const int first_m = (pid / per_group) * GM;
-    const int gsize = min(GM, p.n_mtiles - first_m);
-    const int tm = first_m + (pid % per_group) % gsize;
-    const int tn = (pid % per_group) / gsize;
+    int tm, tn;
+    tile_at<GM>(xcd_order(blockIdx.x, gridDim.x), p.n_mtiles, p.n_ntiles, tm, tn);
     TilePos tp;
     tp.n0 = tn * OUTN;
     tp.W = p.W;
@@ -227,17 +235,12 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const floatx4 (&
 }
 
 template <int EPI, bool GROUPED>
-__global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmParams p) {
+__device__ __forceinline__ void tile_256(const GemmParams& p, const TilePos& tp, char* smem) {
     constexpr int BM = 256, BN = 256, WM = 2, WN = 4, BK = GEMM_BK;
     constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 16, TN = WTN / 16;   // 128 x 64 per wave, 8 x 4 MFMA tiles
     constexpr int HT = 128 * BK;                    // elements of a half tile (one LDS slot)
-    constexpr int OUTN = EPI == 1 ? BN / 2 : BN;
     constexpr int WOUT = EPI == 1 ? WTN / 2 : WTN;  // output columns per wave
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16* lds = reinterpret_cast<bf16*>(smem);
-
-    const TilePos tp = find_tile<GROUPED, BM, OUTN, 4>(p);
-    if (tp.rows_valid <= 0) return;
     const int64_t m0 = tp.m0;
     const int rows_valid = tp.rows_valid, n0 = tp.n0;
     const bf16* Wb = tp.W;
@@ -388,16 +391,12 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmParams p) {
 // owns of a k-tile; 11 or 12 of them may still fly when the next phase's operands must be there.
 // ---------------------------------------------------------------------------
 template <int EPI, bool GROUPED>
-__global__ __launch_bounds__(512) void gemm_bf16_half_kernel(const GemmParams p) {
-    constexpr int BM = 128, BN = 256, WN = 4, BK = GEMM_BK;
+__device__ __forceinline__ void tile_128(const GemmParams& p, const TilePos& tp, char* smem) {
+    constexpr int WN = 4, BK = GEMM_BK;
     constexpr int WTM = 64, WTN = 64, TM = WTM / 16, TN = WTN / 16;
     constexpr int HT = 128 * BK;
-    constexpr int OUTN = EPI == 1 ? BN / 2 : BN;
     constexpr int WOUT = EPI == 1 ? WTN / 2 : WTN;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16* lds = reinterpret_cast<bf16*>(smem);
-    const TilePos tp = find_tile<GROUPED, BM, OUTN, 8>(p);
-    if (tp.rows_valid <= 0) return;
     const int n0 = tp.n0;
     const int t = threadIdx.x;
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -501,6 +500,52 @@ __global__ __launch_bounds__(512) void gemm_bf16_half_kernel(const GemmParams p)
     ring_barrier<0>();   // the repeated loads of the last k-tile must not land in the slabs
     store_tile<EPI, GROUPED, TM, TN>(p, acc, reinterpret_cast<float*>(smem) + wave * 32 * (WOUT + 4), lane, wm * WTM, tp.rows_valid,
                                      tp.m0, n0 + wn * WOUT);
+}
+
+// Plain products: the output is cut into slots of 256 x 256 (groups of 4 row tiles, as above); the first n_full of them
+// are a workgroup each, the others two workgroups of 128 x 256, and last come the halves of a bottom row tile of at most
+// 128 rows: a last round that whole tiles would fill by half or less takes half tiles, which need 0.6 of the time, and the
+// short ones fill units that the round leaves idle.  Against one form for all of a call (us): 2 * 14336 x 4096 at 1652 rows
+// 351 -> 280 (672 whole and 112 half tiles; before, 1456 halves), N 4096 K 14336 at 4600 rows 478 -> 446, at 9000 rows
+// 877 -> 774, N 5120 K 2880 at 4600 rows 106 -> 95; the other calls of a sweep of 8 products at 40 row counts within 1 %.
+// Routed products: a workgroup per tile of the map, in the form that its rows need.
+template <int EPI, bool GROUPED>
+__global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmParams p) {
+    constexpr int OUTN = EPI == 1 ? 128 : 256;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    if constexpr (GROUPED) {
+        const TilePos tp = p.g.mtile == 256 ? find_tile<true, 256, OUTN, 4>(p) : find_tile<true, 128, OUTN, 8>(p);
+        if (tp.rows_valid <= 0) return;
+        if (tp.rows_valid > 128)
+            tile_256<EPI, true>(p, tp, smem);
+        else
+            tile_128<EPI, true>(p, tp, smem);
+    } else {
+        const int i = blockIdx.x;
+        int tm, tn;
+        TilePos tp;
+        tp.W = p.W;
+        if (i < p.n_full) {
+            tile_at<4>(xcd_order(i, p.n_full), p.n_mtiles, p.n_ntiles, tm, tn);
+            tp.m0 = (int64_t)tm * 256;
+            tp.n0 = tn * OUTN;
+            tp.rows_valid = (int)min((int64_t)256, p.M - tp.m0);
+            tile_256<EPI, false>(p, tp, smem);
+        } else {
+            const int h = xcd_order(i - p.n_full, gridDim.x - p.n_full);
+            const int slot = p.n_full + h / 2, slots = p.n_mtiles * p.n_ntiles;
+            if (slot < slots) {
+                tile_at<4>(slot, p.n_mtiles, p.n_ntiles, tm, tn);
+                tp.m0 = (int64_t)tm * 256 + (h & 1) * 128;
+            } else {
+                tn = h - 2 * (slots - p.n_full);
+                tp.m0 = (int64_t)p.n_mtiles * 256;
+            }
+            tp.n0 = tn * OUTN;
+            tp.rows_valid = (int)min((int64_t)128, p.M - tp.m0);
+            tile_128<EPI, false>(p, tp, smem);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -619,23 +664,41 @@ static int launch_small(compact_ctx* ctx, GemmParams& p, hipStream_t s, int k_sl
     return COMPACT_OK;
 }
 
-// H: the 128 x 256 form
-template <int EPI, bool GROUPED, bool H>
-static int launch_cfg(compact_ctx* ctx, GemmParams& p, hipStream_t s) {
-    constexpr int OUTN = EPI == 1 ? 128 : 256, BM = H ? 128 : 256;
-    if (!GROUPED) p.n_mtiles = (int)((p.M + BM - 1) / BM);
-    p.n_ntiles = (p.N + OUTN - 1) / OUTN;
-    constexpr size_t smem = (size_t)(H ? 9 : 8) * 128 * GEMM_BK * sizeof(bf16);   // the ring; the epilogue's slabs fit in
+// How the 256 x 256 kernel cuts M rows: slots of 256 x 256 (a last row tile of more than 128 rows is one), and 128 x 256
+// tiles of a bottom row tile of at most 128 rows.
+struct LargeTiles {
+    int64_t slots;
+    int64_t bottom;
+};
+static LargeTiles large_tiles(int64_t M, int n_ntiles) {
+    const int64_t rest = M % 256;
+    return {(M / 256 + (rest > 128 ? 1 : 0)) * n_ntiles, rest > 0 && rest <= 128 ? n_ntiles : 0};
+}
+
+// n_full (plain products): slots of 256 x 256 that are whole tiles, see the kernel
+template <int EPI, bool GROUPED>
+static int launch_large(compact_ctx* ctx, GemmParams& p, int64_t n_full, hipStream_t s) {
+    constexpr int OUTN = EPI == 1 ? 128 : 256;
+    constexpr size_t smem = (size_t)9 * 128 * GEMM_BK * sizeof(bf16);   // the larger ring; the epilogue's slabs fit in
     static_assert((size_t)8 * 32 * (OUTN / 4 + 4) * sizeof(float) <= smem, "the epilogue's slabs fit the ring");
-    auto kern = H ? gemm_bf16_half_kernel<EPI, GROUPED> : gemm_bf16_kernel<EPI, GROUPED>;
+    auto kern = gemm_bf16_kernel<EPI, GROUPED>;
     static bool attr_set = false;
     if (!attr_set) {
         HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
         attr_set = true;
     }
-    const int64_t tiles = (int64_t)p.n_mtiles * p.n_ntiles;
-    if (tiles == 0) return COMPACT_OK;
-    kern<<<dim3((unsigned)tiles), 512, smem, s>>>(p);
+    p.n_ntiles = (p.N + OUTN - 1) / OUTN;
+    int64_t wgs;
+    if (GROUPED) {
+        wgs = (int64_t)p.n_mtiles * p.n_ntiles;
+    } else {
+        const LargeTiles lt = large_tiles(p.M, p.n_ntiles);
+        p.n_mtiles = (int)(lt.slots / p.n_ntiles);
+        p.n_full = (int)std::min(n_full, lt.slots);
+        wgs = p.n_full + 2 * (lt.slots - p.n_full) + lt.bottom;
+    }
+    if (wgs == 0) return COMPACT_OK;
+    kern<<<dim3((unsigned)wgs), 512, smem, s>>>(p);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
@@ -669,12 +732,44 @@ static double tile_cost(int form, double row_tiles, int N, int K, int epilogue, 
     return rounds * ((K / GEMM_BK) * (f.t_idle + f.t_load * tiles / (rounds * n_cus)) + f.t_tile);
 }
 
-static int pick_tile(int64_t M, int N, int K, int epilogue, int n_cus) {
-    int best = TILE_256;
+// The 256 x 256 kernel: cost with n_full whole tiles, then `halves` 128 x 256 ones, each handed to the unit that is free
+// first.  Workgroups are dealt to the eight XCDs round robin whatever their length, so the fullest XCD counts.
+static double large_cost(int64_t n_full, int64_t halves, int K, int n_cus) {
+    const TileForm &F = tile_forms[TILE_256], &H = tile_forms[TILE_128];
+    const int nk = K / GEMM_BK, cus = std::max(1, n_cus / 8);
+    const int64_t nf = (n_full + 7) / 8, nh = (halves + 7) / 8, busy = nf % cus, idle = cus - busy;
+    double u = 1.0, end = 0;
+    for (int pass = 0; pass < 2; ++pass) {   // the times depend on the average load, and it on the times
+        const double tf = nk * (F.t_idle + F.t_load * u) + F.t_tile, th = nk * (H.t_idle + H.t_load * u) + H.t_tile;
+        double ti = nf / cus * tf, tb = ti + tf;   // when the units with a tile less, and the others, are free
+        end = busy ? tb : ti;
+        for (int64_t left = nh; left > 0;) {
+            double& t = ti <= tb ? ti : tb;
+            left -= ti <= tb ? idle : busy;
+            end = std::max(end, t += th);
+        }
+        u = std::min(1.0, (nf * tf + nh * th) / (end * cus));
+    }
+    return end;
+}
+
+static int pick_tile(int64_t M, int N, int K, int epilogue, int n_cus, int64_t* n_full) {
+    // every slot a whole tile, whole rounds of them and the rest in halves, one round less, or halves only
+    const int outn = epilogue == 1 ? 128 : 256, n_ntiles = (N + outn - 1) / outn;
+    const LargeTiles lt = large_tiles(M, n_ntiles);
+    const int64_t whole = lt.slots - lt.slots % n_cus;
     double best_cost = 0;
-    for (int form = 0; form < TILE_FORMS; ++form) {
+    for (const int64_t cut : {(int64_t)0, std::max<int64_t>(0, whole - n_cus), whole, lt.slots}) {
+        const double c = large_cost(cut, 2 * (lt.slots - cut) + lt.bottom, K, n_cus);
+        if (cut == 0 || c < best_cost) {
+            best_cost = c;
+            *n_full = cut;
+        }
+    }
+    int best = *n_full > 0 ? TILE_256 : TILE_128;
+    for (int form = TILE_128 + 1; form < TILE_FORMS; ++form) {
         const double c = tile_cost(form, (double)((M + tile_forms[form].bm - 1) / tile_forms[form].bm), N, K, epilogue, n_cus);
-        if (form == 0 || c < best_cost) {
+        if (c < best_cost) {
             best = form;
             best_cost = c;
         }
@@ -704,10 +799,10 @@ int gemm_bf16_group_mtile(int64_t rows, int n_experts, int F, int d, int n_cus) 
 }
 
 template <int EPI, bool GROUPED>
-static int launch_form(compact_ctx* ctx, int form, GemmParams& p, hipStream_t s) {
+static int launch_form(compact_ctx* ctx, int form, int64_t n_full, GemmParams& p, hipStream_t s) {
     switch (form) {
-        case TILE_256: return launch_cfg<EPI, GROUPED, false>(ctx, p, s);
-        case TILE_128: return launch_cfg<EPI, GROUPED, true>(ctx, p, s);
+        case TILE_256: return launch_large<EPI, GROUPED>(ctx, p, n_full, s);
+        case TILE_128: return launch_large<EPI, GROUPED>(ctx, p, 0, s);
         case TILE_64_128: return launch_small<64, 128, 2, 4, 6, EPI, GROUPED>(ctx, p, s);
         default: break;
     }
@@ -742,20 +837,22 @@ int launch_gemm_bf16(compact_ctx* ctx, const bf16* A, const bf16* B, const void*
         p.n_mtiles = grouped->n_mtiles;
         const int form = grouped->mtile == 256 ? TILE_256 : grouped->mtile == 128 ? TILE_128 : TILE_64_128;
         if (tile_forms[form].bm != grouped->mtile) return set_err(ctx, COMPACT_EINVAL, "no grouped GEMM of this row-tile height");
-        return epilogue == 1 ? launch_form<1, true>(ctx, form, p, s) : launch_form<0, true>(ctx, form, p, s);
+        return epilogue == 1 ? launch_form<1, true>(ctx, form, 0, p, s) : launch_form<0, true>(ctx, form, 0, p, s);
     }
-    const int form = pick_tile(M, N, K, epilogue, n_cus);
-    if (epilogue == 1) return launch_form<1, false>(ctx, form, p, s);
-    if (epilogue == 2) return launch_form<2, false>(ctx, form, p, s);
-    return launch_form<0, false>(ctx, form, p, s);
+    int64_t n_full = 0;
+    const int form = pick_tile(M, N, K, epilogue, n_cus, &n_full);
+    if (epilogue == 1) return launch_form<1, false>(ctx, form, n_full, p, s);
+    if (epilogue == 2) return launch_form<2, false>(ctx, form, n_full, p, s);
+    return launch_form<0, false>(ctx, form, n_full, p, s);
 }
 
-// For the tests, not part of compact.h: the product in tile form `form`, or in the one the rule picks (-1); `picked` receives
-// the rule's form.  And the row-tile height of the grouped products.
+// For the tests, not part of compact.h: the product in tile form `form` (TILE_FORMS: whole tiles and halves mixed, as many slots
+// in either), or in the one the rule picks (-1); `picked` receives the rule's form.  And the row-tile height of the grouped
+// products.
 extern "C" int compact_test_gemm_form(compact_ctx* ctx, int32_t form, const void* a, const void* b, const void* r, void* c, int64_t M,
                                       int32_t N, int32_t K, int32_t epilogue, int32_t* picked, void* hip_stream) {
     if (!ctx || !a || !b || !c || !picked || M < 1 || N < 8 || N % 8 != 0 || K < GEMM_BK || K % GEMM_BK != 0 || form < -1 ||
-        form >= TILE_FORMS || (epilogue != 0 && epilogue != 1))
+        form > TILE_FORMS || (epilogue != 0 && epilogue != 1))
         return COMPACT_EINVAL;
     int n_cus = 0;
     if (int rc = device_cu_count(ctx, &n_cus)) return rc;
@@ -767,10 +864,18 @@ extern "C" int compact_test_gemm_form(compact_ctx* ctx, int32_t form, const void
     p.M = M;
     p.N = N;
     p.K = K;
-    *picked = pick_tile(M, N, K, epilogue, n_cus);
-    if (form < 0) form = *picked;
+    int64_t n_full = 0;
+    *picked = pick_tile(M, N, K, epilogue, n_cus, &n_full);
+    if (form < 0)
+        form = *picked;
+    else
+        n_full = large_tiles(M, (N + (epilogue == 1 ? 127 : 255)) / (epilogue == 1 ? 128 : 256)).slots;
+    if (form == TILE_FORMS) {
+        form = TILE_256;
+        n_full /= 2;
+    }
     hipStream_t s = (hipStream_t)hip_stream;
-    return epilogue == 1 ? launch_form<1, false>(ctx, form, p, s) : launch_form<0, false>(ctx, form, p, s);
+    return epilogue == 1 ? launch_form<1, false>(ctx, form, n_full, p, s) : launch_form<0, false>(ctx, form, n_full, p, s);
 }
 extern "C" int compact_test_group_mtile(compact_ctx* ctx, int64_t rows, int32_t n_experts, int32_t F, int32_t d, int32_t* mtile) {
     int n_cus = 0;

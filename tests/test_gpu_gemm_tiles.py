@@ -72,6 +72,28 @@ def test_every_tile_form_at_its_edges(K, epi, res):
             assert torch.equal(c, first), (M, N, FORMS[form])
 
 
+# whole tiles, halves of the other slots and a bottom row tile of at most 128 rows in one launch: no whole tile, one, several; last
+# row tiles of 1, 128, 129 and 255 rows; workgroup counts that the XCDs do not share evenly
+@pytest.mark.parametrize("epi,res", [(0, True), (1, False)])
+@pytest.mark.parametrize("M,N,K", [(255, 264, 192), (385, 520, 64), (640, 1032, 256), (1153, 776, 320), (1791, 2056, 128)])
+def test_whole_and_half_tiles_in_one_launch(M, N, K, epi, res):
+    lay = B.Layer(DENSE, None)
+    a, b = rnd((M, K), torch.bfloat16, 3), rnd(((2 if epi else 1) * N, K), torch.bfloat16, 4, std=0.05)
+    r = rnd((M, N), torch.bfloat16, 5) if res else None
+    A, Bm = to_numpy_f64(a), to_numpy_f64(b)
+    ref = O.silu(O.linear(A, Bm[:N])) * O.linear(A, Bm[N:]) if epi else O.linear(A, Bm) + (to_numpy_f64(r) if res else 0.0)
+    first = None
+    for form in (len(FORMS), 5):   # mixed, 64 x 64
+        c = torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device="cuda")
+        gemm_form(lay, form, a, b, r, c[:M], epi)
+        torch.cuda.synchronize()
+        assert bool((c[M] == 7.0).all())
+        if first is None:
+            assert rel_err(to_numpy_f64(c[:M]), ref) < 1e-2
+            first = c
+        assert torch.equal(c, first)
+
+
 def test_the_rule_picks_every_tile_form():
     """Calls at which each form is the cheapest by the rule: a retuned table that drops one shows up here."""
     lay = B.Layer(DENSE, None)
