@@ -390,6 +390,17 @@ static int check_blocks(compact_ctx* ctx, int n_blocks, const int32_t* cu) {
     return COMPACT_OK;
 }
 
+// Query tiles block by block, the longest block first, so that the tiles in flight share their keys; inside a block the
+// tile with the most keys first, so that the last ones to start are short.
+static void sort_query_tiles(Plan& p) {
+    const std::vector<BlockMeta>& mt = p.meta;
+    std::stable_sort(p.q_tiles.begin(), p.q_tiles.end(), [&mt](const TileItem& a, const TileItem& b) {
+        const int la = mt[a.block].prior + mt[a.block].len, lb = mt[b.block].prior + mt[b.block].len;
+        if (la != lb) return la > lb;
+        return a.block != b.block ? a.block < b.block : a.row0 > b.row0;
+    });
+}
+
 // extend: the rows of the call are appended behind the h_len[b] rows the cache holds
 static void build_prefill_plan(const compact_kv* kv, int n_blocks, const int32_t* cu, Plan& p, bool extend = false) {
     p.meta.resize(n_blocks);
@@ -405,11 +416,7 @@ static void build_prefill_plan(const compact_kv* kv, int n_blocks, const int32_t
         for (int r = 0; r < m.len; r += ROPE_TILE) p.rope_tiles.push_back({b, r});
         for (int r = 0; r < m.len; r += PREFILL_QTILE) p.q_tiles.push_back({b, r});
     }
-    // causal work of a query tile grows with its cache row: heaviest first
-    const std::vector<BlockMeta>& mt = p.meta;
-    std::stable_sort(p.q_tiles.begin(), p.q_tiles.end(), [&mt](const TileItem& a, const TileItem& b) {
-        return mt[a.block].prior + a.row0 > mt[b.block].prior + b.row0;
-    });
+    sort_query_tiles(p);
 }
 
 // Work list of the split-KV decode attention: every DECODE_CHUNK-row chunk that some
@@ -466,14 +473,22 @@ static int gemm_partials(compact_ctx* ctx, const void* A, const void* B, float* 
 // ---------------------------------------------------------------------------
 // prefill
 // ---------------------------------------------------------------------------
-static int run_attn_prefill(compact_ctx* ctx, const Plan& p, int n_blocks, const void* qkv, const compact_kv* kv, void* o,
-                            hipStream_t s) {
+// scaled: the q rows carry the attention's factor (bf16 only)
+static int run_attn_prefill(compact_ctx* ctx, const Plan& p, int n_blocks, const void* qkv, bool scaled, const compact_kv* kv,
+                            void* o, hipStream_t s) {
     ProfileScope ps(ctx, COMPACT_K_ATTN_PREFILL, s);
     if (ctx->cfg.dtype == COMPACT_BF16)
-        return launch_attn_prefill_bf16(ctx, p.d_meta, p.d_q_tiles, (int)p.q_tiles.size(), (const bf16*)qkv,
+        return launch_attn_prefill_bf16(ctx, p.d_meta, p.d_q_tiles, (int)p.q_tiles.size(), (const bf16*)qkv, scaled,
                                         (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)o, s);
     return launch_attn_prefill_f32(ctx, p.d_meta, n_blocks, p.max_len, p.max_keys(), (const float*)qkv, (const float*)kv->d_k,
                                    (const float*)kv->d_v, (float*)o, s);
+}
+
+static int rope_and_attend(compact_ctx* ctx, const Plan& p, int n_blocks, void* qkv, const compact_kv* kv, void* o, hipStream_t s) {
+    const bool bf = ctx->cfg.dtype == COMPACT_BF16;
+    TRY(launch_rope_kvwrite(ctx, p.d_meta, p.d_rope_tiles, (int)p.rope_tiles.size(), qkv, kv->d_k, kv->d_v,
+                            attn_prefill_q_scale(ctx->cfg), bf ? n_blocks : 0, s));
+    return run_attn_prefill(ctx, p, n_blocks, qkv, bf, kv, o, s);
 }
 
 static int moe_ffn_rows(compact_ctx* ctx, const compact_weights* w, const void* m, const void* h, bool h_is_f32,
@@ -494,8 +509,7 @@ static int prefill_impl(compact_ctx* ctx, const compact_weights* w, int n_blocks
     if (!plan.d_meta) TRY(upload_plan(ctx, plan, s));   // a depth of layers shares one plan
     TRY(launch_rmsnorm(ctx, x, false, w->g_attn, b.n, T, s));
     TRY(gemm_full(ctx, b.n, w->w_qkv, nullptr, false, b.qkv, T, Dtot, c.d_model, 0, s));
-    TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), b.qkv, kv->d_k, kv->d_v, s));
-    TRY(run_attn_prefill(ctx, plan, n_blocks, b.qkv, kv, b.o, s));
+    TRY(rope_and_attend(ctx, plan, n_blocks, b.qkv, kv, b.o, s));
     TRY(gemm_full(ctx, b.o, w->w_o, x, false, b.h, T, c.d_model, Dq, 2, s));   // h = x + o Wo^T, kept in fp32
     TRY(launch_rmsnorm(ctx, b.h, true, w->g_ffn, b.n, T, s));
     if (c.n_experts == 0) {
@@ -1117,12 +1131,7 @@ extern "C" int compact_mixed_forward(compact_ctx* ctx, const compact_weights* w,
             }
             Tm += cnt;
         }
-        {
-            const std::vector<BlockMeta>& mt = plan.meta;
-            std::stable_sort(plan.q_tiles.begin(), plan.q_tiles.end(), [&mt](const TileItem& a, const TileItem& b2) {
-                return mt[a.block].prior + a.row0 > mt[b2.block].prior + b2.row0;
-            });
-        }
+        sort_query_tiles(plan);
         MixExtra mx;
         mx.dec_meta = put(plan.extra, dec_meta);
         mx.qrow = put(plan.extra, qrow);
@@ -1135,11 +1144,13 @@ extern "C" int compact_mixed_forward(compact_ctx* ctx, const compact_weights* w,
         TRY(launch_move_rows(ctx, d_x_prefill, d_x_decode, d_src, xp, nullptr, nullptr, Tm, s));
         TRY(launch_rmsnorm(ctx, xp, false, w->g_attn, pb.n, Tm, s));
         TRY(gemm_full(ctx, pb.n, w->w_qkv, nullptr, false, pb.qkv, Tm, Dtot, c.d_model, 0, s));
-        TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), pb.qkv, kv->d_k, kv->d_v, s));
+        // (the decode attention scales its q rows itself)
+        TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), pb.qkv, kv->d_k, kv->d_v,
+                                attn_prefill_q_scale(c), bf ? n_chunk : 0, s));
         if (bf) {
             {
                 ProfileScope ps(ctx, COMPACT_K_ATTN_PREFILL, s);
-                TRY(launch_attn_prefill_bf16(ctx, plan.d_meta, plan.d_q_tiles, (int)plan.q_tiles.size(), (const bf16*)pb.qkv,
+                TRY(launch_attn_prefill_bf16(ctx, plan.d_meta, plan.d_q_tiles, (int)plan.q_tiles.size(), (const bf16*)pb.qkv, true,
                                              (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)pb.o, s));
             }
             if (n_dec > 0)   // one query row per decoding block, read in place from the packed QKV rows
@@ -1668,7 +1679,7 @@ extern "C" int compact_rope_kvwrite(compact_ctx* ctx, int32_t n_blocks, const in
     Plan plan;
     build_prefill_plan(kv, n_blocks, h_cu_seqlens, plan);
     TRY(upload_plan(ctx, plan, s));
-    TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), d_qkv, kv->d_k, kv->d_v, s));
+    TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), d_qkv, kv->d_k, kv->d_v, 1.0f, 0, s));
     for (int b = 0; b < n_blocks; ++b) kv->h_len[b] = h_cu_seqlens[b + 1] - h_cu_seqlens[b];
     return COMPACT_OK;
 }
@@ -1709,7 +1720,24 @@ extern "C" int compact_attn_prefill(compact_ctx* ctx, int32_t n_blocks, const in
     Plan plan;
     build_prefill_plan(kv, n_blocks, h_cu_seqlens, plan);
     TRY(upload_plan(ctx, plan, s));
-    return run_attn_prefill(ctx, plan, n_blocks, d_qkv, kv, d_o, s);
+    return run_attn_prefill(ctx, plan, n_blocks, d_qkv, false, kv, d_o, s);
+}
+
+// For the tests, not part of compact.h: rotation, cache append and attention as a prefill does them (the attention's factor in
+// the q rows before they are rounded, at head_dim 64).
+extern "C" int compact_test_rope_attn(compact_ctx* ctx, int32_t n_blocks, const int32_t* h_cu_seqlens, void* d_qkv, compact_kv* kv,
+                                      void* d_o, void* hip_stream) {
+    if (!ctx || !d_qkv || !d_o || ctx->cfg.dtype != COMPACT_BF16) return COMPACT_EINVAL;
+    TRY(check_blocks(ctx, n_blocks, h_cu_seqlens));
+    TRY(check_kv(ctx, kv, n_blocks));
+    for (int b = 0; b < n_blocks; ++b)
+        if (h_cu_seqlens[b + 1] - h_cu_seqlens[b] > kv->h_capacity[b])
+            return set_err(ctx, COMPACT_ECAPACITY, "block does not fit its KV slab");
+    hipStream_t s = (hipStream_t)hip_stream;
+    Plan plan;
+    build_prefill_plan(kv, n_blocks, h_cu_seqlens, plan);
+    TRY(upload_plan(ctx, plan, s));
+    return rope_and_attend(ctx, plan, n_blocks, d_qkv, kv, d_o, s);
 }
 
 extern "C" int compact_attn_decode(compact_ctx* ctx, int32_t n_blocks, const void* d_q, const compact_kv* kv, void* d_o,

@@ -1,0 +1,68 @@
+"""Prefill attention as a prefill runs it (rotation, cache append, attention) against the fp64 definition: the edges of its
+key tiles and halves, every share of the KV heads among the XCDs, references that move."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import layer as O
+from paper_2605_23296_amd import binding as B
+from paper_2605_23296_amd.workloads import LayerConfig, to_numpy_f64
+from tests.test_gpu_kernels import rnd
+from tests.util import rel_err, rms_err
+
+pytestmark = pytest.mark.gpu
+
+
+def run(layer, lens, qkv):
+    lay = B.Layer(layer, None)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    kv = B.KVCache(layer, [L + 3 for L in lens], "cuda", torch.bfloat16)
+    kv.k.fill_(float("nan"))   # rows past a block's length must never reach a result
+    kv.v.fill_(float("nan"))
+    o = torch.empty((int(cu[-1]), layer.Dq), dtype=torch.bfloat16, device="cuda")
+    lay.check(lay.L.compact_test_rope_attn(lay.ctx, C.c_int32(len(lens)), cu.ctypes.data_as(C.POINTER(C.c_int32)),
+                                           C.c_void_p(qkv.data_ptr()), C.byref(kv.c), C.c_void_p(o.data_ptr()),
+                                           C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    torch.cuda.synchronize()
+    return to_numpy_f64(o), cu
+
+
+def check(layer, lens, qkv):
+    x = to_numpy_f64(qkv)
+    o, cu = run(layer, lens, qkv)
+    Dq, Dkv, hd = layer.Dq, layer.Dkv, layer.head_dim
+    for b, L in enumerate(lens):
+        rows, pos = x[cu[b]:cu[b + 1]], np.arange(L)
+        q = O.rope(rows[:, :Dq].reshape(L, -1, hd), pos, layer.rope_theta)
+        k = O.rope(rows[:, Dq:Dq + Dkv].reshape(L, -1, hd), pos, layer.rope_theta)
+        ref = O.gqa_attention(q, k, rows[:, Dq + Dkv:].reshape(L, -1, hd), visible=pos + 1).reshape(L, Dq)
+        # q, k, the probabilities and the output are each rounded to 8 mantissa bits once: 0.3 % of the rms, the worst of
+        # 10^6 values at five sigma (the bounds of the kernel tests beside this file)
+        assert rms_err(o[cu[b]:cu[b + 1]], ref) < 6e-3, (b, L)
+        assert rel_err(o[cu[b]:cu[b + 1]], ref) < 5e-2, (b, L)
+
+
+# KV heads that the eight XCDs share 1, 2, 4 and 8 ways, and that they have several of; groups of 1, 2, 3, 8 and 16
+@pytest.mark.parametrize("hq,hkv,hd", [(3, 1, 64), (16, 1, 64), (4, 2, 64), (9, 3, 64), (32, 4, 64), (8, 8, 64), (24, 12, 64),
+                                       (2, 1, 128), (6, 2, 128), (5, 5, 128), (8, 4, 128), (16, 16, 128)])
+def test_edges_of_key_tiles_and_halves(hq, hkv, hd):
+    layer = LayerConfig(d_model=64, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, ffn_dim=64, rope_theta=500000.0, dtype="bf16")
+    lens = [1, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 160, 191, 193, 257, 320, 449]
+    check(layer, lens, rnd((sum(lens), layer.Dq + 2 * layer.Dkv), torch.bfloat16, 21))
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("step", [32, 64, 200])
+def test_reference_that_moves(hd, step):
+    """Scores that outgrow the reference by 2^9 every `step` keys, in the rotary pair that positions up to a thousand leave
+    practically unrotated: whichever half of a tile it falls into, accumulators and the next half's scores follow."""
+    layer = LayerConfig(d_model=64, n_q_heads=4, n_kv_heads=2, head_dim=hd, ffn_dim=64, rope_theta=500000.0, dtype="bf16")
+    lens = [1, 70, 500, 777]
+    qkv = rnd((sum(lens), layer.Dq + 2 * layer.Dkv), torch.bfloat16, 22)
+    q, k = qkv[:, :layer.Dq].view(-1, 4, hd), qkv[:, layer.Dq:layer.Dq + layer.Dkv].view(-1, 2, hd)
+    q[:, :, hd // 2 - 1], q[:, :, hd - 1], k[:, :, hd - 1] = 16.0, 0.0, 0.0
+    j = torch.cat([torch.arange(n) for n in lens]).to(qkv.device)
+    k[:, :, hd // 2 - 1] = ((j // step) * (9.0 / (16.0 * 1.4426950408889634 / np.sqrt(hd)))).to(qkv.dtype)[:, None]
+    check(layer, lens, qkv)
