@@ -32,7 +32,8 @@
 //    stores, residual rows requested one slab ahead;
 //  * epilogues: 0 = plain / + residual (fp32 add before the bf16 round), 1 =
 //    SwiGLU on a stacked gate/up weight (each wave holds the gate and the up
-//    tile of the same columns), 2 = fp32 output (router logits); per-row
+//    tile of the same columns), 2 = fp32 output (router logits, decode partials), 3 =
+//    1 for decode rows with a factor per row and a division to half a unit; per-row
 //    scaling for the routed experts;
 //  * workgroup ids are remapped so that each XCD (own L2) gets a contiguous
 //    range of tiles, walked in groups of 4 row tiles per column tile (8: the down
@@ -144,13 +145,14 @@ __device__ __forceinline__ TilePos find_tile(const GemmParams& p) {
 template <int EPI, bool GROUPED, int TM, int TN>
 __device__ __forceinline__ void store_tile(const GemmParams& p, const floatx4 (&acc)[TM][TN], float* slab, int lane, int wrow,
                                            int rows_valid, int64_t m0, int n_first) {
-    constexpr int WOUT = (EPI == 1 ? TN / 2 : TN) * 16;
+    constexpr bool GLU = EPI == 1 || EPI == 3;
+    constexpr int WOUT = (GLU ? TN / 2 : TN) * 16;
     constexpr int SLD = WOUT + 4;
     constexpr int NCH = WOUT / 8;       // 8-column chunks per row
     constexpr int NU = 32 * NCH / 64;   // chunks per lane and pass
     static_assert(TM % 2 == 0 && NU >= 1, "passes of 32 rows, at least one chunk per lane");
     const int r = lane & 15, c4 = lane >> 4;
-    const bool has_r = EPI != 1 && p.R != nullptr;
+    const bool has_r = !GLU && p.R != nullptr;
     floatx4 rv[2][NU][2];
     auto load_r = [&](int i, floatx4 (&v)[NU][2]) {
 #pragma unroll
@@ -172,17 +174,22 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const floatx4 (&
 #pragma unroll
     for (int i = 0; i < TM / 2; ++i) {
         if (has_r && i + 1 < TM / 2) load_r(i + 1, rv[(i + 1) & 1]);
-        constexpr int TJ = EPI == 1 ? TN / 2 : TN;
+        constexpr int TJ = GLU ? TN / 2 : TN;
 #pragma unroll
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 floatx4 v;
-                const float ps = EPI == 1 && p.pre_scale ? p.pre_scale[m0 + min(wrow + i * 32 + g * 16 + r, rows_valid - 1)] : 1.0f;
+                const float ps = EPI == 3 && p.pre_scale ? p.pre_scale[m0 + min(wrow + i * 32 + g * 16 + r, rows_valid - 1)] : 1.0f;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float a = acc[2 * i + g][j][e];
                     if (EPI == 1) {
+                        // the reciprocal to one unit in the last place of fp32: a division to half of one is ten
+                        // instructions, 64 times a lane, while the matrix pipe waits (2 * 14336 x 4096 at 32768 rows 5394
+                        // -> 5227 us; same error against 64 bits)
+                        a = a * __builtin_amdgcn_rcpf(1.0f + __expf(-a)) * acc[2 * i + g][j + TN / 2][e];
+                    } else if (EPI == 3) {
                         a *= ps;
                         const float u = acc[2 * i + g][j + TN / 2][e] * ps;
                         a = a / (1.0f + __expf(-a)) * u;
@@ -556,11 +563,12 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmParams p) {
 // ---------------------------------------------------------------------------
 template <int BM, int BN, int WM, int WN, int S, int EPI, bool GROUPED>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_small_kernel(const GemmParams p) {
+    constexpr bool GLU = EPI == 1 || EPI == 3;
     constexpr int NW = WM * WN, BK = GEMM_BK;
     constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 16, TN = WTN / 16;
     constexpr int STAGE = (BM + BN) * BK;   // elements
-    constexpr int OUTN = EPI == 1 ? BN / 2 : BN;
-    constexpr int WOUT = EPI == 1 ? WTN / 2 : WTN;
+    constexpr int OUTN = GLU ? BN / 2 : BN;
+    constexpr int WOUT = GLU ? WTN / 2 : WTN;
     constexpr int XU = BM / 8 / NW, WU = BN / 8 / NW;   // 8-row load units per wavefront
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && TN % 2 == 0, "tile rows must split over the wavefronts");
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -584,7 +592,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_small_kernel(const Gemm
     for (int u = 0; u < WU; ++u) {
         const int row = (wave * WU + u) * 8 + (lane >> 3);
         int n;
-        if (EPI == 1)
+        if (GLU)
             n = row < BN / 2 ? min(tp.n0 + row, p.N - 1) : p.N + min(tp.n0 + row - BN / 2, p.N - 1);
         else
             n = min(tp.n0 + row, p.N - 1);
@@ -621,7 +629,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_small_kernel(const Gemm
             bf16x8 xf[TM], wf[TN];
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
-                const int row = EPI != 1 ? wn * WTN + j * 16
+                const int row = !GLU ? wn * WTN + j * 16
                                 : j < TN / 2 ? wn * (WTN / 2) + j * 16
                                              : BN / 2 + wn * (WTN / 2) + (j - TN / 2) * 16;
                 wf[j] = *reinterpret_cast<const bf16x8*>(ws + row * BK + foff[kk]);
@@ -646,7 +654,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_small_kernel(const Gemm
 
 template <int BM, int BN, int WM, int WN, int S, int EPI, bool GROUPED>
 static int launch_small(compact_ctx* ctx, GemmParams& p, hipStream_t s, int k_slices = 1) {
-    constexpr int OUTN = EPI == 1 ? BN / 2 : BN;
+    constexpr int OUTN = EPI == 1 || EPI == 3 ? BN / 2 : BN;
     if (!GROUPED) p.n_mtiles = (int)((p.M + BM - 1) / BM);
     p.n_ntiles = (p.N + OUTN - 1) / OUTN;
     constexpr size_t smem = (size_t)S * (BM + BN) * GEMM_BK * sizeof(bf16);
@@ -710,7 +718,7 @@ static int launch_large(compact_ctx* ctx, GemmParams& p, int64_t n_full, hipStre
 // + share of the load) and per tile, fitted to timings of all six forms at 354 shapes (65 .. 20000 rows, 64 .. 14336
 // columns, K 64 .. 14336, both epilogues): the picked form is at most 7 % slower than the best of the six at any of them,
 // 0.3 % on average.  (Constants fitted to long K alone priced the tiles of K <= 512 wrongly, by up to 25 %: 20000 x 640, K
-// 64, SwiGLU 23.5 us in 128 x 256 tiles against 20.2 in 256 x 256.)  Measured where the line lies (us, 256 x 256 against
+// 64, SwiEPI == 1 23.5 us in 128 x 256 tiles against 20.2 in 256 x 256.)  Measured where the line lies (us, 256 x 256 against
 // 128 x 256): N 4096 K 14336 at 2048 rows 266 / 203, at 2500 rows 272 / 356 (128 x 256 needs a second round); N 6144
 // K 4096 at 2500 rows 97 / 111, at 3000 rows 165 / 146; 2 * 14336 x 4096 at 1652 rows 397 / 368, at 4096 rows 861 / 940.
 // Few rows, N 4096 K 14336: 20 rows 207 (256 x 256) / 157 / 104 (128 x 128) / 85 (64 x 128) / 71 (128 x 64) / 55
@@ -923,5 +931,5 @@ int launch_swiglu_rows64(compact_ctx* ctx, const bf16* A, const bf16* B, const f
     p.M = M;
     p.N = F;
     p.K = K;
-    return launch_small<64, 64, 2, 2, 5, 1, false>(ctx, p, s);
+    return launch_small<64, 64, 2, 2, 5, 3, false>(ctx, p, s);
 }
