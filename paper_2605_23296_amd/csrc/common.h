@@ -127,6 +127,16 @@ __device__ __forceinline__ void load16_to_lds(const void* gptr, void* lds_base) 
     (void)lds_base;
 #endif
 }
+// the same with 4 bytes a lane
+__device__ __forceinline__ void load4_to_lds(const void* gptr, void* lds_base) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gptr,
+                                     (__attribute__((address_space(3))) void*)lds_base, 4, 0, 0);
+#else
+    (void)gptr;
+    (void)lds_base;
+#endif
+}
 __device__ __forceinline__ void wait_all_memory() {
 #if defined(__HIP_DEVICE_COMPILE__)
     __builtin_amdgcn_s_waitcnt(0);

@@ -59,6 +59,7 @@ struct GemmParams {
     int N;  // output columns (F for the SwiGLU epilogue, whose W has 2N rows)
     int K;
     int n_mtiles, n_ntiles;
+    int touch;   // 256 x 256 kernel, plain product in halves: weight lines are touched ahead
     int n_full;  // 256 x 256 kernel, plain product: workgroups that take a whole tile (the others take halves)
     int r_f32;  // the residual R is fp32 rather than bf16
     const float* pre_scale;   // SwiGLU: factor of every row's products before the silu (null = 1)
@@ -397,8 +398,16 @@ __device__ __forceinline__ void tile_256(const GemmParams& p, const TilePos& tp,
 // W1); the ring holds three k-tiles (nine slots, 144 KB).  A phase requests three of the six 8-row pieces a wavefront
 // owns of a k-tile; 11 or 12 of them may still fly when the next phase's operands must be there.
 // ---------------------------------------------------------------------------
-template <int EPI, bool GROUPED>
-__device__ __forceinline__ void tile_128(const GemmParams& p, const TilePos& tp, char* smem) {
+// TOUCH: weight lines are touched ahead of the ring, this workgroup's share among eight of the same columns.  A CU has some 50
+// KB of loads in flight, so weights that come from HBM, 900 ns away, limit it to 27 bytes a clock, a k-tile to 0.85 us, whatever
+// the ring holds; all eight workgroups ask for the same lines at the same time and wait alike.  With an eighth of
+// the lines touched by each of them four k-tiles ahead, the loads find them in the L2: K 14336, N 4096, weights in HBM, 1100
+// rows 179 -> 148 us, 1652 rows 184 -> 155, 2048 rows 190 -> 170; N 2880 K 4096 at 1652 rows 51 -> 45 (eight k-tiles ahead 1 %
+// slower, sixteen 3 %; with four sharers at 700 rows 48 -> 50; in calls of several rounds, whose later ones find
+// the weights, N 4096 K 14336 at 4100 rows 442 -> 451; N 1536 K 1024 13.4 -> 14.4).  The whole prefill of 1652 rows 667 ->
+// 652 us, where the down projection's epilogue reads and writes as well.
+template <int EPI, bool GROUPED, bool TOUCH>
+__device__ __forceinline__ void tile_128(const GemmParams& p, const TilePos& tp, char* smem, int share) {
     constexpr int WN = 4, BK = GEMM_BK;
     constexpr int WTM = 64, WTN = 64, TM = WTM / 16, TN = WTN / 16;
     constexpr int HT = 128 * BK;
@@ -451,6 +460,17 @@ __device__ __forceinline__ void tile_128(const GemmParams& p, const TilePos& tp,
             for (int nt = 0; nt < 2; ++nt)
                 f[nt][kk] = *reinterpret_cast<const bf16x8*>(ws + (buf * 3 + 2 * j) * HT + nt * 16 * BK + foff[kk]);
     };
+    // wavefront `share` touches a line of each of 64 of the tile's weight rows, of every other k-tile
+    const bf16* tsrc = nullptr;
+    if (TOUCH) {
+        const int row = (wave & 3) * 64 + lane;
+        const int n = EPI == 1 ? min(n0 + (row & 127), p.N - 1) + (row >> 7) * p.N : min(n0 + row, p.N - 1);
+        tsrc = tp.W + (int64_t)n * p.K;
+    }
+    auto touch = [&](int kt) __attribute__((always_inline)) {
+        if (TOUCH && wave == share && (kt & 1) == wave >> 2 && kt < nk)
+            load4_to_lds(tsrc + kt * BK, smem + 9 * HT * sizeof(bf16) + wave * 256);
+    };
     bf16x8 xf[4][2], w0[2][2], w1[2][2];
     auto mfmas = [&](auto jtag, const bf16x8 (&wf)[2][2]) {
         constexpr int j = decltype(jtag)::value;
@@ -473,6 +493,7 @@ __device__ __forceinline__ void tile_128(const GemmParams& p, const TilePos& tp,
         gload(2, 0, kt + 2, b2);
         gload(2, 1, kt + 2, b2);
         gload(0, 0, kt + 3, b0);
+        touch(kt + 4);
         ring_barrier<11>();
         mfmas(std::integral_constant<int, 0>{}, w0);
         read_w(1, b0, w1);
@@ -526,7 +547,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmParams p) {
         if (tp.rows_valid > 128)
             tile_256<EPI, true>(p, tp, smem);
         else
-            tile_128<EPI, true>(p, tp, smem);
+            tile_128<EPI, true, false>(p, tp, smem, 0);
     } else {
         const int i = blockIdx.x;
         int tm, tn;
@@ -541,16 +562,21 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(const GemmParams p) {
         } else {
             const int h = xcd_order(i - p.n_full, gridDim.x - p.n_full);
             const int slot = p.n_full + h / 2, slots = p.n_mtiles * p.n_ntiles;
+            int share = -1;
             if (slot < slots) {
                 tile_at<4>(slot, p.n_mtiles, p.n_ntiles, tm, tn);
                 tp.m0 = (int64_t)tm * 256 + (h & 1) * 128;
+                if (p.touch && tm / 4 * 4 + 4 <= p.n_mtiles) share = tm % 4 * 2 + (h & 1);
             } else {
                 tn = h - 2 * (slots - p.n_full);
                 tp.m0 = (int64_t)p.n_mtiles * 256;
             }
             tp.n0 = tn * OUTN;
             tp.rows_valid = (int)min((int64_t)128, p.M - tp.m0);
-            tile_128<EPI, false>(p, tp, smem);
+            if (share >= 0)
+                tile_128<EPI, false, true>(p, tp, smem, share);
+            else
+                tile_128<EPI, false, false>(p, tp, smem, 0);
         }
     }
 }
@@ -685,9 +711,9 @@ static LargeTiles large_tiles(int64_t M, int n_ntiles) {
 
 // n_full (plain products): slots of 256 x 256 that are whole tiles, see the kernel
 template <int EPI, bool GROUPED>
-static int launch_large(compact_ctx* ctx, GemmParams& p, int64_t n_full, hipStream_t s) {
+static int launch_large(compact_ctx* ctx, GemmParams& p, int64_t n_full, int n_cus, hipStream_t s) {
     constexpr int OUTN = EPI == 1 ? 128 : 256;
-    constexpr size_t smem = (size_t)9 * 128 * GEMM_BK * sizeof(bf16);   // the larger ring; the epilogue's slabs fit in
+    constexpr size_t smem = (size_t)9 * 128 * GEMM_BK * sizeof(bf16) + 2048;   // the larger ring; the epilogue's slabs fit in
     static_assert((size_t)8 * 32 * (OUTN / 4 + 4) * sizeof(float) <= smem, "the epilogue's slabs fit the ring");
     auto kern = gemm_bf16_kernel<EPI, GROUPED>;
     static bool attr_set = false;
@@ -704,6 +730,7 @@ static int launch_large(compact_ctx* ctx, GemmParams& p, int64_t n_full, hipStre
         p.n_mtiles = (int)(lt.slots / p.n_ntiles);
         p.n_full = (int)std::min(n_full, lt.slots);
         wgs = p.n_full + 2 * (lt.slots - p.n_full) + lt.bottom;
+        p.touch = p.n_full == 0 && wgs <= n_cus && p.K >= 2048;   // see tile_128
     }
     if (wgs == 0) return COMPACT_OK;
     kern<<<dim3((unsigned)wgs), 512, smem, s>>>(p);
@@ -807,10 +834,10 @@ int gemm_bf16_group_mtile(int64_t rows, int n_experts, int F, int d, int n_cus) 
 }
 
 template <int EPI, bool GROUPED>
-static int launch_form(compact_ctx* ctx, int form, int64_t n_full, GemmParams& p, hipStream_t s) {
+static int launch_form(compact_ctx* ctx, int form, int64_t n_full, GemmParams& p, int n_cus, hipStream_t s) {
     switch (form) {
-        case TILE_256: return launch_large<EPI, GROUPED>(ctx, p, n_full, s);
-        case TILE_128: return launch_large<EPI, GROUPED>(ctx, p, 0, s);
+        case TILE_256: return launch_large<EPI, GROUPED>(ctx, p, n_full, n_cus, s);
+        case TILE_128: return launch_large<EPI, GROUPED>(ctx, p, 0, n_cus, s);
         case TILE_64_128: return launch_small<64, 128, 2, 4, 6, EPI, GROUPED>(ctx, p, s);
         default: break;
     }
@@ -845,13 +872,13 @@ int launch_gemm_bf16(compact_ctx* ctx, const bf16* A, const bf16* B, const void*
         p.n_mtiles = grouped->n_mtiles;
         const int form = grouped->mtile == 256 ? TILE_256 : grouped->mtile == 128 ? TILE_128 : TILE_64_128;
         if (tile_forms[form].bm != grouped->mtile) return set_err(ctx, COMPACT_EINVAL, "no grouped GEMM of this row-tile height");
-        return epilogue == 1 ? launch_form<1, true>(ctx, form, 0, p, s) : launch_form<0, true>(ctx, form, 0, p, s);
+        return epilogue == 1 ? launch_form<1, true>(ctx, form, 0, p, n_cus, s) : launch_form<0, true>(ctx, form, 0, p, n_cus, s);
     }
     int64_t n_full = 0;
     const int form = pick_tile(M, N, K, epilogue, n_cus, &n_full);
-    if (epilogue == 1) return launch_form<1, false>(ctx, form, n_full, p, s);
-    if (epilogue == 2) return launch_form<2, false>(ctx, form, n_full, p, s);
-    return launch_form<0, false>(ctx, form, n_full, p, s);
+    if (epilogue == 1) return launch_form<1, false>(ctx, form, n_full, p, n_cus, s);
+    if (epilogue == 2) return launch_form<2, false>(ctx, form, n_full, p, n_cus, s);
+    return launch_form<0, false>(ctx, form, n_full, p, n_cus, s);
 }
 
 // For the tests, not part of compact.h: the product in tile form `form` (TILE_FORMS: whole tiles and halves mixed, as many slots
@@ -883,7 +910,7 @@ extern "C" int compact_test_gemm_form(compact_ctx* ctx, int32_t form, const void
         n_full /= 2;
     }
     hipStream_t s = (hipStream_t)hip_stream;
-    return epilogue == 1 ? launch_form<1, false>(ctx, form, n_full, p, s) : launch_form<0, false>(ctx, form, n_full, p, s);
+    return epilogue == 1 ? launch_form<1, false>(ctx, form, n_full, p, n_cus, s) : launch_form<0, false>(ctx, form, n_full, p, n_cus, s);
 }
 extern "C" int compact_test_group_mtile(compact_ctx* ctx, int64_t rows, int32_t n_experts, int32_t F, int32_t d, int32_t* mtile) {
     int n_cus = 0;

@@ -94,6 +94,24 @@ def test_whole_and_half_tiles_in_one_launch(M, N, K, epi, res):
         assert torch.equal(c, first)
 
 
+# half tiles in one round, K of 2048 and more: eight workgroups share out the weight lines that are touched ahead; groups of four
+# 256-row tiles with and without a rest, K whose last k-tiles nobody touches, columns past the last tile
+@pytest.mark.parametrize("M,N,K,epi", [(1024, 1000, 2048, 0), (1153, 2056, 2112, 0), (1300, 264, 2240, 1), (2048, 520, 4160, 1)])
+def test_half_tiles_that_touch_weight_lines_ahead(M, N, K, epi):
+    lay = B.Layer(DENSE, None)
+    a, b = rnd((M, K), torch.bfloat16, 3), rnd(((1 + epi) * N, K), torch.bfloat16, 4, std=0.05)
+    out = []
+    for form in (1, 5):   # 128 x 256, 64 x 64
+        out.append(torch.full((M + 1, N), 7.0, dtype=torch.bfloat16, device="cuda"))
+        gemm_form(lay, form, a, b, None, out[-1][:M], epi)
+    torch.cuda.synchronize()
+    rows = [0, 127, 128, 600, 1023, M - 1]
+    A, Bm = to_numpy_f64(a[rows]), to_numpy_f64(b)
+    ref = O.silu(O.linear(A, Bm[:N])) * O.linear(A, Bm[N:]) if epi else O.linear(A, Bm)
+    assert rel_err(to_numpy_f64(out[0][rows]), ref) < 1e-2
+    assert torch.equal(out[0], out[1]) and bool((out[0][M] == 7.0).all())
+
+
 def test_the_rule_picks_every_tile_form():
     """Calls at which each form is the cheapest by the rule: a retuned table that drops one shows up here."""
     lay = B.Layer(DENSE, None)
