@@ -82,18 +82,24 @@ int launch_mxfp4_dequant(compact_ctx* ctx, const uint8_t* codes, const uint8_t* 
 // ---------------------------------------------------------------------------
 // Per-expert weight streaming for routed decode rows, 4-bit weights:
 // partials[slice][sorted row][N] = X[rows of expert e, kslice] W_e[N, kslice]^T.
-// grid (k-slices, N / 64, experts); 4 wavefronts of 16 weight rows each.  X, like the scales, lands in LDS directly, its source
-// rows looked up before the weights are asked for (16 x 8192, a step: 252 -> 247 us when only the rows that are there were staged).
+// One workgroup per k-slice, 64 weight rows and expert tile; 4 wavefronts of 16 weight rows each.  X, like the scales, lands in
+// LDS directly, its source rows looked up before the weights are asked for (16 x 8192, a step: 252 -> 247 us when only the rows
+// that are there were staged).  A row's codes are K / 2 and its scales K / 32 bytes, so the slices share 128-byte lines (K 2880:
+// 512 of 1440 bytes touch five lines, and the scales of all three slices lie in the same ones): the slices of the same rows run
+// on one XCD (slice_item), whose L2 asks for a line once.  Bound by HBM: gate/up + down of 16 rows of the 120B-shaped layer
+// (640 MB) 120 -> 113 us, a step 228 -> 221; d 1600, F 1088, 64 experts, 16 rows 88 -> 84; K a multiple of 256 as before.  Four
+// neighbouring lanes on 64 bytes of a row gain nothing (56.5 and 57.6 us a launch), 8 or 16 wavefronts a workgroup lose (60 -> 61, 64.5).
 // ---------------------------------------------------------------------------
 struct MxGroup {
-    const int32_t* expert_list;  // [gridDim.z] experts to run, -1 = none (null: expert = blockIdx.z)
-    const int32_t* tile_row0;    // [gridDim.z] first sorted row of the grid slice's tile (null: the expert's first row)
-    const int32_t* tile_rows;    // [gridDim.z] its rows, at most 16 (null: all of the expert's rows)
+    const int32_t* expert_list;  // [n_tiles] experts to run, -1 = none (null: tile e = expert e)
+    const int32_t* tile_row0;    // [n_tiles] first sorted row of the tile (null: the expert's first row)
+    const int32_t* tile_rows;    // [n_tiles] its rows, at most 16 (null: all of the expert's rows)
     const int32_t* offsets;    // [E + 1] rows of every expert in the expert-sorted order
     const int32_t* a_gather;   // [total_rows] source row of X, or null (X already sorted)
     int64_t q_expert_stride;   // bytes between consecutive experts' codes
     int64_t s_expert_stride;   // bytes between consecutive experts' scales
     int total_rows;
+    int n_tiles;               // entries of the list, or experts
 };
 
 __global__ __launch_bounds__(256) void gemm_skinny_mxfp4_kernel(const bf16* __restrict__ X, const uint8_t* __restrict__ Wq,
@@ -104,18 +110,20 @@ __global__ __launch_bounds__(256) void gemm_skinny_mxfp4_kernel(const bf16* __re
     bf16* xs = reinterpret_cast<bf16*>(smem);  // [16][LDX]
     const int lane = threadIdx.x & 63, wave = wave_index();
     const int r = lane & 15, c = lane >> 4;
-    const int e = grp.expert_list ? grp.expert_list[blockIdx.z] : (int)blockIdx.z;
+    const SliceItem it = slice_item(blockIdx.x, (K + MX_KSLICE - 1) / MX_KSLICE, (N + 63) / 64);
+    const int slice = it.slice, y = it.col, z = it.tile;
+    if (z >= grp.n_tiles) return;
+    const int e = grp.expert_list ? grp.expert_list[z] : z;
     if (e < 0) return;
-    const int row_base = grp.tile_row0 ? grp.tile_row0[blockIdx.z] : grp.offsets[e];
-    const int M = min(grp.tile_rows ? grp.tile_rows[blockIdx.z] : grp.offsets[e + 1] - row_base, 16);
+    const int row_base = grp.tile_row0 ? grp.tile_row0[z] : grp.offsets[e];
+    const int M = min(grp.tile_rows ? grp.tile_rows[z] : grp.offsets[e + 1] - row_base, 16);
     if (M <= 0) return;   // nobody was routed to this expert
     Wq += (size_t)e * grp.q_expert_stride;
     Ws += (size_t)e * grp.s_expert_stride;
-    const int slice = blockIdx.x;
     const int k0 = slice * MX_KSLICE;
     const int klen = min(MX_KSLICE, K - k0);
     const int nblk = klen / MX_BLOCK;            // blocks of this slice
-    const int n0 = (blockIdx.y * 4 + wave) * 16;
+    const int n0 = (y * 4 + wave) * 16;
     const bool active = n0 < N;
     uint8_t* const scales = reinterpret_cast<uint8_t*>(smem) + 16 * LDX * sizeof(bf16) + wave * MX_WAVE_BYTES;   // [16 rows][32]
 
@@ -198,10 +206,12 @@ int launch_gemm_skinny_grouped_mxfp4(compact_ctx* ctx, const bf16* X, const int3
                                      int n_listed, const int32_t* tile_row0, const int32_t* tile_rows) {
     if (N % 16 != 0 || K % MX_BLOCK != 0) return set_err(ctx, COMPACT_ESHAPE, "4-bit weight streaming needs N % 16 == 0 and K % 32 == 0");
     if (ks != mxfp4_ksplit(K)) return set_err(ctx, COMPACT_EINVAL, "unexpected K split");
-    MxGroup g{expert_list, tile_row0, tile_rows, offsets, a_gather, (int64_t)N * (K / 2), (int64_t)N * (K / MX_BLOCK), total_rows};
-    dim3 grid(ks, (N + 63) / 64, expert_list ? n_listed : n_experts);
+    const int n_tiles = expert_list ? n_listed : n_experts;
+    MxGroup g{expert_list, tile_row0, tile_rows, offsets, a_gather, (int64_t)N * (K / 2), (int64_t)N * (K / MX_BLOCK), total_rows, n_tiles};
+    const int64_t grid = slice_items(ks, (N + 63) / 64, n_tiles);
+    if (grid >= 1 << 24) return set_err(ctx, COMPACT_ESHAPE, "too many workgroups for 4-bit weight streaming");
     constexpr int smem = 16 * (MX_KSLICE + 8) * (int)sizeof(bf16) + 4 * MX_WAVE_BYTES;
-    gemm_skinny_mxfp4_kernel<<<grid, 256, smem, s>>>(X, Wq, Ws, partials, N, K, g);
+    gemm_skinny_mxfp4_kernel<<<(unsigned)grid, 256, smem, s>>>(X, Wq, Ws, partials, N, K, g);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }

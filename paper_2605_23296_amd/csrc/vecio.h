@@ -48,6 +48,18 @@ __device__ __forceinline__ int wave_index() {
 #endif
 }
 
+// Grouped weight streaming: which k-slice of which column group (of which expert tile) a workgroup of a flat grid takes.  The
+// slices of a group are eight workgroups apart, so that they run on one XCD at about the same time (workgroups are dealt to the
+// eight XCDs in turn): workgroup 8 (ks a + slice) + x takes group 8a + x.  `tile` may lie past the last one.
+struct SliceItem {
+    int slice, col, tile;
+};
+__device__ __forceinline__ SliceItem slice_item(unsigned wg, unsigned ks, unsigned n_cols) {
+    const unsigned i = wg >> 3, g = i / ks * 8 + (wg & 7);
+    return SliceItem{(int)(i % ks), (int)(g % n_cols), (int)(g / n_cols)};
+}
+inline int64_t slice_items(int ks, int n_cols, int n_tiles) { return ((int64_t)n_cols * n_tiles + 7) / 8 * 8 * ks; }
+
 // The rotation of one pair, shared with the decode epilogue.  The contraction is written out: left to the compiler it
 // changes with the code around it, and a row rotated in a prefill would no longer have the bits of the same row rotated
 // in a decode step.
