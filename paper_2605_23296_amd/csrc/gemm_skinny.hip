@@ -13,6 +13,7 @@
 //  * the K-split depends on K alone, never on the number of activation rows,
 //    so a block's result does not depend on the batch it is decoded in.
 #include "common.h"
+#include "vecio.h"
 
 #define SKINNY_KSLICE 512
 #define SKINNY_STEPS (SKINNY_KSLICE / 32)
@@ -23,22 +24,24 @@ int skinny_ksplit(int M, int N, int K) {
     return (K + SKINNY_KSLICE - 1) / SKINNY_KSLICE;
 }
 
-// GROUPED: blockIdx.z is an expert; its rows are rows offsets[e] .. offsets[e+1]-1
+// GROUPED: the grid is flat, blockIdx.x = k-slice, 64 weight rows and expert (slice_item);
+// an expert's rows are rows offsets[e] .. offsets[e+1]-1
 // of the expert-sorted order (at most MT*16 of them), read from X through
 // a_gather (null: X is already in sorted order), multiplied with that expert's
 // weight matrix, and the partials keep the sorted order: P[slice][sorted row][N].
 // Experts nobody was routed to leave at once.  With a tile map (expert_list =
 // the map's experts, tile_row0 / tile_rows its row ranges, tiles of at most MT*16
-// rows) blockIdx.z is a tile: an expert with more rows than a tile holds is
-// streamed once per tile.
+// rows) it is a tile in the expert's place: an expert with more rows than a tile
+// holds is streamed once per tile.
 struct SkinnyGroup {
-    const int32_t* expert_list;  // [gridDim.z] experts to run, -1 = none (null: expert = blockIdx.z)
-    const int32_t* tile_row0;    // [gridDim.z] first sorted row of the tile (null: the expert's first row)
-    const int32_t* tile_rows;    // [gridDim.z] rows of the tile (null: all of the expert's rows)
+    const int32_t* expert_list;  // [n_tiles] experts to run, -1 = none (null: tile e = expert e)
+    const int32_t* tile_row0;    // [n_tiles] first sorted row of the tile (null: the expert's first row)
+    const int32_t* tile_rows;    // [n_tiles] rows of the tile (null: all of the expert's rows)
     const int32_t* offsets;   // [E + 1]
     const int32_t* a_gather;  // [total_rows] or null
     int64_t w_expert_stride;  // elements
     int total_rows;
+    int n_tiles;              // entries of the list, or experts
 };
 
 // Front half of an RMSNorm folded into the activation staging (null g: off): the
@@ -65,25 +68,33 @@ __global__ __launch_bounds__(WAVES * 64, RING < SKINNY_STEPS ? 2 : 1) void gemm_
     bf16* xs = reinterpret_cast<bf16*>(smem);  // [MT*16][LDX]
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
-    int row_base = 0, p_rows = M;
+    int row_base = 0, p_rows = M, slice = blockIdx.x, col = blockIdx.y;
     if (GROUPED) {
-        const int e = grp.expert_list ? grp.expert_list[blockIdx.z] : (int)blockIdx.z;
+        const SliceItem it = slice_item(blockIdx.x, (K + SKINNY_KSLICE - 1) / SKINNY_KSLICE, (N + WAVES * 16 - 1) / (WAVES * 16));
+        slice = it.slice;
+        col = it.col;
+        if (it.tile >= grp.n_tiles) return;
+        const int e = grp.expert_list ? grp.expert_list[it.tile] : it.tile;
         if (e < 0) return;
-        row_base = grp.tile_row0 ? grp.tile_row0[blockIdx.z] : grp.offsets[e];
-        M = min(grp.tile_rows ? grp.tile_rows[blockIdx.z] : grp.offsets[e + 1] - row_base, MT * 16);
+        row_base = grp.tile_row0 ? grp.tile_row0[it.tile] : grp.offsets[e];
+        M = min(grp.tile_rows ? grp.tile_rows[it.tile] : grp.offsets[e + 1] - row_base, MT * 16);
         if (M <= 0) return;
         W += (size_t)e * grp.w_expert_stride;
         p_rows = grp.total_rows;
     }
-    // the K-slice is the fastest grid index: workgroups that run together read
-    // neighbouring slices of the same weight rows (whole DRAM pages), not the same
-    // slice of far-apart rows
-    const int slice = blockIdx.x;
+    // the K-slices of the same weight rows are neighbours in the grid: workgroups that
+    // run together read whole DRAM pages, not the same slice of far-apart rows.  Grouped
+    // (a launch is many rounds of workgroups), they also run on one XCD, where some layers
+    // gain and others stay (1 % either way): whole steps of 16 rows, slices in turn to the
+    // XCDs -> together: d 2880, F 2880, 128 experts 479 -> 466 us; d 2048, F 1024, 16 experts
+    // 79 -> 76; d 2048, F 2048 297 -> 288; d 4096, 2112 and 1600 as before.
+    // Four neighbouring lanes on 64 bytes of a row, moved to operand order by cross-lane
+    // reads, gained another 1-2 % there and lost 1-4 % where the experts fit the caches.
     const int k0 = slice * SKINNY_KSLICE;
     const int klen = min(SKINNY_KSLICE, K - k0);
     const int nsteps = klen / 32;
     const int r = lane & 15, c = lane >> 4;
-    const int n0 = (blockIdx.y * WAVES + wave) * 16;
+    const int n0 = (col * WAVES + wave) * 16;
     const bool active = n0 < N;
 
     // the weight stream goes first: everything below overlaps with it
@@ -252,10 +263,11 @@ int launch_gemm_skinny_grouped(compact_ctx* ctx, const bf16* X, const int32_t* a
                                const int32_t* tile_rows) {
     if (N % 16 != 0 || K % 64 != 0) return set_err(ctx, COMPACT_ESHAPE, "weight-streaming GEMM needs N % 16 == 0 and K % 64 == 0");
     if (ks != skinny_ksplit(1, N, K)) return set_err(ctx, COMPACT_EINVAL, "unexpected K split");
-    SkinnyGroup g{expert_list, tile_row0, tile_rows, offsets, a_gather, w_expert_stride, total_rows};
-    dim3 grid(ks, (N + 63) / 64, expert_list ? n_listed : n_experts);
+    SkinnyGroup g{expert_list, tile_row0, tile_rows, offsets, a_gather, w_expert_stride, total_rows, expert_list ? n_listed : n_experts};
+    const int64_t grid = slice_items(ks, (N + 63) / 64, g.n_tiles);
+    if (grid >= 1 << 24) return set_err(ctx, COMPACT_ESHAPE, "too many workgroups for weight streaming");
     const size_t smem = (size_t)16 * (SKINNY_KSLICE + 8) * sizeof(bf16);
-    gemm_skinny_kernel<1, true, 4><<<grid, 256, smem, s>>>(X, W, partials, 0, N, K, g, SkinnyNormIn{});
+    gemm_skinny_kernel<1, true, 4><<<(unsigned)grid, 256, smem, s>>>(X, W, partials, 0, N, K, g, SkinnyNormIn{});
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
