@@ -177,6 +177,19 @@ def test_dense_decode_with_17_to_64_blocks(n_blocks):
         assert vec_rel_err(g["y_decode"][:, 0], full["y_decode"][:, b]) < 4e-3
 
 
+@pytest.mark.parametrize("d_model,ffn_dim", [(64, 64), (320, 448), (384, 2112), (1088, 192)])
+def test_gate_up_of_17_to_32_rows_has_the_bits_of_more(d_model, ffn_dim):
+    """Up to 32 rows the gate/up projection's tiles are 32 rows high, beyond it 64, over the same sums: the FFN widths are on and
+    off their 32 columns, one, five, six and seventeen k-tiles against a ring of six, and every block has the same bits in a step
+    of 17, 31 and 32 rows as in one of 33, which is checked against the oracle."""
+    layer = LayerConfig(d_model=d_model, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn_dim=ffn_dim, rope_theta=500000.0, dtype="bf16")
+    inp = make_inputs(Workload("gate_up_rows", layer, [1 + b % 5 for b in range(33)], 33, 2), gain_jitter=True)
+    full = check_dense(inp, sampled=False)
+    for n in (17, 31, 32):
+        few = H.gpu_forward(sub_batch(inp, range(n)))
+        assert np.array_equal(few["y_decode"], full["y_decode"][:, :n]), n
+
+
 @pytest.mark.parametrize("d_model,n_q_heads", [(1024, 4), (1024, 16), (2048, 16), (2048, 4)])
 def test_dense_steps_round_the_ffn_input_alike_in_both_families(d_model, n_q_heads):
     """A dense step of 17 blocks adds its projections in another order than a step of at most 16, and nothing more: the FFN
