@@ -3,8 +3,9 @@
 // contiguous along K.
 //
 // Shape of the kernel (gfx950):
-//  * one workgroup = one 256 x 256 output tile, 8 wavefronts of 128 x 64, K walked
-//    in tiles of 64 (a k-tile row is one 128-byte line);
+//  * one workgroup = one 256 x 256 output tile (or a half of one, see tile_128; both
+//    kinds share a launch), 8 wavefronts of 128 x 64, K walked in tiles of 64 (a
+//    k-tile row is one 128-byte line);
 //  * the k-tiles of X and W pass through LDS as half tiles of 128 rows (16 KB), a
 //    ring of eight of them (two k-tiles, 128 KB), filled by 16-byte direct-to-LDS
 //    global loads; a half tile is requested seven phases before the one that reads
@@ -39,9 +40,9 @@
 //    range of tiles, walked in groups of 4 row tiles per column tile (8: the down
 //    projection 3 % slower, the others equal; 16: 7 .. 13 % slower).
 // Bound: the power limit (the gate/up projection of that pass: matrix pipe 85 % busy at
-// 1.60 GHz; a probe whose loads all hit L2 ran at a clock 9 % higher).  8B-shaped layer, 32768 rows, before -> now:
-// QKV 1479 -> 1297 us, O 1045 -> 922, gate/up 6290 -> 5560 (1.38 PFLOP/s), down
-// 3418 -> 2890 (1.33); 1652 rows 104 -> 92, 91 -> 79, 419 -> 371, 304 -> 253.
+// 1.60 GHz; a probe whose loads all hit L2 ran at a clock 9 % higher).  8B-shaped layer, 32768
+// rows: QKV 1.08 ms, O 0.85, gate/up 5.28 (1.46 PFLOP/s), down 2.55 (1.51); in the form of lock steps 1.48, 1.05, 6.29
+// and 3.42.  1652 rows, where rounds of workgroups count: 85, 60, 280 and 192 us (104, 91, 419, 304).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -745,7 +746,7 @@ static int launch_large(compact_ctx* ctx, GemmParams& p, int64_t n_full, int n_c
 // + share of the load) and per tile, fitted to timings of all six forms at 354 shapes (65 .. 20000 rows, 64 .. 14336
 // columns, K 64 .. 14336, both epilogues): the picked form is at most 7 % slower than the best of the six at any of them,
 // 0.3 % on average.  (Constants fitted to long K alone priced the tiles of K <= 512 wrongly, by up to 25 %: 20000 x 640, K
-// 64, SwiEPI == 1 23.5 us in 128 x 256 tiles against 20.2 in 256 x 256.)  Measured where the line lies (us, 256 x 256 against
+// 64, SwiGLU 23.5 us in 128 x 256 tiles against 20.2 in 256 x 256.)  Measured where the line lies (us, 256 x 256 against
 // 128 x 256): N 4096 K 14336 at 2048 rows 266 / 203, at 2500 rows 272 / 356 (128 x 256 needs a second round); N 6144
 // K 4096 at 2500 rows 97 / 111, at 3000 rows 165 / 146; 2 * 14336 x 4096 at 1652 rows 397 / 368, at 4096 rows 861 / 940.
 // Few rows, N 4096 K 14336: 20 rows 207 (256 x 256) / 157 / 104 (128 x 128) / 85 (64 x 128) / 71 (128 x 64) / 55
