@@ -293,6 +293,11 @@ struct Plan {
         for (const BlockMeta& m : meta) most = std::max(most, m.prior + m.len);
         return most;
     }
+    int max_capacity() const {
+        int most = 0;
+        for (const BlockMeta& m : meta) most = std::max(most, m.capacity);
+        return most;
+    }
     // device views
     const BlockMeta* d_meta = nullptr;
     const TileItem* d_rope_tiles = nullptr;
@@ -478,8 +483,8 @@ static int run_attn_prefill(compact_ctx* ctx, const Plan& p, int n_blocks, const
                             void* o, hipStream_t s) {
     ProfileScope ps(ctx, COMPACT_K_ATTN_PREFILL, s);
     if (ctx->cfg.dtype == COMPACT_BF16)
-        return launch_attn_prefill_bf16(ctx, p.d_meta, p.d_q_tiles, (int)p.q_tiles.size(), (const bf16*)qkv, scaled,
-                                        (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)o, s);
+        return launch_attn_prefill_bf16(ctx, p.d_meta, p.max_capacity(), p.d_q_tiles, (int)p.q_tiles.size(), (const bf16*)qkv,
+                                        scaled, (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)o, s);
     return launch_attn_prefill_f32(ctx, p.d_meta, n_blocks, p.max_len, p.max_keys(), (const float*)qkv, (const float*)kv->d_k,
                                    (const float*)kv->d_v, (float*)o, s);
 }
@@ -1150,8 +1155,8 @@ extern "C" int compact_mixed_forward(compact_ctx* ctx, const compact_weights* w,
         if (bf) {
             {
                 ProfileScope ps(ctx, COMPACT_K_ATTN_PREFILL, s);
-                TRY(launch_attn_prefill_bf16(ctx, plan.d_meta, plan.d_q_tiles, (int)plan.q_tiles.size(), (const bf16*)pb.qkv, true,
-                                             (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)pb.o, s));
+                TRY(launch_attn_prefill_bf16(ctx, plan.d_meta, plan.max_capacity(), plan.d_q_tiles, (int)plan.q_tiles.size(),
+                                             (const bf16*)pb.qkv, true, (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)pb.o, s));
             }
             if (n_dec > 0)   // one query row per decoding block, read in place from the packed QKV rows
                 TRY(launch_attn_decode_bf16(ctx, (const BlockMeta*)(plan.d_extra + mx.dec_meta), plan.d_kv_chunks,

@@ -106,8 +106,9 @@ __device__ __forceinline__ void phase_barrier() {
 }
 
 // SCALED: the query rows carry the factor log2(e) / sqrt(hd) already (applied before they were rounded).
-template <int HD, bool SCALED>
-__global__ __launch_bounds__(256, HD == 64 ? 3 : 2) void attn_prefill_bf16_kernel(const BlockMeta* __restrict__ meta,
+// FAR: a block of the call has a slab of 4 GiB or more per KV head, whose V^T rows 32-bit offsets do not reach.
+template <int HD, bool SCALED, bool FAR>
+__global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf16_kernel(const BlockMeta* __restrict__ meta,
                                                                      const TileItem* __restrict__ qtiles,
                                                                      const bf16* __restrict__ qkv,
                                                                      const bf16* __restrict__ kbase,
@@ -180,16 +181,29 @@ __global__ __launch_bounds__(256, HD == 64 ? 3 : 2) void attn_prefill_bf16_kerne
         const int vrow = L >> 3, vc = (L & 7) ^ swz<8>(vrow);
         voff[i] = (unsigned)(vrow * bm.capacity + vc * 8) * 2u;
     }
-    const unsigned slab_bytes = (unsigned)bm.capacity * HD * 2u;   // one KV head's K slab, and its V^T slab
+    const unsigned slab_bytes = (unsigned)bm.capacity * HD * 2u;   // one KV head's K slab, and its V^T slab (below 4 GiB)
     // A tile has descriptors of its own, from its first byte to the slab's end: K rows and V^T columns past the slab read
     // zeros, and so does a tile past the last one; rows past the block's end inside the slab read whatever is there (their
     // scores are masked, their V^T columns are zeroed by fix_tail).
+    // FAR: K tiles have descriptors of their own 64 rows (fewer at the slab's end), V^T chunks go by 64-bit addresses, those
+    // past a row's end by that of the row's last chunk (zeroed by fix_tail like the others).
     auto issue_k = [&](int kt, int i) __attribute__((always_inline)) {
+        if constexpr (FAR) {
+            const unsigned bytes = kt < n_tiles ? (unsigned)min(KV_TILE, bm.capacity - kt * KV_TILE) * HD * 2u : 0u;
+            buf_load16_to_lds(raw_buffer(kslab + (size_t)kt * KTILE, bytes), lds + (kt & 1) * KTILE + (i * NW + wave) * 64 * 8, koff[i]);
+            return;
+        }
         const int off = kt * KV_TILE * HD;
         const __amdgpu_buffer_rsrc_t rs = raw_buffer(kslab + off, kt < n_tiles ? slab_bytes - 2u * off : 0u);
         buf_load16_to_lds(rs, lds + (kt & 1) * KTILE + (i * NW + wave) * 64 * 8, koff[i]);
     };
-    auto issue_v = [&](int kt, int i) __attribute__((always_inline)) {
+    auto issue_v = [&](int kt, int i) __attribute__((always_inline)) {   // kt < n_tiles
+        if constexpr (FAR) {
+            const int vrow = ((i * NW + wave) * 64 + lane) >> 3, col = kt * KV_TILE + (((lane & 7) ^ swz<8>(vrow)) << 3);
+            load16_to_lds(vslab + (size_t)vrow * bm.capacity + min(col, bm.capacity - 8),
+                          lds + (2 + (kt & 1)) * KTILE + (i * NW + wave) * 64 * 8);
+            return;
+        }
         const int off = kt * KV_TILE;
         const __amdgpu_buffer_rsrc_t rs = raw_buffer(vslab + off, kt < n_tiles ? slab_bytes - 2u * off : 0u);
         buf_load16_to_lds(rs, lds + (2 + (kt & 1)) * KTILE + (i * NW + wave) * 64 * 8, voff[i]);
@@ -435,11 +449,11 @@ __global__ __launch_bounds__(256, HD == 64 ? 3 : 2) void attn_prefill_bf16_kerne
     }
 }
 
-template <int HD, bool SCALED>
+template <int HD, bool SCALED, bool FAR>
 static int launch_prefill_variant(compact_ctx* ctx, const BlockMeta* d_meta, const TileItem* d_qtiles, int n_qtiles,
                                   const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s) {
     const compact_layer_cfg& c = ctx->cfg;
-    auto kern = attn_prefill_bf16_kernel<HD, SCALED>;
+    auto kern = attn_prefill_bf16_kernel<HD, SCALED, FAR>;
     const size_t smem = (size_t)4 * KV_TILE * HD * sizeof(bf16);
     static bool attr_set = false;
     if (!attr_set) {
@@ -457,11 +471,14 @@ static int launch_prefill_variant(compact_ctx* ctx, const BlockMeta* d_meta, con
 // What the q rows of a prefill carry (1: nothing).  At head_dim 128 the matrix pipe is the longer part: the kernel multiplies.
 float attn_prefill_q_scale(const compact_layer_cfg& c) { return c.head_dim == 64 ? LOG2E / sqrtf((float)c.head_dim) : 1.0f; }
 
-int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, const TileItem* d_qtiles, int n_qtiles,
+// `far`: see the kernel.  Slabs below 4 GiB keep the descriptors, which need no 64-bit address per lane.
+int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, int max_capacity, const TileItem* d_qtiles, int n_qtiles,
                              const bf16* qkv, bool scaled, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s) {
     if (n_qtiles == 0) return COMPACT_OK;
-    auto launch = ctx->cfg.head_dim == 128 ? launch_prefill_variant<128, false>
-                  : scaled                 ? launch_prefill_variant<64, true>
-                                           : launch_prefill_variant<64, false>;
+    const int hd = ctx->cfg.head_dim;
+    const bool far = (int64_t)max_capacity * hd * (int64_t)sizeof(bf16) >= (int64_t)1 << 32;
+    auto launch = hd == 128 ? (far ? launch_prefill_variant<128, false, true> : launch_prefill_variant<128, false, false>)
+                  : scaled  ? (far ? launch_prefill_variant<64, true, true> : launch_prefill_variant<64, true, false>)
+                            : (far ? launch_prefill_variant<64, false, true> : launch_prefill_variant<64, false, false>);
     return launch(ctx, d_meta, d_qtiles, n_qtiles, qkv, d_k, d_v, o, s);
 }

@@ -283,8 +283,8 @@ int launch_attn_decode_f32(compact_ctx* ctx, const BlockMeta* d_meta, int n_bloc
                            const float* d_k, const float* d_v, float* o, hipStream_t s);
 
 // attn_prefill.hip (bf16 MFMA)
-// scaled: the q rows carry the factor attn_prefill_q_scale()
-int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, const TileItem* d_qtiles, int n_qtiles,
+// max_capacity: of the call's blocks.  scaled: the q rows carry the factor attn_prefill_q_scale()
+int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, int max_capacity, const TileItem* d_qtiles, int n_qtiles,
                              const bf16* qkv, bool scaled, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s);
 float attn_prefill_q_scale(const compact_layer_cfg& c);
 

@@ -66,3 +66,31 @@ def test_reference_that_moves(hd, step):
     j = torch.cat([torch.arange(n) for n in lens]).to(qkv.device)
     k[:, :, hd // 2 - 1] = ((j // step) * (9.0 / (16.0 * 1.4426950408889634 / np.sqrt(hd)))).to(qkv.dtype)[:, None]
     check(layer, lens, qkv)
+
+
+@pytest.mark.parametrize("hq,hkv,hd,cap", [(2, 1, 128, 1 << 24), (3, 1, 128, (1 << 25) + 8), (2, 1, 64, 1 << 25), (1, 1, 64, (1 << 26) + 72)])
+def test_slabs_of_4_gib_and_more_per_kv_head(hq, hkv, hd, cap):
+    """Offsets inside a KV head's slab leave 32 bits at 4 GiB (2^24 rows of 128, 2^25 of 64): a block's result has the bits that it
+    has in a small slab, wherever in the call the large slab stands, with and without the factor in its q rows."""
+    layer = LayerConfig(d_model=64, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, ffn_dim=64, rope_theta=500000.0, dtype="bf16")
+    lens = [65, 333, 40]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    qkv = rnd((sum(lens), layer.Dq + 2 * layer.Dkv), torch.bfloat16, 23)
+    out = []
+    for caps in ([72, 336, 40], [72, cap, 40]):
+        for scaled in (True, False):
+            lay, kv = B.Layer(layer, None), B.KVCache(layer, caps, "cuda", torch.bfloat16)
+            x, o = qkv.clone(), torch.empty((sum(lens), layer.Dq), dtype=torch.bfloat16, device="cuda")
+            if scaled:
+                lay.check(lay.L.compact_test_rope_attn(lay.ctx, C.c_int32(3), cu.ctypes.data_as(C.POINTER(C.c_int32)),
+                                                       C.c_void_p(x.data_ptr()), C.byref(kv.c), C.c_void_p(o.data_ptr()),
+                                                       C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+            else:
+                lay.compact_rope_kvwrite(cu, x, kv)
+                lay.compact_attn_prefill(cu, x, kv, o)
+            torch.cuda.synchronize()
+            out.append(o)
+            del kv
+    torch.cuda.empty_cache()
+    assert torch.equal(out[2], out[0]) and torch.equal(out[3], out[1])
+    assert bool(torch.isfinite(out[0].float()).all()) and rel_err(to_numpy_f64(out[1]), to_numpy_f64(out[0])) < 5e-2
