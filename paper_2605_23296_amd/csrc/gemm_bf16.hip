@@ -34,7 +34,7 @@
 //  * epilogues: 0 = plain / + residual (fp32 add before the bf16 round), 1 =
 //    SwiGLU on a stacked gate/up weight (each wave holds the gate and the up
 //    tile of the same columns), 2 = fp32 output (router logits, decode partials), 3 =
-//    1 for decode rows with a factor per row and a division to half a unit; per-row
+//    1 with a factor per row (decode); per-row
 //    scaling for the routed experts;
 //  * workgroup ids are remapped so that each XCD (own L2) gets a contiguous
 //    range of tiles, walked in groups of 4 row tiles per column tile (8: the down
@@ -63,7 +63,7 @@ struct GemmParams {
     int touch;   // 256 x 256 kernel, plain product in halves: weight lines are touched ahead
     int n_full;  // 256 x 256 kernel, plain product: workgroups that take a whole tile (the others take halves)
     int r_f32;  // the residual R is fp32 rather than bf16
-    const float* pre_scale;   // SwiGLU: factor of every row's products before the silu (null = 1)
+    const float* pre_scale;   // epilogue 3: factor of every row's products before the silu (null = 1)
     GroupedArgs g;
 };
 
@@ -186,14 +186,15 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const floatx4 (&
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     float a = acc[2 * i + g][j][e];
-                    if (EPI == 1) {
-                        // the reciprocal to one unit in the last place of fp32: a division to half of one is ten
-                        // instructions, 64 times a lane, while the matrix pipe waits (2 * 14336 x 4096 at 32768 rows 5394
-                        // -> 5227 us; same error against 64 bits)
-                        a = a * __builtin_amdgcn_rcpf(1.0f + __expf(-a)) * acc[2 * i + g][j + TN / 2][e];
-                    } else if (EPI == 3) {
-                        a *= ps;
-                        const float u = acc[2 * i + g][j + TN / 2][e] * ps;
+                    if (GLU) {
+                        float u = acc[2 * i + g][j + TN / 2][e];
+                        if (EPI == 3) {
+                            a *= ps;
+                            u *= ps;
+                        }
+                        // A division to half a unit in the last place is ten instructions, 64 times a lane, while the matrix
+                        // pipe waits.  The reciprocal instruction (one and a half units with its product) saves 3 us of a
+                        // tile's 96, but changes a bf16 result in one of 180000 places.
                         a = a / (1.0f + __expf(-a)) * u;
                     }
                     v[e] = a;

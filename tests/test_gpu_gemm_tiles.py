@@ -1,6 +1,7 @@
 """The tile form of a projection is picked by the size of the call; an output has the same bits in all of them."""
 import ctypes as C
 
+import numpy as np
 import pytest
 import torch
 
@@ -110,6 +111,27 @@ def test_half_tiles_that_touch_weight_lines_ahead(M, N, K, epi):
     ref = O.silu(O.linear(A, Bm[:N])) * O.linear(A, Bm[N:]) if epi else O.linear(A, Bm)
     assert rel_err(to_numpy_f64(out[0][rows]), ref) < 1e-2
     assert torch.equal(out[0], out[1]) and bool((out[0][M] == 7.0).all())
+
+
+def test_the_swiglu_divides_to_half_a_unit():
+    """silu(a) u with a and u exact products of two bf16 values, so that every step of the fp32 formula is known (the exponential
+    is the hardware's exp2 of a * log2(e), which torch.exp2 calls too; division and products are rounded once each).  Every tile
+    form has exactly those bits; a quotient off by one unit would change a bf16 result in about 2^-16 of the places."""
+    lay = B.Layer(DENSE, None)
+    M, N, K = 1152, 4104, 64
+    a, b = torch.zeros((M, K), dtype=torch.bfloat16, device="cuda"), torch.zeros((2 * N, K), dtype=torch.bfloat16, device="cuda")
+    a[:, 0], b[:, 0] = rnd((M,), torch.bfloat16, 6, std=1.5), rnd((2 * N,), torch.bfloat16, 7, std=1.5)
+    x, w = a[:, 0].float(), b[:, 0].float()
+    g, up = x[:, None] * w[:N], x[:, None] * w[N:]
+    den = (1.0 + torch.exp2(g * -1.44269504).cpu()).numpy()
+    q, up = g.cpu().numpy() / den, up.cpu().numpy()
+    bf = lambda v: torch.from_numpy(v).to(torch.bfloat16)
+    want, off = bf(q * up), bf(np.nextafter(q, np.float32(0)) * up)
+    assert int((off != want).sum()) > 20
+    for form in range(len(FORMS) + 1):
+        c = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        gemm_form(lay, form, a, b, None, c, 1)
+        assert torch.equal(c.cpu(), want), (form, int((c.cpu() != want).sum()))
 
 
 def test_the_rule_picks_every_tile_form():
