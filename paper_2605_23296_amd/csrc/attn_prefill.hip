@@ -38,6 +38,7 @@
 // Before, head_dim 128 had workgroups of two heads whose wavefronts took turns at
 // matrix and softmax phases between barriers, head_dim 64 ran scores, softmax and output
 // one after the other in each of three wavefronts per SIMD.
+#include <algorithm>
 #include <numeric>
 #include <type_traits>
 
@@ -127,10 +128,11 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     // with the others of the same heads tile by tile, and goes through one KV head's tiles before the next one's, the
     // group's query heads side by side: what is in flight on an XCD reads the keys of a block or two (8 blocks of 4096: 1155
     // -> 1080 us, 16 of 8192 at head_dim 64: 8470 -> 8060; tiles of all blocks in flight everywhere before).
-    const int G = Hq / Hkv, x = blockIdx.x % 8, share = 8 / xcd_heads, per = (n_qtiles + share - 1) / share;
-    const int i_tile = blockIdx.x / 8 / G % per * share + x / xcd_heads;
-    const int kvh = blockIdx.x / 8 / G / per * xcd_heads + x % xcd_heads, head = kvh * G + blockIdx.x / 8 % G;
-    if (i_tile >= n_qtiles) return;
+    const int wg = blockIdx.y * gridDim.x + blockIdx.x;
+    const int G = Hq / Hkv, x = wg % 8, share = 8 / xcd_heads, per = (n_qtiles + share - 1) / share;
+    const int i_tile = wg / 8 / G % per * share + x / xcd_heads;
+    const int kvh = wg / 8 / G / per * xcd_heads + x % xcd_heads, head = kvh * G + wg / 8 % G;
+    if (i_tile >= n_qtiles || kvh >= Hkv) return;
     const TileItem it = qtiles[i_tile];
     const BlockMeta bm = meta[it.block];
     const int t = threadIdx.x, lane = t & 63;
@@ -461,7 +463,11 @@ static int launch_prefill_variant(compact_ctx* ctx, const BlockMeta* d_meta, con
         attr_set = true;
     }
     const int xcd_heads = std::gcd(8, c.n_kv_heads), share = 8 / xcd_heads;
-    const unsigned grid = 8u * (c.n_q_heads / xcd_heads) * ((n_qtiles + share - 1) / share);
+    // One grid dimension takes 2^32 threads and drops what is over without an error: beyond 2^20 workgroups the grid has rows of as
+    // many, a multiple of 8, so that a workgroup's number still says which XCD it is dealt to.
+    const int64_t wgs = (int64_t)8 * (c.n_q_heads / xcd_heads) * ((n_qtiles + share - 1) / share), row = 1 << 20;
+    if (wgs > INT32_MAX - row) return set_err(ctx, COMPACT_ESHAPE, "too many query tiles and heads for one call");
+    const dim3 grid((unsigned)std::min(wgs, row), (unsigned)((wgs + row - 1) / row));
     kern<<<grid, 256, smem, s>>>(d_meta, d_qtiles, qkv, d_k, d_v, o, c.n_q_heads, c.n_kv_heads, n_qtiles, xcd_heads,
                                  LOG2E / sqrtf((float)c.head_dim));
     LAUNCH_CHECK(ctx);

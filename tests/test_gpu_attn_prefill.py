@@ -94,3 +94,18 @@ def test_slabs_of_4_gib_and_more_per_kv_head(hq, hkv, hd, cap):
     torch.cuda.empty_cache()
     assert torch.equal(out[2], out[0]) and torch.equal(out[3], out[1])
     assert bool(torch.isfinite(out[0].float()).all()) and rel_err(to_numpy_f64(out[1]), to_numpy_f64(out[0])) < 5e-2
+
+
+def test_more_workgroups_than_one_grid_dimension_takes():
+    """2^18 + 1 blocks of one token at 64 query heads are more than the 2^24 workgroups of 256 that a grid's first dimension holds.
+    A token that attends itself alone gives its value row back, exactly."""
+    layer = LayerConfig(d_model=64, n_q_heads=64, n_kv_heads=4, head_dim=64, ffn_dim=64, rope_theta=500000.0, dtype="bf16")
+    n = (1 << 18) + 1
+    qkv = rnd((n, layer.Dq + 2 * layer.Dkv), torch.bfloat16, 24)
+    lay, kv = B.Layer(layer, None), B.KVCache(layer, [1] * n, "cuda", torch.bfloat16)
+    o, cu = torch.zeros((n, layer.Dq), dtype=torch.bfloat16, device="cuda"), np.arange(n + 1, dtype=np.int32)
+    lay.check(lay.L.compact_test_rope_attn(lay.ctx, C.c_int32(n), cu.ctypes.data_as(C.POINTER(C.c_int32)), C.c_void_p(qkv.data_ptr()),
+                                           C.byref(kv.c), C.c_void_p(o.data_ptr()), C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    torch.cuda.synchronize()
+    v = qkv[:, layer.Dq + layer.Dkv:].view(n, 4, 1, 64).expand(n, 4, 16, 64).reshape(n, layer.Dq)
+    assert torch.equal(o, v)
