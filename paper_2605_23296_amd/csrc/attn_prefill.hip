@@ -106,6 +106,26 @@ __device__ __forceinline__ void phase_barrier() {
 #endif
 }
 
+// Which (query tile, head) a workgroup takes.  Workgroups are dealt to the XCDs (an L2 each) round robin: XCD x takes KV heads
+// x % xcd_heads + k xcd_heads, shared with the others of the same heads unit by unit (a unit: a query tile of a KV head, for
+// all query heads of its group, side by side), and goes through one KV head's tiles before the next one's: what is in flight on
+// an XCD reads the keys of a block or two (8 blocks of 4096: 1155 -> 1080 us, 16 of 8192 at head_dim 64: 8470 -> 8060; tiles of
+// all blocks in flight everywhere before).  The sharers take their units forwards and backwards in turn, since a block's tiles
+// come by length, and count them through all their heads: 40 + 5 heads of 128, a whole call of 512 rows behind 8192 183 us
+// (263 in one direction and from the same XCD for every head, which left four of the eight idle), 4 blocks of 4096 863 (945).
+struct PrefillPlace {
+    int tile, kvh, g;   // kvh >= n_kv_heads: nothing to do
+};
+__host__ __device__ inline PrefillPlace prefill_place(int wg, int group, int n_qtiles, int xcd_heads) {
+    const int x = wg % 8, share = 8 / xcd_heads, s = x / xcd_heads, round = wg / 8 / group;
+    const int unit = round * share + (round & 1 ? share - 1 - s : s);
+    return PrefillPlace{unit % n_qtiles, unit / n_qtiles * xcd_heads + x % xcd_heads, wg / 8 % group};
+}
+static int64_t prefill_workgroups(int n_q_heads, int n_kv_heads, int n_qtiles, int xcd_heads) {
+    const int64_t share = 8 / xcd_heads, units = (int64_t)(n_kv_heads / xcd_heads) * n_qtiles;
+    return 8 * (n_q_heads / n_kv_heads) * ((units + share - 1) / share);
+}
+
 // SCALED: the query rows carry the factor log2(e) / sqrt(hd) already (applied before they were rounded).
 // FAR: a block of the call has a slab of 4 GiB or more per KV head, whose V^T rows 32-bit offsets do not reach.
 template <int HD, bool SCALED, bool FAR>
@@ -124,16 +144,10 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     extern __shared__ __attribute__((aligned(16))) char smem[];
     bf16* lds = reinterpret_cast<bf16*>(smem);  // [2 K tiles | 2 V^T tiles]
 
-    // Workgroups are dealt to the XCDs (an L2 each) round robin: XCD x takes the KV heads x % xcd_heads + k xcd_heads, shared
-    // with the others of the same heads tile by tile, and goes through one KV head's tiles before the next one's, the
-    // group's query heads side by side: what is in flight on an XCD reads the keys of a block or two (8 blocks of 4096: 1155
-    // -> 1080 us, 16 of 8192 at head_dim 64: 8470 -> 8060; tiles of all blocks in flight everywhere before).
-    const int wg = blockIdx.y * gridDim.x + blockIdx.x;
-    const int G = Hq / Hkv, x = wg % 8, share = 8 / xcd_heads, per = (n_qtiles + share - 1) / share;
-    const int i_tile = wg / 8 / G % per * share + x / xcd_heads;
-    const int kvh = wg / 8 / G / per * xcd_heads + x % xcd_heads, head = kvh * G + wg / 8 % G;
-    if (i_tile >= n_qtiles || kvh >= Hkv) return;
-    const TileItem it = qtiles[i_tile];
+    const PrefillPlace pl = prefill_place(blockIdx.y * gridDim.x + blockIdx.x, Hq / Hkv, n_qtiles, xcd_heads);
+    if (pl.kvh >= Hkv) return;
+    const int kvh = pl.kvh, head = kvh * (Hq / Hkv) + pl.g;
+    const TileItem it = qtiles[pl.tile];
     const BlockMeta bm = meta[it.block];
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -462,10 +476,10 @@ static int launch_prefill_variant(compact_ctx* ctx, const BlockMeta* d_meta, con
         HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
         attr_set = true;
     }
-    const int xcd_heads = std::gcd(8, c.n_kv_heads), share = 8 / xcd_heads;
+    const int xcd_heads = std::gcd(8, c.n_kv_heads);
     // One grid dimension takes 2^32 threads and drops what is over without an error: beyond 2^20 workgroups the grid has rows of as
     // many, a multiple of 8, so that a workgroup's number still says which XCD it is dealt to.
-    const int64_t wgs = (int64_t)8 * (c.n_q_heads / xcd_heads) * ((n_qtiles + share - 1) / share), row = 1 << 20;
+    const int64_t wgs = prefill_workgroups(c.n_q_heads, c.n_kv_heads, n_qtiles, xcd_heads), row = 1 << 20;
     if (wgs > INT32_MAX - row) return set_err(ctx, COMPACT_ESHAPE, "too many query tiles and heads for one call");
     const dim3 grid((unsigned)std::min(wgs, row), (unsigned)((wgs + row - 1) / row));
     kern<<<grid, 256, smem, s>>>(d_meta, d_qtiles, qkv, d_k, d_v, o, c.n_q_heads, c.n_kv_heads, n_qtiles, xcd_heads,
@@ -487,4 +501,17 @@ int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, int max_
                   : scaled  ? (far ? launch_prefill_variant<64, true, true> : launch_prefill_variant<64, true, false>)
                             : (far ? launch_prefill_variant<64, false, true> : launch_prefill_variant<64, false, false>);
     return launch(ctx, d_meta, d_qtiles, n_qtiles, qkv, d_k, d_v, o, s);
+}
+
+// For the tests, not part of compact.h: query tile, KV head and query head of the workgroups 0 .. n - 1 of a call with n_qtiles
+// query tiles (KV heads past the last one: nothing to do); returns the number of the call's workgroups.
+extern "C" int64_t compact_test_prefill_place(int32_t n_q_heads, int32_t n_kv_heads, int32_t n_qtiles, int32_t n, int32_t* out) {
+    const int xcd_heads = std::gcd(8, n_kv_heads), group = n_q_heads / n_kv_heads;
+    for (int i = 0; i < n; ++i) {
+        const PrefillPlace pl = prefill_place(i, group, n_qtiles, xcd_heads);
+        out[3 * i] = pl.tile;
+        out[3 * i + 1] = pl.kvh;
+        out[3 * i + 2] = pl.kvh * group + pl.g;
+    }
+    return prefill_workgroups(n_q_heads, n_kv_heads, n_qtiles, xcd_heads);
 }

@@ -383,3 +383,27 @@ def test_prefix_stack_call_rejects_bad_arguments_without_a_device():
     t32, _b = kvarr([16, 16, 16], [0, 0, 0], n=1)
     pl = (C.c_int32 * 3)(10, 20, 100)
     assert flay.L.compact_prefix_stack_forward(flay.ctx, 1, w32, 3, pl, 100, x, 2, x, s32, t32, x, ws, 1 << 40, None) == 5
+
+
+@pytest.mark.parametrize("hq,hkv", [(1, 1), (16, 1), (6, 2), (9, 3), (16, 4), (40, 5), (24, 6), (7, 7), (32, 8), (24, 12), (36, 12), (16, 16)])
+@pytest.mark.parametrize("n_blocks,tiles", [(1, 1), (1, 4), (3, 1), (1, 5), (1, 16), (4, 32), (7, 9)])
+def test_prefill_attention_shares_its_tiles_out_evenly(hq, hkv, n_blocks, tiles):
+    """Every query tile of every head goes to one workgroup.  The eight XCDs, to which workgroups are dealt in turn, differ by one
+    tile of one KV head at the most, and none has the keys of two longest tiles more to read than its even share."""
+    L = B.lib()
+    L.compact_test_prefill_place.restype = C.c_int64
+    n_q = n_blocks * tiles
+    args = [C.c_int32(v) for v in (hq, hkv, n_q)]
+    n = L.compact_test_prefill_place(*args, C.c_int32(0), None)
+    out = (C.c_int32 * (3 * n))()
+    assert L.compact_test_prefill_place(*args, C.c_int32(n), out) == n
+    place = [(i % 8, out[3 * i], out[3 * i + 1], out[3 * i + 2]) for i in range(n) if out[3 * i + 1] < hkv]
+    assert sorted((t, h) for _, t, _, h in place) == [(t, h) for t in range(n_q) for h in range(hq)]
+    assert all(h // (hq // hkv) == kv for _, _, kv, h in place)
+    units, keys = [0] * 8, [0] * 8
+    for x, t, _, _ in place:
+        units[x] += 1
+        keys[x] += tiles - t % tiles   # a block's tiles come longest first
+    group = hq // hkv
+    assert max(units) - min(units) <= group
+    assert max(keys) <= sum(keys) / 8 + 2 * group * tiles
