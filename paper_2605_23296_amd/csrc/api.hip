@@ -478,22 +478,19 @@ static int gemm_partials(compact_ctx* ctx, const void* A, const void* B, float* 
 // ---------------------------------------------------------------------------
 // prefill
 // ---------------------------------------------------------------------------
-// scaled: the q rows carry the attention's factor (bf16 only)
-static int run_attn_prefill(compact_ctx* ctx, const Plan& p, int n_blocks, const void* qkv, bool scaled, const compact_kv* kv,
-                            void* o, hipStream_t s) {
+static int run_attn_prefill(compact_ctx* ctx, const Plan& p, int n_blocks, const void* qkv, const compact_kv* kv, void* o,
+                            hipStream_t s) {
     ProfileScope ps(ctx, COMPACT_K_ATTN_PREFILL, s);
     if (ctx->cfg.dtype == COMPACT_BF16)
         return launch_attn_prefill_bf16(ctx, p.d_meta, p.max_capacity(), p.d_q_tiles, (int)p.q_tiles.size(), (const bf16*)qkv,
-                                        scaled, (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)o, s);
+                                        (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)o, s);
     return launch_attn_prefill_f32(ctx, p.d_meta, n_blocks, p.max_len, p.max_keys(), (const float*)qkv, (const float*)kv->d_k,
                                    (const float*)kv->d_v, (float*)o, s);
 }
 
 static int rope_and_attend(compact_ctx* ctx, const Plan& p, int n_blocks, void* qkv, const compact_kv* kv, void* o, hipStream_t s) {
-    const bool bf = ctx->cfg.dtype == COMPACT_BF16;
-    TRY(launch_rope_kvwrite(ctx, p.d_meta, p.d_rope_tiles, (int)p.rope_tiles.size(), qkv, kv->d_k, kv->d_v,
-                            attn_prefill_q_scale(ctx->cfg), bf ? n_blocks : 0, s));
-    return run_attn_prefill(ctx, p, n_blocks, qkv, bf, kv, o, s);
+    TRY(launch_rope_kvwrite(ctx, p.d_meta, p.d_rope_tiles, (int)p.rope_tiles.size(), qkv, kv->d_k, kv->d_v, s));
+    return run_attn_prefill(ctx, p, n_blocks, qkv, kv, o, s);
 }
 
 static int moe_ffn_rows(compact_ctx* ctx, const compact_weights* w, const void* m, const void* h, bool h_is_f32,
@@ -1149,14 +1146,12 @@ extern "C" int compact_mixed_forward(compact_ctx* ctx, const compact_weights* w,
         TRY(launch_move_rows(ctx, d_x_prefill, d_x_decode, d_src, xp, nullptr, nullptr, Tm, s));
         TRY(launch_rmsnorm(ctx, xp, false, w->g_attn, pb.n, Tm, s));
         TRY(gemm_full(ctx, pb.n, w->w_qkv, nullptr, false, pb.qkv, Tm, Dtot, c.d_model, 0, s));
-        // (the decode attention scales its q rows itself)
-        TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), pb.qkv, kv->d_k, kv->d_v,
-                                attn_prefill_q_scale(c), bf ? n_chunk : 0, s));
+        TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), pb.qkv, kv->d_k, kv->d_v, s));
         if (bf) {
             {
                 ProfileScope ps(ctx, COMPACT_K_ATTN_PREFILL, s);
                 TRY(launch_attn_prefill_bf16(ctx, plan.d_meta, plan.max_capacity(), plan.d_q_tiles, (int)plan.q_tiles.size(),
-                                             (const bf16*)pb.qkv, true, (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)pb.o, s));
+                                             (const bf16*)pb.qkv, (const bf16*)kv->d_k, (const bf16*)kv->d_v, (bf16*)pb.o, s));
             }
             if (n_dec > 0)   // one query row per decoding block, read in place from the packed QKV rows
                 TRY(launch_attn_decode_bf16(ctx, (const BlockMeta*)(plan.d_extra + mx.dec_meta), plan.d_kv_chunks,
@@ -1684,7 +1679,7 @@ extern "C" int compact_rope_kvwrite(compact_ctx* ctx, int32_t n_blocks, const in
     Plan plan;
     build_prefill_plan(kv, n_blocks, h_cu_seqlens, plan);
     TRY(upload_plan(ctx, plan, s));
-    TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), d_qkv, kv->d_k, kv->d_v, 1.0f, 0, s));
+    TRY(launch_rope_kvwrite(ctx, plan.d_meta, plan.d_rope_tiles, (int)plan.rope_tiles.size(), d_qkv, kv->d_k, kv->d_v, s));
     for (int b = 0; b < n_blocks; ++b) kv->h_len[b] = h_cu_seqlens[b + 1] - h_cu_seqlens[b];
     return COMPACT_OK;
 }
@@ -1725,11 +1720,10 @@ extern "C" int compact_attn_prefill(compact_ctx* ctx, int32_t n_blocks, const in
     Plan plan;
     build_prefill_plan(kv, n_blocks, h_cu_seqlens, plan);
     TRY(upload_plan(ctx, plan, s));
-    return run_attn_prefill(ctx, plan, n_blocks, d_qkv, false, kv, d_o, s);
+    return run_attn_prefill(ctx, plan, n_blocks, d_qkv, kv, d_o, s);
 }
 
-// For the tests, not part of compact.h: rotation, cache append and attention as a prefill does them (the attention's factor in
-// the q rows before they are rounded, at head_dim 64).
+// For the tests, not part of compact.h: rotation, cache append and attention as a prefill does them.
 extern "C" int compact_test_rope_attn(compact_ctx* ctx, int32_t n_blocks, const int32_t* h_cu_seqlens, void* d_qkv, compact_kv* kv,
                                       void* d_o, void* hip_stream) {
     if (!ctx || !d_qkv || !d_o || ctx->cfg.dtype != COMPACT_BF16) return COMPACT_EINVAL;

@@ -23,11 +23,12 @@
 //    softmax behind the MFMAs).  Steps of 64 tokens instead of 32 keep 64 registers more
 //    of scores and probabilities, which costs head_dim 64 its third wavefront per
 //    SIMD (8840 against 8470 us below);
-//  * at head_dim 64 a tile is 512 clocks of MFMAs and 540 of vector instructions:
-//    the scores start from minus the softmax's reference (MFMA accumulators) and
-//    the queries carry log2(e) / sqrt(hd) from before their rounding, so that no multiply-add
-//    stands between a score and its exponential (16 fewer of 106 instructions per half
-//    tile, 9320 -> 8800 us by itself);
+//  * the factor log2(e) / sqrt(hd) stands in the multiply-add before the exponential.
+//    In the queries it would save head_dim 64 16 of 106 vector instructions per half tile
+//    (2048 rows behind 16384, 64 + 8 heads, whole call of small products: 593 us instead of
+//    644).  But where the rotation is slow a rotated query is close to a bf16 value, and the
+//    factor takes it away from there before it is rounded: 0.5 to 3 % more error
+//    against 64 bits, whatever the scores' size;
 //  * causal tiles above the diagonal are skipped per wavefront; rows of the
 //    V^T tile past the block's length are zeroed when staged.
 // Bound: power.  16 blocks of 8192, 64 + 8 heads of 64: 9120 -> 8060 us (1.09
@@ -126,9 +127,8 @@ static int64_t prefill_workgroups(int n_q_heads, int n_kv_heads, int n_qtiles, i
     return 8 * (n_q_heads / n_kv_heads) * ((units + share - 1) / share);
 }
 
-// SCALED: the query rows carry the factor log2(e) / sqrt(hd) already (applied before they were rounded).
 // FAR: a block of the call has a slab of 4 GiB or more per KV head, whose V^T rows 32-bit offsets do not reach.
-template <int HD, bool SCALED, bool FAR>
+template <int HD, bool FAR>
 __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf16_kernel(const BlockMeta* __restrict__ meta,
                                                                      const TileItem* __restrict__ qtiles,
                                                                      const bf16* __restrict__ qkv,
@@ -172,11 +172,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
 #pragma unroll
         for (int e = 0; e < 16; ++e) oacc[d][e] = 0.f;
     float l_run = 0.f;
-    // the scaling reference, negated; SCALED: what the score accumulators start from (every element the same)
-    float neg_m1 = 0.f;
-    floatx16 neg_m;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) neg_m[e] = 0.f;
+    float neg_m = 0.f;   // the scaling reference, negated
 
     const int q_hi_wg = min(prior + it.row0 + PREFILL_QTILE, len) - 1;   // last query row of the workgroup
     const int q_lo_wave = prior + it.row0 + wave * 32;                     // first query row of this wave
@@ -266,8 +262,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     auto v_frag = [&](int stage, int d, int u) __attribute__((always_inline)) {
         return *reinterpret_cast<const bf16x8*>(smem + vfo[u] + 2 * ((2 + stage) * KTILE + d * 32 * KV_TILE));
     };
-    auto s_start = [&]() __attribute__((always_inline)) {
-        if constexpr (SCALED) return neg_m;
+    auto zeros = []() __attribute__((always_inline)) {
         floatx16 z;
 #pragma unroll
         for (int e = 0; e < 16; ++e) z[e] = 0.f;
@@ -275,7 +270,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     };
     // probabilities of a half against the reference as it stands; the lane's sum of its 16 values
     auto prob = [&](float x) __attribute__((always_inline)) {
-        return __builtin_amdgcn_exp2f(SCALED ? x : __builtin_fmaf(x, scale_log2, neg_m1));
+        return __builtin_amdgcn_exp2f(__builtin_fmaf(x, scale_log2, neg_m));
     };
     auto probs = [&](const floatx16& s, uintx4 (&p)[2]) __attribute__((always_inline)) {
         float ps = 0.f;
@@ -292,29 +287,19 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     // it stands and looks at nothing but their sum: while every lane's sum of its 16 values stays below 2^12, fp32 sums and
     // bf16 probabilities carry them without loss and the half's maximum is never formed.  Otherwise, and on the first half,
     // the exact maximum is taken, the reference moves there, the accumulators are rescaled and the probabilities are
-    // formed again.  `nxt`: the scores of the half after it, which have started from the old reference.
+    // formed again.
     // (Query columns past the block's end see unmasked cache rows past it -- whatever the slab holds -- and must not take
     // part in the decision: a row's bits may depend on its own block only.)
-    auto settle = [&](float ps, bool first, floatx16& s, floatx16& nxt, uintx4 (&p)[2]) __attribute__((always_inline)) {
+    auto settle = [&](float ps, bool first, const floatx16& s, uintx4 (&p)[2]) __attribute__((always_inline)) {
         if (__builtin_expect(first || __any(!(ps < 4096.0f) && qrow < len), 0)) {
             float mx = -INFINITY;
 #pragma unroll
             for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[e]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            if constexpr (!SCALED) mx = __builtin_fmaf(mx, scale_log2, neg_m1);
+            mx = __builtin_fmaf(fmaxf(mx, __shfl_xor(mx, 32, 64)), scale_log2, neg_m);
             const float up = first ? mx : fmaxf(mx, 0.f);   // finite: half 0 holds token 0 <= every query row
             const float corr = first ? 1.f : __builtin_amdgcn_exp2f(-up);
             l_run *= corr;
-            if constexpr (SCALED) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    s[e] -= up;
-                    nxt[e] -= up;
-                    neg_m[e] -= up;
-                }
-            } else {
-                neg_m1 -= up;
-            }
+            neg_m -= up;
 #pragma unroll
             for (int d = 0; d < DT; ++d)
 #pragma unroll
@@ -366,7 +351,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
             if (i & 1)
                 oacc[m % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g], __builtin_bit_cast(bf16x8, pp[m / DT]), oacc[m % DT], 0, 0, 0);
             else
-                sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g], qf[m], m ? sn : s_start(), 0, 0, 0);
+                sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[g], qf[m], m ? sn : zeros(), 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int e = (i + PRE) * PER; e < (i + PRE + 1) * PER && e < 16; ++e) pv[e] = prob(sc[e]);
@@ -380,7 +365,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        settle(ps, false, sc, sn, pn);
+        settle(ps, false, sc, pn);
     };
     auto issue = [&](int J) __attribute__((always_inline)) {
 #pragma unroll
@@ -406,11 +391,11 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     phase_barrier();
 #pragma unroll
     for (int m = 0; m < KK; ++m) {
-        se = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(0, 0, m), qf[m], m ? se : s_start(), 0, 0, 0);
-        so = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(0, 1, m), qf[m], m ? so : s_start(), 0, 0, 0);
+        se = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(0, 0, m), qf[m], m ? se : zeros(), 0, 0, 0);
+        so = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(0, 1, m), qf[m], m ? so : zeros(), 0, 0, 0);
     }
     mask(0, se);
-    settle(0.f, true, se, so, pe);
+    settle(0.f, true, se, pe);
     landed(0);
     int J = 1;
 #pragma unroll 1
@@ -434,7 +419,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
             oacc[m % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(stage, m % DT, m / DT), __builtin_bit_cast(bf16x8, pe[m / DT]),
                                                                    oacc[m % DT], 0, 0, 0);
         if (more) {
-            settle(ps, false, so, se, po);
+            settle(ps, false, so, po);
 #pragma unroll
             for (int m = 0; m < KK; ++m)
                 oacc[m % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(stage, m % DT, 2 + m / DT), __builtin_bit_cast(bf16x8, po[m / DT]),
@@ -465,11 +450,11 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     }
 }
 
-template <int HD, bool SCALED, bool FAR>
+template <int HD, bool FAR>
 static int launch_prefill_variant(compact_ctx* ctx, const BlockMeta* d_meta, const TileItem* d_qtiles, int n_qtiles,
                                   const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s) {
     const compact_layer_cfg& c = ctx->cfg;
-    auto kern = attn_prefill_bf16_kernel<HD, SCALED, FAR>;
+    auto kern = attn_prefill_bf16_kernel<HD, FAR>;
     const size_t smem = (size_t)4 * KV_TILE * HD * sizeof(bf16);
     static bool attr_set = false;
     if (!attr_set) {
@@ -488,18 +473,14 @@ static int launch_prefill_variant(compact_ctx* ctx, const BlockMeta* d_meta, con
     return COMPACT_OK;
 }
 
-// What the q rows of a prefill carry (1: nothing).  At head_dim 128 the matrix pipe is the longer part: the kernel multiplies.
-float attn_prefill_q_scale(const compact_layer_cfg& c) { return c.head_dim == 64 ? LOG2E / sqrtf((float)c.head_dim) : 1.0f; }
-
 // `far`: see the kernel.  Slabs below 4 GiB keep the descriptors, which need no 64-bit address per lane.
 int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, int max_capacity, const TileItem* d_qtiles, int n_qtiles,
-                             const bf16* qkv, bool scaled, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s) {
+                             const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s) {
     if (n_qtiles == 0) return COMPACT_OK;
     const int hd = ctx->cfg.head_dim;
     const bool far = (int64_t)max_capacity * hd * (int64_t)sizeof(bf16) >= (int64_t)1 << 32;
-    auto launch = hd == 128 ? (far ? launch_prefill_variant<128, false, true> : launch_prefill_variant<128, false, false>)
-                  : scaled  ? (far ? launch_prefill_variant<64, true, true> : launch_prefill_variant<64, true, false>)
-                            : (far ? launch_prefill_variant<64, false, true> : launch_prefill_variant<64, false, false>);
+    auto launch = hd == 128 ? (far ? launch_prefill_variant<128, true> : launch_prefill_variant<128, false>)
+                            : (far ? launch_prefill_variant<64, true> : launch_prefill_variant<64, false>);
     return launch(ctx, d_meta, d_qtiles, n_qtiles, qkv, d_k, d_v, o, s);
 }
 

@@ -153,9 +153,8 @@ static inline size_t dtype_size(int dtype) { return dtype == COMPACT_BF16 ? 2 : 
 // norm_rope.hip
 // x_is_f32: the input rows are fp32 (the prefill residual stream) instead of the storage type
 int launch_rmsnorm(compact_ctx* ctx, const void* x, bool x_is_f32, const void* g, void* y, int64_t rows, hipStream_t s);
-// the rotated q rows of the first n_scaled blocks are multiplied by q_scale before they are rounded
 int launch_rope_kvwrite(compact_ctx* ctx, const BlockMeta* d_meta, const TileItem* d_tiles, int n_tiles,
-                        void* qkv, void* d_k, void* d_v, float q_scale, int n_scaled, hipStream_t s);
+                        void* qkv, void* d_k, void* d_v, hipStream_t s);
 // decode: reduce ks split partials of the QKV projection, rotate, append K/V, emit q
 // norm (nullable): the partials were formed from un-normalised rows; every row is
 // multiplied by its 1 / rms first
@@ -283,10 +282,9 @@ int launch_attn_decode_f32(compact_ctx* ctx, const BlockMeta* d_meta, int n_bloc
                            const float* d_k, const float* d_v, float* o, hipStream_t s);
 
 // attn_prefill.hip (bf16 MFMA)
-// max_capacity: of the call's blocks.  scaled: the q rows carry the factor attn_prefill_q_scale()
+// max_capacity: of the call's blocks
 int launch_attn_prefill_bf16(compact_ctx* ctx, const BlockMeta* d_meta, int max_capacity, const TileItem* d_qtiles, int n_qtiles,
-                             const bf16* qkv, bool scaled, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s);
-float attn_prefill_q_scale(const compact_layer_cfg& c);
+                             const bf16* qkv, const bf16* d_k, const bf16* d_v, bf16* o, hipStream_t s);
 
 // attn_decode.hip (bf16 MFMA, split-KV)
 size_t attn_decode_partial_floats(const compact_layer_cfg& cfg, int n_blocks, int max_chunks);

@@ -79,7 +79,7 @@ template <typename T>
 __global__ __launch_bounds__(NT) void rope_kvwrite_kernel(const BlockMeta* __restrict__ meta,
                                                           const TileItem* __restrict__ tiles, T* __restrict__ qkv,
                                                           T* __restrict__ kbase, T* __restrict__ vbase, int Hq, int Hkv,
-                                                          int hd, double log2_theta, float q_scale, int n_scaled) {
+                                                          int hd, double log2_theta) {
     extern __shared__ char smem[];
     const int half = hd / 2;
     float2* cs = reinterpret_cast<float2*>(smem);                       // [ROPE_TILE][half]
@@ -111,7 +111,6 @@ __global__ __launch_bounds__(NT) void rope_kvwrite_kernel(const BlockMeta* __res
     const int h_lo = part * (Hq + Hkv) / parts, h_hi = (part + 1) * (Hq + Hkv) / parts;
     const int per_tok = (h_hi - h_lo) * chunks, total = ntok * per_tok;
     T* kslab = kbase + bm.slab;
-    const float qs = it.block < n_scaled ? q_scale : 1.0f;
     for (int idx0 = threadIdx.x; idx0 < total; idx0 += NT * ROPE_BATCH) {
         float lo[ROPE_BATCH][8], hi[ROPE_BATCH][8];
 #pragma unroll
@@ -129,13 +128,10 @@ __global__ __launch_bounds__(NT) void rope_kvwrite_kernel(const BlockMeta* __res
             const int tok = idx / per_tok, r = idx - tok * per_tok;
             const int head = h_lo + r / chunks, c = r % chunks;
             float olo[8], ohi[8];
-            const float hs = head < Hq ? qs : 1.0f;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float2 t = cs[tok * half + c * 8 + j];
                 rotate(lo[u][j], hi[u][j], t.x, t.y, olo[j], ohi[j]);
-                olo[j] *= hs;
-                ohi[j] *= hs;
             }
             T* dst = rows + (size_t)tok * ld + head * hd + c * 8;
             if (head >= Hq) dst = kslab + ((size_t)(head - Hq) * bm.capacity + bm.prior + p0 + tok) * hd + c * 8;
@@ -175,7 +171,7 @@ __global__ __launch_bounds__(NT) void rope_kvwrite_kernel(const BlockMeta* __res
 }
 
 int launch_rope_kvwrite(compact_ctx* ctx, const BlockMeta* d_meta, const TileItem* d_tiles, int n_tiles, void* qkv,
-                        void* d_k, void* d_v, float q_scale, int n_scaled, hipStream_t s) {
+                        void* d_k, void* d_v, hipStream_t s) {
     if (n_tiles == 0) return COMPACT_OK;
     const compact_layer_cfg& c = ctx->cfg;
     const double l2t = log2((double)c.rope_theta);
@@ -188,10 +184,10 @@ int launch_rope_kvwrite(compact_ctx* ctx, const BlockMeta* d_meta, const TileIte
     const dim3 grid(n_tiles, parts);
     if (c.dtype == COMPACT_BF16)
         rope_kvwrite_kernel<bf16><<<grid, NT, smem, s>>>(d_meta, d_tiles, (bf16*)qkv, (bf16*)d_k, (bf16*)d_v,
-                                                         c.n_q_heads, c.n_kv_heads, c.head_dim, l2t, q_scale, n_scaled);
+                                                         c.n_q_heads, c.n_kv_heads, c.head_dim, l2t);
     else
         rope_kvwrite_kernel<float><<<grid, NT, smem, s>>>(d_meta, d_tiles, (float*)qkv, (float*)d_k, (float*)d_v,
-                                                          c.n_q_heads, c.n_kv_heads, c.head_dim, l2t, q_scale, n_scaled);
+                                                          c.n_q_heads, c.n_kv_heads, c.head_dim, l2t);
     LAUNCH_CHECK(ctx);
     return COMPACT_OK;
 }
