@@ -131,3 +131,13 @@ def test_a_query_is_rounded_only_by_its_rotation(hd, key):
     o, ref = weight_of_one_key(hd, key)
     want = torch.from_numpy(ref).to(torch.float32).to(torch.bfloat16).double().numpy()
     assert float((o != want).mean()) < 5e-3
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("key", [32, 45, 63])
+def test_the_largest_weight_of_the_first_key_tile_is_one(hd, key):
+    """The softmax's first reference is the largest score of 64 keys, not of the first 32: the largest weight among them is 1 and is
+    not rounded."""
+    o, ref = weight_of_one_key(hd, key)
+    want = torch.from_numpy(ref).to(torch.float32).to(torch.bfloat16).double().numpy()
+    assert float((o != want).mean()) < 5e-3
