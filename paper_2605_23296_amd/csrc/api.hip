@@ -806,7 +806,7 @@ static int decode_part(compact_ctx* ctx, const compact_weights* w, int n_total, 
             // partials in the expert-sorted row order), SwiGLU, down projection, and a
             // combine that applies the gate weights to the fp32 sums.  The routing plan (one
             // workgroup, at most 256 routed rows = 64 blocks at top-4) cuts every expert's rows
-            // into tiles of 16, one grid slice each: an expert with more than 16 rows (possible
+            // into tiles of 16, with workgroups of their own: an expert with more than 16 rows (possible
             // beyond 16 blocks) is streamed once per tile.
             const int rk = N * c.top_k;
             if (!fused_route) TRY(launch_moe_plan(ctx, idx, gate, N, 16, b.plan, s));

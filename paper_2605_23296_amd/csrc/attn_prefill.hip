@@ -288,7 +288,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     // bf16 probabilities carry them without loss and the half's maximum is never formed.  Otherwise
     // the exact maximum is taken, the reference moves there, the accumulators are rescaled and the probabilities are
     // formed again.  The first half takes the maximum of the whole first tile (`other`: its second half), so that the largest weight
-    // of a row's first 64 keys is 1, which is not rounded: with the first half's own, 0.2 to 1 % more error against 64 bits.
+    // of a row's first 64 keys is 1, which is not rounded: with the first half's own, 0.1 to 1 % more error against 64 bits.
     // (Query columns past the block's end see unmasked cache rows past it -- whatever the slab holds -- and must not take
     // part in the decision: a row's bits may depend on its own block only.)
     auto settle = [&](float ps, bool first, const floatx16& s, const floatx16& other, uintx4 (&p)[2]) __attribute__((always_inline)) {

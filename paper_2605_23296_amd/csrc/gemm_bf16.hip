@@ -402,12 +402,11 @@ __device__ __forceinline__ void tile_256(const GemmParams& p, const TilePos& tp,
 // ---------------------------------------------------------------------------
 // TOUCH: weight lines are touched ahead of the ring, this workgroup's share among eight of the same columns.  A CU has some 50
 // KB of loads in flight, so weights that come from HBM, 900 ns away, limit it to 27 bytes a clock, a k-tile to 0.85 us, whatever
-// the ring holds; all eight workgroups ask for the same lines at the same time and wait alike.  With an eighth of
-// the lines touched by each of them four k-tiles ahead, the loads find them in the L2: K 14336, N 4096, weights in HBM, 1100
-// rows 179 -> 148 us, 1652 rows 184 -> 155, 2048 rows 190 -> 170; N 2880 K 4096 at 1652 rows 51 -> 45 (eight k-tiles ahead 1 %
-// slower, sixteen 3 %; with four sharers at 700 rows 48 -> 50; in calls of several rounds, whose later ones find
-// the weights, N 4096 K 14336 at 4100 rows 442 -> 451; N 1536 K 1024 13.4 -> 14.4).  The whole prefill of 1652 rows 667 ->
-// 652 us, where the down projection's epilogue reads and writes as well.
+// the ring holds; all eight workgroups ask for the same lines at the same time and wait alike.  With an eighth of the lines
+// touched by each of them four k-tiles ahead, the loads find them in the L2 (eight k-tiles ahead 1 % slower, sixteen 3 %; with
+// four sharers at 700 rows 48 -> 50 us).  Row tiles behind the last whole group of four and a bottom half tile touch nothing (80
+// of 208 workgroups at 1652 rows and N 4096), and where the XCDs' ranges of the order cut a group of sharers in two (3 of the 16
+// groups there), either L2 holds only the lines that its own workgroups touched.
 template <int EPI, bool GROUPED, bool TOUCH>
 __device__ __forceinline__ void tile_128(const GemmParams& p, const TilePos& tp, char* smem, int share) {
     constexpr int WN = 4, BK = GEMM_BK;
@@ -732,7 +731,14 @@ static int launch_large(compact_ctx* ctx, GemmParams& p, int64_t n_full, int n_c
         p.n_mtiles = (int)(lt.slots / p.n_ntiles);
         p.n_full = (int)std::min(n_full, lt.slots);
         wgs = p.n_full + 2 * (lt.slots - p.n_full) + lt.bottom;
-        p.touch = p.n_full == 0 && wgs <= n_cus && p.K >= 2048;   // see tile_128
+        // Touches (tile_128) where the call is one round of half tiles: later rounds find the weights (N 4096 K 14336 at 4100
+        // rows 442 -> 451 us).  From HBM, N 1088 .. 6144, K 2048 .. 14336 and 1024 .. 4600 rows, they gain 2 to 17 % (N 4096: K 2048
+        // at 1400 rows 31.2 -> 27.2, K 14336 at 1100 rows 179 -> 148, at 1652 189 -> 163, at 2048 191 -> 176); weights
+        // that the 256 MB cache still holds lose 1 to 8 % (K 2048 at 1100 rows 23.0 -> 24.3).  Whole prefills without them:
+        // layer of 436 MB 0.996 .. 1.034 of the time with them, layers of 20 to 120 MB called again and again 0.980 .. 1.031.
+        // K 1024 gains as much from HBM (18.7 -> 17.2) and loses as much from the cache (14.2 -> 14.8), and a layer so
+        // narrow is more often there.
+        p.touch = p.n_full == 0 && wgs <= n_cus && p.K >= 2048;
     }
     if (wgs == 0) return COMPACT_OK;
     kern<<<dim3((unsigned)wgs), 512, smem, s>>>(p);
@@ -742,16 +748,19 @@ static int launch_large(compact_ctx* ctx, GemmParams& p, int64_t n_full, int n_c
 
 // ---------------------------------------------------------------------------
 // Which tile.  Every form adds an output's products in the same order, so the choice changes no bit and may look at
-// the number of rows.  Cost of a call = rounds of workgroups over the compute units x time of one tile; the time of
-// a k-tile rises with the share u of busy units (power and L2 traffic).  Constants: microseconds per k-tile (idle chip
-// + share of the load) and per tile, fitted to timings of all six forms at 354 shapes (65 .. 20000 rows, 64 .. 14336
-// columns, K 64 .. 14336, both epilogues): the picked form is at most 7 % slower than the best of the six at any of them,
-// 0.3 % on average.  (Constants fitted to long K alone priced the tiles of K <= 512 wrongly, by up to 25 %: 20000 x 640, K
-// 64, SwiGLU 23.5 us in 128 x 256 tiles against 20.2 in 256 x 256.)  Measured where the line lies (us, 256 x 256 against
-// 128 x 256): N 4096 K 14336 at 2048 rows 266 / 203, at 2500 rows 272 / 356 (128 x 256 needs a second round); N 6144
-// K 4096 at 2500 rows 97 / 111, at 3000 rows 165 / 146; 2 * 14336 x 4096 at 1652 rows 397 / 368, at 4096 rows 861 / 940.
-// Few rows, N 4096 K 14336: 20 rows 207 (256 x 256) / 157 / 104 (128 x 128) / 85 (64 x 128) / 71 (128 x 64) / 55
-// (64 x 64); 300 rows 211 / 167 / 109 / 94 / 81 / 112; 1000 rows 243 / 187 / 140 / 190 / 192 / 232.
+// the number of rows.  The 256 x 256 kernel is priced at four cuts into whole and half tiles, by units that take the next
+// tile when they are free (large_cost), the smaller forms by rounds of workgroups over the compute units x time of one tile
+// (tile_cost); the time of a k-tile rises with the share u of busy units (power and L2 traffic).  Constants: microseconds per
+// k-tile (idle chip + share of the load) and per tile, fitted to timings of the six forms apart; they know neither the shared
+// launch of whole and half tiles nor the weight lines that half tiles touch ahead.  The pick against the best of the six
+// forms and of half the slots as whole tiles, 360 calls (18 products, 64 .. 14336 columns, K 64 .. 14336, both
+// epilogues, at 20 row counts from 65 to 20000, weights from HBM): of the 300 that take 8 us and more 0.6 % slower on average
+// and five by 5 to 10.5 % (N 1088 K 2112 at 3700 rows 28.9 us as 128 x 64, 26.2 as half tiles; N 4096 K 14336 at 4600 rows
+// 444, 414 with half the slots whole); the shorter ones, K of 64 to 512, 5 % on average and 1.1 us at most.
+// Measured where the lines lie (us, 256 x 256 / 128 x 256): N 4096 K 14336 at 2048 rows 243 / 178, at 2500 rows 235 / 324
+// (half tiles need a second round); N 6144 K 4096 at 2500 rows 91 / 109, at 3000 rows 154 / 136, and 126 mixed.
+// Few rows, N 4096 K 14336: 65 rows 176 (256 x 256) / 176 / 113 (128 x 128) / 78 (64 x 128) / 76 (128 x 64) / 56
+// (64 x 64); 400 rows 219 / 157 / 109 / 88 / 84 / 110; 1024 rows 246 / 151 / 131 / 187 / 185 / 219.
 // ---------------------------------------------------------------------------
 struct TileForm {
     int bm, bn;
@@ -960,9 +969,10 @@ int launch_swiglu_rows64(compact_ctx* ctx, const bf16* A, const bf16* B, const f
     p.M = M;
     p.N = F;
     p.K = K;
-    // up to 32 rows: half the activation loads and none of them twice; a stage is 12 KB then, so one more fits beside a
-    // second workgroup.  N 2 * 14336, K 4096, 24 rows 48.5 -> 46.6 us.  Output and down projection, a workgroup per CU,
-    // keep the 64-row tile: 31.9 us together against 31.5 with six stages of the lower one and 33.4 with ten.
+    // Up to 32 rows: half the activation loads (rows past the last one are loaded again up to the 32nd, not the 64th); a stage is
+    // 12 KB then, so one more fits beside a second workgroup.  N 2 * 14336, K 4096, 24 rows 48.5 -> 46.6 us.  Output and down
+    // projection, a workgroup per CU, keep the 64-row tile: 31.9 us together against 31.5 with six stages of the lower one and
+    // 33.4 with ten.
     if (M <= 32) return launch_small<32, 64, 1, 2, 6, 3, false>(ctx, p, s);
     return launch_small<64, 64, 2, 2, 5, 3, false>(ctx, p, s);
 }

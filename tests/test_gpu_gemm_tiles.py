@@ -74,9 +74,11 @@ def test_every_tile_form_at_its_edges(K, epi, res):
 
 
 # whole tiles, halves of the other slots and a bottom row tile of at most 128 rows in one launch: no whole tile, one, several; last
-# row tiles of 1, 128, 129 and 255 rows; workgroup counts that the XCDs do not share evenly
+# row tiles of 1, 76, 128, 129 and 255 rows, the first three a bottom strip beside whole and half tiles; workgroup counts that the
+# XCDs do not share evenly
 @pytest.mark.parametrize("epi,res", [(0, True), (1, False)])
-@pytest.mark.parametrize("M,N,K", [(255, 264, 192), (385, 520, 64), (640, 1032, 256), (1153, 776, 320), (1791, 2056, 128)])
+@pytest.mark.parametrize("M,N,K", [(255, 264, 192), (385, 520, 64), (640, 1032, 256), (1153, 776, 320), (1791, 2056, 128), (200, 136, 64),
+                                   (513, 1032, 192), (1100, 776, 128)])
 def test_whole_and_half_tiles_in_one_launch(M, N, K, epi, res):
     lay = B.Layer(DENSE, None)
     a, b = rnd((M, K), torch.bfloat16, 3), rnd(((2 if epi else 1) * N, K), torch.bfloat16, 4, std=0.05)
