@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     for (int d = 0; d < DT; ++d)
 #pragma unroll
         for (int e = 0; e < 16; ++e) oacc[d][e] = 0.f;
-    float l_run = 0.f;
+    float l_run = 0.f, l_even = 0.f;   // sums of the probabilities: of whole tiles, and of a tile's first half
     float neg_m = 0.f;   // the scaling reference, negated
 
     const int q_hi_wg = min(prior + it.row0 + PREFILL_QTILE, len) - 1;   // last query row of the workgroup
@@ -268,12 +268,11 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
         for (int e = 0; e < 16; ++e) z[e] = 0.f;
         return z;
     };
-    // probabilities of a half against the reference as it stands; the lane's sum of its 16 values
+    // probabilities of a half against the reference as it stands; `ps` and the lane's 16 values
     auto prob = [&](float x) __attribute__((always_inline)) {
         return __builtin_amdgcn_exp2f(__builtin_fmaf(x, scale_log2, neg_m));
     };
-    auto probs = [&](const floatx16& s, uintx4 (&p)[2]) __attribute__((always_inline)) {
-        float ps = 0.f;
+    auto probs = [&](float ps, const floatx16& s, uintx4 (&p)[2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
             const float a = prob(s[e]), b = prob(s[e + 1]);
@@ -284,14 +283,17 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
         return ps;
     };
     // The running maximum is only a scaling reference.  The common case takes the probabilities against the reference as
-    // it stands and looks at nothing but their sum: while every lane's sum of its 16 values stays below 2^12, fp32 sums and
+    // it stands and looks at nothing but their sum: while every lane's sum of a tile's 32 values stays below 2^12, fp32 sums and
     // bf16 probabilities carry them without loss and the half's maximum is never formed.  Otherwise
     // the exact maximum is taken, the reference moves there, the accumulators are rescaled and the probabilities are
     // formed again.  The first half takes the maximum of the whole first tile (`other`: its second half), so that the largest weight
     // of a row's first 64 keys is 1, which is not rounded: with the first half's own, 0.1 to 1 % more error against 64 bits.
+    // A tile's values are summed one after the other through both halves (`ps`: an odd half's sum has begun with l_even) before
+    // they join those of the tiles before.
     // (Query columns past the block's end see unmasked cache rows past it -- whatever the slab holds -- and must not take
     // part in the decision: a row's bits may depend on its own block only.)
-    auto settle = [&](float ps, bool first, const floatx16& s, const floatx16& other, uintx4 (&p)[2]) __attribute__((always_inline)) {
+    auto settle = [&](float ps, bool odd, bool first, const floatx16& s, const floatx16& other, uintx4 (&p)[2])
+                      __attribute__((always_inline)) {
         if (__builtin_expect(first || __any(!(ps < 4096.0f) && qrow < len), 0)) {
             float mx = -INFINITY;
 #pragma unroll
@@ -305,9 +307,12 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
             for (int d = 0; d < DT; ++d)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) oacc[d][e] *= corr;
-            ps = probs(s, p);
+            ps = probs(odd ? l_even * corr : 0.f, s, p);
         }
-        l_run += ps;
+        if (odd)
+            l_run += ps;
+        else
+            l_even = ps;
     };
     auto mask = [&](int n, floatx16& s) __attribute__((always_inline)) {
         if (__builtin_expect(n * 32 + 31 <= q_lo_wave, 1)) return;   // wholly below the wavefront's diagonal
@@ -332,7 +337,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
             const int i = g % NM, tt = g / NM, m = i / 2;
             fr[g] = i & 1 ? v_frag(1 - stage, m % DT, 2 * tt + m / DT) : k_frag(stage, tt, m);
         };
-        float ps = 0.f, pv[16];
+        float ps = part == 0 ? l_even : 0.f, pv[16];   // part 0 is an odd half
         auto add = [&](int e) __attribute__((always_inline)) {
             ps += pv[e];
             if (e & 1) pn[e >> 3][(e >> 1) & 3] = here((int)pack_bf16x2(pv[e - 1], pv[e]));   // not sunk below the branch
@@ -366,7 +371,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        settle(ps, false, sc, sc, pn);
+        settle(ps, part == 0, false, sc, sc, pn);
     };
     auto issue = [&](int J) __attribute__((always_inline)) {
 #pragma unroll
@@ -397,7 +402,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     }
     mask(0, se);
     mask(1, so);
-    settle(0.f, true, se, so, pe);
+    settle(0.f, false, true, se, so, pe);
     landed(0);
     int J = 1;
 #pragma unroll 1
@@ -411,21 +416,23 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
     {
         const int stage = (J - 1) & 1, n = 2 * J - 1;
         const bool more = n * 32 <= q_lo_wave + 31;
-        float ps = 0.f;
+        float ps = l_even;
         if (more) {
             mask(n, so);
-            ps = probs(so, po);
+            ps = probs(ps, so, po);
         }
 #pragma unroll
         for (int m = 0; m < KK; ++m)
             oacc[m % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(stage, m % DT, m / DT), __builtin_bit_cast(bf16x8, pe[m / DT]),
                                                                    oacc[m % DT], 0, 0, 0);
         if (more) {
-            settle(ps, false, so, so, po);
+            settle(ps, true, false, so, so, po);
 #pragma unroll
             for (int m = 0; m < KK; ++m)
                 oacc[m % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(stage, m % DT, 2 + m / DT), __builtin_bit_cast(bf16x8, po[m / DT]),
                                                                        oacc[m % DT], 0, 0, 0);
+        } else {
+            l_run += ps;
         }
     }
     if (J < n_tiles) landed(J++);

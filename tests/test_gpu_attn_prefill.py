@@ -141,3 +141,43 @@ def test_the_largest_weight_of_the_first_key_tile_is_one(hd, key):
     o, ref = weight_of_one_key(hd, key)
     want = torch.from_numpy(ref).to(torch.float32).to(torch.bfloat16).double().numpy()
     assert float((o != want).mean()) < 5e-3
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_probabilities_are_summed_tile_by_tile(hd):
+    """Key 0 alone has a score and a value, and a rotation of none, so that every step in fp32 is known (the exponential is the
+    hardware's exp2, which torch.exp2 calls too): a lane has the keys whose number's bit 3 is its own, sums a tile's 32 one after
+    the other and adds the tiles.  The output has exactly those bits; sums of half tiles would change some."""
+    layer = LayerConfig(d_model=64, n_q_heads=32, n_kv_heads=8, head_dim=hd, ffn_dim=64, rope_theta=500000.0, dtype="bf16")
+    L, gen, f32 = 700, torch.Generator().manual_seed(27), np.float32
+    qkv = torch.zeros((L, layer.Dq + 2 * layer.Dkv), dtype=torch.bfloat16, device="cuda")
+    qv = (4.0 + 8.0 * torch.rand((L, 32), generator=gen)).to(torch.bfloat16)
+    qkv[:, :layer.Dq].view(L, 32, hd)[:, :, hd // 2 - 1] = qv.cuda()
+    qkv[0, layer.Dq:layer.Dq + layer.Dkv].view(8, hd)[:, hd // 2 - 1] = 4.0
+    qkv[0, layer.Dq + layer.Dkv:] = rnd((layer.Dkv,), torch.bfloat16, 28)
+    v0 = np.repeat(qkv[0, layer.Dq + layer.Dkv:].float().cpu().numpy().reshape(8, hd), 4, axis=0)
+
+    scale = f32(f32(1.4426950408889634) / f32(np.sqrt(hd)))
+    s = qv.double().numpy() * 4.0
+    ref = (s * np.float64(scale)).astype(f32)
+    exp2 = lambda x: torch.exp2(torch.from_numpy(x.astype(f32)).cuda()).cpu().numpy()
+    first, others = exp2(s * np.float64(scale) - ref), exp2(-ref)
+    got = qkv.clone()
+    o, _ = run(layer, [L], got)
+
+    def outputs(keys):   # sums of `keys` keys at a time
+        total = []
+        for lane in (0, 1):
+            t = np.zeros((L, 32), f32)
+            for k0 in range(0, L, keys):
+                part = np.zeros((L, 32), f32)
+                for k in (k for k in range(k0, min(k0 + keys, L)) if k >> 3 & 1 == lane):
+                    part[k:] += first[k:] if k == 0 else others[k:]
+                t += part
+            total.append(t)
+        inv = f32(1) / (total[0] + total[1])
+        return torch.from_numpy(v0[None] * inv[:, :, None]).to(torch.bfloat16).double().numpy().reshape(L, -1)
+
+    want = outputs(64)
+    assert int((outputs(32) != want).sum()) > 5
+    assert np.array_equal(o, want), int((o != want).sum())
