@@ -282,22 +282,31 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
         }
         return ps;
     };
+    auto mask = [&](int n, floatx16& s) __attribute__((always_inline)) {
+        if (__builtin_expect(n * 32 + 31 <= q_lo_wave, 1)) return;   // wholly below the wavefront's diagonal
+        const int q = here(qrow) - n * 32 - h * 8;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            if ((e >> 3) * 16 + (e & 7) > q) s[e] = -INFINITY;
+    };
     // The running maximum is only a scaling reference.  The common case takes the probabilities against the reference as
     // it stands and looks at nothing but their sum: while every lane's sum of a tile's 32 values stays below 2^12, fp32 sums and
     // bf16 probabilities carry them without loss and the half's maximum is never formed.  Otherwise
     // the exact maximum is taken, the reference moves there, the accumulators are rescaled and the probabilities are
-    // formed again.  The first half takes the maximum of the whole first tile (`other`: its second half), so that the largest weight
-    // of a row's first 64 keys is 1, which is not rounded: with the first half's own, 0.1 to 1 % more error against 64 bits.
+    // formed again.  A first half takes the maximum of its whole tile (its second half's scores, n + 1, are in `other`), so that
+    // the tile's largest weight is 1, which is not rounded: with the half's own, 0.1 to 1 % more error against 64 bits, most
+    // by the first tile.
     // A tile's values are summed one after the other through both halves (`ps`: an odd half's sum has begun with l_even) before
     // they join those of the tiles before.
     // (Query columns past the block's end see unmasked cache rows past it -- whatever the slab holds -- and must not take
     // part in the decision: a row's bits may depend on its own block only.)
-    auto settle = [&](float ps, bool odd, bool first, const floatx16& s, const floatx16& other, uintx4 (&p)[2])
+    auto settle = [&](int n, float ps, bool odd, bool first, const floatx16& s, floatx16& other, uintx4 (&p)[2])
                       __attribute__((always_inline)) {
         if (__builtin_expect(first || __any(!(ps < 4096.0f) && qrow < len), 0)) {
             float mx = -INFINITY;
+            if (!odd) mask(n + 1, other);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) mx = fmaxf(mx, first ? fmaxf(s[e], other[e]) : s[e]);
+            for (int e = 0; e < 16; ++e) mx = fmaxf(mx, odd ? s[e] : fmaxf(s[e], other[e]));
             mx = __builtin_fmaf(fmaxf(mx, __shfl_xor(mx, 32, 64)), scale_log2, neg_m);
             const float up = first ? mx : fmaxf(mx, 0.f);   // finite: half 0 holds token 0 <= every query row
             const float corr = first ? 1.f : __builtin_amdgcn_exp2f(-up);
@@ -313,13 +322,6 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
             l_run += ps;
         else
             l_even = ps;
-    };
-    auto mask = [&](int n, floatx16& s) __attribute__((always_inline)) {
-        if (__builtin_expect(n * 32 + 31 <= q_lo_wave, 1)) return;   // wholly below the wavefront's diagonal
-        const int q = here(qrow) - n * 32 - h * 8;
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-            if ((e >> 3) * 16 + (e & 7) > q) s[e] = -INFINITY;
     };
 
     // Step J of a wavefront, with K of tile J and V^T of tile J - 1, is twice (first for n = 2J - 1, then for n = 2J) QK^T of
@@ -371,7 +373,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        settle(ps, part == 0, false, sc, sc, pn);
+        settle(2 * J - 1 + part, ps, part == 0, false, sc, sn, pn);
     };
     auto issue = [&](int J) __attribute__((always_inline)) {
 #pragma unroll
@@ -401,8 +403,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
         so = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(0, 1, m), qf[m], m ? so : zeros(), 0, 0, 0);
     }
     mask(0, se);
-    mask(1, so);
-    settle(0.f, false, true, se, so, pe);
+    settle(0, 0.f, false, true, se, so, pe);
     landed(0);
     int J = 1;
 #pragma unroll 1
@@ -426,7 +427,7 @@ __global__ __launch_bounds__(256, HD == 64 && !FAR ? 3 : 2) void attn_prefill_bf
             oacc[m % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(stage, m % DT, m / DT), __builtin_bit_cast(bf16x8, pe[m / DT]),
                                                                    oacc[m % DT], 0, 0, 0);
         if (more) {
-            settle(ps, true, false, so, so, po);
+            settle(n, ps, true, false, so, se, po);
 #pragma unroll
             for (int m = 0; m < KK; ++m)
                 oacc[m % DT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(stage, m % DT, 2 + m / DT), __builtin_bit_cast(bf16x8, po[m / DT]),

@@ -104,15 +104,17 @@ def test_more_workgroups_than_one_grid_dimension_takes():
     assert torch.equal(o, v)
 
 
-def weight_of_one_key(hd, key):
-    """A block of 160 tokens whose values are zero but for one key's, and whose scores are zero but for that key's, 2 .. 6: the key's
-    query and key entries lie in the rotary pair that these positions leave where it is.  Returns output and its fp64 value."""
+def weight_of_one_key(hd, key, size=0.5, rivals=()):
+    """A block of 160 tokens whose values are zero but for one key's, and whose scores are zero but for that key's, `size` times
+    4 .. 12, and those of `rivals` (key, size): the query and key entries lie in the rotary pair that these positions leave where
+    it is.  Returns output and its fp64 value."""
     layer = LayerConfig(d_model=64, n_q_heads=8, n_kv_heads=2, head_dim=hd, ffn_dim=64, rope_theta=500000.0, dtype="bf16")
     L, gen = 160, torch.Generator().manual_seed(25)
     qkv = torch.zeros((L, layer.Dq + 2 * layer.Dkv), dtype=torch.bfloat16, device="cuda")
     q, k = qkv[:, :layer.Dq].view(L, 8, hd), qkv[:, layer.Dq:layer.Dq + layer.Dkv].view(L, 2, hd)
     q[:, :, hd // 2 - 1] = (4.0 + 8.0 * torch.rand((L, 8), generator=gen)).to(torch.bfloat16).cuda()
-    k[key, :, hd // 2 - 1] = 0.5 * np.sqrt(hd)
+    for j, f in ((key, size),) + tuple(rivals):
+        k[j, :, hd // 2 - 1] = f * np.sqrt(hd)
     qkv[key, layer.Dq + layer.Dkv:] = rnd((layer.Dkv,), torch.bfloat16, 26)
     x = to_numpy_f64(qkv)
     o, _ = run(layer, [L], qkv)
@@ -181,3 +183,13 @@ def test_probabilities_are_summed_tile_by_tile(hd):
     want = outputs(64)
     assert int((outputs(32) != want).sum()) > 5
     assert np.array_equal(o, want), int((o != want).sum())
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("key", [96, 104, 127])
+def test_a_reference_that_moves_takes_the_whole_tile(hd, key):
+    """The reference moves at the first half of the second tile, by a key 2^13 and more above what came before: to the largest
+    score of the tile, which lies in its second half, so that this key's weight is 1."""
+    o, ref = weight_of_one_key(hd, key, 2.5, ((70, 2.25),))
+    want = torch.from_numpy(ref).to(torch.float32).to(torch.bfloat16).double().numpy()
+    assert float((o != want).mean()) < 5e-3
