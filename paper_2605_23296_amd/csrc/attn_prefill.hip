@@ -22,7 +22,7 @@
 //    MFMA by MFMA, in an order that is written out (the compiler's own leaves the
 //    softmax behind the MFMAs).  Steps of 64 tokens instead of 32 keep 64 registers more
 //    of scores and probabilities, which costs head_dim 64 its third wavefront per
-//    SIMD (8840 against 8470 us below);
+//    SIMD (4 % of the time);
 //  * the factor log2(e) / sqrt(hd) stands in the multiply-add before the exponential.
 //    In the queries it would save head_dim 64 16 of 106 vector instructions per half tile
 //    (2048 rows behind 16384, 64 + 8 heads, whole call of small products: 593 us instead of
@@ -31,14 +31,17 @@
 //    against 64 bits, whatever the scores' size;
 //  * causal tiles above the diagonal are skipped per wavefront; rows of the
 //    V^T tile past the block's length are zeroed when staged.
-// Bound: power.  16 blocks of 8192, 64 + 8 heads of 64: 9120 -> 8060 us (1.09
-// PFLOP/s) with the matrix pipe 67 % busy (before: 54 %) and the vector ALU 76 %,
-// clocks per tile and SIMD 942 -> 762, but the clock falls with them; 8 blocks of
-// 4096, 32 + 8 heads of 128: 1138 -> 1056 us (1.04 PFLOP/s), pipe 57 -> 64 %;
-// 2048 rows behind 6144: 238 -> 240; blocks of 61 to 517 tokens: 26.8 -> 21.6.
+// Bound: power.  16 blocks of 8192, 64 + 8 heads of 64: 9217 -> 8546 us (1.03
+// PFLOP/s) with the matrix pipe 62 % busy (before: 54 %), clocks per tile and SIMD 942
+// -> 830, but the clock falls with them; 8 blocks of 4096, 32 + 8 heads of 128: 1145
+// -> 998 us (1.10 PFLOP/s), pipe 58 -> 69 %; 2048 rows behind 6144: 229 -> 221; blocks of
+// 61 to 517 tokens: 26.2 -> 18.4 (inside the passes, one card).
 // Before, head_dim 128 had workgroups of two heads whose wavefronts took turns at
 // matrix and softmax phases between barriers, head_dim 64 ran scores, softmax and output
-// one after the other in each of three wavefronts per SIMD.
+// one after the other in each of three wavefronts per SIMD.  The former, which staged K
+// and V once for two heads, was faster in one kind of call: an even group of heads of 128 and one round of
+// workgroups as long as each other (2048 rows behind 16384, 32 + 8 heads: whole
+// call of small products 549 -> 564 to 576 us).
 #include <algorithm>
 #include <numeric>
 #include <type_traits>
@@ -110,8 +113,8 @@ __device__ __forceinline__ void phase_barrier() {
 // Which (query tile, head) a workgroup takes.  Workgroups are dealt to the XCDs (an L2 each) round robin: XCD x takes KV heads
 // x % xcd_heads + k xcd_heads, shared with the others of the same heads unit by unit (a unit: a query tile of a KV head, for
 // all query heads of its group, side by side), and goes through one KV head's tiles before the next one's: what is in flight on
-// an XCD reads the keys of a block or two (8 blocks of 4096: 1155 -> 1080 us, 16 of 8192 at head_dim 64: 8470 -> 8060; tiles of
-// all blocks in flight everywhere before).  The sharers take their units forwards and backwards in turn, since a block's tiles
+// an XCD reads the keys of a block or two (tiles of all blocks in flight everywhere: 8 blocks of 4096 7 % slower, 16 of 8192 at
+// head_dim 64 5 %).  The sharers take their units forwards and backwards in turn, since a block's tiles
 // come by length, and count them through all their heads: 40 + 5 heads of 128, a whole call of 512 rows behind 8192 183 us
 // (263 in one direction and from the same XCD for every head, which left four of the eight idle), 4 blocks of 4096 863 (945).
 struct PrefillPlace {

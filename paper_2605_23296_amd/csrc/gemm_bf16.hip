@@ -41,8 +41,8 @@
 //    projection 3 % slower, the others equal; 16: 7 .. 13 % slower).
 // Bound: the power limit (the gate/up projection of that pass: matrix pipe 85 % busy at
 // 1.60 GHz; a probe whose loads all hit L2 ran at a clock 9 % higher).  8B-shaped layer, 32768
-// rows: QKV 1.08 ms, O 0.85, gate/up 5.28 (1.46 PFLOP/s), down 2.55 (1.51); in the form of lock steps 1.48, 1.05, 6.29
-// and 3.42.  1652 rows, where rounds of workgroups count: 85, 60, 280 and 192 us (104, 91, 419, 304).
+// rows: QKV 1.14 ms, O 0.82, gate/up 5.11 (1.51 PFLOP/s), down 2.52 (1.53); in the form of lock steps 1.48, 1.05, 6.29
+// and 3.42.  1652 rows, where rounds of workgroups count: 86, 60, 286 and 195 us (104, 91, 419, 304).
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -193,8 +193,9 @@ __device__ __forceinline__ void store_tile(const GemmParams& p, const floatx4 (&
                             u *= ps;
                         }
                         // A division to half a unit in the last place is ten instructions, 64 times a lane, while the matrix
-                        // pipe waits.  The reciprocal instruction (one and a half units with its product) saves 3 us of a
-                        // tile's 96, but changes a bf16 result in one of 180000 places.
+                        // pipe waits.  The reciprocal instruction (one and a half units with its product) saves 1 to 2 % (2 * 14336
+                        // x 4096 at 32768 rows 5111 -> 5069 us, routed 16 x 8192 13874 -> 13581), but changes a bf16
+                        // result in one of 180000 places.
                         a = a / (1.0f + __expf(-a)) * u;
                     }
                     v[e] = a;
